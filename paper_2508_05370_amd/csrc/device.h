@@ -1387,36 +1387,31 @@ struct ZbSink {
   }
 };
 
-// Iteration time from the end of each stage's last op: the max over stages
-// of that end plus the stage's DP sync, walking the stages with the same
-// shift so that no array is indexed at run time.
+// The syncs x[s] each stage of the pipeline waits for, costed by this lane
+// alone: with the per-class layout read from the plan pass's row, otherwise
+// found stage by stage (shifted into place so that no array is indexed at
+// run time).
 template <int S, int kMode, bool kHet, bool kOvl, bool kHier>
-__device__ __forceinline__ double dp_tail(const Tab& t, const Hot<kMode>& h, const Plan& p, double (&last)[S],
+__device__ __forceinline__ void own_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, double (&x)[S],
                                           const uint64_t* drow) {
   if constexpr (kHet) {
-    // per-class layout: the syncs the plan pass stored for this pipeline's stages
-    double T = 0;
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const double e = last[s] + (double)drow[s];
-      T = e > T ? e : T;
-    }
-    return T;
+    for (int s = 0; s < S; ++s) x[s] = (double)drow[s];
+    return;
   }
   const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
-  double T = 0;
   uint32_t lo = 0;
+#pragma unroll
+  for (int s = 0; s < S; ++s) x[s] = 0;
   for (uint32_t s = 0; s < (uint32_t)S; ++s) {
     const uint32_t hi = cut_at(p, s);
     const uint64_t d = kOvl ? overlap_tail<kMode, kHier>(t, h, p, s, lo, hi, (uint32_t)(p.tc >> (4 * s)) & 15, rp, rpe)
                             : stage_dp<kMode, kHier>(t, h, p, s, hi - lo, rp, rpe);
-    const double e = last[0] + (double)d;
-    T = e > T ? e : T;
 #pragma unroll
-    for (int i = 0; i + 1 < S; ++i) last[i] = last[i + 1];
+    for (int i = 0; i + 1 < S; ++i) x[i] = x[i + 1];
+    x[S - 1] = (double)d;
     lo = hi;
   }
-  return T;
 }
 
 template <int S, int v>
@@ -1481,242 +1476,188 @@ __global__ void __launch_bounds__(256) k_plan_syncs(Tab t, const PackedPlan* __r
 // ---------------------------------------------------------------- 1F1B pipeline
 // Schedule of one class (S stages, M micro-batches per replica): stage s runs
 // W_s = min(S-1-s, M) forwards, then pairs (forward, backward), then its last
-// W_s backwards.  Evaluation order that respects every dependency:
-//   warm-up rows m = 0..: stages s < S-1-m run F(s, m), ascending s;
-//   then for each backward index i, descending s: F(s, i + W_s) if it exists,
-//   then B(s, i).
-// Descending s lets B(s, i) read B(s+1, i) just computed while F(s, .) still
-// sees stage s-1's previous forward.  Iterations where every stage has its
-// forward form the steady loop; the last min(S-1, M) iterations, where the
-// upper stages have run out of forwards, are unrolled.
-//   out_f[s] end of the latest forward on stage s, last[s] end of its latest op.
-// Each schedule node is end = max(previous end on the stage, input end + hop)
-// + duration: 3 VALU ops in fp64, 5 in u64 (64-bit add is one v_lshl_add_u64,
-// max is a compare and two selects).
+// W_s backwards.  F(s, m), B(s, i) are the ends of forward m and backward i:
+//   F(s, m) = max(previous op's end on s, F(s-1, m) + c_{s-1}) + f_s
+//   B(s, i) = max(previous op's end on s, B(s+1, i) + c_s) + b_s,
+// and the pipeline's time is T = max_s B(s, M-1) + x_s (x_s: the gradient
+// sync that waits for stage s), the longest path of a graph whose nodes are
+// the ops.  Times are integers carried exactly in fp64.
+//
+// Four things make that path cheap:
+//  * Potentials.  Measured from phi_s = f_0 + sum_{j<s} (c_j + f_{j+1}) -- the
+//    end of F(s, 0) -- and B from phi_s + b_s, the edges F(s-1,m) -> F(s,m) and
+//    F(s,.) -> B(s,.) cost nothing, B(s,.) -> F(s,.) costs a_s = f_s + b_s and
+//    B(s+1,i) -> B(s,i) costs d_s = 2 c_s + f_{s+1} + b_{s+1}.  A steady
+//    iteration (a backward, then a forward, on every stage, from the last to
+//    the first) is then
+//      B = max(F_s, B + d_s);  F_s = max(B + a_s, F_{s-1})
+//    -- 4 fp64 operations per stage (6 on the times themselves), with the S
+//    values F_s as the whole state; B is carried from stage to stage.
+//  * Warm-up in closed form.  Forward m <= W_s of stage s follows forwards
+//    only, and its longest path spends its m micro-batches at the slowest of
+//    the stages 0..s: F(s, m) = m max_{j<=s} f_j.  The iteration above starts
+//    from F_s = F(s, min(S-1-s, M-1)).
+//  * Drain from the end.  After F(s, M-1) a stage runs backwards only: e_s is
+//    the longest path from B(s, M-1-min(S-1-s, M-1)) to the end of the
+//    iteration, syncs included, found backwards before the loop; the schedule
+//    ends with T = max_s B_s + e_s.
+//  * Periodic regime.  One iteration maps the state to maxima of (component +
+//    constant) terms, so adding a constant lam to every component adds lam to
+//    every component of the result: once an iteration advances every
+//    component by the same lam, every later one does too, and the remaining r
+//    steady iterations collapse into F += r lam, exactly.
+// In fp64 every value is at most T: if T stays below 2^53 nothing was rounded,
+// otherwise the pipeline is redone in u64.
 typedef uint64_t StageRec[kMaxStages][kRecWords];
 
 __device__ __forceinline__ double vmax(double a, double b) { return __builtin_fmax(a, b); }
 __device__ __forceinline__ uint64_t vmax(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
-// Periodic regime.  One steady iteration maps the state x = (out_f[0..S-2],
-// last[0..S-1]) to a max of (component + constant) terms, so adding a constant
-// lam to every component of x adds lam to every component of the result.
-// Hence once an iteration advances every component by the same lam, every
-// later one does too, and the remaining r steady iterations collapse into
-// x += r * lam, exactly (in fp64 every value stays below 2^53 or the pipeline
-// is redone in u64).  On the workloads here most schedules reach that regime
-// within a few iterations after the warm-up, against a hundred or more
-// micro-batches.  A wave waits at most kPeriodicBudget steady iterations for
-// its lanes; a lane still aperiodic by then is deferred to a full-loop pass,
-// so one aperiodic schedule does not hold 63 periodic ones.
+// A wave waits at most kPeriodicBudget steady iterations for its lanes; a lane
+// still aperiodic by then is deferred to a full-loop pass, so one aperiodic
+// schedule does not hold 63 periodic ones.
 constexpr int kPeriodicBudget = 40;
 
 template <int S, typename V>
-__device__ __forceinline__ void steady_iter(const V (&f)[S], const V (&b)[S], const V (&c)[S], V (&out_f)[S],
-                                            V (&last)[S]) {
-#pragma unroll
-  for (int s = S - 1; s >= 0; --s) {
-    const V st = s == 0 ? last[0] : vmax(last[s], out_f[s - 1] + c[s - 1]);
-    out_f[s] = st + f[s];
-    const V sb = s == S - 1 ? out_f[s] : vmax(out_f[s], last[s + 1] + c[s]);
-    last[s] = sb + b[s];
-  }
-}
+struct Chain {
+  V a[S], d[S], e[S], f[S];   // d[S-1] unused
+};
 
-// kJump: take the periodic shortcut; then `skipped` returns the steady
-// iterations it skipped, or -1 if the lane is deferred (result not computed).
-// Returns false for a deferred lane; else last[s] = end of stage s's last op.
-template <int S, typename V, bool kJump, bool kFallback = false>
-__device__ __forceinline__ bool pipe(const V (&f)[S], const V (&b)[S], const V (&c)[S], uint32_t M, int& skipped,
-                                     V (&last)[S]) {
-  V out_f[S];
+// The chain of a pipeline from its stages' forward, backward and hop times and
+// syncs.  kZb, the zero-bubble order (ZB-H1, Qi et al. 2024): b is the
+// input-gradient pass, w the weight-gradient pass; stage s runs W(s, i - s)
+// right after B(s, i) once i >= s, and its last min(s, M) W passes at the end.
+// A W only delays its stage, so it adds w to a_s (from iteration s on), to the
+// backwards-only edges of the drain and, min(s + 1, M) times, to the end.
+template <int S, typename V, bool kZb>
+__device__ __forceinline__ void reduce_chain(const V (&f)[S], const V (&b)[S], const V (&w)[S], const V (&c)[S],
+                                             const V (&x)[S], uint32_t M, Chain<S, V>& h) {
+  const int m_ = (int)M;
+#pragma unroll
+  for (int s = 0; s < S; ++s) h.d[s] = s + 1 < S ? c[s] + c[s] + f[s + 1] + b[s + 1] : (V)0;
+  V phi = 0;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
-    out_f[s] = 0;
-    last[s] = 0;
+    phi += s ? c[s - 1] + f[s] : f[0];
+    V y = phi + b[s] + x[s];
+    if (kZb) y += (V)(s + 1 < m_ ? s + 1 : m_) * w[s];
+    h.e[s] = s ? vmax(y, h.e[s - 1] + h.d[s - 1]) : y;
   }
-  const int m_ = (int)M;
 #pragma unroll
-  for (int m = 0; m < S - 1; ++m) {
-    if (m < m_) {
+  for (int k = 1; k < S; ++k) {
+    if (k < m_) {
 #pragma unroll
-      for (int s = 0; s < S - 1 - m; ++s) {
-        const V st = s == 0 ? last[0] : vmax(last[s], out_f[s - 1] + c[s - 1]);
-        out_f[s] = st + f[s];
-        last[s] = out_f[s];
+      for (int s = 0; s <= S - 1 - k; ++s) {
+        V y = h.e[s] + b[s];
+        if (kZb) y += m_ - 1 - k >= s ? w[s] : (V)0;
+        h.e[s] = s ? vmax(y, h.e[s - 1] + h.d[s - 1]) : y;
       }
     }
   }
-  int left = m_ - (S - 1);
-  skipped = 0;
-  if (kJump) {
-    int budget = kPeriodicBudget;
-    while (left >= 2 && budget > 0) {
-      steady_iter<S, V>(f, b, c, out_f, last);
-      // second iteration of the pair: does every state value advance by lam?
-      bool same = true;
-      V lam = 0;
+  V fm = 0;
 #pragma unroll
-      for (int s = S - 1; s >= 0; --s) {
-        const V st = s == 0 ? last[0] : vmax(last[s], out_f[s - 1] + c[s - 1]);
-        const V nf = st + f[s];
-        if (s < S - 1) same = same && nf - out_f[s] == lam;
-        out_f[s] = nf;
-        const V nl = (s == S - 1 ? nf : vmax(nf, last[s + 1] + c[s])) + b[s];
-        if (s == S - 1) lam = nl - last[s];
-        else same = same && nl - last[s] == lam;
-        last[s] = nl;
-      }
-      left -= 2;
-      budget -= 2;
-      if (same) {
-        const V k = (V)left * lam;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-          out_f[s] += k;
-          last[s] += k;
-        }
-        skipped = left;
-        left = 0;
-      }
-    }
-    if (left == 1) {
-      steady_iter<S, V>(f, b, c, out_f, last);
-      left = 0;
-    }
-    if (kFallback) {
-      // still aperiodic after the budget: the rest of the steady loop here
-      for (; left > 0; --left) steady_iter<S, V>(f, b, c, out_f, last);
-    } else if (left > 0) {
-      skipped = -1;
-      return false;
-    }
-  } else {
-    // two iterations per trip: the next iteration's upper stages overlap
-    // this one's backward chain
-#pragma unroll 2
-    for (int i = 0; i < left; ++i) steady_iter<S, V>(f, b, c, out_f, last);
+  for (int s = 0; s < S; ++s) {
+    fm = vmax(fm, f[s]);
+    h.a[s] = f[s] + b[s] + (kZb ? w[s] : (V)0);
+    h.f[s] = (V)(S - 1 - s < m_ - 1 ? S - 1 - s : m_ - 1) * fm;
   }
-#pragma unroll
-  for (int tr = 0; tr < S - 1; ++tr) {
-    if (tr >= S - 1 - m_) {
-#pragma unroll
-      for (int s = S - 1; s >= 0; --s) {
-        if (s > tr) {
-          const V st = vmax(last[s], out_f[s - 1] + c[s - 1]);
-          out_f[s] = st + f[s];
-          const V sb = s == S - 1 ? out_f[s] : vmax(out_f[s], last[s + 1] + c[s]);
-          last[s] = sb + b[s];
-        } else {
-          last[s] = (s == S - 1 ? last[s] : vmax(last[s], last[s + 1] + c[s])) + b[s];
-        }
-      }
-    }
-  }
-  return true;
 }
 
-// Zero-bubble order (ZB-H1, Qi et al. 2024): pipe's evaluation order with a
-// stage's backward pass split into bi, the input gradient stage s-1 waits
-// for (eb = its end), and w, the weight gradient (half of the backward
-// compute; the MoE all-to-all stays in bi).  After B(s, i) stage s runs
-// W(s, i - s) once i >= s -- a pure delay on the stage, its B having run
-// before -- and its last min(s, M) W passes at the end.  From i = S - 1 on
-// every steady iteration runs every stage's W, so the same map repeats and
-// the periodic shortcut applies as in pipe (state out_f[0..S-2],
-// last[0..S-1]; the B end of stage s + 1 is read only by stage s, right
-// after, in the same iteration, so it is one carried value).  kJump:
-// shortcut pairs within the budget, then the whole loop; otherwise the
-// whole loop.
-template <int S, typename V>
-__device__ __forceinline__ void zb_iter(const V (&f)[S], const V (&bi)[S], const V (&w)[S], const V (&c)[S], int i,
-                                        int tr, V (&out_f)[S], V (&last)[S]) {
-  V eb = 0;
+// Iteration i on stages S-1 .. lo (lo = 0: a steady iteration).  kZb: before
+// iteration s stage s has no W to run yet.
+template <int S, typename V, bool kZb>
+__device__ __forceinline__ V chain_iter(Chain<S, V>& h, const V (&w)[S], int i, int lo) {
+  V B = 0;
 #pragma unroll
   for (int s = S - 1; s >= 0; --s) {
-    if (s > tr) {   // the stage still runs a forward in this iteration
-      const V st = s == 0 ? last[0] : vmax(last[s], out_f[s - 1] + c[s - 1]);
-      out_f[s] = st + f[s];
-      const V sb = s == S - 1 ? out_f[s] : vmax(out_f[s], eb + c[s]);
-      eb = sb + bi[s];
-    } else {
-      eb = (s == S - 1 ? last[s] : vmax(last[s], eb + c[s])) + bi[s];
+    if (s >= lo) {
+      B = s == S - 1 ? h.f[s] : vmax(h.f[s], B + h.d[s]);
+      const V n = B + (kZb ? (i >= s ? h.a[s] : h.a[s] - w[s]) : h.a[s]);
+      h.f[s] = s ? vmax(n, h.f[s - 1]) : n;
     }
-    last[s] = i >= s ? eb + w[s] : eb;
+  }
+  return B;
+}
+
+// The steady iterations with the periodic shortcut, checked on the second
+// iteration of each pair: `left` iterations on entry, those not run on return
+// (0 unless the budget ran out).
+template <int S, typename V>
+__device__ __forceinline__ void chain_jump(Chain<S, V>& h, int& left, int budget, int& skipped) {
+  while (left >= 2 && budget > 0) {
+    chain_iter<S, V, false>(h, h.a, 0, 0);
+    bool same = true;
+    V lam = 0, B = 0;
+#pragma unroll
+    for (int s = S - 1; s >= 0; --s) {
+      B = s == S - 1 ? h.f[s] : vmax(h.f[s], B + h.d[s]);
+      const V n = s ? vmax(B + h.a[s], h.f[s - 1]) : B + h.a[s];
+      if (s == S - 1) lam = n - h.f[s];
+      else same = same && n - h.f[s] == lam;
+      h.f[s] = n;
+    }
+    left -= 2;
+    budget -= 2;
+    if (same) {
+      const V k = (V)left * lam;
+#pragma unroll
+      for (int s = 0; s < S; ++s) h.f[s] += k;
+      skipped = left;
+      left = 0;
+    }
+  }
+  if (left == 1) {
+    chain_iter<S, V, false>(h, h.a, 0, 0);
+    left = 0;
   }
 }
 
-template <int S, typename V, bool kJump, bool kFallback = false>
-__device__ __forceinline__ bool pipe_zb(const V (&f)[S], const V (&bi)[S], const V (&w)[S], const V (&c)[S], uint32_t M,
-                                        int& skipped,
-                                        V (&last)[S]) {
-  V out_f[S];
-#pragma unroll
-  for (int s = 0; s < S; ++s) out_f[s] = last[s] = 0;
+// After the steady iterations: stage t runs its last pair in step t, and the
+// iteration ends with e_t after its next backward.  With M < S the first
+// stages have run all their forwards before their first backward: their
+// backwards follow step S - M's.
+template <int S, typename V, bool kZb>
+__device__ __forceinline__ V chain_end(Chain<S, V>& h, const V (&w)[S], uint32_t M) {
   const int m_ = (int)M;
+  V T = 0;
 #pragma unroll
-  for (int m = 0; m < S - 1; ++m) {
-    if (m < m_) {
+  for (int t = 0; t < S; ++t) {
+    if (t >= S - m_) {
+      V B = t == S - 1 ? (V)0 : chain_iter<S, V, kZb>(h, w, m_ - S + t, t + 1);
+      B = t == S - 1 ? h.f[t] : vmax(h.f[t], B + h.d[t]);
+      T = vmax(T, B + h.e[t]);
+      if (t > 0 && t == S - m_) {
 #pragma unroll
-      for (int s = 0; s < S - 1 - m; ++s) {
-        const V st = s == 0 ? last[0] : vmax(last[s], out_f[s - 1] + c[s - 1]);
-        out_f[s] = st + f[s];
-        last[s] = out_f[s];
+        for (int s = S - 2; s >= 0; --s)
+          if (s < t) {
+            B = vmax(h.f[s], B + h.d[s]);
+            T = vmax(T, B + h.e[s]);
+          }
       }
     }
   }
-  const int left = m_ - (S - 1);
+  return T;
+}
+
+// The time of a chain of M micro-batches.  kJump: with the periodic shortcut;
+// `skipped` returns the steady iterations it skipped.  Returns false for a
+// lane still aperiodic after the budget (T not computed), unless kFallback,
+// which runs the rest of the loop in place.
+template <int S, typename V, bool kZb, bool kJump, bool kFallback = false>
+__device__ __forceinline__ bool chain_time(Chain<S, V>& h, const V (&w)[S], uint32_t M, int& skipped, V& T) {
+  int left = (int)M - S;
   skipped = 0;
-  int i = 0;
-  for (; i < left && i < S - 1; ++i) zb_iter<S, V>(f, bi, w, c, i, -1, out_f, last);
-  int rem = left - i;
-  if (kJump) {
-    int budget = kPeriodicBudget;
-    while (rem >= 2 && budget > 0) {
-      zb_iter<S, V>(f, bi, w, c, S, -1, out_f, last);
-      bool same = true;
-      V lam = 0, eb = 0;
-#pragma unroll
-      for (int s = S - 1; s >= 0; --s) {
-        const V st = s == 0 ? last[0] : vmax(last[s], out_f[s - 1] + c[s - 1]);
-        const V nf = st + f[s];
-        if (s < S - 1) same = same && nf - out_f[s] == lam;
-        out_f[s] = nf;
-        const V sb = s == S - 1 ? nf : vmax(nf, eb + c[s]);
-        eb = sb + bi[s];
-        const V nl = eb + w[s];
-        if (s == S - 1) lam = nl - last[s];
-        else same = same && nl - last[s] == lam;
-        last[s] = nl;
-      }
-      rem -= 2;
-      budget -= 2;
-      if (same) {
-        const V k = (V)rem * lam;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-          out_f[s] += k;
-          last[s] += k;
-        }
-        skipped = rem;
-        rem = 0;
-      }
-    }
-    if (rem == 1) {
-      zb_iter<S, V>(f, bi, w, c, S, -1, out_f, last);
-      rem = 0;
-    }
-    if (rem > 0 && !kFallback) {   // still aperiodic: the deferred pass runs the whole loop
-      skipped = -1;
-      return false;
-    }
+  if (kZb) {   // from iteration S - 1 on every stage runs its W
+    int i = 0;
+    for (; i < left && i < S - 1; ++i) chain_iter<S, V, true>(h, w, i, 0);
+    left -= i;
   }
-  for (; rem > 0; --rem) zb_iter<S, V>(f, bi, w, c, S, -1, out_f, last);
-#pragma unroll
-  for (int tr = 0; tr < S - 1; ++tr)
-    if (tr >= S - 1 - m_) zb_iter<S, V>(f, bi, w, c, m_ - S + 1 + tr, tr, out_f, last);
-#pragma unroll
-  for (int s = 0; s < S; ++s) last[s] += (V)(s < m_ ? s : m_) * w[s];
+  if (kJump) {
+    chain_jump<S, V>(h, left, kPeriodicBudget, skipped);
+    if (!kFallback && left > 0) return false;
+  }
+  for (; left > 0; --left) chain_iter<S, V, false>(h, h.a, 0, 0);
+  T = chain_end<S, V, kZb>(h, w, M);
   return true;
 }
 
@@ -1759,81 +1700,62 @@ struct EvalBufs {
 // stay aperiodic).  With a context that enables two-level collectives, whose
 // sync code the first pass lacks, it sends every other shared-layout
 // pipeline to the deferred lists.
-// DP tail of a plan-sorted pipeline (first pass, shared layout, G > 1 classes
-// on G adjacent lanes): the lane of class c costs the syncs of stages c,
-// c + G, ... (each the same for every class of the plan) into its plan's row
-// of the wavefront's LDS exchange area, then every lane of the plan reads
-// the whole row.  Every lane of the plan takes part, deferred ones included
-// (the syncs do not depend on the recurrence).
-template <int S, int kMode, bool kHier>
-__device__ __forceinline__ double grouped_tail(const Tab& t, const Hot<kMode>& h, const Plan& p, const double (&last)[S],
-                                               double* xw, const uint32_t* bw = nullptr) {
-  const uint32_t G = p.G, lane = threadIdx.x & 63u;
-  double* x = xw + (lane / G) * xchg_row(S);
-  const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
-  // bw: every lane's stage placements from its setup (S per lane); the
-  // plan's G lanes start at lane - c
-  const uint32_t* bl = bw ? bw + (lane - p.c) * S : nullptr;
-  if (bw) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-  for (uint32_t s = p.c; s < (uint32_t)S; s += G) {
-    const uint32_t lo = s ? cut_at(p, s - 1) : 0;
-    x[s] = (double)stage_dp<kMode, kHier>(t, h, p, s, cut_at(p, s) - lo, rp, rpe, bl);
-  }
-  // the rows are written and read by the lanes of one wavefront, whose LDS
+// DP syncs of a plan-sorted pipeline (first and variant passes, shared layout,
+// G classes on G adjacent lanes): the lane of class c costs the syncs of
+// stages c, c + G, ... (each the same for every class of the plan) into its
+// plan's column of the wavefront's LDS exchange area (x[64 s + first lane of
+// the plan], the syncs of stage s); every lane of the plan reads the column.
+__device__ __forceinline__ void wave_sync_lds() {
+  // the area is written and read by the lanes of one wavefront, whose LDS
   // accesses complete in order; the fences keep the compiler from moving
-  // the reads above the writes of the other lanes
+  // reads above the writes of the other lanes
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  double T = 0;
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const double v = last[s] + x[s];
-    T = v > T ? v : T;
+}
+
+template <int S, int kMode, bool kHier>
+__device__ __forceinline__ void grouped_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, double* x,
+                                              uint32_t lead, const uint32_t* bw = nullptr) {
+  const uint32_t G = p.G;
+  const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
+  // bw: every lane's stage placements from its setup (S per lane)
+  const uint32_t* bl = bw ? bw + lead * S : nullptr;
+  if (bw) wave_sync_lds();
+  for (uint32_t s = p.c; s < (uint32_t)S; s += G) {
+    const uint32_t lo = s ? cut_at(p, s - 1) : 0;
+    x[s * 64 + lead] = (double)stage_dp<kMode, kHier>(t, h, p, s, cut_at(p, s) - lo, rp, rpe, bl);
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  return T;
+  wave_sync_lds();
 }
 
 // The same for an overlapped plan (variant pass): the lane of class c costs
 // the syncs of stages c, c + G, ... (one layer's bucket per stage, the
-// embedding's and the head's) into its plan's row, then every lane walks its
-// own buckets' readiness against them.
+// embedding's and the head's, in columns S and S + 1) into its plan's column,
+// then every lane walks its own buckets' readiness against them and leaves
+// the tail of stage s in its own column.
 template <int S, int kMode>
-__device__ __forceinline__ double grouped_overlap_tail(const Tab& t, const Hot<kMode>& h, const Plan& p,
-                                                       double (&last)[S], double* xw) {
+__device__ __forceinline__ void grouped_overlap_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, double* x,
+                                                      uint32_t lead) {
   const uint32_t G = p.G, lane = threadIdx.x & 63u;
-  double* x = xw + (lane / G) * xchg_row(S);
   const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
   for (uint32_t s = p.c; s < (uint32_t)S; s += G) {
     const OvlSyncs y = overlap_syncs<kMode, true>(t, h, p, s, rp, rpe);
-    x[s] = (double)y.dl;
-    if (s == 0) x[xchg_row(S) - 2] = (double)y.demb;
-    if (s == (uint32_t)S - 1) x[xchg_row(S) - 1] = (double)y.dhead;
+    x[s * 64 + lead] = (double)y.dl;
+    if (s == 0) x[S * 64 + lead] = (double)y.demb;
+    if (s == (uint32_t)S - 1) x[(S + 1) * 64 + lead] = (double)y.dhead;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const OvlSyncs ends = {0, (uint64_t)x[xchg_row(S) - 2], (uint64_t)x[xchg_row(S) - 1]};
-  double T = 0;
+  wave_sync_lds();
+  const OvlSyncs ends = {0, (uint64_t)x[S * 64 + lead], (uint64_t)x[(S + 1) * 64 + lead]};
   uint32_t lo = 0;
   for (uint32_t s = 0; s < (uint32_t)S; ++s) {
     const uint32_t hi = cut_at(p, s);
-    const OvlSyncs y = {(uint64_t)x[s], ends.demb, ends.dhead};
-    const double e = last[0] + (double)overlap_walk<kMode>(t, h, p, s, lo, hi, (uint32_t)(p.tc >> (4 * s)) & 15, y);
-    T = e > T ? e : T;
-#pragma unroll
-    for (int i = 0; i + 1 < S; ++i) last[i] = last[i + 1];
+    const OvlSyncs y = {(uint64_t)x[s * 64 + lead], ends.demb, ends.dhead};
+    const double e = (double)overlap_walk<kMode>(t, h, p, s, lo, hi, (uint32_t)(p.tc >> (4 * s)) & 15, y);
+    wave_sync_lds();   // every lane of the plan has read stage s's bucket
+    x[s * 64 + lane] = e;
     lo = hi;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  return T;
 }
 
 template <int S, bool kFull, int kMode, bool kHet, bool kOvl = false, bool kZb = false>
@@ -1842,51 +1764,47 @@ __device__ __forceinline__ void eval_one(const Tab& t, const Hot<kMode>& h, cons
   // plan-sorted pipelines of the first or the variant pass (shared layout)
   constexpr bool kGrouped = !kFull && !kHet;
   typename std::conditional<kZb, ZbSink<S>, RegSink<S>>::type r;
-  uint32_t M;
   const Plan p = load_plan<kHet>(e.packed, e.pcut, slot);
-  {
-    if (!kFull && !kHet && !kOvl && !kZb) {
-      // (overlap and zero-bubble plans left for the variant pass in k_eval)
-      if (t.ccl_hier) {
-        e.deferred[e.sstart[kMaxStages - S] + atomicAdd(&e.ctr[1 + kMaxStages - S], 1u)] = slot;
-        return;
-      }
+  if (!kFull && !kHet && !kOvl && !kZb) {
+    // (overlap and zero-bubble plans left for the variant pass in k_eval)
+    if (t.ccl_hier) {
+      e.deferred[e.sstart[kMaxStages - S] + atomicAdd(&e.ctr[1 + kMaxStages - S], 1u)] = slot;
+      return;
     }
-    M = class_mb(p);
-    if constexpr (kGrouped && !kZb)
-      if (bw) r.bs = bw + (threadIdx.x & 63u) * S;
-    class_setup<kMode, kHet>(t, h, p, slot & 3, r, nullptr);
   }
-  int skipped;
-  double last[S];
-  bool done = true;
+  const uint32_t M = class_mb(p), G = p.G;
+  if constexpr (kGrouped && !kZb)
+    if (bw) r.bs = bw + (threadIdx.x & 63u) * S;
+  class_setup<kMode, kHet>(t, h, p, slot & 3, r, nullptr);
+  Chain<S, double> ch;
+  {
+    double x[S];
+    if constexpr (kGrouped) {
+      const uint32_t lane = threadIdx.x & 63u, lead = lane - p.c;
+      if constexpr (kOvl) grouped_overlap_syncs<S, kMode>(t, h, p, xw, lead);
+      else grouped_syncs<S, kMode, kZb>(t, h, p, xw, lead, kZb ? nullptr : bw);
+#pragma unroll
+      for (int s = 0; s < S; ++s) x[s] = xw[s * 64 + (kOvl ? lane : lead)];
+      wave_sync_lds();
+    } else {
+      own_syncs<S, kMode, kHet, kOvl, true>(t, h, p, x, kHet ? e.hdp + (size_t)slot * kMaxStages : nullptr);
+    }
+    if constexpr (kZb) reduce_chain<S, double, true>(r.f, r.bi, r.w, r.c, x, M, ch);
+    else reduce_chain<S, double, false>(r.f, r.b, r.b, r.c, x, M, ch);
+  }
   // the first and variant passes take the periodic shortcut and defer the
   // lanes still aperiodic after the budget; the deferred pass runs the whole loop
-  if constexpr (kZb) done = pipe_zb<S, double, !kFull>(r.f, r.bi, r.w, r.c, M, skipped, last);
-  else done = pipe<S, double, !kFull>(r.f, r.b, r.c, M, skipped, last);
-  // With up to kKeepPlanS stages the plan stays in registers through the
-  // recurrence (whose state is small); longer pipelines read it again for
-  // the DP tail (an L2 hit) rather than hold it: the lane's own slot passed
-  // through a shuffle is opaque to the compiler, which would otherwise reuse
-  // the first load
-  constexpr int kKeepPlanS = 8;
-  const uint32_t slot2 = S <= kKeepPlanS ? slot : __shfl(slot, (int)(threadIdx.x & 63u));
-  double T;
-  const Plan p2 = S <= kKeepPlanS ? p : load_plan<kHet>(e.packed, e.pcut, slot2);
-  if (kGrouped && p2.G > 1) {   // G is the same in the whole wavefront
-    if constexpr (kOvl) T = grouped_overlap_tail<S, kMode>(t, h, p2, last, xw);
-    else T = grouped_tail<S, kMode, kZb>(t, h, p2, last, xw, kZb ? nullptr : bw);
-  } else {
-    T = done ? dp_tail<S, kMode, kHet, kOvl, kFull || kOvl || kZb>(t, h, p2, last,
-                                                                   kHet ? e.hdp + (size_t)slot2 * kMaxStages : nullptr)
-             : 0;
-  }
+  int skipped;
+  double T = 0;
+  bool done;
+  if constexpr (kZb) done = chain_time<S, double, true, !kFull>(ch, r.w, M, skipped, T);
+  else done = chain_time<S, double, false, !kFull>(ch, ch.a, M, skipped, T);
   if constexpr (kGrouped) {
     // the plan's G pipelines sit on adjacent lanes from a multiple of G, all
     // of them here: the first one stores the largest result of the finished
     // ones (one store per plan; the deferred and the u64 passes, later in
     // stream order, raise it with atomicMax)
-    const uint32_t G = p2.G, lane = threadIdx.x & 63u, lead = lane - lane % G;
+    const uint32_t lane = threadIdx.x & 63u, lead = lane - p.c;
     const bool mine = done && T < kExact;
     double v = mine ? T : 0;
     for (uint32_t c = 1; c < G; ++c) {
@@ -2188,7 +2106,7 @@ constexpr uint32_t kEvalThreads = 256;
 // each holding a full LDS allocation); the waves of the grid take the
 // group's 64-pipeline tiles in a fixed stride, heaviest tiles first.
 template <int GRP, int kMode, bool kHet>
-__global__ void __launch_bounds__(kEvalThreads) k_eval(Tab t, EvalBufs e) {
+__global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(Tab t, EvalBufs e) {
   constexpr int kTop = kMaxStages - 4 * GRP;   // stage counts kTop-3 .. kTop
   extern __shared__ uint4 lds[];
   const uint32_t lo = e.sstart[4 * GRP], hi = e.sstart[4 * GRP + 4];
@@ -2201,9 +2119,9 @@ __global__ void __launch_bounds__(kEvalThreads) k_eval(Tab t, EvalBufs e) {
   uint32_t* bw = nullptr;   // and its stage-placement cache, when the group has one
   if constexpr (!kHet) {
     char* const x0 = (char*)lds + (kMode < 2 ? t.lds_bytes : 0);
-    xw = (double*)x0 + (threadIdx.x >> 6) * xchg_wave(GRP);
+    xw = (double*)x0 + (threadIdx.x >> 6) * xchg_wave(GRP, false);
     if (GRP < 2 && ((t.bcache >> GRP) & 1))
-      bw = (uint32_t*)(x0 + xchg_bytes(GRP)) + (threadIdx.x >> 6) * bcache_words(GRP);
+      bw = (uint32_t*)(x0 + xchg_bytes(GRP, false)) + (threadIdx.x >> 6) * bcache_words(GRP);
   }
   for (uint32_t base = lo + blockIdx.x * kEvalThreads + (threadIdx.x & ~63u); base < hi; base += stride) {
     const uint32_t pos = base + (threadIdx.x & 63u);
@@ -2361,7 +2279,7 @@ __global__ void __launch_bounds__(kEvalThreads) k_variant(const Tab* __restrict_
   const Hot<kMode> h(t, lds);
   const uint32_t waves = gridDim.x * wpb;
   // the wavefront's row of the zero-bubble plans' DP exchange area (as k_eval's)
-  double* xw = (double*)((char*)lds + (kMode < 2 ? t.lds_bytes : 0)) + (threadIdx.x >> 6) * xchg_wave(GRP);
+  double* xw = (double*)((char*)lds + (kMode < 2 ? t.lds_bytes : 0)) + (threadIdx.x >> 6) * xchg_wave(GRP, true);
   for (uint32_t q = blockIdx.x * wpb + (threadIdx.x >> 6); q < tiles; q += waves) {
     const uint32_t j = (q >= q1) + (q >= q2) + (q >= q3);
     const uint32_t first = j == 0 ? 0 : j == 1 ? q1 : j == 2 ? q2 : q3;
@@ -2383,22 +2301,22 @@ __global__ void __launch_bounds__(kEvalThreads) k_variant(const Tab* __restrict_
 template <int S>
 __device__ __forceinline__ uint64_t redo_one(const StageRec& R, const uint64_t (&W)[kMaxStages], bool zb,
                                              uint32_t M) {
-  uint64_t f[S], b[S], w[S], c[S], last[S];
+  uint64_t f[S], b[S], w[S], c[S], x[S], T = 0;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     f[s] = R[s][0];
     w[s] = zb ? W[s] : 0;
     b[s] = R[s][1] - w[s];
     c[s] = R[s][2];
+    x[s] = R[s][3];
   }
-  // the periodic shortcut holds in any exact arithmetic: pairs within the
-  // budget, then the rest of the loop in place
+  // the zero-bubble chain with w = 0 is the plain one; the periodic shortcut
+  // holds in any exact arithmetic: pairs within the budget, then the rest of
+  // the loop in place
+  Chain<S, uint64_t> h;
   int skipped;
-  if (zb) pipe_zb<S, uint64_t, true, true>(f, b, w, c, M, skipped, last);
-  else pipe<S, uint64_t, true, true>(f, b, c, M, skipped, last);
-  uint64_t T = 0;
-#pragma unroll
-  for (int s = 0; s < S; ++s) T = vmax(T, last[s] + R[s][3]);
+  reduce_chain<S, uint64_t, true>(f, b, w, c, x, M, h);
+  chain_time<S, uint64_t, true, true, true>(h, w, M, skipped, T);
   return T;
 }
 

@@ -21,7 +21,7 @@ hipError_t launch_group_v(const Tab& t, const EvalArgs& a, uint32_t max_tasks, i
   const uint32_t need = nb > 0 ? (uint32_t)nb : 1, grid = 4 * t.grid_eval[g] < need ? 4 * t.grid_eval[g] : need;
   // the shared layout's plan-sorted groups add their plans' DP exchange area
   const size_t lds = (kMode < 2 ? t.lds_bytes : 0) +
-                    (!kHet ? xchg_bytes(g) + (((t.bcache >> g) & 1) ? bcache_bytes(g) : 0) : 0);
+                    (!kHet ? xchg_bytes(g, false) + (((t.bcache >> g) & 1) ? bcache_bytes(g) : 0) : 0);
   if (g == 0) k_eval<0, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(t, e);
   else if (g == 1) k_eval<1, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(t, e);
   else if (g == 2) k_eval<2, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(t, e);
@@ -40,7 +40,7 @@ hipError_t occupancy_first_v(int nb[4], size_t lds, uint32_t bcache) {
   const void* k[4] = {(const void*)k_eval<0, kMode, false>, (const void*)k_eval<1, kMode, false>,
                       (const void*)k_eval<2, kMode, false>, (const void*)k_eval<3, kMode, false>};
   for (int i = 0; i < 4; ++i) {
-    const size_t b = lds + xchg_bytes(i) + (((bcache >> i) & 1) ? bcache_bytes(i) : 0);
+    const size_t b = lds + xchg_bytes(i, false) + (((bcache >> i) & 1) ? bcache_bytes(i) : 0);
     hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[i], k[i], kEvalThreads, b);
     if (r != hipSuccess) return r;
   }
@@ -58,7 +58,7 @@ template <int kMode>
 hipError_t launch_variant_v(const Tab& t, const EvalArgs& a, int g, hipStream_t s) {
   const EvalBufs e = eval_bufs(a);
   const uint32_t grid = t.grid_variant[g];
-  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) + xchg_bytes(g);
+  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) + xchg_bytes(g, true);
   if (g == 0) k_variant<0, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
   else if (g == 1) k_variant<1, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
   else if (g == 2) k_variant<2, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
@@ -72,7 +72,7 @@ hipError_t occupancy_variant_v(int nb[4], size_t lds) {
   const void* k[4] = {(const void*)k_variant<0, kMode>, (const void*)k_variant<1, kMode>,
                       (const void*)k_variant<2, kMode>, (const void*)k_variant<3, kMode>};
   for (int i = 0; i < 4; ++i) {
-    hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[i], k[i], kEvalThreads, lds + xchg_bytes(i));
+    hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[i], k[i], kEvalThreads, lds + xchg_bytes(i, true));
     if (r != hipSuccess) return r;
   }
   return hipSuccess;

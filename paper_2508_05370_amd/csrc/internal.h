@@ -36,14 +36,14 @@ constexpr uint32_t kGroupPad = 64 * kSuperBuckets;
 constexpr uint32_t kNoSlot = 0xffffffffu;
 __host__ __device__ constexpr uint32_t plans_per_wave(uint32_t G) { return G == 3 ? 21 : 64 / G; }
 // LDS of the first and variant passes over plan-sorted pipelines: per
-// wavefront, a row of DP syncs for each of up to 32 plans (one per stage of
-// the kernel's largest stage count, and two more for the embedding's and the
-// head's buckets of an overlapped sync), exchanged between the lanes of each
-// plan
-constexpr uint32_t kXchgPlans = 32;
-__host__ __device__ constexpr uint32_t xchg_row(uint32_t S) { return (S + 3) / 4 * 4 + 2; }
-__host__ __device__ constexpr uint32_t xchg_wave(int group) { return kXchgPlans * xchg_row(kMaxStages - 4 * group); }
-__host__ __device__ constexpr uint32_t xchg_bytes(int group) { return 4 * xchg_wave(group) * 8; }
+// wavefront one column of 64 doubles per stage (up to the kernel's largest
+// stage count, and in the variant pass two more for the embedding's and the
+// head's buckets of an overlapped sync), where the lanes of a plan exchange
+// its stages' syncs.
+__host__ __device__ constexpr uint32_t xchg_wave(int group, bool variant) {
+  return 64u * ((uint32_t)(kMaxStages - 4 * group) + (variant ? 2u : 0u));
+}
+__host__ __device__ constexpr uint32_t xchg_bytes(int group, bool variant) { return 4 * xchg_wave(group, variant) * 8; }
 // The first pass of the two long stage-count groups keeps each lane's stage
 // placements (first device in the pool, u32 per stage) in LDS from setup to
 // the DP tail, where the plan's lanes read each other's instead of counting
