@@ -19,14 +19,12 @@ hipError_t launch_plan_syncs(const Tab& t, const PackedPlan* packed, const uint4
                              int64_t n, uint64_t* hdp, uint32_t* pc, uint32_t* perm, hipStream_t s);
 hipError_t launch_stages(const Tab& t, const PackedPlan* packed, const uint4* pcut, const uint32_t* meta, int64_t n,
                          uint64_t* out_stage, hipStream_t s);
-hipError_t launch_scan(const uint32_t* hist, uint32_t* cursor, uint32_t* sstart, uint32_t* sbase, bool grouped,
-                       uint32_t* ids, hipStream_t s);
-hipError_t launch_scatter(const uint16_t* keys, uint32_t nslots, uint32_t* cursor, const uint32_t* sbase, bool grouped,
-                          uint32_t* ids, hipStream_t s);
-hipError_t launch_first(const Tab& t, const EvalArgs& a, uint32_t max_tasks, hipStream_t s);
-hipError_t launch_group(const Tab& t, const EvalArgs& a, uint32_t max_tasks, int g, hipStream_t s);
-hipError_t launch_variant(const Tab& t, const EvalArgs& a, int g, hipStream_t s);
-hipError_t launch_deferred(const Tab& t, const EvalArgs& a, uint32_t max_tasks, hipStream_t s);
+hipError_t launch_scan(const Work& w, bool grouped, hipStream_t s);
+hipError_t launch_scatter(const Work& w, uint32_t n, hipStream_t s);
+hipError_t launch_group(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s);
+hipError_t launch_variant(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s);
+hipError_t launch_il(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s);
+hipError_t launch_rest(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s);
 hipError_t launch_argmin(const uint64_t* t, int64_t n, int64_t base, sim_best* b, hipStream_t s);
 hipError_t launch_best_reduce(const sim_best* in, int64_t n, sim_best* out, hipStream_t s);
 hipError_t launch_node_probe(double* sink, int blocks, int iters, hipStream_t s);
@@ -238,11 +236,35 @@ static bool side_streams(sim_ctx* c, hipStream_t s, SideStreams* out) {
   return true;
 }
 
+// Clear the counters, check and pack the plans, and sort them (events: the
+// call may record timing events).
+static hipError_t order_chunk(sim_ctx* c, const Work& W, const sim_plans& p, int64_t n, uint64_t* out, bool events,
+                              hipStream_t s) {
+  const bool het = p.chdr != nullptr;
+  EventPair ev;
+  hipError_t e = launch_fill32(W.hist, kCounters, 0, s);
+  const bool timed = events && e == hipSuccess && begin_event(c, 1, s, &ev);
+  if (e == hipSuccess) e = launch_prep(c->tab, p, n, out, W.packed, W.pcut, W.meta, W.hist, W.keys, s);
+  if (timed) end_event(c, 1, s, &ev);
+  if (e == hipSuccess && het)
+    e = launch_plan_syncs(c->tab, W.packed, W.pcut, W.meta, n, W.hdp, W.ctr + kEvalCounters, W.perm, s);
+  if (e == hipSuccess) e = launch_scan(W, !het, s);
+  if (e == hipSuccess) e = launch_scatter(W, (uint32_t)(het ? n * 4 : n), s);
+  return e;
+}
+static EvalBufs eval_bufs(const sim_ctx* c, const Work& W, uint64_t* out) {
+  return {W.packed, W.pcut, W.hdp, W.order, W.gstart, W.tstart, W.cinfo, out, W.ctr, W.ovf, W.cont,
+          c->timing ? (unsigned long long*)c->skipped_ops : nullptr, c->dtab};
+}
+// Tiles of n plans at most: the pipelines' lanes, and a partly filled tile per group.
+static uint32_t max_tiles(int64_t n) { return (uint32_t)(n * kMaxClasses / 63 + kGroups + 1); }
+
 // Chunks of kChunk plans (one chunk up to 2 kChunk).  With more than one chunk, the four stage-count
 // groups of chunk i's first pass run on two side streams (paired as
-// kGroupStream says), and its deferred pass on a third that waits for them,
-// while the call's stream packs and sorts chunk i + 1.  The two workspaces alternate; the call's
-// stream waits for chunk i's deferred pass before reusing its workspace for
+// kGroupStream says), and its interleaved plans, continuation lists and redo
+// on a third that waits for them, while the call's stream packs and sorts
+// chunk i + 1.  The two workspaces alternate; the call's
+// stream waits for chunk i's last pass before reusing its workspace for
 // chunk i + 2 and, at the end, for the last one.
 extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uint64_t* out, void* stream) {
   if (!c || !plans_ok(plans, n) || (n > 0 && !out)) return SIM_EINVAL;
@@ -274,10 +296,11 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
   }
   void* ws = nullptr;
   const bool het = plans->chdr != nullptr;
-  hipError_t e = hipMallocFromPoolAsync(&ws, nbuf * work_bytes(ch, het), c->pool, s);
+  const size_t bytes = work_bytes(ch, het, kContPerPlan);
+  hipError_t e = hipMallocFromPoolAsync(&ws, nbuf * bytes, c->pool, s);
   if (e != hipSuccess) ws = nullptr;
   Work w[2];
-  for (int j = 0; ws && j < nbuf; ++j) w[j] = carve((char*)ws + j * work_bytes(ch, het), ch, het);
+  for (int j = 0; ws && j < nbuf; ++j) w[j] = carve((char*)ws + j * bytes, ch, het, kContPerPlan);
   EventPair call, ev;
   bool tcall = ws && begin_event(c, 2, s, &call);
   bool joined = true;
@@ -291,23 +314,14 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
     if (p.cut) p.cut += off;
     if (het) { p.chdr += off; p.ccut += off; }
     if (i >= 2) e = hipStreamWaitEvent(s, done(b), 0);
-    if (e == hipSuccess) e = launch_fill32(W.hist, kCounters, 0, s);
-    bool t1 = e == hipSuccess && begin_event(c, 1, s, &ev);
-    if (e == hipSuccess) e = launch_prep(c->tab, p, cn, out + off, W.packed, W.pcut, W.meta, W.hist, W.keys, s);
-    if (t1) end_event(c, 1, s, &ev);
-    // (the plan order goes to the variant-tile array, unused in this layout until the deferred sort)
-    if (e == hipSuccess && het)
-      e = launch_plan_syncs(c->tab, W.packed, W.pcut, W.meta, cn, W.hdp, W.ctr + kEvalCounters, W.vlist, s);
-    // shared-layout calls sort plans by plan: the scan and the scatter mark
-    // the padding lanes
-    if (e == hipSuccess) e = launch_scan(W.hist, W.cursor, W.sstart, W.sbase, !het, W.ids, s);
-    if (e == hipSuccess) e = launch_scatter(W.keys, (uint32_t)(cn * 4), W.cursor, W.sbase, !het, W.ids, s);
-    const EvalArgs a = {W.packed, W.pcut, W.hdp, W.meta, W.ids, W.sstart, out + off, W.ctr, W.deferred, W.vlist,
-                        c->timing ? c->skipped_ops : nullptr, c->dtab};
+    if (e == hipSuccess) e = order_chunk(c, W, p, cn, out + off, true, s);
+    const EvalBufs a = eval_bufs(c, W, out + off);
+    const uint32_t tiles = max_tiles(cn);
     EventPair e0;
     bool t0 = e == hipSuccess && begin_event(c, 0, s, &e0);
     if (nbuf == 1) {
-      if (e == hipSuccess) e = launch_first(c->tab, a, (uint32_t)(cn * 4), s);
+      for (int g = 0; g < 4 && e == hipSuccess; ++g) e = launch_group(c->tab, a, tiles, g, s);
+      for (int g = 0; g < 4 && e == hipSuccess; ++g) e = launch_variant(c->tab, a, tiles, g, s);
       if (t0) end_event(c, 0, s, &e0);
       if (e != hipSuccess) break;
     } else {
@@ -316,8 +330,8 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
       for (int g = 0; g < 4 && e == hipSuccess; ++g) {
         const hipStream_t gs = side.grp[kGroupStream[g]];
         e = hipStreamWaitEvent(gs, sorted(b), 0);
-        if (e == hipSuccess) e = launch_group(c->tab, a, (uint32_t)(cn * 4), g, gs);
-        if (e == hipSuccess) e = launch_variant(c->tab, a, g, gs);
+        if (e == hipSuccess) e = launch_group(c->tab, a, tiles, g, gs);
+        if (e == hipSuccess) e = launch_variant(c->tab, a, tiles, g, gs);
         if (e == hipSuccess) e = hipEventRecord(fin(b, g), gs);
         if (e == hipSuccess) e = hipStreamWaitEvent(aux, fin(b, g), 0);
       }
@@ -325,7 +339,8 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
       if (e != hipSuccess) break;
     }
     bool t3 = begin_event(c, 3, aux, &ev);
-    e = launch_deferred(c->tab, a, (uint32_t)(cn * 4), aux);
+    e = launch_il(c->tab, a, tiles, aux);
+    if (e == hipSuccess) e = launch_rest(c->tab, a, tiles, aux);
     if (t3) end_event(c, 3, aux, &ev);
     if (nbuf == 2) {
       const hipError_t r = hipEventRecord(done(b), aux);
@@ -368,17 +383,14 @@ extern "C" int sim_eval_plans_noalloc(sim_ctx* c, const sim_plans* plans, int64_
   if (hipSetDevice(c->device) != hipSuccess) return SIM_EHIP;
   void* ws = nullptr;
   if (noalloc_scratch(c->device, &ws) != 0) return SIM_EHIP;
-  const Work W = carve(ws, n, het);
-  hipError_t e = launch_fill32(W.hist, kCounters, 0, s);
-  if (e == hipSuccess) e = launch_prep(c->tab, *plans, n, out, W.packed, W.pcut, W.meta, W.hist, W.keys, s);
-  if (e == hipSuccess && het)
-    e = launch_plan_syncs(c->tab, W.packed, W.pcut, W.meta, n, W.hdp, W.ctr + kEvalCounters, W.vlist, s);
-  if (e == hipSuccess) e = launch_scan(W.hist, W.cursor, W.sstart, W.sbase, !het, W.ids, s);
-  if (e == hipSuccess) e = launch_scatter(W.keys, (uint32_t)(n * 4), W.cursor, W.sbase, !het, W.ids, s);
-  const EvalArgs a = {W.packed, W.pcut, W.hdp, W.meta, W.ids, W.sstart, out, W.ctr, W.deferred, W.vlist,
-                      c->timing ? c->skipped_ops : nullptr, c->dtab};
-  if (e == hipSuccess) e = launch_first(c->tab, a, (uint32_t)(n * 4), s);
-  if (e == hipSuccess) e = launch_deferred(c->tab, a, (uint32_t)(n * 4), s);
+  const Work W = carve(ws, n, het, kContPerPlanNoAlloc);
+  hipError_t e = order_chunk(c, W, *plans, n, out, false, s);
+  const EvalBufs a = eval_bufs(c, W, out);
+  const uint32_t tiles = max_tiles(n);
+  for (int g = 0; g < 4 && e == hipSuccess; ++g) e = launch_group(c->tab, a, tiles, g, s);
+  for (int g = 0; g < 4 && e == hipSuccess; ++g) e = launch_variant(c->tab, a, tiles, g, s);
+  if (e == hipSuccess) e = launch_il(c->tab, a, tiles, s);
+  if (e == hipSuccess) e = launch_rest(c->tab, a, tiles, s);
   // a stream under graph capture records nothing here: the launches become
   // graph nodes, and the caller owns the graph's completion
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

@@ -4,38 +4,37 @@
 // Data flow of one chunk of plans (all in HBM):
 //   k_prep     one plan per lane: decode and check the plan, pack it into 80
 //              contiguous bytes, and count it per bucket: in the shared
-//              layout the whole plan by (stages, classes, longest
-//              micro-batch count), otherwise each pipeline (one per replica
-//              class) by its own.
-//   k_scan     one block: bucket offsets, longest pipelines first; a
-//              plan-sorted (stages, classes) group takes whole wavefronts.
-//   k_scatter  places the ids: a plan-sorted plan's G pipelines on adjacent
-//              lanes of one wavefront, so that a wavefront runs one stage
-//              count, one class count and similar micro-batch counts.
+//              layout the whole plan by (kind of schedule or interleaved
+//              shape, stages, classes, longest micro-batch count), with the
+//              per-class layout each pipeline (one per replica class).
+//   k_scan     one block: first entry of each bucket, entry and tile of each
+//              group, places of the continuation lists.
+//   k_scatter  places the plans (pipelines) in that order.
 //   k_plan_hist, k_plan_scatter, k_plan_syncs (per-class layout only) the
 //              syncs of every (class, stage), once per plan, plans sorted by
 //              the length of their segment walks.
-//   k_eval     one pipeline per lane, one launch per group of four stage
-//              counts.  Overlap and zero-bubble plans are handed to the
-//              variant pass first.  Setup: place the class on its device
+//   k_eval     one tile of a group per wavefront, a pipeline per lane, the G
+//              pipelines of a plan on adjacent lanes; one launch per four
+//              stage counts, 1F1B plans.  Setup: place the class on its device
 //              pools, read stage compute from the layer prefix tables, find
 //              each group's slowest link with range-max tables, and cost the
-//              TP/EP/PP collectives.  Then the 1F1B recurrence, unrolled per
-//              stage count so that all per-stage state stays in VGPRs; times
-//              are integers carried exactly in fp64 (3 VALU ops per schedule
-//              node).  Once a steady iteration advances the whole schedule
-//              state by one constant, the remaining steady iterations are
-//              added in one step (periodic shortcut); lanes still aperiodic
-//              after a fixed budget are deferred.  Then the DP syncs, shared
-//              over a plan's lanes, and one store of the plan's time.
-//   k_variant  the overlap and zero-bubble plans of each group, the same way.
-//   k_defer_hist, k_defer_sort  the deferred lists sorted by micro-batch count.
-//   k_deferred the interleaved-1F1B pipelines, then the deferred pipelines of
-//              all stage counts (full steady loop).
+//              TP/EP/PP collectives and (shared over a plan's lanes) the DP
+//              syncs.  Then the 1F1B recurrence, unrolled per stage count so
+//              that all per-stage state stays in VGPRs.  Once a steady
+//              iteration advances the whole state by one constant, the
+//              remaining ones are added in one step (periodic shortcut); lanes
+//              still aperiodic after a fixed budget leave for a continuation
+//              list.  One store of the plan's time.
+//   k_variant  the overlap and zero-bubble plans, the same way.
+//   k_il       the interleaved plans.
+//   k_cont     the first continuation list, with full wavefronts of it.
+//   k_power    what is still left, a pipeline per wavefront, by powers of the
+//              iteration's max-plus matrix.
 //   k_redo_u64 pipelines whose time reached 2^53 ps, again in u64.
 //              Later passes raise a plan's time with atomic max.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <limits.h>
 
 #include <type_traits>
 
@@ -134,30 +133,35 @@ __device__ __forceinline__ void ring_parts(uint32_t p, double rp, uint32_t zero,
   }
 }
 
-// micro-batch counts: exact up to 64, then steps of 16 up to 1088
+// micro-batch counts: exact up to 20, then two buckets per power of two (a
+// pipeline runs at most its first pass's budget of steady iterations, so
+// larger counts need no finer sort)
 __device__ __forceinline__ uint32_t m_bucket(uint32_t M) {
-  if (M <= 64) return M - 1;
-  const uint32_t b = 64 + (M - 65) / 16;
-  return b < kBucketsM - 1 ? b : kBucketsM - 1;
+  if (M <= 20) return M - 1;
+  const uint32_t e = 31u - __clz(M), j = 2 * (e - 4) + ((M >> (e - 1)) & 1);
+  return 20 + (j < 11 ? j : 11);
 }
-// ascending key: more stages first, then more classes, then more micro-batches
-__device__ __forceinline__ uint32_t bucket_key(uint32_t S, uint32_t G, uint32_t M) {
-  return ((kMaxStages - S) * kMaxClasses + (kMaxClasses - G)) * kBucketsM + (kBucketsM - 1 - m_bucket(M));
+__device__ __forceinline__ uint32_t bucket(uint32_t group, uint32_t M) {
+  return group * kBucketsM + (kBucketsM - 1 - m_bucket(M));
 }
-// interleaved pipelines: after all others, one group per (S, v), more
-// micro-batches first (q = M / S exact from 2 to 49).  M is a multiple of S
-// below 2^16, so M times the approximate reciprocal of S rounds to q.
-__device__ __forceinline__ uint32_t il_group(uint32_t S, uint32_t v) { return (S - 2) * 3 + (v - 2); }
-__device__ __forceinline__ uint32_t il_key(uint32_t S, uint32_t v, uint32_t M) {
-  const uint32_t q = (uint32_t)((float)M * __builtin_amdgcn_rcpf((float)S) + 0.5f) - 2;
-  return kPlainBuckets + il_group(S, v) * kIlBucketsQ + (kIlBucketsQ - 1 - (q < kIlBucketsQ - 1 ? q : kIlBucketsQ - 1));
+__host__ __device__ constexpr uint32_t plain_group(uint32_t kind, uint32_t S, uint32_t G) {
+  return (kind * kMaxStages + kMaxStages - S) * kMaxClasses + kMaxClasses - G;
 }
 // (S, v) shapes of interleaved pipelines: S v <= 16 virtual stages
 #define HETSIM_IL_SHAPES(X) \
   X(2, 2) X(2, 3) X(2, 4) X(3, 2) X(3, 3) X(3, 4) X(4, 2) X(4, 3) X(4, 4) X(5, 2) X(5, 3) X(6, 2) X(7, 2) X(8, 2)
+// their index in that list
+__host__ __device__ constexpr uint32_t il_shape(uint32_t S, uint32_t v) {
+  return S <= 4 ? (S - 2) * 3 + v - 2 : S == 5 ? 7 + v : S + 5;
+}
+static_assert(il_shape(4, 4) == 8 && il_shape(5, 2) == 9 && il_shape(5, 3) == 10 && il_shape(8, 2) == kIlShapes - 1,
+              "interleaved shapes");
+__host__ __device__ constexpr uint32_t il_group(uint32_t S, uint32_t v, uint32_t G) {
+  return kPlainGroups + il_shape(S, v) * kMaxClasses + kMaxClasses - G;
+}
 
 // pipeline metadata word: S | G << 5 | M << 8 | (v - 1) << 24 (0 = no pipeline);
-// bucket keys travel as u16, kNoKey = no pipeline
+// bucket keys travel as u16, kNoKey = no plan (or pipeline)
 constexpr uint32_t kNoKey = 0xffff;
 static_assert(kBuckets < kNoKey, "bucket keys fit 16 bits");
 
@@ -476,10 +480,9 @@ __device__ __forceinline__ bool fits_memory(const Tab& t, const Checked& r) {
 // Decode and check plan i (every rule of the plan layout); on success pack it
 // (with the per-class layout, the class header word goes to pad0 and each
 // class's cut row to pcut[4 i + c]).  Writes out[i] (0 = valid, to be raised
-// by the pipelines; else invalid) and the per-pipeline metadata
-// S | G << 5 | M << 8 | (v - 1) << 24 with the class's own S (0 = no pipeline),
-// and (keys, when given) each pipeline's bucket (kNoKey = no pipeline); with
-// keys, valid plans sorted by plan get no metadata.
+// by the pipelines; else invalid), and when given the per-pipeline metadata
+// S | G << 5 | M << 8 | (v - 1) << 24 with the class's own S (0 = no pipeline)
+// and the bucket keys, counted in hist.
 template <bool kHet>
 __global__ void __launch_bounds__(256) k_prep(Tab t, sim_plans pl, int64_t n, uint64_t* __restrict__ out,
                                               PackedPlan* __restrict__ packed, uint4* __restrict__ pcut,
@@ -509,33 +512,42 @@ __global__ void __launch_bounds__(256) k_prep(Tab t, sim_plans pl, int64_t n, ui
         for (int c = 0; c < 4; ++c) pcut[4 * i + c] = make_uint4(r.cw[c][0], r.cw[c][1], r.cw[c][2], r.cw[c][3]);
       }
     }
-    uint32_t m[4], key[4], Mmax = 0;
+    uint32_t m[4], Mmax = 0;
 #pragma unroll
     for (uint32_t c = 0; c < 4; ++c) {
       m[c] = 0;
-      key[c] = kNoKey;
       if (ok && c < G) {
         const uint32_t reps = r.cls[c] & 0xffff, M = ((r.cls[c] >> 16) + reps - 1) / reps;
         m[c] = r.S[c] | (G << 5) | (M << 8) | ((r.v - 1) << 24);
         Mmax = M > Mmax ? M : Mmax;
       }
     }
-    // plans sorted by plan (their class 0 carries the key, ranked by the
-    // longest class), the others by pipeline
-    const bool by_plan = !kHet && ok && r.v == 1;
-#pragma unroll
-    for (uint32_t c = 0; c < 4; ++c) {
-      if (ok && c < G && (!by_plan || c == 0)) {
-        const uint32_t M = by_plan ? Mmax : m[c] >> 8 & 0xffff;
-        key[c] = r.v > 1 ? il_key(r.S[c], r.v, M) : bucket_key(r.S[c], G, M);
-        if (hist) atomicAdd(&lh[key[c]], 1u);
+    // bucket keys: of the plan, ranked by its longest class, or with the
+    // per-class layout of each pipeline
+    if (keys && !kHet) {
+      uint32_t key = kNoKey;
+      if (ok) {
+        const uint32_t S = r.S[0], kind = (r.hdr >> 16) & 1 ? 2 : (r.hdr >> 13) & 1;
+        // (interleaved: Mmax is a multiple of S below 2^16, so its product with
+        // the approximate reciprocal rounds to the quotient)
+        key = r.v > 1 ? bucket(il_group(S, r.v, G), (uint32_t)((float)Mmax * __builtin_amdgcn_rcpf((float)S) + 0.5f))
+                      : bucket(plain_group(kind, S, G), Mmax);
+        if (hist) atomicAdd(&lh[key], 1u);
       }
+      keys[i] = (uint16_t)key;
     }
-    // one 16-byte and one 8-byte store per plan (the workspace is 256-byte
-    // aligned; a caller's class array may be aligned to 4 bytes only).  An
-    // evaluation call (keys given) reads no metadata of the plans it sorts by
-    // plan: only its other pipelines get it
-    if (!keys || !by_plan) {
+    if (keys && kHet) {
+      uint32_t key[4];
+#pragma unroll
+      for (uint32_t c = 0; c < 4; ++c) {
+        key[c] = m[c] ? bucket(plain_group(0, r.S[c], G), m[c] >> 8 & 0xffff) : kNoKey;
+        if (hist && m[c]) atomicAdd(&lh[key[c]], 1u);
+      }
+      reinterpret_cast<uint2*>(keys)[i] = make_uint2(key[0] | key[1] << 16, key[2] | key[3] << 16);
+    }
+    // one 16-byte store per plan (the workspace is 256-byte aligned; a
+    // caller's class array may be aligned to 4 bytes only)
+    if (meta) {
       if (((uintptr_t)meta & 15) == 0) {
         reinterpret_cast<uint4*>(meta)[i] = make_uint4(m[0], m[1], m[2], m[3]);
       } else {
@@ -543,7 +555,6 @@ __global__ void __launch_bounds__(256) k_prep(Tab t, sim_plans pl, int64_t n, ui
         for (int c = 0; c < 4; ++c) meta[i * 4 + c] = m[c];
       }
     }
-    if (keys) reinterpret_cast<uint2*>(keys)[i] = make_uint2(key[0] | key[1] << 16, key[2] | key[3] << 16);
   }
   if (hist) {
     __syncthreads();
@@ -1387,36 +1398,8 @@ struct ZbSink {
   }
 };
 
-// The syncs x[s] each stage of the pipeline waits for, costed by this lane
-// alone: with the per-class layout read from the plan pass's row, otherwise
-// found stage by stage (shifted into place so that no array is indexed at
-// run time).
-template <int S, int kMode, bool kHet, bool kOvl, bool kHier>
-__device__ __forceinline__ void own_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, double (&x)[S],
-                                          const uint64_t* drow) {
-  if constexpr (kHet) {
-#pragma unroll
-    for (int s = 0; s < S; ++s) x[s] = (double)drow[s];
-    return;
-  }
-  const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
-  uint32_t lo = 0;
-#pragma unroll
-  for (int s = 0; s < S; ++s) x[s] = 0;
-  for (uint32_t s = 0; s < (uint32_t)S; ++s) {
-    const uint32_t hi = cut_at(p, s);
-    const uint64_t d = kOvl ? overlap_tail<kMode, kHier>(t, h, p, s, lo, hi, (uint32_t)(p.tc >> (4 * s)) & 15, rp, rpe)
-                            : stage_dp<kMode, kHier>(t, h, p, s, hi - lo, rp, rpe);
-#pragma unroll
-    for (int i = 0; i + 1 < S; ++i) x[i] = x[i + 1];
-    x[S - 1] = (double)d;
-    lo = hi;
-  }
-}
-
 template <int S, int v>
 __device__ __forceinline__ void il_records(const Tab& t, const Hot<2>& h, const Plan& p, uint64_t* o);
-__device__ __forceinline__ uint32_t il_shape(uint32_t S, uint32_t v) { return S | (v - 1) << 5; }
 
 // per (class, stage) quantities of every plan, in plan order; for an
 // interleaved pipeline per virtual stage (hops and syncs per device, in the
@@ -1433,7 +1416,7 @@ __global__ void __launch_bounds__(256) k_stages(Tab t, const PackedPlan* __restr
     uint64_t* o = out_stage + slot * (kMaxStages * kRecWords);
     switch (il_shape(p.S, p.v)) {
 #define X(S_, V_)                        \
-  case S_ | (V_ - 1) << 5:               \
+  case il_shape(S_, V_):                   \
     il_records<S_, V_>(t, h, p, o);      \
     break;
       HETSIM_IL_SHAPES(X)
@@ -1513,10 +1496,12 @@ typedef uint64_t StageRec[kMaxStages][kRecWords];
 __device__ __forceinline__ double vmax(double a, double b) { return __builtin_fmax(a, b); }
 __device__ __forceinline__ uint64_t vmax(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
-// A wave waits at most kPeriodicBudget steady iterations for its lanes; a lane
-// still aperiodic by then is deferred to a full-loop pass, so one aperiodic
-// schedule does not hold 63 periodic ones.
-constexpr int kPeriodicBudget = 40;
+// A wavefront of the first pass waits this many steady iterations for its
+// lanes, then the aperiodic ones leave for the continuation lists.  Most
+// schedules are periodic after a few iterations, later with more stages; at
+// S + 8, 16-18 % of the random sweeps' 16-stage pipelines leave, 6-9 % of the
+// 8-stage and 2-4 % of the 4-stage ones.
+__host__ __device__ constexpr int first_budget(int S) { return S + 8; }
 
 template <int S, typename V>
 struct Chain {
@@ -1593,7 +1578,7 @@ __device__ __forceinline__ void chain_jump(Chain<S, V>& h, int& left, int budget
       B = s == S - 1 ? h.f[s] : vmax(h.f[s], B + h.d[s]);
       const V n = s ? vmax(B + h.a[s], h.f[s - 1]) : B + h.a[s];
       if (s == S - 1) lam = n - h.f[s];
-      else same = same && n - h.f[s] == lam;
+      else same = same & (n - h.f[s] == lam);
       h.f[s] = n;
     }
     left -= 2;
@@ -1639,12 +1624,11 @@ __device__ __forceinline__ V chain_end(Chain<S, V>& h, const V (&w)[S], uint32_t
   return T;
 }
 
-// The time of a chain of M micro-batches.  kJump: with the periodic shortcut;
-// `skipped` returns the steady iterations it skipped.  Returns false for a
-// lane still aperiodic after the budget (T not computed), unless kFallback,
-// which runs the rest of the loop in place.
-template <int S, typename V, bool kZb, bool kJump, bool kFallback = false>
-__device__ __forceinline__ bool chain_time(Chain<S, V>& h, const V (&w)[S], uint32_t M, int& skipped, V& T) {
+// The time of a chain of M micro-batches with the periodic shortcut, the
+// whole loop in place where it stays aperiodic; `skipped` returns the steady
+// iterations it skipped.
+template <int S, typename V, bool kZb>
+__device__ __forceinline__ V chain_time(Chain<S, V>& h, const V (&w)[S], uint32_t M, int& skipped) {
   int left = (int)M - S;
   skipped = 0;
   if (kZb) {   // from iteration S - 1 on every stage runs its W
@@ -1652,68 +1636,233 @@ __device__ __forceinline__ bool chain_time(Chain<S, V>& h, const V (&w)[S], uint
     for (; i < left && i < S - 1; ++i) chain_iter<S, V, true>(h, w, i, 0);
     left -= i;
   }
-  if (kJump) {
-    chain_jump<S, V>(h, left, kPeriodicBudget, skipped);
-    if (!kFallback && left > 0) return false;
-  }
-  for (; left > 0; --left) chain_iter<S, V, false>(h, h.a, 0, 0);
-  T = chain_end<S, V, kZb>(h, w, M);
-  return true;
+  chain_jump<S, V>(h, left, INT_MAX, skipped);
+  return chain_end<S, V, kZb>(h, w, M);
 }
 
-// Integers below 2^53 are exact in fp64.  Every value the fp64 pass computes
-// is at most the end of some op, which is at most T, so if T < 2^53 no
-// rounding ever happened.  Otherwise the pipeline goes on an overflow list
-// and k_redo_u64 evaluates it again in u64, outside the hot kernels.
+// If T < 2^53 no rounding ever happened (every value the fp64 pass computes is
+// the length of a path, at most T).  Otherwise the pipeline goes on the redo
+// list and k_redo_u64 evaluates it again in u64, outside the hot kernels.
 constexpr double kExact = 9007199254740992.0;
 
-// Device buffers of one evaluation pass over a chunk.
-struct EvalBufs {
-  const PackedPlan* packed;
-  const uint4* pcut;        // per-class layout: cut row of pipeline slot at [slot]
-  const uint64_t* hdp;      // per-class layout: the syncs of pipeline slot's stages at [16 slot, + 16)
-  const uint32_t* meta;
-  const uint32_t* ids;      // pipeline ids sorted by bucket
-  const uint32_t* sstart;   // [16 - S]: start of the S-stage pipelines in ids; [16] = total
-  uint64_t* out;
-  uint32_t* ctr;            // [0] overflow count, [1 + 16 - S] deferred S-stage pipelines,
-                            // [kVariantCtr + 16 - S] S-stage overlap and zero-bubble pipelines
-  uint32_t* ovf;            // overflow list (fp64 result reached 2^53)
-  uint32_t* deferred;       // deferred S-stage pipelines at [sstart[16 - S], ...)
-  uint32_t* vlist;          // S-stage overlap and zero-bubble tiles at [sstart[16 - S], ...): each a
-                            // first-pass wavefront's lanes as they were (kNoSlot elsewhere)
-  unsigned long long* skipped_ops;   // optional: recurrence ops skipped by the shortcut
-  const Tab* dtab;          // the Tab in device memory
-};
-
-// Pipelines are sorted by stage count (descending), so each group of four
-// stage counts is a contiguous range of ids; one kernel per group keeps the
-// register footprint, and so the occupancy, of small pipelines independent of
-// the 16-stage code.  Block b of group g runs the g-th range's pipelines
-// [64b, 64b + 64); blocks past the range return at once.  This first pass
-// takes the periodic shortcut and defers the lanes still aperiodic after the
-// budget; k_deferred runs those through the whole steady loop.
-// kOvl: the pipeline's plan overlaps its gradient sync with the last
-// backward pass; kZb: it runs the zero-bubble order.  The first pass (kFull
-// false) sends both kinds to the variant lists, so that its kernels carry
-// neither; k_variant runs them with the shortcut (the whole loop where they
-// stay aperiodic).  With a context that enables two-level collectives, whose
-// sync code the first pass lacks, it sends every other shared-layout
-// pipeline to the deferred lists.
-// DP syncs of a plan-sorted pipeline (first and variant passes, shared layout,
-// G classes on G adjacent lanes): the lane of class c costs the syncs of
-// stages c, c + G, ... (each the same for every class of the plan) into its
-// plan's column of the wavefront's LDS exchange area (x[64 s + first lane of
-// the plan], the syncs of stage s); every lane of the plan reads the column.
+// Order of LDS accesses within a wavefront: its lanes' accesses complete in
+// order; the fences keep the compiler from moving one lane's reads above other
+// lanes' writes.
 __device__ __forceinline__ void wave_sync_lds() {
-  // the area is written and read by the lanes of one wavefront, whose LDS
-  // accesses complete in order; the fences keep the compiler from moving
-  // reads above the writes of the other lanes
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// ---------------------------------------------------------------- continuation lists
+// Offer a pipeline's chain with `left` steady iterations to run to list kList
+// (1 or 2) of its stage count; false if the list is full.
+template <int S, int kList>
+__device__ __forceinline__ bool cont_push(const EvalBufs& e, const Chain<S, double>& h, int left, uint32_t slot) {
+  constexpr int j = kMaxStages - S, info = 32 * (kList - 1) + j;
+  const uint32_t cap = e.cinfo[info + 16] * 64u;
+  const uint32_t pos = atomicAdd(&e.ctr[1 + kMaxStages * (kList - 1) + j], 1u);
+  if (pos >= cap) return false;
+  double* q = e.cont + (size_t)e.cinfo[info] * (kContUnit / 8) + (size_t)(pos >> 6) * (256 * S) + (pos & 63u);
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    q[64 * s] = h.f[s];
+    q[64 * (S + s)] = h.a[s];
+    if (s < S - 1) q[64 * (2 * S + s)] = h.d[s];
+    q[64 * (3 * S + s)] = h.e[s];
+  }
+  *(uint2*)&q[64 * (3 * S - 1)] = make_uint2((uint32_t)left, slot);
+  return true;
+}
+
+__device__ __forceinline__ void count_skipped(const EvalBufs& e, int S, int skipped) {
+  if (e.skipped_ops && skipped > 0)
+    atomicAdd(e.skipped_ops + ((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % kSkipSlots) * kSkipStride,
+              (unsigned long long)skipped * (unsigned long long)(6 * (S - 1) + 2));
+}
+
+// Raise a plan's time (the result word is in place since k_prep).
+__device__ __forceinline__ void raise_time(const EvalBufs& e, uint32_t slot, double T) {
+  if (T < kExact) atomicMax((unsigned long long*)&e.out[slot >> 2], (unsigned long long)T);
+  else e.ovf[atomicAdd(&e.ctr[0], 1u)] = slot;
+}
+
+// Steady iterations k_cont gives a pipeline before it moves to the second
+// list, and how many must be left then.
+constexpr int kContBudget = 48, kPowerMin = 32;
+
+// Schedules that are not periodic after a few iterations mostly drift, often
+// with a period of two iterations: each stage advances at its own rate, and a
+// queue between two of them fills or drains until the order of a max changes.
+// Let q iterations advance the state by a vector D.  If, in q further
+// iterations, every max's argument carries its rate on so that the rates come
+// out as D again, and the state has moved by D, then the state moves by D
+// every q iterations for as long as no argument is overtaken: at least
+// J = min lead / (rate of the other - rate of the argument) times.  All of
+// them are taken in one step.  (A periodic schedule is the case of equal
+// rates, J without bound.)
+//
+// One iteration with the rates r of the state (on return of the new state).
+// The argument of max(x, y) is x if the difference x - y, or at a tie that of
+// the rates, is positive: the sign of (x - y) + 2^-60 (rx - ry), as all are
+// integers below 2^53.  J: lowered to the bound -(x - y) / (rx - ry) where
+// that is positive, as the bits of an fp32 number read unsigned, so that
+// negative bounds (and the tiny negative number a tie gives) and NaN are
+// larger than any positive one.
+template <int S>
+__device__ __forceinline__ void rate_iter(Chain<S, double>& h, double (&r)[S], uint32_t& J) {
+  double B = 0, rB = 0;
+  auto pick = [&](double x, double rx, double y, double ry, double& v, double& rv) {
+    const double dx = x - y, dr = rx - ry;
+    v = vmax(x, y);
+    rv = __builtin_fma(dr, 0x1p-60, dx) > 0 ? rx : ry;
+    const float j = __builtin_fmaf(-(float)dx, __builtin_amdgcn_rcpf((float)dr), -1e-30f);
+    const uint32_t b = __float_as_uint(j);
+    J = b < J ? b : J;
+  };
+#pragma unroll
+  for (int s = S - 1; s >= 0; --s) {
+    if (s == S - 1) {
+      B = h.f[s];
+      rB = r[s];
+    } else {
+      pick(h.f[s], r[s], B + h.d[s], rB, B, rB);
+    }
+    if (s) {
+      pick(B + h.a[s], rB, h.f[s - 1], r[s - 1], h.f[s], r[s]);
+    } else {
+      h.f[0] = B + h.a[0];
+      r[0] = rB;
+    }
+  }
+}
+
+// Go on with a pipeline of the first list, q = 1, 2 in turn: q iterations find
+// D; if all its components are equal the schedule has period q.  Otherwise the
+// next q iterations say whether D repeats, and where it does q more follow the
+// rates.  (A plain 16-stage iteration takes 0.12 us, one with rates 1 us.  On
+// the random sweeps 9 in 10 of these pipelines end within 30 iterations; in a
+// sweep of a million plans the slowest would take all of its 500-1100.)
+template <int S>
+__device__ __forceinline__ void cont_one(const EvalBufs& e, const double* tile) {
+  Chain<S, double> h;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    h.f[s] = tile[64 * s];
+    h.a[s] = tile[64 * (S + s)];
+    h.d[s] = s < S - 1 ? tile[64 * (2 * S + s)] : 0;
+  }
+  const uint2 ls = *(const uint2*)&tile[64 * (3 * S - 1)];
+  int left = (int)ls.x, skipped = 0, q = 1, budget = kContBudget;
+  const uint32_t slot = ls.y;
+  while (left >= 3 * q && budget > 0) {
+    double o[S], D[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) o[s] = h.f[s];
+    for (int i = 0; i < q; ++i) chain_iter<S, double, false>(h, h.a, 0, 0);
+    left -= q;
+    budget -= q;
+    bool same = true;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      D[s] = h.f[s] - o[s];
+      same = same & (D[s] == D[0]);
+    }
+    if (same) {
+      const int k = left / q;
+#pragma unroll
+      for (int s = 0; s < S; ++s) h.f[s] += (double)k * D[0];
+      left -= k * q;
+      skipped += k * q;
+    } else {
+#pragma unroll
+      for (int s = 0; s < S; ++s) o[s] = h.f[s];
+      for (int i = 0; i < q; ++i) chain_iter<S, double, false>(h, h.a, 0, 0);
+      left -= q;
+      budget -= q;
+      bool ok = true;
+#pragma unroll
+      for (int s = 0; s < S; ++s) ok = ok & (h.f[s] - o[s] == D[s]);
+      if (ok) {
+        double r[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          o[s] = h.f[s];
+          r[s] = D[s];
+        }
+        uint32_t J = __float_as_uint(1e9f);
+        for (int i = 0; i < q; ++i) rate_iter<S>(h, r, J);
+        left -= q;
+        budget -= q;
+#pragma unroll
+        for (int s = 0; s < S; ++s) ok = ok & (r[s] == D[s]) & (h.f[s] - o[s] == D[s]);
+        if (ok) {
+          // (the fp32 quotient, shortened by more than its error)
+          const float bound = __uint_as_float(J) * 0.99999f;
+          const int room = left / q, k = bound < (float)room ? (int)bound : room;
+#pragma unroll
+          for (int s = 0; s < S; ++s) h.f[s] += (double)k * D[s];
+          left -= k * q;
+          skipped += k * q;
+        }
+      }
+    }
+    q = 3 - q;
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s) h.e[s] = tile[64 * (3 * S + s)];
+  // out of budget: the second list, or the rest here if little is left or the list is full
+  if (left >= kPowerMin && cont_push<S, 2>(e, h, left, slot)) {
+    count_skipped(e, S, skipped);
+    return;
+  }
+  for (; left > 0; --left) chain_iter<S, double, false>(h, h.a, 0, 0);
+  // (M enters the end only where it is below S: never here)
+  raise_time(e, slot, chain_end<S, double, false>(h, h.a, S));
+  count_skipped(e, S, skipped);
+}
+
+// Tile `tile` of 64 (or entry of 1) of a list: its stage count S and place in
+// the list; false past the last one.  Most stages first.
+template <int kList, uint32_t kPer>
+__device__ __forceinline__ bool cont_find(const EvalBufs& e, uint32_t q, uint32_t& S, uint32_t& tile, uint32_t& n) {
+  uint32_t before = 0;
+  for (uint32_t j = 0; j < (uint32_t)kMaxStages; ++j) {
+    const uint32_t cap = e.cinfo[32 * (kList - 1) + 16 + j] * 64u, c = e.ctr[1 + kMaxStages * (kList - 1) + j];
+    n = c < cap ? c : cap;
+    const uint32_t nt = (n + kPer - 1) / kPer;
+    if (q < before + nt) {
+      S = kMaxStages - j;
+      tile = q - before;
+      return true;
+    }
+    before += nt;
+  }
+  return false;
+}
+
+// The time of a plan whose G pipelines sit on adjacent lanes from `lead` on,
+// all of them here: the first one stores the largest result of the finished
+// ones (one store per plan; later passes raise it with atomicMax).  G is the
+// same in the whole wavefront.
+__device__ __forceinline__ void store_plan_time(const EvalBufs& e, uint32_t slot, uint32_t G, uint32_t lead, bool done,
+                                                double T) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const bool mine = done && T < kExact;
+  double v = mine ? T : 0;
+  for (uint32_t c = 1; c < G; ++c) {
+    const double u = __shfl(v, (int)(lead + c));
+    if (lane == lead) v = u > v ? u : v;
+  }
+  if (lane == lead && v > 0) e.out[slot >> 2] = (uint64_t)v;
+  if (done && !mine) e.ovf[atomicAdd(&e.ctr[0], 1u)] = slot;
+}
+
+// DP syncs of a plan-sorted pipeline (first and variant passes, shared layout,
+// G classes on G adjacent lanes): the lane of class c costs the syncs of
+// stages c, c + G, ... (each the same for every class of the plan) into its
+// plan's column of the wavefront's LDS exchange area (x[64 s + first lane of
+// the plan], the syncs of stage s); every lane of the plan reads the column.
 template <int S, int kMode, bool kHier>
 __device__ __forceinline__ void grouped_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, double* x,
                                               uint32_t lead, const uint32_t* bw = nullptr) {
@@ -1758,99 +1907,67 @@ __device__ __forceinline__ void grouped_overlap_syncs(const Tab& t, const Hot<kM
   }
 }
 
-template <int S, bool kFull, int kMode, bool kHet, bool kOvl = false, bool kZb = false>
+// One pipeline of the first pass (kKind 0) or of the variant pass (overlapped
+// sync, zero-bubble order; with two-level collectives, kHier, also plain
+// ones): setup, syncs, chain, and the recurrence with the first pass's budget.
+// xw: the wavefront's exchange columns (shared layout); bw: its placement
+// cache, when the group has one.
+template <int S, int kMode, bool kHet, int kKind, bool kHier>
 __device__ __forceinline__ void eval_one(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t slot,
-                                         double* xw = nullptr, uint32_t* bw = nullptr) {
-  // plan-sorted pipelines of the first or the variant pass (shared layout)
-  constexpr bool kGrouped = !kFull && !kHet;
+                                         double* xw, uint32_t* bw = nullptr) {
+  constexpr bool kZb = kKind == 2, kOvl = kKind == 1;
+  const uint32_t lane = threadIdx.x & 63u;
   typename std::conditional<kZb, ZbSink<S>, RegSink<S>>::type r;
   const Plan p = load_plan<kHet>(e.packed, e.pcut, slot);
-  if (!kFull && !kHet && !kOvl && !kZb) {
-    // (overlap and zero-bubble plans left for the variant pass in k_eval)
-    if (t.ccl_hier) {
-      e.deferred[e.sstart[kMaxStages - S] + atomicAdd(&e.ctr[1 + kMaxStages - S], 1u)] = slot;
-      return;
-    }
-  }
-  const uint32_t M = class_mb(p), G = p.G;
-  if constexpr (kGrouped && !kZb)
-    if (bw) r.bs = bw + (threadIdx.x & 63u) * S;
+  const uint32_t M = class_mb(p), G = p.G, lead = lane - p.c;
+  if constexpr (!kHet && !kZb)
+    if (bw) r.bs = bw + lane * S;
   class_setup<kMode, kHet>(t, h, p, slot & 3, r, nullptr);
   Chain<S, double> ch;
   {
     double x[S];
-    if constexpr (kGrouped) {
-      const uint32_t lane = threadIdx.x & 63u, lead = lane - p.c;
+    if constexpr (!kHet) {
       if constexpr (kOvl) grouped_overlap_syncs<S, kMode>(t, h, p, xw, lead);
-      else grouped_syncs<S, kMode, kZb>(t, h, p, xw, lead, kZb ? nullptr : bw);
+      else grouped_syncs<S, kMode, kHier>(t, h, p, xw, lead, kZb ? nullptr : bw);
 #pragma unroll
       for (int s = 0; s < S; ++s) x[s] = xw[s * 64 + (kOvl ? lane : lead)];
       wave_sync_lds();
     } else {
-      own_syncs<S, kMode, kHet, kOvl, true>(t, h, p, x, kHet ? e.hdp + (size_t)slot * kMaxStages : nullptr);
+      // per-class layout: the syncs the plan pass stored for this pipeline's stages
+      const uint64_t* drow = e.hdp + (size_t)slot * kMaxStages;
+#pragma unroll
+      for (int s = 0; s < S; ++s) x[s] = (double)drow[s];
     }
     if constexpr (kZb) reduce_chain<S, double, true>(r.f, r.bi, r.w, r.c, x, M, ch);
     else reduce_chain<S, double, false>(r.f, r.b, r.b, r.c, x, M, ch);
   }
-  // the first and variant passes take the periodic shortcut and defer the
-  // lanes still aperiodic after the budget; the deferred pass runs the whole loop
-  int skipped;
-  double T = 0;
-  bool done;
-  if constexpr (kZb) done = chain_time<S, double, true, !kFull>(ch, r.w, M, skipped, T);
-  else done = chain_time<S, double, false, !kFull>(ch, ch.a, M, skipped, T);
-  if constexpr (kGrouped) {
-    // the plan's G pipelines sit on adjacent lanes from a multiple of G, all
-    // of them here: the first one stores the largest result of the finished
-    // ones (one store per plan; the deferred and the u64 passes, later in
-    // stream order, raise it with atomicMax)
-    const uint32_t lane = threadIdx.x & 63u, lead = lane - p.c;
-    const bool mine = done && T < kExact;
-    double v = mine ? T : 0;
-    for (uint32_t c = 1; c < G; ++c) {
-      const double u = __shfl(v, (int)(lead + c));
-      if (lane == lead) v = u > v ? u : v;
-    }
-    if (lane == lead && v > 0) e.out[slot >> 2] = (uint64_t)v;
-    if (!done) {
-      e.deferred[e.sstart[kMaxStages - S] + atomicAdd(&e.ctr[1 + kMaxStages - S], 1u)] = slot;
-      return;
-    }
-    if (!mine) e.ovf[atomicAdd(&e.ctr[0], 1u)] = slot;
-  } else {
-    if (!done) {
-      e.deferred[e.sstart[kMaxStages - S] + atomicAdd(&e.ctr[1 + kMaxStages - S], 1u)] = slot;
-      return;
-    }
-    if (T < kExact) {
-      atomicMax((unsigned long long*)&e.out[slot >> 2], (unsigned long long)T);
-    } else {
-      e.ovf[atomicAdd(&e.ctr[0], 1u)] = slot;
-    }
+  int left = (int)M - S, skipped = 0, budget = first_budget(S);
+  if constexpr (kZb) {   // from iteration S - 1 on every stage runs its W
+    int i = 0;
+    for (; i < left && i < S - 1; ++i) chain_iter<S, double, true>(ch, r.w, i, 0);
+    left -= i;
   }
-  if (e.skipped_ops && skipped > 0)
-    atomicAdd(e.skipped_ops + ((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % kSkipSlots) * kSkipStride,
-              (unsigned long long)skipped * (unsigned long long)(6 * (S - 1) + 2));
-}
-
-// Deferred pass of one pipeline: the whole loop (plain, overlap or zero-bubble, by its header).
-template <int S, int kMode, bool kHet>
-__device__ __forceinline__ void eval_deferred(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t slot) {
-  const uint32_t hdr = kHet ? 0 : e.packed[slot >> 2].hdr;
-  if (!kHet && ((hdr >> 16) & 1)) eval_one<S, true, kMode, false, false, true>(t, h, e, slot);
-  else if (!kHet && ((hdr >> 13) & 1)) eval_one<S, true, kMode, false, true, false>(t, h, e, slot);
-  else eval_one<S, true, kMode, kHet>(t, h, e, slot);
-}
-
-// Variant pass of one pipeline (shared layout): overlapped gradient sync or
-// the zero-bubble order, with the periodic shortcut; lanes still aperiodic
-// after the budget go to the deferred lists (the deferred pass runs them
-// through the whole loop).
-template <int S, int kMode>
-__device__ __forceinline__ void eval_variant(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t slot,
-                                             double* xw) {
-  if ((e.packed[slot >> 2].hdr >> 16) & 1) eval_one<S, false, kMode, false, false, true>(t, h, e, slot, xw);
-  else eval_one<S, false, kMode, false, true>(t, h, e, slot, xw);
+  bool done = true;
+  while (true) {
+    chain_jump<S, double>(ch, left, budget, skipped);
+    if (left <= 0) break;
+    if (cont_push<S, 1>(e, ch, left, slot)) {
+      done = false;
+      break;
+    }
+    budget = INT_MAX;
+  }
+  double T = 0;
+  if (done) {
+    if constexpr (kZb) T = chain_end<S, double, true>(ch, r.w, M);
+    else T = chain_end<S, double, false>(ch, ch.a, M);
+    count_skipped(e, S, skipped);
+  }
+  if constexpr (kHet) {
+    if (done) raise_time(e, slot, T);
+  } else {
+    store_plan_time(e, slot, G, lead, done, T);
+  }
 }
 
 // ---------------------------------------------------------------- interleaved 1F1B
@@ -2076,223 +2193,162 @@ __device__ __forceinline__ void il_records(const Tab& t, const Hot<2>& h, const 
   }
 }
 
+// One plan-sorted interleaved pipeline: as eval_one, the lane of class c costs
+// the syncs of devices c, c + G, ... for all lanes of its plan.
 template <int S, int v, int kMode>
-__device__ __forceinline__ void eval_il(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t slot) {
+__device__ __forceinline__ void eval_il(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t slot,
+                                        double* x) {
+  const uint32_t lane = threadIdx.x & 63u;
   double busy[S];
   int skipped;
+  uint32_t G, lead;
   {
     double f[S * v], b[S * v], c[S];
     uint32_t M;
     {
       const Plan p = load_plan<false>(e.packed, e.pcut, slot);
+      G = p.G;
+      lead = lane - p.c;
+      const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
+      for (uint32_t s = p.c; s < (uint32_t)S; s += G)
+        x[s * 64 + lead] = (double)stage_dp(t, h, p, s, il_device_ns<S, v>(p, (int)s), rp, rpe);
       il_setup<S, v, kMode, double>(t, h, p, f, b, c);
       M = class_mb(p);
     }
     il_pipe<S, v, double, true>(f, b, c, M, busy, skipped);
   }
-  // the tail reads the plan again (as eval_one does) rather than keeping it
-  // in registers through the recurrence
-  const uint32_t slot2 = __shfl(slot, (int)(threadIdx.x & 63u));
-  const double T = il_tail<S, v, kMode, double>(t, h, load_plan<false>(e.packed, e.pcut, slot2), busy);
-  if (T < kExact) atomicMax((unsigned long long*)&e.out[slot >> 2], (unsigned long long)T);
-  else e.ovf[atomicAdd(&e.ctr[0], 1u)] = slot;
+  wave_sync_lds();
+  double T = 0;
+#pragma unroll
+  for (int s = 0; s < S; ++s) T = vmax(T, busy[s] + x[s * 64 + lead]);
+  wave_sync_lds();
+  store_plan_time(e, slot, G, lead, true, T);
 }
 
 // Blocks of four waves share one LDS copy of the table image.
 constexpr uint32_t kEvalThreads = 256;
 
-// The grid is capped at a few times the blocks that fit at once (a launch
-// over the whole chunk would mostly start blocks past the group's range,
-// each holding a full LDS allocation); the waves of the grid take the
-// group's 64-pipeline tiles in a fixed stride, heaviest tiles first.
+// The group of tile q, which is one of groups [g0, g0 + n) (q is uniform in the
+// wavefront, so this is scalar code).
+__device__ __forceinline__ uint32_t tile_group(const EvalBufs& e, uint32_t q, uint32_t g0, uint32_t n) {
+  uint32_t g = g0;
+  for (uint32_t j = 1; j < n; ++j) g += q >= e.tstart[g0 + j] ? 1u : 0u;
+  return g;
+}
+
+// This lane's pipeline of tile q of group g: false if it has none.
+template <bool kHet>
+__device__ __forceinline__ bool tile_slot(const EvalBufs& e, uint32_t q, uint32_t g, uint32_t& slot) {
+  const uint32_t lane = threadIdx.x & 63u, G = kHet ? 1 : kMaxClasses - g % kMaxClasses;
+  const uint32_t per = kHet ? 64 : plans_per_tile(G), j = lane / G, r = (q - e.tstart[g]) * per + j;
+  const uint32_t first = e.gstart[g];
+  if (j >= per || r >= e.gstart[g + 1] - first) return false;
+  const uint32_t x = e.order[first + r];
+  slot = kHet ? x : x * kMaxClasses + (lane - j * G);
+  return true;
+}
+
+// First pass over the four stage counts of group GRP, 1F1B plans.  One kernel
+// per four stage counts keeps the register footprint, and so the occupancy, of
+// small pipelines independent of the 16-stage code.  The grid is capped at a
+// few times the blocks that fit at once (each block holds a copy of the table
+// image); its waves take the group's tiles in a fixed stride, heaviest first.
 template <int GRP, int kMode, bool kHet>
 __global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(Tab t, EvalBufs e) {
   constexpr int kTop = kMaxStages - 4 * GRP;   // stage counts kTop-3 .. kTop
+  constexpr uint32_t g0 = 16 * GRP;
   extern __shared__ uint4 lds[];
-  const uint32_t lo = e.sstart[4 * GRP], hi = e.sstart[4 * GRP + 4];
-  if (lo + blockIdx.x * kEvalThreads >= hi) return;   // the whole block, before any barrier
+  const uint32_t lo = e.tstart[g0], hi = e.tstart[g0 + 16];
+  if (lo + blockIdx.x * (kEvalThreads / 64) >= hi) return;   // the whole block, before any barrier
   fill_lds<kMode>(t, lds);
   const Hot<kMode> h(t, lds);
-  const uint32_t stride = gridDim.x * kEvalThreads;
-  // the wavefront's row of the plan-sorted groups' LDS exchange area
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // the wavefront's exchange columns and its stage-placement cache, when the group has one
   double* xw = nullptr;
-  uint32_t* bw = nullptr;   // and its stage-placement cache, when the group has one
+  uint32_t* bw = nullptr;
   if constexpr (!kHet) {
     char* const x0 = (char*)lds + (kMode < 2 ? t.lds_bytes : 0);
-    xw = (double*)x0 + (threadIdx.x >> 6) * xchg_wave(GRP, false);
+    xw = (double*)x0 + wave * xchg_wave(GRP, false);
     if (GRP < 2 && ((t.bcache >> GRP) & 1))
-      bw = (uint32_t*)(x0 + xchg_bytes(GRP, false)) + (threadIdx.x >> 6) * bcache_words(GRP);
+      bw = (uint32_t*)(x0 + xchg_bytes(GRP, false)) + wave * bcache_words(GRP);
   }
-  for (uint32_t base = lo + blockIdx.x * kEvalThreads + (threadIdx.x & ~63u); base < hi; base += stride) {
-    const uint32_t pos = base + (threadIdx.x & 63u);
-    bool pending = pos < hi;
-    const uint32_t slot = pending ? e.ids[pos] : 0;
-    pending = pending && slot != kNoSlot;   // padding lanes of plan-sorted groups
-    const uint32_t hdr = !pending || kHet ? 0 : e.packed[slot >> 2].hdr;
-    const uint32_t S = !pending ? 0 : kHet ? e.meta[slot] & 31 : ((hdr >> 4) & 15) + 1;
-    if constexpr (!kHet) {
-      // overlap and zero-bubble plans go to the variant pass: the wavefront
-      // (one stage count: the plan-sorted groups are padded to whole
-      // wavefronts) takes one 64-slot tile and every lane writes its own
-      // position, the slot of an overlap or zero-bubble plan or kNoSlot, so
-      // that the tile keeps its plans' lanes together; the lane that takes
-      // the tile is the one readfirstlane reads.  That needs every lane of
-      // the wavefront here, which the loop's single uniform latch gives; if
-      // a compiler ever split the wavefront at this point, the tile would
-      // have holes, so a partial wavefront hands such lanes to the deferred
-      // lists instead (whole loop per lane, plans need not stay whole there).
-      const bool var = pending && (((hdr >> 13) & 1) | ((hdr >> 16) & 1));
-      const uint64_t vb = __ballot(var);
-      if (vb) {
-        if (__ballot(1) == ~0ull) {
-          const uint32_t Sv = __builtin_amdgcn_readfirstlane(__shfl(S, __ffsll((unsigned long long)vb) - 1));
-          uint32_t tile = 0;
-          if ((threadIdx.x & 63u) == 0) tile = atomicAdd(&e.ctr[kVariantCtr + kMaxStages - Sv], 64u);
-          tile = __builtin_amdgcn_readfirstlane(tile);
-          e.vlist[e.sstart[kMaxStages - Sv] + tile + (threadIdx.x & 63u)] = var ? slot : kNoSlot;
-        } else if (var) {
-          e.deferred[e.sstart[kMaxStages - S] + atomicAdd(&e.ctr[1 + kMaxStages - S], 1u)] = slot;
-        }
-        pending = pending && !var;
-      }
-    }
-    // one pass per distinct stage count present in the wavefront (usually one)
-    while (true) {
-      const uint64_t live = __ballot(pending);
-      if (!live) break;
-      const uint32_t S0 = __builtin_amdgcn_readfirstlane(__shfl(S, __ffsll((unsigned long long)live) - 1));
-      if (pending && S == S0) {
-        if (S0 == kTop) eval_one<kTop, false, kMode, kHet>(t, h, e, slot, xw, bw);
-        else if (S0 == kTop - 1) eval_one<kTop - 1, false, kMode, kHet>(t, h, e, slot, xw, bw);
-        else if (S0 == kTop - 2) eval_one<kTop - 2, false, kMode, kHet>(t, h, e, slot, xw, bw);
-        else eval_one<kTop - 3, false, kMode, kHet>(t, h, e, slot, xw, bw);
-        pending = false;
-      }
-    }
+  for (uint32_t q = lo + blockIdx.x * (kEvalThreads / 64) + wave; q < hi; q += gridDim.x * (kEvalThreads / 64)) {
+    const uint32_t g = tile_group(e, q, g0, 16), S = kTop - (g - g0) / kMaxClasses;
+    uint32_t slot;
+    if (!tile_slot<kHet>(e, q, g, slot)) continue;
+    if (S == kTop) eval_one<kTop, kMode, kHet, 0, false>(t, h, e, slot, xw, bw);
+    else if (S == kTop - 1) eval_one<kTop - 1, kMode, kHet, 0, false>(t, h, e, slot, xw, bw);
+    else if (S == kTop - 2) eval_one<kTop - 2, kMode, kHet, 0, false>(t, h, e, slot, xw, bw);
+    else eval_one<kTop - 3, kMode, kHet, 0, false>(t, h, e, slot, xw, bw);
   }
 }
 
-// Interleaved pipelines (shared layout) of one 64-pipeline tile starting at
-// sorted id `base` (ids below hi): one pass per (S, v) present in the tile.
-template <int kMode>
-__device__ __forceinline__ void il_tile(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t base,
-                                        uint32_t hi) {
-  const uint32_t pos = base + (threadIdx.x & 63u);
-  bool pending = pos < hi;
-  const uint32_t slot = pending ? e.ids[pos] : 0;
-  const uint32_t m = pending ? e.meta[slot] : 0;
-  const uint32_t key = il_shape(m & 31, (m >> 24) + 1);
-  while (true) {
-    const uint64_t live = __ballot(pending);
-    if (!live) break;
-    const uint32_t k0 = __builtin_amdgcn_readfirstlane(__shfl(key, __ffsll((unsigned long long)live) - 1));
-    if (pending && key == k0) {
-      switch (k0) {
-#define X(S_, V_)                          \
-  case S_ | (V_ - 1) << 5:                 \
-    eval_il<S_, V_, kMode>(t, h, e, slot); \
-    break;
-        HETSIM_IL_SHAPES(X)
-#undef X
-        default: break;
-      }
-      pending = false;
-    }
-  }
+// Overlap and zero-bubble plans of the four stage counts of group GRP (as
+// k_eval's groups), and with two-level collectives, whose sync code k_eval
+// lacks, the plain ones too.  The Tab is read from its copy in device memory:
+// this kernel holds every kind's code, and with the Tab as a by-value argument
+// the compiler copied the whole argument block to private memory in every
+// wave.  A block with no tile returns before touching LDS, so a launch over
+// empty lists costs next to nothing.
+template <int S, int kMode>
+__device__ __forceinline__ void eval_kind(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t kind,
+                                          uint32_t slot, double* xw) {
+  if (kind == 2) eval_one<S, kMode, false, 2, true>(t, h, e, slot, xw);
+  else if (kind == 1) eval_one<S, kMode, false, 1, true>(t, h, e, slot, xw);
+  else eval_one<S, kMode, false, 0, true>(t, h, e, slot, xw);
 }
-
-// Deferred pipelines of every stage count in one launch, so that the long
-// serial chains of the different stage counts overlap.  Tiles of 64 are
-// dealt round-robin to the waves of the grid: first the interleaved
-// pipelines (shared layout; sorted ids [sstart[16], sstart[16 + 21]), so a
-// tile mostly holds one (S, v) and one micro-batch count), then the
-// deferred S-stage pipelines at [sstart[16 - S], + ctr[1 + 16 - S]), tile q
-// located by walking the sixteen list lengths (16 stages first).  The Tab
-// is read from its copy in device memory: this kernel holds every pipeline
-// kind's code, and with the Tab as a by-value argument the compiler copied
-// the whole argument block to private memory in every wave.
-template <int kMode, bool kHet>
-__global__ void __launch_bounds__(kEvalThreads) k_deferred(const Tab* __restrict__ tp, EvalBufs e) {
-  const Tab& t = *tp;
-  extern __shared__ uint4 lds[];
-  fill_lds<kMode>(t, lds);
-  const Hot<kMode> h(t, lds);
-  const uint32_t waves = gridDim.x * (kEvalThreads / 64);
-  const uint32_t il_lo = kHet ? 0 : e.sstart[kMaxStages], il_hi = kHet ? 0 : e.sstart[kMaxStages + kIlGroups];
-  const uint32_t il_tiles = (il_hi - il_lo + 63) >> 6;
-  for (uint32_t q = blockIdx.x * (kEvalThreads / 64) + (threadIdx.x >> 6);; q += waves) {
-    if (!kHet && q < il_tiles) {
-      il_tile<kMode>(t, h, e, il_lo + q * 64u, il_hi);
-      continue;
-    }
-    uint32_t j = 0, before = il_tiles, nt = 0;
-    for (; j < kMaxStages; ++j) {
-      nt = (e.ctr[1 + j] + 63) >> 6;
-      if (q < before + nt) break;
-      before += nt;
-    }
-    if (j == kMaxStages) return;
-    const uint32_t off = (q - before) * 64u + (threadIdx.x & 63u);
-    if (off >= e.ctr[1 + j]) continue;
-    const uint32_t slot = e.vlist[e.sstart[j] + off];   // the deferred list, sorted
-    switch (kMaxStages - j) {
-      case 1: eval_deferred<1, kMode, kHet>(t, h, e, slot); break;
-      case 2: eval_deferred<2, kMode, kHet>(t, h, e, slot); break;
-      case 3: eval_deferred<3, kMode, kHet>(t, h, e, slot); break;
-      case 4: eval_deferred<4, kMode, kHet>(t, h, e, slot); break;
-      case 5: eval_deferred<5, kMode, kHet>(t, h, e, slot); break;
-      case 6: eval_deferred<6, kMode, kHet>(t, h, e, slot); break;
-      case 7: eval_deferred<7, kMode, kHet>(t, h, e, slot); break;
-      case 8: eval_deferred<8, kMode, kHet>(t, h, e, slot); break;
-      case 9: eval_deferred<9, kMode, kHet>(t, h, e, slot); break;
-      case 10: eval_deferred<10, kMode, kHet>(t, h, e, slot); break;
-      case 11: eval_deferred<11, kMode, kHet>(t, h, e, slot); break;
-      case 12: eval_deferred<12, kMode, kHet>(t, h, e, slot); break;
-      case 13: eval_deferred<13, kMode, kHet>(t, h, e, slot); break;
-      case 14: eval_deferred<14, kMode, kHet>(t, h, e, slot); break;
-      case 15: eval_deferred<15, kMode, kHet>(t, h, e, slot); break;
-      default: eval_deferred<16, kMode, kHet>(t, h, e, slot); break;
-    }
-  }
-}
-
-// Overlap and zero-bubble pipelines of the four stage counts of group GRP
-// (as k_eval's groups), taken from the tiles the first pass filled: the
-// S-stage tiles start at sstart[16 - S] and take ctr[kVariantCtr + 16 - S]
-// slots, each tile one first-pass wavefront's lanes (plans whole, kNoSlot
-// elsewhere), dealt round-robin to the waves of the grid.  The Tab is read from its copy
-// in device memory, as in k_deferred.  A block with no tile returns before
-// touching LDS, so a launch over empty lists costs next to nothing.
 template <int GRP, int kMode>
 __global__ void __launch_bounds__(kEvalThreads) k_variant(const Tab* __restrict__ tp, EvalBufs e) {
   constexpr int kTop = kMaxStages - 4 * GRP;   // stage counts kTop-3 .. kTop
-  const uint32_t c0 = e.ctr[kVariantCtr + kMaxStages - kTop], c1 = e.ctr[kVariantCtr + kMaxStages - kTop + 1];
-  const uint32_t c2 = e.ctr[kVariantCtr + kMaxStages - kTop + 2], c3 = e.ctr[kVariantCtr + kMaxStages - kTop + 3];
-  // first tile of each list
-  const uint32_t q1 = (c0 + 63) >> 6, q2 = q1 + ((c1 + 63) >> 6), q3 = q2 + ((c2 + 63) >> 6);
-  const uint32_t tiles = q3 + ((c3 + 63) >> 6);
-  const uint32_t wpb = kEvalThreads / 64;
-  if (blockIdx.x * wpb >= tiles) return;   // the whole block, before any barrier
+  constexpr uint32_t g0 = 16 * GRP, kStep = kMaxStages * kMaxClasses;
   const Tab& t = *tp;
+  const uint32_t n0 = t.ccl_hier ? e.tstart[g0 + 16] - e.tstart[g0] : 0;
+  const uint32_t n1 = n0 + e.tstart[kStep + g0 + 16] - e.tstart[kStep + g0];
+  const uint32_t tiles = n1 + e.tstart[2 * kStep + g0 + 16] - e.tstart[2 * kStep + g0];
+  if (blockIdx.x * (kEvalThreads / 64) >= tiles) return;   // the whole block, before any barrier
   extern __shared__ uint4 lds[];
   fill_lds<kMode>(t, lds);
   const Hot<kMode> h(t, lds);
-  const uint32_t waves = gridDim.x * wpb;
-  // the wavefront's row of the zero-bubble plans' DP exchange area (as k_eval's)
-  double* xw = (double*)((char*)lds + (kMode < 2 ? t.lds_bytes : 0)) + (threadIdx.x >> 6) * xchg_wave(GRP, true);
-  for (uint32_t q = blockIdx.x * wpb + (threadIdx.x >> 6); q < tiles; q += waves) {
-    const uint32_t j = (q >= q1) + (q >= q2) + (q >= q3);
-    const uint32_t first = j == 0 ? 0 : j == 1 ? q1 : j == 2 ? q2 : q3;
-    const uint32_t cnt = j == 0 ? c0 : j == 1 ? c1 : j == 2 ? c2 : c3;
-    const uint32_t off = (q - first) * 64u + (threadIdx.x & 63u);
-    if (off >= cnt) continue;
-    const uint32_t S = kTop - j;
-    const uint32_t slot = e.vlist[e.sstart[kMaxStages - S] + off];
-    if (slot == kNoSlot) continue;
-    if (j == 0) eval_variant<kTop, kMode>(t, h, e, slot, xw);
-    else if (j == 1) eval_variant<kTop - 1, kMode>(t, h, e, slot, xw);
-    else if (j == 2) eval_variant<kTop - 2, kMode>(t, h, e, slot, xw);
-    else eval_variant<kTop - 3, kMode>(t, h, e, slot, xw);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double* xw = (double*)((char*)lds + (kMode < 2 ? t.lds_bytes : 0)) + wave * xchg_wave(GRP, true);
+  for (uint32_t w = blockIdx.x * (kEvalThreads / 64) + wave; w < tiles; w += gridDim.x * (kEvalThreads / 64)) {
+    const uint32_t kind = w < n0 ? 0 : w < n1 ? 1 : 2, first = kind * kStep + g0;
+    const uint32_t q = e.tstart[first] + (w - (kind == 0 ? 0 : kind == 1 ? n0 : n1));
+    const uint32_t g = tile_group(e, q, first, 16), S = kTop - (g - first) / kMaxClasses;
+    uint32_t slot;
+    if (!tile_slot<false>(e, q, g, slot)) continue;
+    if (S == kTop) eval_kind<kTop, kMode>(t, h, e, kind, slot, xw);
+    else if (S == kTop - 1) eval_kind<kTop - 1, kMode>(t, h, e, kind, slot, xw);
+    else if (S == kTop - 2) eval_kind<kTop - 2, kMode>(t, h, e, kind, slot, xw);
+    else eval_kind<kTop - 3, kMode>(t, h, e, kind, slot, xw);
+  }
+}
+
+// Interleaved plans: tiles of one shape (S, v) and class count.  (The Tab: as
+// k_variant's.)
+template <int kMode>
+__global__ void __launch_bounds__(kEvalThreads) k_il(const Tab* __restrict__ tp, EvalBufs e) {
+  const Tab& t = *tp;
+  const uint32_t lo = e.tstart[kPlainGroups], hi = e.tstart[kGroups];
+  if (lo + blockIdx.x * (kEvalThreads / 64) >= hi) return;   // the whole block, before any barrier
+  extern __shared__ uint4 lds[];
+  fill_lds<kMode>(t, lds);
+  const Hot<kMode> h(t, lds);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double* xw = (double*)((char*)lds + (kMode < 2 ? t.lds_bytes : 0)) + wave * kIlXchg;
+  for (uint32_t q = lo + blockIdx.x * (kEvalThreads / 64) + wave; q < hi; q += gridDim.x * (kEvalThreads / 64)) {
+    const uint32_t g = tile_group(e, q, kPlainGroups, kGroups - kPlainGroups);
+    uint32_t slot;
+    if (!tile_slot<false>(e, q, g, slot)) continue;
+    switch ((g - kPlainGroups) / kMaxClasses) {
+#define X(S_, V_)                          \
+  case il_shape(S_, V_):                   \
+    eval_il<S_, V_, kMode>(t, h, e, slot, xw); \
+    break;
+      HETSIM_IL_SHAPES(X)
+#undef X
+      default: break;
+    }
   }
 }
 
@@ -2301,7 +2357,7 @@ __global__ void __launch_bounds__(kEvalThreads) k_variant(const Tab* __restrict_
 template <int S>
 __device__ __forceinline__ uint64_t redo_one(const StageRec& R, const uint64_t (&W)[kMaxStages], bool zb,
                                              uint32_t M) {
-  uint64_t f[S], b[S], w[S], c[S], x[S], T = 0;
+  uint64_t f[S], b[S], w[S], c[S], x[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     f[s] = R[s][0];
@@ -2311,13 +2367,11 @@ __device__ __forceinline__ uint64_t redo_one(const StageRec& R, const uint64_t (
     x[s] = R[s][3];
   }
   // the zero-bubble chain with w = 0 is the plain one; the periodic shortcut
-  // holds in any exact arithmetic: pairs within the budget, then the rest of
-  // the loop in place
+  // holds in any exact arithmetic
   Chain<S, uint64_t> h;
   int skipped;
   reduce_chain<S, uint64_t, true>(f, b, w, c, x, M, h);
-  chain_time<S, uint64_t, true, true, true>(h, w, M, skipped, T);
-  return T;
+  return chain_time<S, uint64_t, true>(h, w, M, skipped);
 }
 
 template <bool kHet>
@@ -2333,7 +2387,7 @@ __global__ void __launch_bounds__(64) k_redo_u64(Tab t, EvalBufs e) {
       int skipped;
       switch (il_shape(S, p.v)) {
 #define X(S_, V_)                                                    \
-  case S_ | (V_ - 1) << 5:                                           \
+  case il_shape(S_, V_):                                             \
     r = il_time<S_, V_, 2, uint64_t, true>(t, h, p, skipped);        \
     break;
         HETSIM_IL_SHAPES(X)

@@ -13,28 +13,23 @@ constexpr int kMaxStages = 16;
 constexpr int kMaxClasses = 4;
 constexpr int kRecWords = 4;                    // per (plan, class, stage): fwd, bwd, hop, dp
 constexpr int kPlanWords = kMaxClasses * kMaxStages * kRecWords;
-constexpr int kBucketsM = 128;                  // micro-batch-count buckets per (stages, classes)
-constexpr int kPlainBuckets = kMaxStages * kMaxClasses * kBucketsM;
-// Interleaved 1F1B pipelines (S = 2..8 devices, v = 2..4 chunks, S v <= 16)
-// sort after all others, in groups keyed (S - 2) * 3 + (v - 2), each of
-// kIlBucketsQ micro-batch buckets.
-constexpr int kIlGroups = 21;
-constexpr int kIlBucketsQ = 48;
-constexpr int kBuckets = kPlainBuckets + 1024;
-static_assert(kIlGroups * kIlBucketsQ <= 1024, "interleaved buckets");
-// sstart: [16 - S] first sorted id of the S-stage pipelines, [16 + q] first
-// id of interleaved group q, [16 + kIlGroups] the total
-constexpr int kSstartWords = kMaxStages + kIlGroups + 1;
-// Plans of the shared layout with one model chunk per device are sorted by
-// plan: the G pipelines of a plan take G adjacent lanes of one wavefront,
-// every wavefront holds plans of one stage count and one class count (64 / G
-// plans of them, 21 when G = 3), and each (stages, classes) bucket starts on
-// a wavefront boundary.  kGroupPad bounds the padding lanes this adds to a
-// chunk; padding lanes hold kNoSlot.
-constexpr uint32_t kSuperBuckets = kMaxStages * kMaxClasses;
-constexpr uint32_t kGroupPad = 64 * kSuperBuckets;
-constexpr uint32_t kNoSlot = 0xffffffffu;
-__host__ __device__ constexpr uint32_t plans_per_wave(uint32_t G) { return G == 3 ? 21 : 64 / G; }
+// Order of a chunk.  Shared-layout plans are sorted by plan into groups of one
+// kind of schedule, stage count S and class count G, and inside a group into
+// micro-batch buckets (most micro-batches first); with the per-class layout
+// the pipelines are sorted one by one (kind 0).  Groups: 64 per kind (more
+// stages first, then more classes), then four per interleaved shape (S, v).
+// A group's plans are dealt to tiles of one wavefront each: the G pipelines of
+// a plan on G adjacent lanes, 64 / G plans per tile (21 when G = 3); the
+// per-class layout has one pipeline per lane.  order[] holds the plans (or
+// pipelines) group by group, gstart[g] the first of group g, tstart[g] its
+// first tile.
+constexpr int kKinds = 3;                       // 0: 1F1B; 1: overlapped gradient sync; 2: zero-bubble order
+constexpr int kBucketsM = 32;
+constexpr int kIlShapes = 14;                   // (S, v) of interleaved plans: S v <= 16
+constexpr uint32_t kPlainGroups = kKinds * kMaxStages * kMaxClasses;
+constexpr uint32_t kGroups = kPlainGroups + kIlShapes * kMaxClasses;
+constexpr uint32_t kBuckets = kGroups * kBucketsM;
+__host__ __device__ constexpr uint32_t plans_per_tile(uint32_t G) { return G == 3 ? 21 : 64 / G; }
 // LDS of the first and variant passes over plan-sorted pipelines: per
 // wavefront one column of 64 doubles per stage (up to the kernel's largest
 // stage count, and in the variant pass two more for the embedding's and the
@@ -44,6 +39,8 @@ __host__ __device__ constexpr uint32_t xchg_wave(int group, bool variant) {
   return 64u * ((uint32_t)(kMaxStages - 4 * group) + (variant ? 2u : 0u));
 }
 __host__ __device__ constexpr uint32_t xchg_bytes(int group, bool variant) { return 4 * xchg_wave(group, variant) * 8; }
+// the interleaved pass: a column per device (at most 8)
+constexpr uint32_t kIlXchg = 64u * 8u, kIlXchgBytes = 4 * kIlXchg * 8;
 // The first pass of the two long stage-count groups keeps each lane's stage
 // placements (first device in the pool, u32 per stage) in LDS from setup to
 // the DP tail, where the plan's lanes read each other's instead of counting
@@ -126,100 +123,139 @@ struct Tab {
   uint32_t mode;
   const void* img;                // the image in device memory (16-byte aligned)
   uint32_t grid_eval[4];          // blocks of each first-pass kernel that fit the device at once
-  uint32_t grid_deferred;
+  uint32_t grid_il;               // blocks of the interleaved kernel that fit the device at once
+  uint32_t grid_cont;             // blocks of the continuation kernels that fit the device at once
   uint32_t grid_variant[4];       // blocks of each variant-pass kernel that fit the device at once
   uint32_t bcache;                // bit g: first-pass group g keeps stage placements in LDS (when that
                                   // costs no occupancy)
 };
 
-// Device buffers of one evaluation pass over a chunk, as the host hands them
-// to the launcher.  sstart[16 - S] is the first sorted id of the S-stage
-// pipelines, sstart[16] their total and the first id of the interleaved
-// pipelines (layout above).  ctr[0] counts overflowed pipelines,
-// ctr[1 + 16 - S] the S-stage pipelines deferred to the full-loop pass,
-// ctr[kVariantCtr + 16 - S] the slots of the S-stage overlap and zero-bubble
-// tiles of the variant pass (64 per tile); the per-class layout's plan-order
-// counters (kPlanSortWords) follow the evaluation counters at ctr +
-// kEvalCounters, and the overflow list follows them at ctr + kEvalCounters +
-// kPlanSortWords.
-constexpr uint32_t kVariantCtr = 1 + kMaxStages;
-// The deferred lists are sorted by micro-batch count before the deferred
-// pass (longest first, kSortBuckets buckets per stage count): their counts
-// at ctr[kSortCtr + 32 j + b], cursors at ctr[kSortCtr + 512 + 32 j + b] for
-// the list of 16 - j stages.
-constexpr uint32_t kSortBuckets = 32;
-constexpr uint32_t kSortCtr = 48;
-constexpr uint32_t kEvalCounters = kSortCtr + 2 * kMaxStages * kSortBuckets;
+// Continuation lists.  A pipeline whose schedule is still aperiodic after the
+// first pass's budget leaves its recurrence state -- 4 S words: F_s, a_s, d_s,
+// e_s and the iterations left with the pipeline's slot -- in a list of its
+// stage count, in tiles of 64 (word r of entry l of a tile at [64 r + l]), and
+// k_cont goes on with full wavefronts of them; what is left after its budget
+// moves on to a second list and k_power.  cinfo[j], j = 16 - S: the
+// list's first 2 KiB unit in the continuation buffer, cinfo[16 + j]: its
+// capacity in tiles (S units each); [32 + j] and [48 + j] the same for the
+// second list.  A pipeline that finds its list full goes on where it is.
+constexpr uint32_t kContUnit = 2048;            // bytes
+constexpr uint32_t kContWords = 64;
+// Counters of a chunk: [0] pipelines to redo in u64, [1 + j] and [17 + j]
+// pipelines offered to the first and second continuation list of 16 - j
+// stages; the per-class layout's plan-order counters (kPlanSortWords) follow
+// them, then the redo list.
+constexpr uint32_t kEvalCounters = 48;
+static_assert(1 + 2 * kMaxStages <= kEvalCounters, "evaluation counters");
 // Per-class layout: plans counting-sorted by (classes, total stages) before
 // the plan-level sync pass -- counts [0, 256), cursors [256, 512), the
 // number of valid plans at 512.
 constexpr uint32_t kPlanBuckets = 256;
 constexpr uint32_t kPlanSortWords = 2 * kPlanBuckets + 1;
-static_assert(kVariantCtr + kMaxStages <= kSortCtr, "evaluation counters");
 // The skipped-work counter is spread over slots on separate cache lines so
 // that the waves of a launch do not serialise on one address.
 constexpr uint32_t kSkipSlots = 512, kSkipStride = 16;
-struct EvalArgs {
+
+// Device buffers of one evaluation pass over a chunk.
+struct EvalBufs {
   const PackedPlan* packed;
-  const void* pcut;            // per-class layout: four 16-byte cut rows per plan; nullptr for the shared layout
-  const uint64_t* hdp;         // per-class layout: per pipeline slot, the syncs its 16 stages wait for
-  const uint32_t* meta;
-  const uint32_t* ids;
-  const uint32_t* sstart;
+  const uint4* pcut;           // per-class layout: cut row of pipeline slot at [slot]; nullptr for the shared layout
+  const uint64_t* hdp;         // per-class layout: the syncs of pipeline slot's stages at [16 slot, + 16)
+  const uint32_t* order;       // plans (shared layout) or pipeline slots (per-class layout) by group
+  const uint32_t* gstart;      // [kGroups + 1]
+  const uint32_t* tstart;      // [kGroups + 1]
+  const uint32_t* cinfo;       // [kContWords]
   uint64_t* out;
   uint32_t* ctr;
-  uint32_t* deferred;          // as long as ids
-  uint32_t* vlist;             // as long as ids: overlap and zero-bubble tiles (kNoSlot where empty)
-  uint64_t* skipped_ops;       // optional: kSkipSlots counters, kSkipStride words apart
-  const Tab* dtab;             // the context's Tab in device memory (read by the deferred pass)
+  uint32_t* ovf;               // pipelines whose fp64 time reached 2^53
+  double* cont;                // the continuation lists
+  unsigned long long* skipped_ops;   // optional: kSkipSlots counters, kSkipStride words apart
+  const Tab* dtab;             // the context's Tab in device memory
 };
 
 constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Workspace of one chunk: packed plans, pipeline metadata, pipeline ids and
-// the deferred lists, bucket counts followed by the evaluation counters and
-// the overflow list (counts and counters cleared together), bucket cursors,
-// the start of each stage count's pipelines, each pipeline's bucket key
-// (u16, written with the metadata and read by the scatter), and with the
-// per-class layout
-// the plans' class cut rows (64 bytes per plan) and the syncs each pipeline's
-// stages wait for (16 u64 per pipeline slot, 512 bytes per plan).
+// Workspace of one chunk: packed plans, their order, bucket counts followed by
+// the evaluation counters and the redo list (counts and counters cleared
+// together), bucket cursors, group and tile starts, the bucket key of each
+// plan (u16; of each pipeline with the per-class layout), the continuation
+// lists, and with the per-class layout the pipeline metadata, the plan order
+// of the sync pass, the plans' class cut rows (64 bytes per plan) and the
+// syncs each pipeline's stages wait for (16 u64 per pipeline slot, 512 bytes
+// per plan).
 constexpr uint32_t kCounters = kBuckets + kEvalCounters + kPlanSortWords;
 struct Work {
   PackedPlan* packed;
   uint4* pcut;
   uint64_t* hdp;
-  uint32_t *meta, *ids, *deferred, *vlist, *hist, *ctr, *cursor, *sstart, *sbase;
+  uint32_t *meta, *perm, *order, *hist, *ctr, *ovf, *cursor, *gstart, *tstart, *cinfo;
   uint16_t* keys;
+  double* cont;
+  uint32_t cont_units;         // size of cont in kContUnit
 };
-// sorted ids (and deferred lists) of a chunk: four lanes per plan at most,
-// plus the padding of the plan-sorted buckets
-constexpr size_t id_words(int64_t ch) { return (size_t)ch * 4 + kGroupPad; }
+// Bytes of the continuation lists: about what k_scan would take for a random
+// sweep's chunk (two to three pipelines per plan), at least one tile of every
+// list.
+constexpr size_t cont_bytes(int64_t ch, size_t per_plan) {
+  const size_t b = (size_t)ch * per_plan;
+  return ((b > (1u << 20) ? b : (1u << 20)) + kContUnit - 1) / kContUnit * kContUnit;
+}
+constexpr size_t kContPerPlan = 224, kContPerPlanNoAlloc = 32;
 constexpr size_t cut_rows_bytes(int64_t ch, bool het) { return het ? align256((size_t)ch * 64) : 0; }
-constexpr size_t het_sync_bytes(int64_t ch, bool het) {
-  return het ? align256((size_t)ch * kMaxClasses * kMaxStages * 8) : 0;
+struct Carver {   // running offset
+  size_t off = 0;
+  constexpr size_t take(size_t bytes) {
+    const size_t r = off;
+    off += align256(bytes);
+    return r;
+  }
+};
+struct WorkOffsets {
+  size_t cont, pcut, hdp, meta, perm, packed, order, hist, cursor, gstart, tstart, cinfo, keys, total;
+};
+constexpr WorkOffsets work_offsets(int64_t ch, bool het, size_t cont_per_plan) {
+  const size_t n = (size_t)ch, np = het ? 4 * n : n, nh = het ? n : 0;
+  Carver c;
+  WorkOffsets o = {};
+  o.cont = c.take(cont_bytes(ch, cont_per_plan));
+  o.pcut = c.take(nh * 64);
+  o.hdp = c.take(nh * kMaxClasses * kMaxStages * 8);
+  o.meta = c.take(nh * 16);
+  o.perm = c.take(nh * 4);
+  o.packed = c.take(n * sizeof(PackedPlan));
+  o.order = c.take(np * 4);
+  o.hist = c.take(kCounters * 4 + n * 16);
+  o.cursor = c.take(kBuckets * 4);
+  o.gstart = c.take((kGroups + 1) * 4);
+  o.tstart = c.take((kGroups + 1) * 4);
+  o.cinfo = c.take(kContWords * 4);
+  o.keys = c.take(np * 2);
+  o.total = c.off;
+  return o;
 }
-constexpr size_t work_bytes(int64_t ch, bool het) {
-  return align256((size_t)ch * sizeof(PackedPlan)) + align256((size_t)ch * 4 * 4) + 3 * align256(id_words(ch) * 4) +
-         align256(kCounters * 4 + (size_t)ch * 4 * 4) + align256(kBuckets * 4) + align256(kSstartWords * 4) +
-         align256(kSuperBuckets * 4) + align256((size_t)ch * 4 * 2) +
-         cut_rows_bytes(ch, het) + het_sync_bytes(ch, het);
+constexpr size_t work_bytes(int64_t ch, bool het, size_t cont_per_plan) {
+  return work_offsets(ch, het, cont_per_plan).total;
 }
-inline Work carve(void* base, int64_t ch, bool het) {
-  Work w;
+inline Work carve(void* base, int64_t ch, bool het, size_t cont_per_plan) {
+  const WorkOffsets o = work_offsets(ch, het, cont_per_plan);
   char* p = (char*)base;
-  w.pcut = het ? (uint4*)p : nullptr; p += cut_rows_bytes(ch, het);
-  w.hdp = het ? (uint64_t*)p : nullptr; p += het_sync_bytes(ch, het);
-  w.packed = (PackedPlan*)p; p += align256((size_t)ch * sizeof(PackedPlan));
-  w.meta = (uint32_t*)p; p += align256((size_t)ch * 16);
-  w.ids = (uint32_t*)p; p += align256(id_words(ch) * 4);
-  w.deferred = (uint32_t*)p; p += align256(id_words(ch) * 4);
-  w.vlist = (uint32_t*)p; p += align256(id_words(ch) * 4);
-  w.hist = (uint32_t*)p; w.ctr = w.hist + kBuckets; p += align256(kCounters * 4 + (size_t)ch * 16);
-  w.cursor = (uint32_t*)p; p += align256(kBuckets * 4);
-  w.sstart = (uint32_t*)p; p += align256(kSstartWords * 4);
-  w.sbase = (uint32_t*)p; p += align256(kSuperBuckets * 4);
-  w.keys = (uint16_t*)p;
+  Work w;
+  w.cont = (double*)(p + o.cont);
+  w.cont_units = (uint32_t)(cont_bytes(ch, cont_per_plan) / kContUnit);
+  w.pcut = het ? (uint4*)(p + o.pcut) : nullptr;
+  w.hdp = het ? (uint64_t*)(p + o.hdp) : nullptr;
+  w.meta = het ? (uint32_t*)(p + o.meta) : nullptr;
+  w.perm = het ? (uint32_t*)(p + o.perm) : nullptr;
+  w.packed = (PackedPlan*)(p + o.packed);
+  w.order = (uint32_t*)(p + o.order);
+  w.hist = (uint32_t*)(p + o.hist);
+  w.ctr = w.hist + kBuckets;
+  w.ovf = w.hist + kCounters;
+  w.cursor = (uint32_t*)(p + o.cursor);
+  w.gstart = (uint32_t*)(p + o.gstart);
+  w.tstart = (uint32_t*)(p + o.tstart);
+  w.cinfo = (uint32_t*)(p + o.cinfo);
+  w.keys = (uint16_t*)(p + o.keys);
   return w;
 }
 
@@ -228,9 +264,10 @@ inline Work carve(void* base, int64_t ch, bool het) {
 // per-class layout, in a static device array (one per GPU).
 constexpr int64_t kNoAllocPlans = 1 << 18;
 constexpr int64_t kNoAllocPlansHet = 1 << 16;
-constexpr size_t kNoAllocBytes = work_bytes(kNoAllocPlans, false) > work_bytes(kNoAllocPlansHet, true)
-                                     ? work_bytes(kNoAllocPlans, false)
-                                     : work_bytes(kNoAllocPlansHet, true);
+constexpr size_t kNoAllocBytes =
+    work_bytes(kNoAllocPlans, false, kContPerPlanNoAlloc) > work_bytes(kNoAllocPlansHet, true, kContPerPlanNoAlloc)
+        ? work_bytes(kNoAllocPlans, false, kContPerPlanNoAlloc)
+        : work_bytes(kNoAllocPlansHet, true, kContPerPlanNoAlloc);
 // Address of this device's copy of that array (the current device); 0 or a
 // HIP error code.
 int noalloc_scratch(int device, void** ptr);

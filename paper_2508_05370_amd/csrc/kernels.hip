@@ -41,94 +41,106 @@ __global__ void k_fill32(uint32_t* p, uint32_t n, uint32_t v) {
   for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gridDim.x * blockDim.x) p[j] = v;
 }
 
-// Bucket offsets.  Plain buckets come in 64 groups of kBucketsM (one group
-// per (stages, classes), more stages first, then more classes), the
-// interleaved buckets after them.  With `grouped` (a shared-layout call),
-// the plain groups count plans, not pipelines: a group of G classes then
-// takes ceil(plans / plans_per_wave(G)) whole wavefronts of lanes, its
-// buckets' cursors count plans from the group's start, and sbase[group] is
-// the group's first lane.  Otherwise (per-class layout) they count pipelines
-// and their cursors are lanes.  sstart[16 - S] = first lane of
-// the S-stage pipelines, sstart[16 + q] = first lane of interleaved group q,
-// sstart[16 + kIlGroups] = all lanes.  Thread tid takes plain buckets
-// [8 tid, 8 tid + 8) (sixteen threads per group) and interleaved bucket
-// kPlainBuckets + tid; one block scan of (plain, interleaved) pairs, then one
-// of the 64 groups' lane counts.
-__global__ void __launch_bounds__(1024) k_scan(const uint32_t* __restrict__ hist, uint32_t* __restrict__ cursor,
-                                               uint32_t* __restrict__ sstart, uint32_t* __restrict__ sbase,
-                                               uint32_t grouped, uint32_t* __restrict__ ids) {
-  constexpr int kPer = kPlainBuckets / 1024;
-  constexpr int kThreadsPerGroup = kBucketsM / kPer;
-  static_assert(kPlainBuckets % 1024 == 0 && kBuckets - kPlainBuckets == 1024, "bucket count");
-  static_assert(kThreadsPerGroup * kSuperBuckets == 1024, "sixteen threads per (stages, classes) group");
-  __shared__ uint2 part[1024];
-  __shared__ uint32_t lanes[kSuperBuckets + 1];
-  uint32_t v[kPer], sum = 0;
-  const uint32_t tid = threadIdx.x;
+// Inclusive sum over a block of 1024 threads (16 wavefronts).
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* part) {
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) { v[j] = hist[tid * kPer + j]; sum += v[j]; }
-  const uint32_t vi = hist[kPlainBuckets + tid];
-  part[tid] = make_uint2(sum, vi);
+  for (uint32_t o = 1; o < 64; o <<= 1) {
+    const uint32_t x = __shfl_up(v, o);
+    v += lane >= o ? x : 0;
+  }
+  if (lane == 63) part[wave] = v;
   __syncthreads();
-  for (uint32_t off = 1; off < 1024; off <<= 1) {
-    const uint2 x = tid >= off ? part[tid - off] : make_uint2(0, 0);
-    __syncthreads();
-    part[tid].x += x.x;
-    part[tid].y += x.y;
-    __syncthreads();
-  }
-  // the group of this thread's buckets, its entries before this thread's
-  const uint32_t grp = tid / kThreadsPerGroup, g0 = grp * kThreadsPerGroup;
-  const uint32_t before_grp = g0 ? part[g0 - 1].x : 0;
-  const bool by_plan = grouped != 0;
-  uint32_t ngrp = 0;
-  if (tid < kSuperBuckets) {
-    // lanes of group tid
-    const uint32_t a = tid * kThreadsPerGroup;
-    ngrp = part[a + kThreadsPerGroup - 1].x - (a ? part[a - 1].x : 0);
-    const uint32_t pw = plans_per_wave(kMaxClasses - tid % kMaxClasses);
-    lanes[tid] = grouped ? (ngrp + pw - 1) / pw * 64u : ngrp;
-  }
+  uint32_t before = 0;
+  for (uint32_t w = 0; w < 16; ++w) before += w < wave ? part[w] : 0;
   __syncthreads();
-  if (tid == 0) {
-    uint32_t run = 0;
-    for (uint32_t q = 0; q < kSuperBuckets; ++q) {
-      const uint32_t x = lanes[q];
-      lanes[q] = run;
-      run += x;
-    }
-    lanes[kSuperBuckets] = run;
-  }
-  __syncthreads();
-  if (tid < kSuperBuckets) sbase[tid] = lanes[tid];
-  // a plan-sorted group's last wavefront, when partly filled: its lanes past
-  // the plans hold no pipeline (k_scatter marks the unused lanes of the full ones)
-  if (grouped && tid < kSuperBuckets) {
-    const uint32_t G = kMaxClasses - tid % kMaxClasses, pw = plans_per_wave(G), r = ngrp % pw;
-    const uint32_t w0 = lanes[tid] + ngrp / pw * 64u;
-    if (r)
-      for (uint32_t q = G * r; q < 64u; ++q) ids[w0 + q] = kNoSlot;
-  }
-  // pipelines of S stages start at group (16 - S) * 4 (four classes first)
-  if (tid < kMaxStages) sstart[tid] = lanes[tid * kMaxClasses];
-  uint32_t run = part[tid].x - sum - before_grp;
-  if (!by_plan) run += lanes[grp];
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) { cursor[tid * kPer + j] = run; run += v[j]; }
-  const uint32_t irun = lanes[kSuperBuckets] + part[tid].y - vi;
-  if (tid % kIlBucketsQ == 0 && tid / kIlBucketsQ <= (uint32_t)kIlGroups) sstart[kMaxStages + tid / kIlBucketsQ] = irun;
-  cursor[kPlainBuckets + tid] = irun;
+  return v + before;
 }
 
-// Place every pipeline id at its bucket's next free lane.  A plain key of a
-// grouped call sits on the plan's class-0 slot and stands for the whole plan: the plan's rank r in its
-// group puts its G pipeline ids on lanes sbase[group] + 64 (r / P) + G (r % P)
-// onward (P = plans_per_wave(G)); the lanes no plan fills are set to kNoSlot
-// here (64 mod G per full wavefront) and by k_scan (a group's last one).
-constexpr int kScatterPer = 64;
-__global__ void __launch_bounds__(256) k_scatter(const uint16_t* __restrict__ keys, uint32_t nslots,
-                                                 uint32_t* __restrict__ cursor, const uint32_t* __restrict__ sbase,
-                                                 uint32_t grouped, uint32_t* __restrict__ ids) {
+// Bucket offsets: cursor[b] the first entry of bucket b in order[], gstart and
+// tstart each group's first entry and tile (grouped: shared layout, plans;
+// otherwise pipelines), and the continuation lists' places and capacities in a
+// buffer of `units` units: of the tiles of S stages (S + 2) / 48 in the first
+// list -- about twice what the first pass leaves on the random sweeps -- and a
+// quarter of that in the second, or as much of it as fits.
+// Four threads per group, eight buckets each.
+__global__ void __launch_bounds__(1024) k_scan(const uint32_t* __restrict__ hist, uint32_t* __restrict__ cursor,
+                                               uint32_t* __restrict__ gstart, uint32_t* __restrict__ tstart,
+                                               uint32_t* __restrict__ cinfo, uint32_t grouped, uint32_t units) {
+  constexpr uint32_t kPer = 8, kThreads = kBuckets / kPer;
+  static_assert(kThreads <= 1024 && kBucketsM / kPer == 4, "four threads per group");
+  __shared__ uint32_t part[16], stiles[kMaxStages];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, grp = tid >> 2;
+  const bool has = tid < kThreads, head = has && (tid & 3) == 0;
+  if (tid < (uint32_t)kMaxStages) stiles[tid] = 0;
+  uint32_t v[kPer], sum = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < kPer; ++j) {
+    v[j] = has ? hist[tid * kPer + j] : 0;
+    sum += v[j];
+  }
+  const uint32_t incl = block_scan(sum, part);
+  uint32_t run = incl - sum;
+  if (has) {
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+      cursor[tid * kPer + j] = run;
+      run += v[j];
+    }
+  }
+  uint32_t n = sum + __shfl_xor(sum, 1);
+  n += __shfl_xor(n, 2);   // the group's entries
+  const uint32_t per = grouped ? plans_per_tile(kMaxClasses - grp % kMaxClasses) : 64u;
+  const uint32_t tiles = head ? (n + per - 1) / per : 0;
+  const uint32_t tincl = block_scan(tiles, part);
+  if (head) {
+    gstart[grp] = incl - sum;
+    tstart[grp] = tincl - tiles;
+    if (grp < kPlainGroups && tiles) atomicAdd(&stiles[grp / kMaxClasses % kMaxStages], tiles);
+  }
+  if (tid == kThreads - 1) {
+    gstart[kGroups] = incl;
+    tstart[kGroups] = tincl;
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const bool on = tid < (uint32_t)kMaxStages;
+    const uint32_t S = on ? kMaxStages - tid : 0;
+    uint32_t cap1 = on ? (stiles[tid] * (S + 2) + 47) / 48 : 0, cap2 = (cap1 + 3) / 4;
+    auto total = [&](uint32_t x) {   // sum over the wavefront
+#pragma unroll
+      for (uint32_t o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+      return x;
+    };
+    auto before = [&](uint32_t x) {   // sum over the lower lanes
+      uint32_t y = x;
+#pragma unroll
+      for (uint32_t o = 1; o < 64; o <<= 1) {
+        const uint32_t z = __shfl_up(y, o);
+        y += lane >= o ? z : 0;
+      }
+      return y - x;
+    };
+    if (total((cap1 + cap2) * S) > units) {
+      // the first lists in proportion, so that the second ones fit in their quarter
+      const uint64_t want = (uint64_t)total(cap1 * S) * 5;
+      cap1 = (uint32_t)((uint64_t)cap1 * units * 4 / want);
+      cap2 = cap1 / 4;
+    }
+    const uint32_t b1 = before(cap1 * S), b2 = total(cap1 * S) + before(cap2 * S);
+    if (on) {
+      cinfo[tid] = b1;
+      cinfo[16 + tid] = cap1;
+      cinfo[32 + tid] = b2;
+      cinfo[48 + tid] = cap2;
+    }
+  }
+}
+
+// Place every plan (or pipeline) at its bucket's next free entry.
+constexpr int kScatterPer = 16;
+__global__ void __launch_bounds__(256) k_scatter(const uint16_t* __restrict__ keys, uint32_t n,
+                                                 uint32_t* __restrict__ cursor, uint32_t* __restrict__ order) {
   constexpr int kPer = kScatterPer;
   __shared__ uint32_t lc[kBuckets];
   for (uint32_t j = threadIdx.x; j < kBuckets; j += blockDim.x) lc[j] = 0;
@@ -137,36 +149,18 @@ __global__ void __launch_bounds__(256) k_scatter(const uint16_t* __restrict__ ke
   const uint32_t first = blockIdx.x * blockDim.x * kPer + threadIdx.x;
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    const uint32_t slot = first + j * blockDim.x;
-    key[j] = 0xffffffffu;
-    rank[j] = 0;
-    if (slot < nslots) {
-      const uint32_t k = keys[slot];
-      if (k != kNoKey) {
-        key[j] = k;
-        rank[j] = atomicAdd(&lc[k], 1u);
-      }
-    }
+    const uint32_t i = first + j * blockDim.x;
+    key[j] = i < n ? keys[i] : kNoKey;
   }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) rank[j] = key[j] != kNoKey ? atomicAdd(&lc[key[j]], 1u) : 0;
   __syncthreads();
   for (uint32_t j = threadIdx.x; j < kBuckets; j += blockDim.x)
     if (lc[j]) lc[j] = atomicAdd(&cursor[j], lc[j]);
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    if (key[j] == 0xffffffffu) continue;
-    const uint32_t slot = first + j * blockDim.x, pos = lc[key[j]] + rank[j];
-    const uint32_t grp = key[j] / kBucketsM, G = kMaxClasses - grp % kMaxClasses;
-    if (grouped && key[j] < kPlainBuckets) {
-      const uint32_t pw = plans_per_wave(G), lane = sbase[grp] + pos / pw * 64u + pos % pw * G;
-      for (uint32_t c = 0; c < G; ++c) ids[lane + c] = slot + c;
-      // the wavefront's last plan marks the lanes that no plan fills (64 mod G)
-      if (pos % pw == pw - 1)
-        for (uint32_t q = G * pw; q < 64u; ++q) ids[lane - (pw - 1) * G + q] = kNoSlot;
-    } else {
-      ids[pos] = slot;
-    }
-  }
+  for (int j = 0; j < kPer; ++j)
+    if (key[j] != kNoKey) order[lc[key[j]] + rank[j]] = first + j * blockDim.x;
 }
 
 // ---------------------------------------------------------------- per-class layout: plan order
@@ -216,7 +210,7 @@ __global__ void __launch_bounds__(256) k_plan_scatter(const uint4* __restrict__ 
   uint32_t key[kPlanPer], rank[kPlanPer];
   for (int j = 0; j < kPlanPer; ++j) {
     const uint32_t i = (blockIdx.x * kPlanPer + j) * 256 + threadIdx.x;
-    key[j] = kNoSlot;
+    key[j] = kNoKey;
     if (i < n) {
       const uint4 m = meta[i];
       if (m.x) {
@@ -229,77 +223,111 @@ __global__ void __launch_bounds__(256) k_plan_scatter(const uint4* __restrict__ 
   if (lc[b]) lc[b] = atomicAdd(&pc[kPlanBuckets + b], lc[b]);
   __syncthreads();
   for (int j = 0; j < kPlanPer; ++j)
-    if (key[j] != kNoSlot) perm[base[key[j]] + lc[key[j]] + rank[j]] = (blockIdx.x * kPlanPer + j) * 256 + threadIdx.x;
+    if (key[j] != kNoKey) perm[base[key[j]] + lc[key[j]] + rank[j]] = (blockIdx.x * kPlanPer + j) * 256 + threadIdx.x;
 }
 
-// ---------------------------------------------------------------- deferred lists
-// Counting sort of the deferred lists by micro-batch count (bucket
-// min(31, M / 16), largest first) into vlist, which the variant pass has
-// finished with: the deferred pass then runs wavefronts of similar trip
-// counts rather than waiting in every wavefront for its longest chain.
-__device__ __forceinline__ uint32_t defer_bucket(const EvalBufs& e, uint32_t slot) {
-  const uint32_t w = e.packed[slot >> 2].cls[slot & 3], reps = w & 0xffff, M = ((w >> 16) + reps - 1) / reps;
-  const uint32_t b = M >> 4;
-  return b < kSortBuckets - 1 ? b : kSortBuckets - 1;
-}
-// entry idx of the concatenated lists -> (list j, position k in it)
-__device__ __forceinline__ bool defer_entry(const EvalBufs& e, uint32_t idx, uint32_t& j, uint32_t& k) {
-  uint32_t before = 0;
-  for (j = 0; j < (uint32_t)kMaxStages; ++j) {
-    const uint32_t n = e.ctr[1 + j];
-    if (idx < before + n) {
-      k = idx - before;
-      return true;
-    }
-    before += n;
-  }
-  return false;
-}
-__global__ void __launch_bounds__(256) k_defer_hist(EvalBufs e) {
-  __shared__ uint32_t hs[kMaxStages * kSortBuckets];
-  for (uint32_t i = threadIdx.x; i < kMaxStages * kSortBuckets; i += blockDim.x) hs[i] = 0;
-  __syncthreads();
-  uint32_t total = 0;
-  for (uint32_t j = 0; j < (uint32_t)kMaxStages; ++j) total += e.ctr[1 + j];
-  for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += gridDim.x * blockDim.x) {
-    uint32_t j, k;
-    if (!defer_entry(e, idx, j, k)) break;
-    atomicAdd(&hs[j * kSortBuckets + defer_bucket(e, e.deferred[e.sstart[j] + k])], 1u);
-  }
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < kMaxStages * kSortBuckets; i += blockDim.x)
-    if (hs[i]) atomicAdd(&e.ctr[kSortCtr + i], hs[i]);
-}
-__global__ void __launch_bounds__(256) k_defer_sort(EvalBufs e) {
-  constexpr uint32_t kN = kMaxStages * kSortBuckets;
-  __shared__ uint32_t base[kN], lc[kN];
-  if (threadIdx.x < (uint32_t)kMaxStages) {   // list j's buckets, largest micro-batch counts first
-    uint32_t run = 0;
-    for (int b = kSortBuckets - 1; b >= 0; --b) {
-      base[threadIdx.x * kSortBuckets + b] = run;
-      run += e.ctr[kSortCtr + threadIdx.x * kSortBuckets + b];
+// ---------------------------------------------------------------- continuation passes
+// The first list: tiles dealt round-robin to the waves of the grid.
+__global__ void __launch_bounds__(256, 2) k_cont(EvalBufs e) {
+  const uint32_t lane = threadIdx.x & 63u, waves = gridDim.x * (blockDim.x >> 6);
+  uint32_t S, tile, n;
+  for (uint32_t q = blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+       cont_find<1, 64>(e, q, S, tile, n); q += waves) {
+    if (tile * 64 + lane >= n) continue;
+    const double* base = e.cont + (size_t)e.cinfo[kMaxStages - S] * (kContUnit / 8) + (size_t)tile * (256 * S) + lane;
+    switch (S) {
+#define X(S_) \
+  case S_: cont_one<S_>(e, base); break;
+      X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+#undef X
+      default: break;
     }
   }
-  uint32_t total = 0;
-  for (uint32_t j = 0; j < (uint32_t)kMaxStages; ++j) total += e.ctr[1 + j];
-  // one entry per thread per round; ranks within the block from LDS counters,
-  // then one global cursor update per (round, bucket)
-  for (uint32_t r0 = blockIdx.x * blockDim.x; r0 < total; r0 += gridDim.x * blockDim.x) {
-    for (uint32_t i = threadIdx.x; i < kN; i += blockDim.x) lc[i] = 0;
-    __syncthreads();
-    uint32_t j = 0, k = 0, slot = 0, b = 0, rank = 0;
-    const bool has = r0 + threadIdx.x < total && defer_entry(e, r0 + threadIdx.x, j, k);
-    if (has) {
-      slot = e.deferred[e.sstart[j] + k];
-      b = j * kSortBuckets + defer_bucket(e, slot);
-      rank = atomicAdd(&lc[b], 1u);
+}
+
+// The second list: one pipeline per wavefront.  A steady iteration is a
+// max-plus linear map of the state; its matrix is squared, and applied to the
+// state at the set bits of the number of iterations left, so a pipeline takes
+// log2(left) steps however its schedule behaves.  Every entry is the weight of
+// a path the schedule contains, so exact like the times.  All stage counts run
+// in a frame of 16 stages, the S stages of the pipeline last: the ones before
+// them hold kNoPath (below every sum of real times), and the frame's shorter
+// steady part (its first stages drain earlier) takes 16 - S iterations off the
+// loop -- hence kPowerMin.  Measured alone: about 8 us for 1000 iterations of
+// 16 stages, where one lane takes 120 us.
+constexpr double kNoPath = -1e30;
+constexpr uint32_t kPowerRow = 17;   // doubles per matrix row: the row groups hit different banks
+__global__ void __launch_bounds__(256) k_power(EvalBufs e) {
+  constexpr int N = kMaxStages;
+  __shared__ double mats[4][2][N * kPowerRow];
+  __shared__ double vec[4][4 * N];
+  const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t j = lane & 15u, g = lane >> 4, waves = gridDim.x * 4;
+  double* const v = vec[wave];
+  uint32_t S, pos, n;
+  for (uint32_t q = blockIdx.x * 4 + wave; cont_find<2, 1>(e, q, S, pos, n); q += waves) {
+    const double* p = e.cont + (size_t)e.cinfo[32 + kMaxStages - S] * (kContUnit / 8) + (size_t)(pos >> 6) * (256 * S) +
+                      (pos & 63u);
+    const uint2 ls = *(const uint2*)&p[64 * (3 * S - 1)];
+    uint32_t left = ls.x - (N - S);
+    // lanes 0-15 the state, 16-31 a, 32-47 d, 48-63 e of frame stage j
+    {
+      const int s = (int)j - (int)(N - S);
+      const bool real = s >= 0 && !(g == 2 && s == (int)S - 1);
+      v[lane] = real ? p[64 * ((g == 3 ? 3 * S : g * S) + s)] : g == 0 || g == 3 ? kNoPath : 0;
     }
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < kN; i += blockDim.x)
-      if (lc[i]) lc[i] = atomicAdd(&e.ctr[kSortCtr + kN + i], lc[i]);
-    __syncthreads();
-    if (has) e.vlist[e.sstart[j] + base[b] + lc[b] + rank] = slot;
-    __syncthreads();
+    wave_sync_lds();
+    Chain<N, double> h;
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+      h.f[s] = s == (int)j ? 0 : kNoPath;
+      h.a[s] = v[N + s];
+      h.d[s] = v[2 * N + s];
+      h.e[s] = v[3 * N + s];
+    }
+    double x = v[j];   // the state, one component per lane (four copies)
+    // column j of the matrix, and the longest path from state component j to the end
+    Chain<N, double> u = h;
+    const double last = chain_end<N, double, false>(u, u.a, N);
+    chain_iter<N, double, false>(h, h.a, 0, 0);
+    double* A = mats[wave][0];
+    double* A2 = mats[wave][1];
+    if (g == 0) {
+#pragma unroll
+      for (int s = 0; s < N; ++s) A[s * kPowerRow + j] = h.f[s];
+    }
+    wave_sync_lds();
+    while (true) {
+      if (left & 1) {
+        v[lane] = x;
+        wave_sync_lds();
+        double y = kNoPath;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y = vmax(y, A[j * kPowerRow + 4 * g + k] + v[4 * g + k]);
+        y = vmax(y, __shfl_xor(y, 16));
+        x = vmax(y, __shfl_xor(y, 32));
+      }
+      left >>= 1;
+      if (!left) break;
+      double c[4] = {kNoPath, kNoPath, kNoPath, kNoPath};
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const double w = A[k * kPowerRow + j];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = vmax(c[i], A[(4 * g + i) * kPowerRow + k] + w);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) A2[(4 * g + i) * kPowerRow + j] = c[i];
+      wave_sync_lds();
+      double* t = A;
+      A = A2;
+      A2 = t;
+    }
+    double T = x + last;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) T = vmax(T, __shfl_xor(T, o));
+    if (lane == 0) raise_time(e, ls.y, T);
+    wave_sync_lds();
   }
 }
 
@@ -418,14 +446,12 @@ hipError_t launch_stages(const Tab& t, const PackedPlan* packed, const uint4* pc
   else k_stages<false><<<blocks_for(n * 4, 256), 256, 0, s>>>(t, packed, pcut, meta, n, out_stage);
   return hipGetLastError();
 }
-hipError_t launch_scan(const uint32_t* hist, uint32_t* cursor, uint32_t* sstart, uint32_t* sbase, bool grouped,
-                       uint32_t* ids, hipStream_t s) {
-  k_scan<<<1, 1024, 0, s>>>(hist, cursor, sstart, sbase, grouped ? 1u : 0u, ids);
+hipError_t launch_scan(const Work& w, bool grouped, hipStream_t s) {
+  k_scan<<<1, 1024, 0, s>>>(w.hist, w.cursor, w.gstart, w.tstart, w.cinfo, grouped ? 1u : 0u, w.cont_units);
   return hipGetLastError();
 }
-hipError_t launch_scatter(const uint16_t* keys, uint32_t nslots, uint32_t* cursor, const uint32_t* sbase, bool grouped,
-                          uint32_t* ids, hipStream_t s) {
-  k_scatter<<<blocks_for(nslots, 256 * kScatterPer), 256, 0, s>>>(keys, nslots, cursor, sbase, grouped ? 1u : 0u, ids);
+hipError_t launch_scatter(const Work& w, uint32_t n, hipStream_t s) {
+  k_scatter<<<blocks_for(n, 256 * kScatterPer), 256, 0, s>>>(w.keys, n, w.cursor, w.order);
   return hipGetLastError();
 }
 // ---------------------------------------------------------------- node-rate probe
@@ -456,12 +482,6 @@ hipError_t launch_node_probe(double* sink, int blocks, int iters, hipStream_t s)
 }
 
 // ---------------------------------------------------------------- evaluation passes
-EvalBufs eval_bufs(const EvalArgs& a) {
-  return {a.packed, (const uint4*)a.pcut, a.hdp, a.meta, a.ids, a.sstart, a.out, a.ctr,
-          a.ctr + kEvalCounters + kPlanSortWords, a.deferred,
-          a.vlist, (unsigned long long*)a.skipped_ops, a.dtab};
-}
-
 // Blocks of each evaluation kernel that fit the device at once.
 int eval_grids(Tab* t) {
   int cus = 0, dev = 0;
@@ -469,7 +489,7 @@ int eval_grids(Tab* t) {
   if (r == hipSuccess) r = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (r != hipSuccess) return (int)r;
   const size_t lds = t->mode < 2 ? t->lds_bytes : 0;
-  int nb[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, nbc[4] = {0, 0, 0, 0};
+  int nb[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, nbc[4] = {0, 0, 0, 0};
   if (t->mode == 0) r = occupancy_first_v<0>(nb, lds, 0);
   else if (t->mode == 1) r = occupancy_first_v<1>(nb, lds, 0);
   else r = occupancy_first_v<2>(nb, lds, 0);
@@ -483,10 +503,12 @@ int eval_grids(Tab* t) {
   for (int i = 0; i < 2; ++i)
     if (nbc[i] == nb[i]) t->bcache |= 1u << i;
   if (r == hipSuccess) {
-    if (t->mode == 0) r = occupancy_deferred_v<0>(nb + 4, lds);
-    else if (t->mode == 1) r = occupancy_deferred_v<1>(nb + 4, lds);
-    else r = occupancy_deferred_v<2>(nb + 4, lds);
+    if (t->mode == 0) r = occupancy_il_v<0>(nb + 4, lds);
+    else if (t->mode == 1) r = occupancy_il_v<1>(nb + 4, lds);
+    else r = occupancy_il_v<2>(nb + 4, lds);
   }
+  if (r == hipSuccess)
+    r = hipOccupancyMaxActiveBlocksPerMultiprocessor(nb + 9, (const void*)k_cont, 256, 0);
   if (r == hipSuccess) {
     if (t->mode == 0) r = occupancy_variant_v<0>(nb + 5, lds);
     else if (t->mode == 1) r = occupancy_variant_v<1>(nb + 5, lds);
@@ -494,55 +516,45 @@ int eval_grids(Tab* t) {
   }
   if (r != hipSuccess) return (int)r;
   for (int i = 0; i < 4; ++i) t->grid_eval[i] = (uint32_t)((nb[i] > 0 ? nb[i] : 1) * cus);
-  t->grid_deferred = (uint32_t)((nb[4] > 0 ? nb[4] : 1) * cus);
+  t->grid_il = (uint32_t)((nb[4] > 0 ? nb[4] : 1) * cus);
+  t->grid_cont = (uint32_t)((nb[9] > 0 ? nb[9] : 1) * cus);
   for (int i = 0; i < 4; ++i) t->grid_variant[i] = (uint32_t)((nb[5 + i] > 0 ? nb[5 + i] : 1) * cus);
   return 0;
 }
 
-// first pass of one stage-count group (g = 0..3) over a chunk
-hipError_t launch_group(const Tab& t, const EvalArgs& a, uint32_t max_tasks, int g, hipStream_t s) {
-  const bool het = a.pcut != nullptr;
-  if (t.mode == 0) return het ? launch_group_v<0, true>(t, a, max_tasks, g, s) : launch_group_v<0, false>(t, a, max_tasks, g, s);
-  if (t.mode == 1) return het ? launch_group_v<1, true>(t, a, max_tasks, g, s) : launch_group_v<1, false>(t, a, max_tasks, g, s);
-  return het ? launch_group_v<2, true>(t, a, max_tasks, g, s) : launch_group_v<2, false>(t, a, max_tasks, g, s);
+// first pass of one stage-count group (g = 0..3) over a chunk (with two-level
+// collectives the shared layout's plans are all the variant pass's)
+hipError_t launch_group(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s) {
+  const bool het = e.pcut != nullptr;
+  if (!het && t.ccl_hier) return hipSuccess;
+  if (t.mode == 0) return het ? launch_group_v<0, true>(t, e, max_tiles, g, s) : launch_group_v<0, false>(t, e, max_tiles, g, s);
+  if (t.mode == 1) return het ? launch_group_v<1, true>(t, e, max_tiles, g, s) : launch_group_v<1, false>(t, e, max_tiles, g, s);
+  return het ? launch_group_v<2, true>(t, e, max_tiles, g, s) : launch_group_v<2, false>(t, e, max_tiles, g, s);
 }
 
-// variant pass of one stage-count group: the overlap and zero-bubble
-// pipelines the group's first pass listed (none with the per-class layout)
-hipError_t launch_variant(const Tab& t, const EvalArgs& a, int g, hipStream_t s) {
-  if (a.pcut) return hipSuccess;
-  if (t.mode == 0) return launch_variant_v<0>(t, a, g, s);
-  if (t.mode == 1) return launch_variant_v<1>(t, a, g, s);
-  return launch_variant_v<2>(t, a, g, s);
+// variant pass of one stage-count group (none with the per-class layout)
+hipError_t launch_variant(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s) {
+  if (e.pcut) return hipSuccess;
+  if (t.mode == 0) return launch_variant_v<0>(t, e, max_tiles, g, s);
+  if (t.mode == 1) return launch_variant_v<1>(t, e, max_tiles, g, s);
+  return launch_variant_v<2>(t, e, max_tiles, g, s);
 }
 
-// first pass over a chunk: k_eval of each stage-count group, in order, then
-// the variant passes
-hipError_t launch_first(const Tab& t, const EvalArgs& a, uint32_t max_tasks, hipStream_t s) {
-  hipError_t r = hipSuccess;
-  for (int g = 0; g < 4 && r == hipSuccess; ++g) r = launch_group(t, a, max_tasks, g, s);
-  for (int g = 0; g < 4 && r == hipSuccess; ++g) r = launch_variant(t, a, g, s);
-  return r;
+// the interleaved plans (none with the per-class layout)
+hipError_t launch_il(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s) {
+  if (e.pcut) return hipSuccess;
+  if (t.mode == 0) return launch_il_v<0>(t, e, max_tiles, s);
+  if (t.mode == 1) return launch_il_v<1>(t, e, max_tiles, s);
+  return launch_il_v<2>(t, e, max_tiles, s);
 }
 
-// then the interleaved and the deferred pipelines, and the u64 redo of the
-// overflowed ones
-hipError_t launch_deferred(const Tab& t, const EvalArgs& a, uint32_t max_tasks, hipStream_t s) {
-  const bool het = a.pcut != nullptr;
-  hipError_t r;
-  {
-    // the deferred lists, sorted by micro-batch count into vlist
-    const EvalBufs e = eval_bufs(a);
-    k_defer_hist<<<64, 256, 0, s>>>(e);
-    k_defer_sort<<<64, 256, 0, s>>>(e);
-    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  }
-  if (t.mode == 0) r = het ? launch_deferred_v<0, true>(t, a, max_tasks, s) : launch_deferred_v<0, false>(t, a, max_tasks, s);
-  else if (t.mode == 1) r = het ? launch_deferred_v<1, true>(t, a, max_tasks, s) : launch_deferred_v<1, false>(t, a, max_tasks, s);
-  else r = het ? launch_deferred_v<2, true>(t, a, max_tasks, s) : launch_deferred_v<2, false>(t, a, max_tasks, s);
-  if (r != hipSuccess) return r;
-  const EvalBufs e = eval_bufs(a);
-  if (het) k_redo_u64<true><<<32, 64, 0, s>>>(t, e);
+// after the first and variant passes: the continuation lists, and the u64
+// redo of the overflowed pipelines
+hipError_t launch_rest(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s) {
+  const uint32_t need = (max_tiles + 3) / 4, grid = need < 1 ? 1 : need < t.grid_cont ? need : t.grid_cont;
+  k_cont<<<grid, 256, 0, s>>>(e);
+  k_power<<<grid, 256, 0, s>>>(e);
+  if (e.pcut) k_redo_u64<true><<<32, 64, 0, s>>>(t, e);
   else k_redo_u64<false><<<32, 64, 0, s>>>(t, e);
   return hipGetLastError();
 }

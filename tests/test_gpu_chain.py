@@ -1,0 +1,90 @@
+"""The pipeline recurrence at the edges of its parts, against the CPU oracle, bit for bit.
+
+The recurrence starts from a closed form of the warm-up, runs steady iterations with a shortcut for
+periodic schedules, hands schedules that stay aperiodic to the continuation lists, and ends with a drain:
+micro-batch counts around each of those lengths for every stage count, every order of passes, and lists
+that are too small for what they are offered.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+KINDS = {"1f1b": 0, "overlap": 1 << 13, "zero_bubble": 1 << 16}
+
+
+def _plans(w, stages, n, seed, batch, classes):
+    """n plans of every stage count in `stages`: random cuts and types, `classes` replicas of one class each
+    (the first with a random share of the micro-batches, at least one each)."""
+    rng = np.random.default_rng(seed)
+    L, K = w["model"]["L"], len(w["cluster"]["types"])
+    tot = n * len(stages)
+    p = dict(hdr=np.zeros(tot, np.uint32), cut=np.zeros((16, tot), np.uint8), cls=np.zeros((4, tot), np.uint32),
+             types=np.zeros((4, tot), np.uint64))
+    i = 0
+    for S in stages:
+        for _ in range(n):
+            p["hdr"][i] = (S - 1) << 4 | (classes - 1) << 8 | int(rng.integers(2)) << 10
+            cuts = np.sort(rng.choice(np.arange(1, L), S - 1, replace=False)) if S > 1 else []
+            for s, v in enumerate(list(cuts) + [L]):
+                p["cut"][s, i] = v
+            share = rng.multinomial(batch - classes, np.ones(classes) / classes) + 1
+            for c in range(classes):
+                p["cls"][c, i] = 1 | int(share[c]) << 16
+                p["types"][c, i] = sum(int(rng.integers(K)) << (4 * s) for s in range(S))
+            i += 1
+    return p
+
+
+def _check(B, O, model, cluster, p, noalloc=False):
+    import torch
+    sim = B.Sim(model, cluster)
+    dp = B.device_plans(p)
+    if noalloc:
+        out = torch.empty(len(p["hdr"]), dtype=torch.int64, device="cuda")
+        sim.eval_plans_noalloc(dp, out=out)
+    else:
+        out = sim.eval_plans(dp)
+    got = B.times_u64(out)
+    want = O.Oracle(model, cluster).eval(p)
+    bad = np.nonzero(got != want)[0]
+    assert bad.size == 0, "%d of %d plans differ, first %d: gpu %d oracle %d" % (
+        bad.size, len(want), bad[0], int(got[bad[0]]), int(want[bad[0]]))
+    assert np.count_nonzero(want != np.uint64(2**64 - 1)) > len(want) // 2
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_05370_amd import binding
+    return binding
+
+
+# warm-up only (fewer micro-batches than stages), no or one or two steady iterations, the first pass's
+# budget (S + 8) and the first continuation pass's (48) and a few around them, long loops
+@pytest.mark.parametrize("batch", [1, 2, 3, 7, 15, 16, 17, 18, 24, 25, 40, 41, 72, 73, 96, 129, 1000])
+def test_micro_batch_counts(B, oracle_mod, workloads, batch):
+    w = workloads.workload(5)
+    model = dict(w["model"], global_batch=batch)
+    for kind, bits in KINDS.items():
+        for classes in (1, 2, 3, 4):
+            if batch < classes:
+                continue
+            p = _plans(w, range(1, 17), 24, 1000 * batch + classes, batch, classes)
+            p["hdr"] |= np.uint32(bits)
+            print("case: %s, %d micro-batches, %d classes" % (kind, batch, classes), flush=True)
+            _check(B, oracle_mod, model, w["cluster"], p)
+
+
+# 16-stage plans over slow links on a workspace with room for few continuations: lists overflow
+@pytest.mark.parametrize("kind", list(KINDS))
+def test_continuation_lists_overflow(B, oracle_mod, workloads, kind):
+    w = workloads.workload(2)
+    model = dict(w["model"], global_batch=160)
+    cluster = dict(w["cluster"], types=[dict(t, nic_MBps=t["nic_MBps"] // 8) for t in w["cluster"]["types"]])
+    p = _plans(w, [16], 20000, 7, 160, 2)
+    p["hdr"] |= np.uint32(KINDS[kind])
+    print("case: %s, %d plans" % (kind, len(p["hdr"])), flush=True)
+    _check(B, oracle_mod, model, cluster, p, noalloc=True)
