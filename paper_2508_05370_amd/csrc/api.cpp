@@ -12,11 +12,11 @@
 
 namespace hetsim {
 hipError_t launch_fill32(uint32_t* p, uint32_t n, uint32_t v, hipStream_t s);
-hipError_t launch_prep(const Tab& t, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed, uint4* pcut,
+hipError_t launch_prep(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed, uint4* pcut,
                        uint32_t* meta, uint32_t* hist, uint16_t* keys, hipStream_t s);
-hipError_t launch_memory(const Tab& t, const sim_plans& p, int64_t n, uint64_t* out, hipStream_t s);
+hipError_t launch_memory(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, hipStream_t s);
 hipError_t launch_plan_syncs(const Tab& t, const PackedPlan* packed, const uint4* pcut, const uint32_t* meta,
-                             int64_t n, uint64_t* hdp, uint32_t* pc, uint32_t* perm, hipStream_t s);
+                             int64_t n, double* hdp, uint32_t* pc, uint32_t* perm, hipStream_t s);
 hipError_t launch_stages(const Tab& t, const PackedPlan* packed, const uint4* pcut, const uint32_t* meta, int64_t n,
                          uint64_t* out_stage, hipStream_t s);
 hipError_t launch_scan(const Work& w, bool grouped, hipStream_t s);
@@ -244,7 +244,7 @@ static hipError_t order_chunk(sim_ctx* c, const Work& W, const sim_plans& p, int
   EventPair ev;
   hipError_t e = launch_fill32(W.hist, kCounters, 0, s);
   const bool timed = events && e == hipSuccess && begin_event(c, 1, s, &ev);
-  if (e == hipSuccess) e = launch_prep(c->tab, p, n, out, W.packed, W.pcut, W.meta, W.hist, W.keys, s);
+  if (e == hipSuccess) e = launch_prep(c->tab, c->dtab, p, n, out, W.packed, W.pcut, W.meta, W.hist, W.keys, s);
   if (timed) end_event(c, 1, s, &ev);
   if (e == hipSuccess && het)
     e = launch_plan_syncs(c->tab, W.packed, W.pcut, W.meta, n, W.hdp, W.ctr + kEvalCounters, W.perm, s);
@@ -420,7 +420,7 @@ extern "C" int sim_eval_stages(sim_ctx* c, const sim_plans* plans, int64_t n, ui
     p.hdr += off; p.cls += off; p.types += off;
     if (p.cut) p.cut += off;
     if (het) { p.chdr += off; p.ccut += off; }
-    e = launch_prep(c->tab, p, cn, nullptr, packed, pcut, out_class + off * 4, nullptr, nullptr, s);
+    e = launch_prep(c->tab, c->dtab, p, cn, nullptr, packed, pcut, out_class + off * 4, nullptr, nullptr, s);
     if (e == hipSuccess)
       e = launch_stages(c->tab, packed, pcut, out_class + off * 4, cn, out_stage + off * 4 * kMaxStages * 4, s);
   }
@@ -441,7 +441,7 @@ extern "C" int sim_eval_memory(sim_ctx* c, const sim_plans* plans, int64_t n, ui
     p.hdr += off; p.cls += off; p.types += off;
     if (p.cut) p.cut += off;
     if (p.chdr) { p.chdr += off; p.ccut += off; }
-    e = launch_memory(c->tab, p, cn, out_mem + off * 4 * kMaxStages, s);
+    e = launch_memory(c->tab, c->dtab, p, cn, out_mem + off * 4 * kMaxStages, s);
   }
   track(c, s);
   return e == hipSuccess ? SIM_OK : SIM_EHIP;

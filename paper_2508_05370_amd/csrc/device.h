@@ -35,6 +35,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <limits.h>
+#include <stddef.h>
 
 #include <type_traits>
 
@@ -45,11 +46,24 @@ namespace hetsim {
 constexpr uint64_t kInvalid = ~0ull;
 
 // ---------------------------------------------------------------- helpers
-// ceil(bytes * bq / 2^16) with bytes < 2^48 and bq < 2^32 (80-bit product)
-__device__ __forceinline__ uint64_t link_ps(uint64_t bytes, uint32_t bq) {
-  uint64_t lo = bytes * (uint64_t)bq;
-  uint64_t hi = __umul64hi(bytes, (uint64_t)bq);
-  return ((hi << 48) | (lo >> 16)) + ((lo & 0xffffull) != 0);
+// Stage and sync times are integers below 2^52 and messages below 2^50 bytes
+// (sim_create checks both), carried in fp64: sums and products of them are
+// exact, and fp64 runs at the full VALU rate, where a 64-bit integer product
+// takes several quarter-rate instructions.
+//
+// ceil(bytes * bq / 2^16): the product with its rounding error, and one more
+// where the rounded product is an integer and the error positive (a rounded
+// product is never above an integer that the exact one does not exceed).
+__device__ __forceinline__ double link_ps(double bytes, uint32_t bq) {
+  const double y = (double)bq * 0x1p-16, h = bytes * y, l = __builtin_fma(bytes, y, -h), c = __builtin_ceil(h);
+  return c + (l > c - h ? 1.0 : 0.0);
+}
+
+// ceil(x / p) for x / p < 2^50 and p >= 1, given rp = RN(1/p): the rounded
+// product is within 1/2 + 2^-2 of x/p, so its remainder's sign decides.
+__device__ __forceinline__ double ceil_div(double x, double p, double rp) {
+  const double q = __builtin_rint(x * rp);
+  return q + (__builtin_fma(-q, p, x) > 0 ? 1.0 : 0.0);
 }
 
 // max over [lo, hi] of a range-max table with row length n
@@ -94,42 +108,37 @@ __device__ __forceinline__ uint64_t div_up_u64(uint64_t x, uint64_t p, double rp
 // (reduce up, broadcast down: 2 ceil(log2 p) latencies, each member's
 // gradient twice over the slowest link); ZeRO's reduce-scatter and
 // all-gather stay rings.
-__device__ __forceinline__ uint64_t ring_sync(uint32_t p, double rp, uint32_t zero, uint64_t grads, uint64_t params,
-                                              uint64_t alpha, uint32_t bq, uint32_t tree) {
-  uint64_t g = div_up(grads, p, rp);
+__device__ __forceinline__ double ring_sync(uint32_t p, double rp, uint32_t zero, double grads, double params,
+                                            double alpha, uint32_t bq, uint32_t tree) {
+  const double g = ceil_div(grads, (double)p, rp), steps = (double)(p - 1);
   if (!zero) {
-    uint64_t steps = 2ull * (p - 1);
-    uint64_t r = steps * alpha + link_ps(steps * g, bq);
+    double r = 2 * steps * alpha + link_ps(2 * steps * g, bq);
     if (tree && p > 1) {
-      const uint64_t lg = 32 - __builtin_clz(p - 1);
-      const uint64_t tt = 2 * lg * alpha + link_ps(2 * grads, bq);
+      const double tt = (double)(2 * (32 - __builtin_clz(p - 1))) * alpha + link_ps(2 * grads, bq);
       r = tt < r ? tt : r;
     }
     return r;
   }
-  uint64_t steps = p - 1;
-  return 2 * steps * alpha + link_ps(steps * g, bq) + link_ps(steps * div_up(params, p, rp), bq);
+  return 2 * steps * alpha + link_ps(steps * g, bq) + link_ps(steps * ceil_div(params, (double)p, rp), bq);
 }
 
 // The same sync as latency steps and link time (the part that concurrent
 // syncs over the same links share); the tree only when strictly faster.
-__device__ __forceinline__ void ring_parts(uint32_t p, double rp, uint32_t zero, uint64_t grads, uint64_t params,
-                                           uint64_t alpha, uint32_t bq, uint32_t tree, uint64_t& lat, uint64_t& bw) {
-  const uint64_t g = div_up(grads, p, rp);
-  lat = 2ull * (p - 1) * alpha;
+__device__ __forceinline__ void ring_parts(uint32_t p, double rp, uint32_t zero, double grads, double params,
+                                           double alpha, uint32_t bq, uint32_t tree, double& lat, double& bw) {
+  const double g = ceil_div(grads, (double)p, rp), steps = (double)(p - 1);
+  lat = 2 * steps * alpha;
   if (!zero) {
-    bw = link_ps(2ull * (p - 1) * g, bq);
+    bw = link_ps(2 * steps * g, bq);
     if (tree && p > 1) {
-      const uint64_t lg = 32 - __builtin_clz(p - 1);
-      const uint64_t tl = 2 * lg * alpha, tb = link_ps(2 * grads, bq);
+      const double tl = (double)(2 * (32 - __builtin_clz(p - 1))) * alpha, tb = link_ps(2 * grads, bq);
       if (tl + tb < lat + bw) {
         lat = tl;
         bw = tb;
       }
     }
   } else {
-    const uint64_t steps = p - 1;
-    bw = link_ps(steps * g, bq) + link_ps(steps * div_up(params, p, rp), bq);
+    bw = link_ps(steps * g, bq) + link_ps(steps * ceil_div(params, (double)p, rp), bq);
   }
 }
 
@@ -251,6 +260,11 @@ __device__ __forceinline__ uint32_t class_mb(const Plan& p) { return (p.nc + p.r
 
 constexpr int kPrepPerThread = 4;
 
+__device__ __forceinline__ void load_check_tab(CheckTab& ct, const Tab* dtab) {
+  const uint32_t* src = (const uint32_t*)static_cast<const CheckTab*>(dtab);
+  for (uint32_t j = threadIdx.x; j < sizeof(CheckTab) / 4; j += blockDim.x) ((uint32_t*)&ct)[j] = src[j];
+}
+
 // Plan i as loaded and checked by one lane: every rule of the plan layout
 // except the memory check.  Per-class quantities are kept per class; with
 // the shared layout every class has the header's.
@@ -265,7 +279,7 @@ struct Checked {
 };
 
 template <bool kHet>
-__device__ __forceinline__ Checked check_plan(const Tab& t, const sim_plans& pl, int64_t i) {
+__device__ __forceinline__ Checked check_plan(const Tab& t, const CheckTab& ct, const sim_plans& pl, int64_t i) {
   Checked r;
   const int64_t st = pl.stride;
   // every plane exists: load before any use
@@ -329,10 +343,10 @@ __device__ __forceinline__ Checked check_plan(const Tab& t, const sim_plans& pl,
         const uint32_t M = (nmb + reps - 1) / reps;
         ok = M % S == 0 && M >= 2 * S;
       }
-      batch += nmb * t.mbs[mic];
+      batch += nmb * ct.mbs[mic];
       psum += reps;
       // every stage's type exists and holds whole TP groups in a node
-      const uint32_t okm = t.type_ok[tpl];
+      const uint32_t okm = ct.type_ok[tpl];
       for (uint32_t s = 0; s < S; ++s) ok = ok && ((okm >> ((uint32_t)(r.tv[c] >> (4 * s)) & 15)) & 1);
     } else {
       r.cls[c] = 0;
@@ -363,12 +377,12 @@ __device__ __forceinline__ Checked check_plan(const Tab& t, const sim_plans& pl,
 // rank holds, and the optimizer state, split with ZeRO over the DP group
 // (all replicas for the non-expert parameters, replicas / EP for the
 // experts).
-__device__ __forceinline__ uint64_t state_bytes(const Tab& t, uint32_t tpl, uint32_t epl, uint32_t zero,
+__device__ __forceinline__ uint64_t state_bytes(const Tab& t, const CheckTab& ct, uint32_t tpl, uint32_t epl, uint32_t zero,
                                                 uint32_t psum, bool first, bool last, uint32_t ns) {
-  uint64_t pd = (uint64_t)ns * t.par_layer[tpl];
-  if (first) pd += t.par_embed[tpl];
-  if (last) pd += t.par_head[tpl];
-  const uint64_t pe = (uint64_t)ns * t.par_expert[tpl][epl];
+  uint64_t pd = (uint64_t)ns * ct.par_layer[tpl];
+  if (first) pd += ct.par_embed[tpl];
+  if (last) pd += ct.par_head[tpl];
+  const uint64_t pe = (uint64_t)ns * ct.par_expert[tpl][epl];
   uint64_t od = t.opt_bytes * pd, oe = t.opt_bytes * pe;
   if (zero) {
     const uint32_t pdx = psum >> epl;
@@ -387,24 +401,24 @@ __device__ __forceinline__ uint32_t checked_cut(const Checked& r, uint32_t c, ui
 }
 
 // State bytes of stage s (ns layers) of class c of a checked plan.
-__device__ __forceinline__ uint64_t class_state_bytes(const Tab& t, const Checked& r, uint32_t c, uint32_t s,
+__device__ __forceinline__ uint64_t class_state_bytes(const Tab& t, const CheckTab& ct, const Checked& r, uint32_t c, uint32_t s,
                                                       uint32_t ns) {
   const uint32_t epl = (r.hdr >> 2) & 3, zero = (r.hdr >> 10) & 1;
-  return state_bytes(t, r.tpl[c], epl, zero, r.psum, s == 0, s == r.S[c] - 1, ns);
+  return state_bytes(t, ct, r.tpl[c], epl, zero, r.psum, s == 0, s == r.S[c] - 1, ns);
 }
 
 // Peak bytes of the devices of stage s (ns layers) of class c: its state plus
 // the activations of the min(PP - s, M) micro-batches 1F1B keeps in flight
 // there (min(PP, M) on every stage under the zero-bubble order, where a
 // micro-batch's activations stay until its weight-gradient pass).
-__device__ __forceinline__ uint64_t class_stage_bytes(const Tab& t, const Checked& r, uint32_t c, uint32_t s,
+__device__ __forceinline__ uint64_t class_stage_bytes(const CheckTab& ct, const Checked& r, uint32_t c, uint32_t s,
                                                       uint32_t ns, uint64_t state) {
   // the micro-batch size: the header's (shared layout) or the class's (per-class layout, header field 0)
   const uint32_t mi = ((r.hdr >> 11) & 3) | cls_mi(r.chdr, c), S = r.S[c];
   const uint32_t reps = r.cls[c] & 0xffff, M = ((r.cls[c] >> 16) + reps - 1) / reps;
   const uint32_t held = ((r.hdr >> 16) & 1) ? S : S - s;
   const uint32_t fly = held < M ? held : M;
-  return state + (uint64_t)ns * fly * t.act_layer[r.tpl[c]][mi];
+  return state + (uint64_t)ns * fly * ct.act_layer[r.tpl[c]][mi];
 }
 
 // Interleaved 1F1B: device s holds virtual stages j S + s (j < v), so its
@@ -423,30 +437,30 @@ __device__ __forceinline__ void il_device_layers(const Checked& r, uint32_t s, u
     nmax = n > nmax ? n : nmax;
   }
 }
-__device__ __forceinline__ uint64_t il_stage_bytes(const Tab& t, const Checked& r, uint32_t c, uint32_t s,
+__device__ __forceinline__ uint64_t il_stage_bytes(const CheckTab& ct, const Checked& r, uint32_t c, uint32_t s,
                                                    uint32_t nmax, uint64_t state) {
   const uint32_t mi = (r.hdr >> 11) & 3, S = r.S[c], v = r.v;
   const uint32_t reps = r.cls[c] & 0xffff, M = ((r.cls[c] >> 16) + reps - 1) / reps;
   const uint32_t w = 2 * (S - 1 - s) + (v - 1) * S + 1;
   const uint32_t fly = w < M * v ? w : M * v;
-  return state + (uint64_t)nmax * fly * t.act_layer[r.tpl[c]][mi];
+  return state + (uint64_t)nmax * fly * ct.act_layer[r.tpl[c]][mi];
 }
 
 // Every device of a checked plan fits its type's memory.  With one layout
 // for all classes a stage's state is the same for every class: computed once.
 template <bool kHet>
-__device__ __forceinline__ bool fits_memory(const Tab& t, const Checked& r) {
+__device__ __forceinline__ bool fits_memory(const Tab& t, const CheckTab& ct, const Checked& r) {
   const uint32_t G = ((r.hdr >> 8) & 3) + 1;
   bool ok = true;
   if (!kHet && r.v > 1) {
     for (uint32_t s = 0; s < r.S[0]; ++s) {
       uint32_t ns, nmax;
       il_device_layers(r, s, ns, nmax);
-      const uint64_t state = class_state_bytes(t, r, 0, s, ns);
+      const uint64_t state = class_state_bytes(t, ct, r, 0, s, ns);
 #pragma unroll
       for (uint32_t c = 0; c < 4; ++c)
         if (c < G)
-          ok = ok && il_stage_bytes(t, r, c, s, nmax, state) <= t.mem_cap[(uint32_t)(r.tv[c] >> (4 * s)) & 15];
+          ok = ok && il_stage_bytes(ct, r, c, s, nmax, state) <= ct.mem_cap[(uint32_t)(r.tv[c] >> (4 * s)) & 15];
     }
     return ok;
   }
@@ -455,11 +469,11 @@ __device__ __forceinline__ bool fits_memory(const Tab& t, const Checked& r) {
     for (uint32_t s = 0; s < r.S[0]; ++s) {
       const uint32_t cut = checked_cut(r, 0, s), ns = cut - prev;
       prev = cut;
-      const uint64_t state = class_state_bytes(t, r, 0, s, ns);
+      const uint64_t state = class_state_bytes(t, ct, r, 0, s, ns);
 #pragma unroll
       for (uint32_t c = 0; c < 4; ++c)
         if (c < G)
-          ok = ok && class_stage_bytes(t, r, c, s, ns, state) <= t.mem_cap[(uint32_t)(r.tv[c] >> (4 * s)) & 15];
+          ok = ok && class_stage_bytes(ct, r, c, s, ns, state) <= ct.mem_cap[(uint32_t)(r.tv[c] >> (4 * s)) & 15];
     }
     return ok;
   }
@@ -470,8 +484,8 @@ __device__ __forceinline__ bool fits_memory(const Tab& t, const Checked& r) {
     for (uint32_t s = 0; s < r.S[c]; ++s) {
       const uint32_t cut = checked_cut(r, c, s), ns = cut - prev;
       prev = cut;
-      const uint64_t v = class_stage_bytes(t, r, c, s, ns, class_state_bytes(t, r, c, s, ns));
-      ok = ok && v <= t.mem_cap[(uint32_t)(r.tv[c] >> (4 * s)) & 15];
+      const uint64_t v = class_stage_bytes(ct, r, c, s, ns, class_state_bytes(t, ct, r, c, s, ns));
+      ok = ok && v <= ct.mem_cap[(uint32_t)(r.tv[c] >> (4 * s)) & 15];
     }
   }
   return ok;
@@ -484,20 +498,21 @@ __device__ __forceinline__ bool fits_memory(const Tab& t, const Checked& r) {
 // S | G << 5 | M << 8 | (v - 1) << 24 with the class's own S (0 = no pipeline)
 // and the bucket keys, counted in hist.
 template <bool kHet>
-__global__ void __launch_bounds__(256) k_prep(Tab t, sim_plans pl, int64_t n, uint64_t* __restrict__ out,
+__global__ void __launch_bounds__(256) k_prep(Tab t, const Tab* __restrict__ dtab, sim_plans pl, int64_t n, uint64_t* __restrict__ out,
                                               PackedPlan* __restrict__ packed, uint4* __restrict__ pcut,
                                               uint32_t* __restrict__ meta, uint32_t* __restrict__ hist,
                                               uint16_t* __restrict__ keys) {
   __shared__ uint32_t lh[kBuckets];
-  if (hist) {
+  __shared__ CheckTab ct;
+  load_check_tab(ct, dtab);
+  if (hist)
     for (uint32_t j = threadIdx.x; j < kBuckets; j += blockDim.x) lh[j] = 0;
-    __syncthreads();
-  }
+  __syncthreads();
   for (int rep = 0; rep < kPrepPerThread; ++rep) {
     const int64_t i = ((int64_t)blockIdx.x * kPrepPerThread + rep) * blockDim.x + threadIdx.x;
     if (i >= n) break;
-    const Checked r = check_plan<kHet>(t, pl, i);
-    const bool ok = r.ok && (!t.mem_check || fits_memory<kHet>(t, r));
+    const Checked r = check_plan<kHet>(t, ct, pl, i);
+    const bool ok = r.ok && (!t.mem_check || fits_memory<kHet>(t, ct, r));
     const uint32_t G = ((r.hdr >> 8) & 3) + 1;
     if (out) out[i] = ok ? 0 : kInvalid;
     if (ok) {
@@ -565,10 +580,13 @@ __global__ void __launch_bounds__(256) k_prep(Tab t, sim_plans pl, int64_t n, ui
 
 // Peak memory of every (class, stage) device of plan i (one plan per lane).
 template <bool kHet>
-__global__ void __launch_bounds__(256) k_memory(Tab t, sim_plans pl, int64_t n, uint64_t* __restrict__ out) {
+__global__ void __launch_bounds__(256) k_memory(Tab t, const Tab* __restrict__ dtab, sim_plans pl, int64_t n, uint64_t* __restrict__ out) {
+  __shared__ CheckTab ct;
+  load_check_tab(ct, dtab);
+  __syncthreads();
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const Checked r = check_plan<kHet>(t, pl, i);
+  const Checked r = check_plan<kHet>(t, ct, pl, i);
   const uint32_t G = ((r.hdr >> 8) & 3) + 1;
   uint64_t* o = out + i * (kMaxClasses * kMaxStages);
 #pragma unroll
@@ -581,10 +599,10 @@ __global__ void __launch_bounds__(256) k_memory(Tab t, sim_plans pl, int64_t n, 
         if (c < G && s < r.S[c] && r.v > 1) {
           uint32_t ns, nmax;
           il_device_layers(r, s, ns, nmax);
-          v = il_stage_bytes(t, r, c, s, nmax, class_state_bytes(t, r, c, s, ns));
+          v = il_stage_bytes(ct, r, c, s, nmax, class_state_bytes(t, ct, r, c, s, ns));
         } else if (c < G && s < r.S[c]) {
           const uint32_t cut = checked_cut(r, c, s);
-          v = class_stage_bytes(t, r, c, s, cut - prev, class_state_bytes(t, r, c, s, cut - prev));
+          v = class_stage_bytes(ct, r, c, s, cut - prev, class_state_bytes(t, ct, r, c, s, cut - prev));
           prev = cut;
         }
       }
@@ -611,15 +629,23 @@ struct Hot {
     const uint4 x = q[0], y = q[1];
     TypeInfo r;
     r.node_off = x.x; r.dev_off = x.y; r.dpl = x.z; r.bq_pcie = x.w;
-    r.a_intra = (uint64_t)y.y << 32 | y.x;
-    r.a_side = (uint64_t)y.w << 32 | y.z;
+    r.a_intra = __hiloint2double((int)y.y, (int)y.x);
+    r.a_side = __hiloint2double((int)y.w, (int)y.z);
     return r;
   }
+  __device__ __forceinline__ const SizeInfo& size() const { return *(const SizeInfo*)(b + t.o_size); }
+  __device__ __forceinline__ const SpeedInfo& speed(uint32_t k) const { return ((const SpeedInfo*)(b + t.o_speed))[k]; }
+  __device__ __forceinline__ double side_alpha(uint32_t k) const {
+    return *(const double*)(b + k * sizeof(TypeInfo) + offsetof(TypeInfo, a_side));
+  }
+  __device__ __forceinline__ double intra_alpha(uint32_t k) const {
+    return *(const double*)(b + k * sizeof(TypeInfo) + offsetof(TypeInfo, a_intra));
+  }
   // {forward, backward} prefix entry
-  __device__ __forceinline__ ulonglong2 pfb(uint32_t i) const { return ((const ulonglong2*)(b + t.o_pfb))[i]; }
-  __device__ __forceinline__ ulonglong2 emb(uint32_t i) const { return ((const ulonglong2*)(b + t.o_emb))[i]; }
-  __device__ __forceinline__ ulonglong2 head(uint32_t i) const { return ((const ulonglong2*)(b + t.o_head))[i]; }
-  __device__ __forceinline__ uint64_t pa(uint32_t i) const { return ((const uint64_t*)(b + t.o_pa))[i]; }
+  __device__ __forceinline__ double2 pfb(uint32_t i) const { return ((const double2*)(b + t.o_pfb))[i]; }
+  __device__ __forceinline__ double2 emb(uint32_t i) const { return ((const double2*)(b + t.o_emb))[i]; }
+  __device__ __forceinline__ double2 head(uint32_t i) const { return ((const double2*)(b + t.o_head))[i]; }
+  __device__ __forceinline__ double pa(uint32_t i) const { return ((const double*)(b + t.o_pa))[i]; }
   __device__ __forceinline__ const uint32_t* rmi() const { return (const uint32_t*)(b + t.o_rmi); }
 };
 
@@ -697,11 +723,32 @@ __device__ __forceinline__ uint32_t dev_before_own(const Plan& p, uint32_t s, ui
   return align_up(ptr, p.tpl) + ((p.rc * count_type(p.tc, k, (1ull << (4 * s)) - 1)) << p.tpl);
 }
 
-// DP sync of stage s (layers [lo, hi), ns = hi - lo) over every replica of
-// every class: one ring across all replicas on the slowest NIC of the
-// participating devices, or inside one node when every replica of the stage
-// sits in the same node; MoE models add the expert ring over the EP-sized
-// groups.  The same for every class of the plan.
+// Parameters one TP rank holds of a layer (and of its experts), the embedding
+// and the head, in fp64.
+struct Params {
+  double layer, expert, embed, head;
+  __device__ __forceinline__ Params(const SizeInfo& z, uint32_t tpl, uint32_t epl)
+      : layer(z.layer[tpl]), expert(z.expert[tpl][epl]), embed(z.embed[tpl]), head(z.head[tpl]) {}
+  __device__ __forceinline__ double stage(uint32_t ns, bool first, bool last) const {
+    return (double)ns * layer + (first ? embed : 0.0) + (last ? head : 0.0);
+  }
+};
+
+// DP sync of a stage over every replica of every class: one ring across all
+// replicas on the slowest NIC of the participating devices, or inside one
+// node when every replica of the stage sits in the same node; MoE models add
+// the expert ring over the EP-sized groups.  The same for every class of the
+// plan.  Its link is put together from each class's share of the stage:
+struct ClassLink {
+  uint32_t bx;     // slowest NIC or PCIe rate of the class's devices
+  uint32_t where;  // type << 24 | the node that holds them all (kNoNode: several)
+};
+constexpr uint32_t kNoNode = 0xffffff;
+struct DpLink {
+  double alpha;
+  uint32_t bq;
+};
+
 // With two-level collectives enabled, hs is the group's shape for them:
 // usable when every class's devices of the stage fill whole nodes with the
 // same number g > 1 of TP groups per node, over N > 1 nodes in all; a_in
@@ -709,17 +756,17 @@ __device__ __forceinline__ uint32_t dev_before_own(const Plan& p, uint32_t s, ui
 struct HierShape {
   bool ok;
   uint32_t g, N, bq_in;
-  uint64_t a_in;
+  double a_in;
 };
 
+// The link of stage s found from the plan alone.
 template <int kMode, bool kHier>
-__device__ __forceinline__ void stage_link(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
-                                           uint64_t& alpha, uint32_t& bq, HierShape& hs,
-                                           const uint32_t* __restrict__ bl = nullptr) {
+__device__ __forceinline__ DpLink stage_link(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
+                                             HierShape& hs) {
   const uint32_t G = p.G, tp = p.tp;
   bool same = true;
   uint32_t k0 = 0, nmin = 0xffffffffu, nmax = 0, bq_dp = 0;
-  uint64_t a_dp = 0;
+  double a_dp = 0;
   hs.ok = kHier && t.ccl_hier != 0;
   hs.g = 0; hs.N = 0; hs.bq_in = 0; hs.a_in = 0;
 #pragma unroll
@@ -727,8 +774,7 @@ __device__ __forceinline__ void stage_link(const Tab& t, const Hot<kMode>& h, co
     if (c2 >= G) continue;
     const uint32_t k2 = (uint32_t)(p.tv[c2] >> (4 * s)) & 15;
     const TypeInfo t2 = h.type(k2);
-    // (bl: the plan's lanes' stage placements, class-major, p.S per class)
-    const uint32_t b2 = bl ? bl[c2 * p.S + s] : placed_before(p, c2, s, k2) * tp, n2 = p.reps[c2] * tp, d2 = t2.dpl;
+    const uint32_t b2 = placed_before(p, c2, s, k2) * tp, n2 = p.reps[c2] * tp, d2 = t2.dpl;
     const uint32_t l2 = t2.node_off + (b2 >> d2), h2 = t2.node_off + ((b2 + n2 - 1) >> d2);
     const uint32_t dl2 = t2.dev_off + b2;
     const uint32_t nic2 = range_max(h.rmn, t.D, dl2, dl2 + n2 - 1);
@@ -750,46 +796,65 @@ __device__ __forceinline__ void stage_link(const Tab& t, const Hot<kMode>& h, co
   }
   hs.ok = hs.ok && hs.g > 1 && hs.N > 1;
   const bool intra = same && nmin == nmax;
-  alpha = intra ? h.type(k0).a_intra : a_dp;
-  bq = intra ? h.rmi()[nmin] : bq_dp;
+  return {intra ? h.intra_alpha(k0) : a_dp, intra ? h.rmi()[nmin] : bq_dp};
+}
+
+// The same link from the classes' shares that the plan's lanes left in LDS
+// (link: class 0's, the others after it).
+template <int kMode>
+__device__ __forceinline__ DpLink exchanged_link(const Hot<kMode>& h, uint32_t G, const uint2* link) {
+  uint32_t w0 = 0, bq_dp = 0;
+  bool same = true;
+  double a = 0;
+#pragma unroll
+  for (uint32_t c2 = 0; c2 < 4; ++c2) {
+    if (c2 >= G) continue;
+    const uint2 l = link[c2];
+    if (c2 == 0) w0 = l.y; else same = same && l.y == w0;
+    bq_dp = l.x > bq_dp ? l.x : bq_dp;
+    const double a2 = h.side_alpha(l.y >> 24);
+    a = a2 > a ? a2 : a;
+  }
+  const bool intra = same && (w0 & kNoNode) != kNoNode;
+  return {intra ? h.intra_alpha(w0 >> 24) : 2 * a, intra ? h.rmi()[w0 & kNoNode] : bq_dp};
 }
 
 // A dense all-reduce of `grads` bytes per member over the group, with the
 // two-level algorithm when the shape allows it and it is faster: the
 // node-local ring over the whole gradient (g members), then the ring
 // across the N nodes over a 1/g shard (g is a power of two).
-__device__ __forceinline__ uint64_t with_hier(uint64_t ring, const HierShape& hs, uint32_t zero, uint64_t grads,
-                                              uint64_t alpha, uint32_t bq) {
+__device__ __forceinline__ double with_hier(double ring, const HierShape& hs, uint32_t zero, double grads,
+                                            const DpLink& l) {
   if (!hs.ok || zero) return ring;
-  const uint32_t lg = __builtin_ctz(hs.g);
-  const uint64_t sh = (grads + hs.g - 1) >> lg;
-  const uint64_t intra = 2ull * (hs.g - 1) * hs.a_in + link_ps(2ull * (hs.g - 1) * sh, hs.bq_in);
-  const uint64_t inter = 2ull * (hs.N - 1) * alpha +
-                         link_ps(2ull * (hs.N - 1) * div_up(sh, hs.N, 1.0 / (double)hs.N), bq);
+  const double g1 = 2.0 * (double)(hs.g - 1), n1 = 2.0 * (double)(hs.N - 1);
+  const double sh = __builtin_ceil(grads / (double)hs.g);
+  const double intra = g1 * hs.a_in + link_ps(g1 * sh, hs.bq_in);
+  const double inter = n1 * l.alpha + link_ps(n1 * ceil_div(sh, (double)hs.N, 1.0 / (double)hs.N), l.bq);
   return intra + inter < ring ? intra + inter : ring;
 }
 
-// kHier: the two-level all-reduce is considered (the first-pass kernels,
-// compiled without it, defer every pipeline when it is enabled).
-template <int kMode, bool kHier = true>
-__device__ __forceinline__ uint64_t stage_dp(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
-                                             uint32_t ns, double rp, double rpe, const uint32_t* bl = nullptr) {
-  if (p.psum <= 1) return 0;
-  const uint32_t tpl = p.tpl, epl = p.epl, S = p.S;
-  uint64_t alpha;
-  uint32_t bq;
-  HierShape hs;
-  stage_link<kMode, kHier>(t, h, p, s, alpha, bq, hs, bl);
-  const uint64_t pd = (uint64_t)ns * t.par_layer[tpl] + (s == 0 ? t.par_embed[tpl] : 0) +
-                      (s == S - 1 ? t.par_head[tpl] : 0);
-  uint64_t tdp = ring_sync(p.psum, rp, p.zero, t.grad_bytes * pd, t.param_bytes * pd, alpha, bq, t.ccl_tree);
-  if (kHier) tdp = with_hier(tdp, hs, p.zero, t.grad_bytes * pd, alpha, bq);
-  const uint32_t pe = p.psum >> epl;
-  if (t.E && pe > 1) {
-    const uint64_t px = (uint64_t)ns * t.par_expert[tpl][epl];
-    tdp += ring_sync(pe, rpe, p.zero, t.grad_bytes * px, t.param_bytes * px, alpha, bq, t.ccl_tree);
-  }
+// The sync of pd parameters (and px expert parameters of a MoE model) per rank
+// over a link.
+template <bool kHier>
+__device__ __forceinline__ double link_dp(const Tab& t, const Plan& p, const DpLink& l, const HierShape& hs,
+                                          double rp, double rpe, double pd, double px) {
+  const double gb = (double)t.grad_bytes, pb = (double)t.param_bytes;
+  double tdp = ring_sync(p.psum, rp, p.zero, gb * pd, pb * pd, l.alpha, l.bq, t.ccl_tree);
+  if (kHier) tdp = with_hier(tdp, hs, p.zero, gb * pd, l);
+  const uint32_t pe = p.psum >> p.epl;
+  if (t.E && pe > 1) tdp += ring_sync(pe, rpe, p.zero, gb * px, pb * px, l.alpha, l.bq, t.ccl_tree);
   return tdp;
+}
+
+// The DP sync of stage s (ns layers) from the plan alone.
+template <int kMode>
+__device__ __forceinline__ double stage_dp(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
+                                           uint32_t ns, double rp, double rpe) {
+  if (p.psum <= 1) return 0;
+  HierShape hs;
+  const DpLink l = stage_link<kMode, true>(t, h, p, s, hs);
+  const Params par(h.size(), p.tpl, p.epl);
+  return link_dp<true>(t, p, l, hs, rp, rpe, par.stage(ns, s == 0, s == p.S - 1), (double)ns * par.expert);
 }
 
 // Gradient sync overlapped with stage s's last backward pass (shared layout;
@@ -804,89 +869,75 @@ __device__ __forceinline__ uint64_t stage_dp(const Tab& t, const Hot<kMode>& h, 
 // bucket (dl; every layer bucket of the stage has the same size) and, on
 // the first and last stages, of the embedding's and the head's buckets.
 struct OvlSyncs {
-  uint64_t dl, demb, dhead;
+  double dl, demb, dhead;
 };
-template <int kMode, bool kHier>
-__device__ __forceinline__ OvlSyncs overlap_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
-                                                  double rp, double rpe) {
+template <int kMode>
+__device__ __forceinline__ OvlSyncs overlap_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s, const DpLink& l,
+                                                  const HierShape& hs, double rp, double rpe) {
   OvlSyncs r = {0, 0, 0};
-  if (p.psum <= 1) return r;
-  const uint32_t tpl = p.tpl, epl = p.epl;
-  uint64_t alpha;
-  uint32_t bq;
-  HierShape hs;
-  stage_link<kMode, kHier>(t, h, p, s, alpha, bq, hs);
-  const uint64_t gb = t.grad_bytes, pb = t.param_bytes;
-  uint64_t dl = ring_sync(p.psum, rp, p.zero, gb * t.par_layer[tpl], pb * t.par_layer[tpl], alpha, bq, t.ccl_tree);
-  dl = with_hier(dl, hs, p.zero, gb * t.par_layer[tpl], alpha, bq);
-  const uint32_t pe = p.psum >> epl;
-  if (t.E && pe > 1)
-    dl += ring_sync(pe, rpe, p.zero, gb * t.par_expert[tpl][epl], pb * t.par_expert[tpl][epl], alpha, bq, t.ccl_tree);
-  r.dl = dl;
-  if (s == 0)
-    r.demb = with_hier(
-        ring_sync(p.psum, rp, p.zero, gb * t.par_embed[tpl], pb * t.par_embed[tpl], alpha, bq, t.ccl_tree), hs, p.zero,
-        gb * t.par_embed[tpl], alpha, bq);
-  if (s == p.S - 1)
-    r.dhead = with_hier(
-        ring_sync(p.psum, rp, p.zero, gb * t.par_head[tpl], pb * t.par_head[tpl], alpha, bq, t.ccl_tree), hs, p.zero,
-        gb * t.par_head[tpl], alpha, bq);
+  const Params par(h.size(), p.tpl, p.epl);
+  const double gb = (double)t.grad_bytes, pb = (double)t.param_bytes;
+  auto ring = [&](double n) {
+    return with_hier(ring_sync(p.psum, rp, p.zero, gb * n, pb * n, l.alpha, l.bq, t.ccl_tree), hs, p.zero, gb * n, l);
+  };
+  r.dl = link_dp<true>(t, p, l, hs, rp, rpe, par.layer, par.expert);
+  if (s == 0) r.demb = ring(par.embed);
+  if (s == p.S - 1) r.dhead = ring(par.head);
   return r;
 }
 
 // The class's part: its buckets' readiness from its own backward compute on
-// device type k, walked against the syncs.
-template <int kMode>
-__device__ __forceinline__ uint64_t overlap_walk(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
-                                                 uint32_t lo, uint32_t hi, uint32_t k, const OvlSyncs& y) {
+// device type k, walked against the syncs.  (In fp64 the result is exact
+// where it is below 2^53; the u64 redo takes int64.)
+template <int kMode, typename V>
+__device__ __forceinline__ V overlap_walk(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
+                                          uint32_t lo, uint32_t hi, uint32_t k, const OvlSyncs& y) {
   if (p.psum <= 1) return 0;
   const uint32_t tpl = p.tpl, mi = p.mi;
   const uint32_t L1 = t.L + 1, epq = t.E ? p.epl : 0;
   const uint32_t row = ((k * 4 + tpl) * t.n_mbs + mi) * t.nep + epq;
-  int64_t D = 0, R = 0, X = 0;
+  V D = 0, R = 0, X = 0;
   if (s == 0) {
-    D += (int64_t)y.demb;
+    D += (V)y.demb;
     X = D;
-    R += (int64_t)h.emb(k * t.n_mbs + mi).y;
+    R += (V)h.emb(k * t.n_mbs + mi).y;
   }
   if (t.uniform_layers) {
     // every layer's backward costs the same r: after layer i of the n the
     // value D - R is (D + dl - R) + i (dl - r), linear in i, so its largest
     // is at the first or the last layer
-    const int64_t n = (int64_t)(hi - lo), dl = (int64_t)y.dl, r = (int64_t)h.pfb(row).y;
-    const int64_t v0 = D + dl - R, v1 = v0 + (n - 1) * (dl - r);
+    const V n = (V)(hi - lo), dl = (V)y.dl, r = (V)h.pfb(row).y;
+    const V v0 = D + dl - R, v1 = v0 + (n - 1) * (dl - r);
     X = v0 > X ? v0 : X;
     X = v1 > X ? v1 : X;
     D += n * dl;
     R += n * r;
   } else {
     for (uint32_t l = lo; l < hi; ++l) {
-      D += (int64_t)y.dl;
+      D += (V)y.dl;
       X = D - R > X ? D - R : X;
-      R += (int64_t)(h.pfb(row * L1 + l + 1).y - h.pfb(row * L1 + l).y);
+      R += (V)(h.pfb(row * L1 + l + 1).y - h.pfb(row * L1 + l).y);
     }
   }
   if (s == p.S - 1) {
-    D += (int64_t)y.dhead;
+    D += (V)y.dhead;
     X = D - R > X ? D - R : X;
   }
-  return (uint64_t)X;
+  return X;
 }
 
-template <int kMode, bool kHier = true>
-__device__ __forceinline__ uint64_t overlap_tail(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
-                                                 uint32_t lo, uint32_t hi, uint32_t k, double rp, double rpe) {
-  return overlap_walk<kMode>(t, h, p, s, lo, hi, k, overlap_syncs<kMode, kHier>(t, h, p, s, rp, rpe));
-}
-
-// The sync that follows stage s of the pipeline's class (shared layout):
-// the stage's whole ring, or with overlap the part of its bucket syncs left
-// after its last backward pass.
+// The sync that follows stage s of the pipeline's class (shared layout), from
+// the plan alone: the stage's whole ring, or with overlap the part of its
+// bucket syncs left after its last backward pass.
 template <int kMode>
 __device__ __forceinline__ uint64_t stage_sync(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
                                                uint32_t lo, uint32_t hi, double rp, double rpe) {
-  if (p.overlap) return overlap_tail(t, h, p, s, lo, hi, (uint32_t)(p.tc >> (4 * s)) & 15, rp, rpe);
-  return stage_dp(t, h, p, s, hi - lo, rp, rpe);
+  if (!p.overlap) return (uint64_t)stage_dp(t, h, p, s, hi - lo, rp, rpe);
+  if (p.psum <= 1) return 0;
+  HierShape hs;
+  const DpLink l = stage_link<kMode, true>(t, h, p, s, hs);
+  return (uint64_t)overlap_walk<kMode, int64_t>(t, h, p, s, lo, hi, (uint32_t)(p.tc >> (4 * s)) & 15,
+                                                overlap_syncs(t, h, p, s, l, hs, rp, rpe));
 }
 
 // Per-class layout.  The gradients of layers [a, e) -- a segment between
@@ -906,9 +957,9 @@ __device__ __forceinline__ uint32_t row_word(const uint4 (&rows)[4], uint32_t c,
 // shard read and written (the roofline time of one elementwise op)
 // (the ceilings through fp64 reciprocals: a 64-bit integer division is a
 // long instruction loop on this ISA)
-__device__ __forceinline__ uint64_t weigh_ps(const Tab& t, uint32_t k, uint64_t n) {
+__device__ __forceinline__ uint64_t weigh_ps(const Tab& t, const SpeedInfo& v, uint64_t n) {
   const uint64_t by = 2000 * t.grad_bytes * n;
-  const uint64_t tc = div_up_u64(n, t.tflops[k], t.rtflops[k]), tm = div_up_u64(by, t.hbm[k], t.rhbm[k]);
+  const uint64_t tc = div_up_u64(n, v.tflops, v.rtflops), tm = div_up_u64(by, v.hbm, v.rhbm);
   return tc > tm ? tc : tm;
 }
 
@@ -928,7 +979,8 @@ __device__ __forceinline__ uint64_t seg_dp(const Tab& t, const Hot<kMode>& h, co
     if (c2 < G) mixed = mixed || cls_mi(p.chdr, c2) != cls_mi(p.chdr, 0);
   bool same = true;
   uint32_t k0 = 0, nmin = 0xffffffffu, nmax = 0, bq_dp = 0;
-  uint64_t a_dp = 0, rs = 0, rs_l = 0, rs_b = 0;
+  double a_dp = 0;
+  uint64_t rs = 0, rs_l = 0, rs_b = 0;
 #pragma unroll
   for (uint32_t c2 = 0; c2 < 4; ++c2) {
     if (c2 >= G) continue;
@@ -961,11 +1013,12 @@ __device__ __forceinline__ uint64_t seg_dp(const Tab& t, const Hot<kMode>& h, co
       // written at the device's HBM rate) when micro-batch sizes differ,
       // then gathered to the coarsest TP layout inside each TP group
       const uint64_t g1 = (1u << (tpl2 - tmin)) - 1;
-      const uint64_t sh = (uint64_t)ns * (t.par_layer[tpl2] + t.par_expert[tpl2][epl]) +
-                          (a == 0 ? t.par_embed[tpl2] : 0) + (e == t.L ? t.par_head[tpl2] : 0);
-      const uint64_t sc = mixed ? weigh_ps(t, k2, sh) : 0;
+      const Params p2(h.size(), tpl2, epl);
+      const uint64_t sh = (uint64_t)(p2.stage(ns, a == 0, e == t.L) + (double)ns * p2.expert);
+      const uint64_t sc = mixed ? weigh_ps(t, h.speed(k2), sh) : 0;
       const uint32_t bq_in = range_max(h.rmi(), t.N, l2, h2);
-      const uint64_t rl = sc + g1 * t2.a_intra, rb = link_ps(g1 * t.grad_bytes * sh, bq_in), r = rl + rb;
+      const uint64_t rl = sc + g1 * (uint64_t)t2.a_intra,
+                     rb = (uint64_t)link_ps((double)(g1 * t.grad_bytes * sh), bq_in), r = rl + rb;
       if (r > rs) {
         rs = r;
         rs_l = rl;
@@ -974,19 +1027,19 @@ __device__ __forceinline__ uint64_t seg_dp(const Tab& t, const Hot<kMode>& h, co
     }
   }
   const bool intra = same && nmin == nmax;
-  const uint64_t alpha = intra ? h.type(k0).a_intra : a_dp;
+  const double alpha = intra ? h.intra_alpha(k0) : a_dp;
   const uint32_t bq = intra ? h.rmi()[nmin] : bq_dp;
-  const uint64_t pd = (uint64_t)ns * t.par_layer[tmin] + (a == 0 ? t.par_embed[tmin] : 0) +
-                      (e == t.L ? t.par_head[tmin] : 0);
-  uint64_t ld = 0, bd = 0, le = 0, be = 0;
-  if (p.psum > 1) ring_parts(p.psum, rp, p.zero, t.grad_bytes * pd, t.param_bytes * pd, alpha, bq, t.ccl_tree, ld, bd);
+  const Params par(h.size(), tmin, epl);
+  const double pd = par.stage(ns, a == 0, e == t.L), gb = (double)t.grad_bytes, pb = (double)t.param_bytes;
+  double ld = 0, bd = 0, le = 0, be = 0;
+  if (p.psum > 1) ring_parts(p.psum, rp, p.zero, gb * pd, pb * pd, alpha, bq, t.ccl_tree, ld, bd);
   const uint32_t pe = p.psum >> epl;
   if (t.E && pe > 1) {
-    const uint64_t px = (uint64_t)ns * t.par_expert[tmin][epl];
-    ring_parts(pe, rpe, p.zero, t.grad_bytes * px, t.param_bytes * px, alpha, bq, t.ccl_tree, le, be);
+    const double px = (double)ns * par.expert;
+    ring_parts(pe, rpe, p.zero, gb * px, pb * px, alpha, bq, t.ccl_tree, le, be);
   }
-  lat = ld + le + rs_l;
-  bw = bd + be + rs_b;
+  lat = (uint64_t)(ld + le) + rs_l;
+  bw = (uint64_t)(bd + be) + rs_b;
   return lat + bw;
 }
 
@@ -1039,10 +1092,12 @@ __device__ __forceinline__ uint32_t row_cut(const uint4 (&rows)[4], uint32_t c, 
 // of the whole model.  Each class's stage holding the current segment, with
 // its placement and links, is recomputed only when the walk crosses one of
 // that class's cuts; a class's running max is stored when it leaves a stage.
-// drow: the plan's four rows of 16 entries (class c, stage s at c*16 + s).
+// drow: the plan's four rows of 16 entries (class c, stage s at c*16 + s).  In
+// fp64: exact below 2^53, and a pipeline that waits for a longer sync is
+// redone in u64.
 template <int kMode>
 __device__ __forceinline__ void het_plan_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p,
-                                               const uint4 (&rows)[4], uint64_t* __restrict__ drow) {
+                                               const uint4 (&rows)[4], double* __restrict__ drow) {
   const uint32_t G = p.G, epl = p.epl;
   const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> epl);
   uint32_t tmin = 3;
@@ -1059,11 +1114,19 @@ __device__ __forceinline__ void het_plan_syncs(const Tab& t, const Hot<kMode>& h
   // cur: the stage's sync so far -- the longest segment, or with contention
   // the largest latency part (cur) and the summed link times (curb)
   uint32_t stg[4], nxt[4], kk[4], nl[4], nh[4], bx[4], bin[4];
-  uint64_t as2[4], ain[4], cur[4], curb[4];
+  double as2[4], ain[4], cur[4], curb[4];
 #pragma unroll
   for (uint32_t c2 = 0; c2 < 4; ++c2) {
     stg[c2] = 0xffffffffu; nxt[c2] = c2 < G ? 0 : 0xffffffffu; kk[c2] = 0; nl[c2] = 0; nh[c2] = 0; bx[c2] = 0;
     bin[c2] = 0; as2[c2] = 0; ain[c2] = 0; cur[c2] = 0; curb[c2] = 0;
+  }
+  const Params par(h.size(), tmin, epl);
+  const double gb = (double)t.grad_bytes, pb = (double)t.param_bytes;
+  double sl[4];   // parameters of a layer on one TP rank of each class
+#pragma unroll
+  for (uint32_t c2 = 0; c2 < 4; ++c2) {
+    const uint32_t tpl2 = cls_tpl(p.chdr, c2);
+    sl[c2] = h.size().layer[tpl2] + h.size().expert[tpl2][epl];
   }
   for (uint32_t a = 0; a < t.L;) {
 #pragma unroll
@@ -1097,7 +1160,7 @@ __device__ __forceinline__ void het_plan_syncs(const Tab& t, const Hot<kMode>& h
     const uint32_t ns = e - a;
     bool same = true;
     uint32_t nmin = 0xffffffffu, nmax = 0, bq_dp = 0;
-    uint64_t a_dp = 0, rs = 0, rs_l = 0, rs_b = 0;
+    double a_dp = 0, rs = 0, rs_l = 0, rs_b = 0;
 #pragma unroll
     for (uint32_t c2 = 0; c2 < 4; ++c2) {
       if (c2 >= G) continue;
@@ -1108,11 +1171,11 @@ __device__ __forceinline__ void het_plan_syncs(const Tab& t, const Hot<kMode>& h
       a_dp = as2[c2] > a_dp ? as2[c2] : a_dp;
       const uint32_t tpl2 = cls_tpl(p.chdr, c2);
       if (tpl2 > tmin || mixed) {
-        const uint64_t g1 = (1u << (tpl2 - tmin)) - 1;
-        const uint64_t sh = (uint64_t)ns * (t.par_layer[tpl2] + t.par_expert[tpl2][epl]) +
-                            (a == 0 ? t.par_embed[tpl2] : 0) + (e == t.L ? t.par_head[tpl2] : 0);
-        const uint64_t rl = (mixed ? weigh_ps(t, kk[c2], sh) : 0) + g1 * ain[c2];
-        const uint64_t rb = link_ps(g1 * t.grad_bytes * sh, bin[c2]), r = rl + rb;
+        const double g1 = (double)((1u << (tpl2 - tmin)) - 1);
+        const double sh = (double)ns * sl[c2] + (a == 0 ? h.size().embed[tpl2] : 0.0) +
+                          (e == t.L ? h.size().head[tpl2] : 0.0);
+        const double rl = (mixed ? (double)weigh_ps(t, h.speed(kk[c2]), (uint64_t)sh) : 0.0) + g1 * ain[c2];
+        const double rb = link_ps(g1 * gb * sh, bin[c2]), r = rl + rb;
         if (r > rs) {
           rs = r;
           rs_l = rl;
@@ -1121,30 +1184,23 @@ __device__ __forceinline__ void het_plan_syncs(const Tab& t, const Hot<kMode>& h
       }
     }
     const bool intra = same && nmin == nmax;
-    const uint64_t alpha = intra ? ain[0] : a_dp;
+    const double alpha = intra ? ain[0] : a_dp;
     const uint32_t bq = intra ? h.rmi()[nmin] : bq_dp;
-    const uint64_t pd = (uint64_t)ns * t.par_layer[tmin] + (a == 0 ? t.par_embed[tmin] : 0) +
-                        (e == t.L ? t.par_head[tmin] : 0);
+    const double pd = par.stage(ns, a == 0, e == t.L), px = (double)ns * par.expert;
     if (!t.contention) {
-      uint64_t x = p.psum <= 1 ? 0 : ring_sync(p.psum, rp, p.zero, t.grad_bytes * pd, t.param_bytes * pd, alpha, bq, t.ccl_tree);
+      double x = p.psum <= 1 ? 0 : ring_sync(p.psum, rp, p.zero, gb * pd, pb * pd, alpha, bq, t.ccl_tree);
       const uint32_t pe = p.psum >> epl;
-      if (t.E && pe > 1) {
-        const uint64_t px = (uint64_t)ns * t.par_expert[tmin][epl];
-        x += ring_sync(pe, rpe, p.zero, t.grad_bytes * px, t.param_bytes * px, alpha, bq, t.ccl_tree);
-      }
+      if (t.E && pe > 1) x += ring_sync(pe, rpe, p.zero, gb * px, pb * px, alpha, bq, t.ccl_tree);
       x += rs;
 #pragma unroll
       for (uint32_t c2 = 0; c2 < 4; ++c2)
         if (c2 < G) cur[c2] = x > cur[c2] ? x : cur[c2];
     } else {
-      uint64_t ld = 0, bd = 0, le = 0, be = 0;
-      if (p.psum > 1) ring_parts(p.psum, rp, p.zero, t.grad_bytes * pd, t.param_bytes * pd, alpha, bq, t.ccl_tree, ld, bd);
+      double ld = 0, bd = 0, le = 0, be = 0;
+      if (p.psum > 1) ring_parts(p.psum, rp, p.zero, gb * pd, pb * pd, alpha, bq, t.ccl_tree, ld, bd);
       const uint32_t pe = p.psum >> epl;
-      if (t.E && pe > 1) {
-        const uint64_t px = (uint64_t)ns * t.par_expert[tmin][epl];
-        ring_parts(pe, rpe, p.zero, t.grad_bytes * px, t.param_bytes * px, alpha, bq, t.ccl_tree, le, be);
-      }
-      const uint64_t l = ld + le + rs_l, b = bd + be + rs_b;
+      if (t.E && pe > 1) ring_parts(pe, rpe, p.zero, gb * px, pb * px, alpha, bq, t.ccl_tree, le, be);
+      const double l = ld + le + rs_l, b = bd + be + rs_b;
 #pragma unroll
       for (uint32_t c2 = 0; c2 < 4; ++c2)
         if (c2 < G) {
@@ -1159,47 +1215,68 @@ __device__ __forceinline__ void het_plan_syncs(const Tab& t, const Hot<kMode>& h
     if (c2 < G) drow[c2 * kMaxStages + stg[c2]] = cur[c2] + curb[c2];
 }
 
-// Forward and backward time of one micro-batch over layers [lo, hi) on the
-// reps * tp devices of the pipeline's class from `base` on in pool k (type
-// ti; bq_in, bq_nic: slowest node fabric and NIC rates over them): the
-// layers, the embedding if `first`, the head if `last`, the TP all-reduces
-// exposed in the forward pass and the MoE all-to-all in both passes.  wc:
-// the weight-gradient pass of the zero-bubble order, half of the backward
-// compute rounded down (the all-to-all carries input gradients: it stays in
-// the input-gradient pass).
+// Where the devices of stage s of the pipeline's class sit: type k, its
+// pool's info, the first device in the pool, the stage's nodes, and the
+// slowest node fabric and NIC rates over the stage's reps * tp devices.
+struct StagePlace {
+  uint32_t k, base, nl, nh, bq_in, bq_nic;
+  TypeInfo ti;
+};
+template <int kMode>
+__device__ __forceinline__ StagePlace stage_place(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t k,
+                                                  uint32_t base) {
+  StagePlace r;
+  r.k = k;
+  r.base = base;
+  r.ti = h.type(k);
+  const uint32_t nd = p.rc * p.tp, dpl = r.ti.dpl, j = 31u - __clz(nd);
+  r.nl = r.ti.node_off + (base >> dpl);
+  r.nh = r.ti.node_off + ((base + nd - 1) >> dpl);
+  r.bq_in = range_max(h.rmi(), t.N, r.nl, r.nh);
+  // (range_max with the level the same for every stage)
+  const uint32_t* row = h.rmn + j * t.D + r.ti.dev_off + base;
+  const uint32_t a = row[0], b = row[nd - (1u << j)];
+  r.bq_nic = a > b ? a : b;
+  return r;
+}
+
+// Forward and backward time of one micro-batch over layers [lo, hi) on a stage
+// of the pipeline's class (act: bytes of its activation): the layers, the embedding if `first`, the head if
+// `last`, the TP all-reduces exposed in the forward pass and the MoE
+// all-to-all in both passes.  wc: the weight-gradient pass of the zero-bubble
+// order, half of the backward compute rounded down (the all-to-all carries
+// input gradients: it stays in the input-gradient pass).
 template <int kMode, bool kHet>
-__device__ __forceinline__ void stage_cost(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t k,
-                                           const TypeInfo& ti, uint32_t base, uint32_t bq_in, uint32_t bq_nic,
-                                           uint32_t lo, uint32_t hi, bool first, bool last, uint64_t& fc,
-                                           uint64_t& bc, uint64_t& wc) {
-  const uint32_t tp = p.tp, ep = p.ep, tpl = p.tpl, epl = p.epl, mi = p.mi, ns = hi - lo, dpl = ti.dpl;
-  const uint64_t act = t.act[mi], act_tp = (act + tp - 1) >> tpl;
+__device__ __forceinline__ void stage_cost(const Tab& t, const Hot<kMode>& h, const Plan& p, const StagePlace& sp,
+                                           double act, uint32_t lo, uint32_t hi, bool first, bool last, double& fc,
+                                           double& bc, double& wc) {
+  const uint32_t tp = p.tp, ep = p.ep, tpl = p.tpl, epl = p.epl, mi = p.mi, ns = hi - lo, dpl = sp.ti.dpl, k = sp.k;
   const uint32_t L1 = t.L + 1, epq = t.E ? p.epl : 0;
-  const uint32_t reps = p.rc;
   const uint32_t row = ((k * 4 + tpl) * t.n_mbs + mi) * t.nep + epq;
   if (t.uniform_layers) {
-    const ulonglong2 lc = h.pfb(row);
-    fc = lc.x * ns;
-    bc = lc.y * ns;
+    const double2 lc = h.pfb(row);
+    fc = lc.x * (double)ns;
+    bc = lc.y * (double)ns;
   } else {
-    const ulonglong2 ph = h.pfb(row * L1 + hi), pl = h.pfb(row * L1 + lo);
+    const double2 ph = h.pfb(row * L1 + hi), pl = h.pfb(row * L1 + lo);
     fc = ph.x - pl.x;
     bc = ph.y - pl.y;
   }
   if (first) {
-    const ulonglong2 em = h.emb(k * t.n_mbs + mi);
+    const double2 em = h.emb(k * t.n_mbs + mi);
     fc += em.x;
     bc += em.y;
   }
   if (last) {
-    const ulonglong2 hd = h.head((k * 4 + tpl) * t.n_mbs + mi);
+    const double2 hd = h.head((k * 4 + tpl) * t.n_mbs + mi);
     fc += hd.x;
     bc += hd.y;
   }
-  wc = bc >> 1;
+  wc = __builtin_floor(bc * 0.5);
   if (tp > 1) {  // TP all-reduces of this stage, exposed in the forward pass
-    const uint64_t steps = (uint64_t)(2 * ns + first) * 2 * (tp - 1);
-    fc += steps * ti.a_intra + link_ps(steps * act_tp, bq_in);
+    const double steps = (double)((2 * ns + first) * 2 * (tp - 1));
+    const double act_tp = __builtin_ceil(__builtin_ldexp(act, -(int)tpl));   // a TP rank's share
+    fc += steps * sp.ti.a_intra + link_ps(steps * act_tp, sp.bq_in);
   }
   if (t.E && ep > 1) {  // dispatch + combine all-to-all in each pass
     // EP groups are blocks of ep*tp devices from base on.  With one TP
@@ -1211,162 +1288,144 @@ __device__ __forceinline__ void stage_cost(const Tab& t, const Hot<kMode>& h, co
     // != 0 the first group to cross is number node/E - 1 - (in-node offset div E).
     const uint32_t E = ep * tp;
     bool intra = E <= (1u << dpl);
-    if (kHet && intra && (base & (E - 1)) != 0) {
-      const uint32_t q = (base & ((1u << dpl) - 1)) / E;
-      intra = reps / ep <= (1u << dpl) / E - 1 - q;
+    if (kHet && intra && (sp.base & (E - 1)) != 0) {
+      const uint32_t q = (sp.base & ((1u << dpl) - 1)) / E;
+      intra = p.rc / ep <= (1u << dpl) / E - 1 - q;
     }
-    const uint64_t alpha = intra ? ti.a_intra : 2 * ti.a_side;
-    const uint32_t bq = intra ? bq_in : (bq_nic > ti.bq_pcie ? bq_nic : ti.bq_pcie);
+    const double alpha = intra ? sp.ti.a_intra : 2 * sp.ti.a_side;
+    const uint32_t bq = intra ? sp.bq_in : (sp.bq_nic > sp.ti.bq_pcie ? sp.bq_nic : sp.ti.bq_pcie);
     const uint32_t pa = (epl * t.n_mbs + mi) * L1;
-    const uint64_t e = (uint64_t)ns * 2 * (ep - 1) * alpha + link_ps(2 * (h.pa(pa + hi) - h.pa(pa + lo)), bq);
+    const double e = (double)(ns * 2 * (ep - 1)) * alpha + link_ps(2 * (h.pa(pa + hi) - h.pa(pa + lo)), bq);
     fc += e;
     bc += e;
   }
 }
 
-// Where the devices of stage s of the pipeline's class sit: type k, its
-// pool's info, the first device in the pool, and the slowest node fabric
-// and NIC rates over the stage's reps * tp devices.
-template <int kMode, bool kHet>
-__device__ __forceinline__ void stage_place(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s, uint32_t& k,
-                                            TypeInfo& ti, uint32_t& base, uint32_t& bq_in, uint32_t& bq_nic) {
-  k = (uint32_t)(p.tc >> (4 * s)) & 15;
-  ti = h.type(k);
-  base = dev_before_own<kHet>(p, s, k);
-  const uint32_t nd = p.rc * p.tp, dpl = ti.dpl;
-  const uint32_t gnl = ti.node_off + (base >> dpl), gnh = ti.node_off + ((base + nd - 1) >> dpl);
-  bq_in = range_max(h.rmi(), t.N, gnl, gnh);
-  const uint32_t dlo = ti.dev_off + base;
-  bq_nic = range_max(h.rmn, t.D, dlo, dlo + nd - 1);
-}
-
 // Rail-only network (Fig. 2): the NIC of local rank r of every node joins
 // rail r and rails do not meet.  A pipeline hop between nodes pairs device i
-// of the sending stage (from bs on, n = reps * tp devices) with device i of
-// the receiving one (from br on); a pair at different local ranks is
+// of the sending stage (n = reps * tp devices) with device i of the receiving
+// one; a pair at different local ranks is
 // forwarded over a node's fabric first -- the sender's, or the receiver's
 // when the sender's nodes hold one device -- which adds that node's latency
-// and the activation at its slowest fabric rate (ins / inr over the
+// and the activation at its slowest fabric rate (over the
 // stage's nodes).  Offsets os, or in their nodes: every pair shares a rank
 // iff os == or and, with different node sizes, the n pairs do not reach the
 // end of the smaller node (past it one rank wraps and the other does not).
-__device__ __forceinline__ uint64_t rail_extra(uint32_t n, const TypeInfo& ts, uint32_t bs, uint32_t ins,
-                                               const TypeInfo& tr, uint32_t br, uint32_t inr, uint64_t act) {
-  const uint32_t ds = 1u << ts.dpl, dr = 1u << tr.dpl, os = bs & (ds - 1), orr = br & (dr - 1);
+__device__ __forceinline__ double rail_extra(uint32_t n, const StagePlace& from, const StagePlace& to, double act) {
+  const uint32_t ds = 1u << from.ti.dpl, dr = 1u << to.ti.dpl, os = from.base & (ds - 1), orr = to.base & (dr - 1);
   const bool same = os == orr && (ds == dr || os + n <= (ds < dr ? ds : dr));
   if (same) return 0;
-  const bool at_s = ts.dpl > 0;
-  return (at_s ? ts.a_intra : tr.a_intra) + link_ps(act, at_s ? ins : inr);
+  const bool at_s = from.ti.dpl > 0;
+  return (at_s ? from.ti.a_intra : to.ti.a_intra) + link_ps(act, at_s ? from.bq_in : to.bq_in);
 }
 
-template <int kMode, bool kHet, typename Sink>
-__device__ __forceinline__ void class_setup(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t c,
-                                            Sink& sink, const uint4* prow) {
+// Hop between two stages of one class, a placed before b when they share a
+// pool: inside a node iff every replica's pair is, i.e. iff a's first device
+// and b's last one share a node.
+__device__ __forceinline__ double hop_ps(const Tab& t, const Plan& p, const StagePlace& a, const StagePlace& b,
+                                         double act, bool a_sends) {
+  const uint32_t dpl = b.ti.dpl, n = p.rc * p.tp;
+  const bool intra = a.k == b.k && (a.base >> dpl) == ((b.base + n - p.tp) >> dpl);
+  const double alpha = intra ? b.ti.a_intra : a.ti.a_side + b.ti.a_side;
+  const uint32_t in = a.bq_in > b.bq_in ? a.bq_in : b.bq_in, nic = a.bq_nic > b.bq_nic ? a.bq_nic : b.bq_nic;
+  const uint32_t pcie = a.ti.bq_pcie > b.ti.bq_pcie ? a.ti.bq_pcie : b.ti.bq_pcie;
+  double hop = alpha + link_ps(act, intra ? in : nic > pcie ? nic : pcie);
+  if (t.rail_only && !intra) hop += a_sends ? rail_extra(n, a, b, act) : rail_extra(n, b, a, act);
+  return hop;
+}
+
+// Setup of a pipeline: the costs of its stages into `sink`.  first_device(s, k)
+// places stage s (of type k) in its pool; placed(s, place) sees where it went.
+// Stage s - 1 of the same pool ends where stage s begins, so hop_ps's order
+// holds.
+template <int kMode, bool kHet, typename Sink, typename First, typename Placed>
+__device__ __forceinline__ void class_setup(const Tab& t, const Hot<kMode>& h, const Plan& p, Sink& sink,
+                                            First first_device, Placed placed) {
   // register sinks fix the stage count at compile time (the plan's S equals it)
-  const uint32_t S = Sink::kS ? (uint32_t)Sink::kS : p.S, tp = p.tp, epl = p.epl;
-  const uint64_t act = t.act[p.mi];
-  const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> epl);
-  const uint32_t reps = p.rc;
-  uint32_t pk = 0, pbase = 0, pnic = 0, pin = 0, lo = 0;
-  TypeInfo pti = {};
+  const uint32_t S = Sink::kS ? (uint32_t)Sink::kS : p.S;
+  const double act = h.size().act[p.mi];
+  uint32_t lo = 0;
+  StagePlace prev = {};
 #pragma unroll Sink::kUnroll
   for (uint32_t s = 0; s < S; ++s) {
-    const uint32_t hi = cut_at(p, s);
-    // ---- this class: compute, TP, EP, hop from the previous stage
-    uint32_t k, base, bq_in, bq_nic;
-    TypeInfo ti;
-    stage_place<kMode, kHet>(t, h, p, s, k, ti, base, bq_in, bq_nic);
-    sink.base(s, base);
-    const uint32_t dpl = ti.dpl;
-    uint64_t fc, bc, wc;
-    stage_cost<kMode, kHet>(t, h, p, k, ti, base, bq_in, bq_nic, lo, hi, s == 0, s == S - 1, fc, bc, wc);
-    uint64_t hop = 0;
-    if (s > 0) {  // hop (s-1) -> s
-      // same pool means the two ranges are adjacent: intra iff the pair spans one node
-      const bool intra = pk == k && (pbase >> dpl) == ((pbase + (2 * reps - 1) * tp) >> dpl);
-      const uint64_t alpha = intra ? ti.a_intra : pti.a_side + ti.a_side;
-      uint32_t bq;
-      if (intra) {
-        bq = pin > bq_in ? pin : bq_in;
-      } else {
-        const uint32_t a = pnic > bq_nic ? pnic : bq_nic;
-        const uint32_t b = pti.bq_pcie > ti.bq_pcie ? pti.bq_pcie : ti.bq_pcie;
-        bq = a > b ? a : b;
-      }
-      hop = alpha + link_ps(act, bq);
-      if (t.rail_only && !intra) hop += rail_extra(reps * tp, pti, pbase, pin, ti, base, bq_in, act);
-    }
-    pk = k; pbase = base; pnic = bq_nic; pin = bq_in; pti = ti;
-    // ---- DP sync of this stage (the sink may leave it for later)
-    uint64_t tdp = 0;
-    if (Sink::kDp) {
-      if (kHet) {
-        uint4 rows[4];
-        load_rows(prow, rows);
-        tdp = het_stage_dp(t, h, p, rows, lo, hi, rp, rpe);
-      } else {
-        tdp = stage_sync(t, h, p, s, lo, hi, rp, rpe);
-      }
-    }
-    sink.put(s, fc, bc, wc, hop, tdp);
+    const uint32_t hi = cut_at(p, s), k = (uint32_t)(p.tc >> (4 * s)) & 15;
+    const StagePlace sp = stage_place<kMode>(t, h, p, k, first_device(s, k));
+    placed(s, sp);
+    double fc, bc, wc;
+    stage_cost<kMode, kHet>(t, h, p, sp, act, lo, hi, s == 0, s == S - 1, fc, bc, wc);
+    const double hop = s > 0 ? hop_ps(t, p, prev, sp, act, true) : 0;
+    prev = sp;
+    sink.put(s, fc, bc, wc, hop, lo, hi);
     lo = hi;
   }
 }
 
-// Sinks of class_setup.  RecSink stores whole stage records in memory order
-// (the hop of the last stage is 0), and, given `w`, each stage's
-// weight-gradient pass.
+// Stage records {forward, backward, hop, sync} in memory order (the hop of the
+// last stage is 0), with the pipeline's syncs found from the plan alone, and,
+// given `w`, each stage's weight-gradient pass.
+template <int kMode, bool kHet>
 struct RecSink {
-  static constexpr bool kDp = true;
   static constexpr int kS = 0, kUnroll = 1;   // stage count taken from the plan
-  __device__ __forceinline__ void base(uint32_t, uint32_t) {}
+  const Tab& t;
+  const Hot<kMode>& h;
+  const Plan& p;
+  const uint4* prow;   // per-class layout: the plan's four cut rows
   uint64_t (&rec)[kMaxStages][kRecWords];
-  uint64_t* w = nullptr;
-  __device__ __forceinline__ void put(uint32_t s, uint64_t fc, uint64_t bc, uint64_t wc, uint64_t hop,
-                                      uint64_t tdp) {
-    rec[s][0] = fc;
-    rec[s][1] = bc;
+  uint64_t* w;
+  __device__ __forceinline__ void put(uint32_t s, double fc, double bc, double wc, double hop, uint32_t lo,
+                                      uint32_t hi) {
+    const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
+    uint64_t tdp;
+    if (kHet) {
+      uint4 rows[4];
+      load_rows(prow, rows);
+      tdp = het_stage_dp(t, h, p, rows, lo, hi, rp, rpe);
+    } else {
+      tdp = stage_sync(t, h, p, s, lo, hi, rp, rpe);
+    }
+    rec[s][0] = (uint64_t)fc;
+    rec[s][1] = (uint64_t)bc;
     rec[s][2] = 0;
     rec[s][3] = tdp;
-    if (w) w[s] = wc;
-    if (s > 0) rec[s - 1][2] = hop;
+    if (w) w[s] = (uint64_t)wc;
+    if (s > 0) rec[s - 1][2] = (uint64_t)hop;
   }
 };
+template <int kMode, bool kHet>
+__device__ __forceinline__ void class_records(const Tab& t, const Hot<kMode>& h, const Plan& p, const uint4* prow,
+                                              uint64_t (&rec)[kMaxStages][kRecWords], uint64_t* w) {
+  RecSink<kMode, kHet> sink{t, h, p, prow, rec, w};
+  class_setup<kMode, kHet>(t, h, p, sink, [&](uint32_t s, uint32_t k) { return dev_before_own<kHet>(p, s, k); },
+                           [](uint32_t, const StagePlace&) {});
+}
 
 // RegSink keeps forward, backward and hop times of an S-stage pipeline in
-// registers as fp64 (every stage quantity is below 2^52, so exact): each
-// stage shifts the arrays down by one and appends, so after S stages stage s
+// registers: each stage shifts the arrays down by one and appends, so after S stages stage s
 // sits at index s; a runtime-indexed array would go through private memory.
 // The stage loop runs S (a compile-time count) times, unrolled by
 // kSetupUnroll: within an unrolled body the shifts are register renames, so
-// the copies are paid once per kSetupUnroll stages.  The DP sync is left to
-// dp_tail, after the recurrence.
+// the copies are paid once per kSetupUnroll stages.
 constexpr int kSetupUnroll = 4;
 
 template <int S>
 struct RegSink {
-  static constexpr bool kDp = false;
   static constexpr int kS = S, kUnroll = kSetupUnroll;
   double f[S], b[S], c[S];
-  uint32_t* bs = nullptr;   // optional: each stage's first device in its pool (LDS)
-  __device__ __forceinline__ void base(uint32_t s, uint32_t b0) {
-    if (bs) bs[s] = b0;
-  }
   __device__ __forceinline__ RegSink() {
 #pragma unroll
     for (int i = 0; i < S; ++i) f[i] = b[i] = c[i] = 0;
   }
-  __device__ __forceinline__ void put(uint32_t s, uint64_t fc, uint64_t bc, uint64_t, uint64_t hop, uint64_t) {
+  __device__ __forceinline__ void put(uint32_t s, double fc, double bc, double, double hop, uint32_t, uint32_t) {
 #pragma unroll
     for (int i = 0; i + 1 < S; ++i) {
       f[i] = f[i + 1];
       b[i] = b[i + 1];
       c[i] = c[i + 1];
     }
-    f[S - 1] = (double)fc;
-    b[S - 1] = (double)bc;
+    f[S - 1] = fc;
+    b[S - 1] = bc;
     c[S - 1] = 0;
-    if (S > 1 && s > 0) c[S - 2] = (double)hop;
+    if (S > 1 && s > 0) c[S - 2] = hop;
   }
 };
 
@@ -1374,15 +1433,13 @@ struct RegSink {
 // the input-gradient pass, and w, the weight-gradient pass.
 template <int S>
 struct ZbSink {
-  static constexpr bool kDp = false;
   static constexpr int kS = S, kUnroll = kSetupUnroll;
-  __device__ __forceinline__ void base(uint32_t, uint32_t) {}
   double f[S], bi[S], w[S], c[S];
   __device__ __forceinline__ ZbSink() {
 #pragma unroll
     for (int i = 0; i < S; ++i) f[i] = bi[i] = w[i] = c[i] = 0;
   }
-  __device__ __forceinline__ void put(uint32_t s, uint64_t fc, uint64_t bc, uint64_t wc, uint64_t hop, uint64_t) {
+  __device__ __forceinline__ void put(uint32_t s, double fc, double bc, double wc, double hop, uint32_t, uint32_t) {
 #pragma unroll
     for (int i = 0; i + 1 < S; ++i) {
       f[i] = f[i + 1];
@@ -1390,11 +1447,11 @@ struct ZbSink {
       w[i] = w[i + 1];
       c[i] = c[i + 1];
     }
-    f[S - 1] = (double)fc;
-    bi[S - 1] = (double)(bc - wc);
-    w[S - 1] = (double)wc;
+    f[S - 1] = fc;
+    bi[S - 1] = bc - wc;
+    w[S - 1] = wc;
     c[S - 1] = 0;
-    if (S > 1 && s > 0) c[S - 2] = (double)hop;
+    if (S > 1 && s > 0) c[S - 2] = hop;
   }
 };
 
@@ -1426,8 +1483,7 @@ __global__ void __launch_bounds__(256) k_stages(Tab t, const PackedPlan* __restr
     return;
   }
   uint64_t rec[kMaxStages][kRecWords];
-  RecSink sink{rec};
-  class_setup<2, kHet>(t, h, p, (uint32_t)(slot & 3), sink, kHet ? pcut + (slot & ~3ll) : nullptr);
+  class_records<2, kHet>(t, h, p, kHet ? pcut + (slot & ~3ll) : nullptr, rec, nullptr);
   uint64_t* o = out_stage + slot * (kMaxStages * kRecWords);
   for (uint32_t s = 0; s < p.S; ++s)
 #pragma unroll
@@ -1442,7 +1498,7 @@ template <int kMode>
 __global__ void __launch_bounds__(256) k_plan_syncs(Tab t, const PackedPlan* __restrict__ packed,
                                                     const uint4* __restrict__ pcut, const uint32_t* __restrict__ perm,
                                                     const uint32_t* __restrict__ pc, int64_t n,
-                                                    uint64_t* __restrict__ hdp) {
+                                                    double* __restrict__ hdp) {
   extern __shared__ uint4 lds[];
   fill_lds<kMode>(t, lds);
   const Hot<kMode> h(t, lds);
@@ -1858,85 +1914,140 @@ __device__ __forceinline__ void store_plan_time(const EvalBufs& e, uint32_t slot
   if (done && !mine) e.ovf[atomicAdd(&e.ctr[0], 1u)] = slot;
 }
 
-// DP syncs of a plan-sorted pipeline (first and variant passes, shared layout,
-// G classes on G adjacent lanes): the lane of class c costs the syncs of
-// stages c, c + G, ... (each the same for every class of the plan) into its
-// plan's column of the wavefront's LDS exchange area (x[64 s + first lane of
-// the plan], the syncs of stage s); every lane of the plan reads the column.
-template <int S, int kMode, bool kHier>
-__device__ __forceinline__ void grouped_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, double* x,
-                                              uint32_t lead, const uint32_t* bw = nullptr) {
-  const uint32_t G = p.G;
-  const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
-  // bw: every lane's stage placements from its setup (S per lane)
-  const uint32_t* bl = bw ? bw + lead * S : nullptr;
-  if (bw) wave_sync_lds();
-  for (uint32_t s = p.c; s < (uint32_t)S; s += G) {
-    const uint32_t lo = s ? cut_at(p, s - 1) : 0;
-    x[s * 64 + lead] = (double)stage_dp<kMode, kHier>(t, h, p, s, cut_at(p, s) - lo, rp, rpe, bl);
+// What the G lanes of a plan-sorted plan (classes 0 .. G - 1 from `lead` on)
+// share in their wavefront's LDS, a column of 64 entries per stage and one of
+// counters per device type:
+//  * placement: cnt[64 k + lane], the devices of type k (in units of the TP
+//    degree) placed before the lane's next stage of that type.  Every lane
+//    counts its own class, takes the sum of the classes before it as its
+//    start, and then draws each stage's first device by an atomic add on its
+//    own counter -- a few LDS accesses per stage, where counting over the
+//    packed types takes some twenty operations per earlier class;
+//  * links: every lane leaves its class's share of each stage's DP link;
+//  * syncs: the lane of class c puts stages c, c + G, ... together and leaves
+//    each stage's sync in the entry of class 0, for all lanes of the plan.
+template <int S>
+struct PlanLanes {
+  uint32_t G, lane, lead;
+  double* col;      // [64 s + lane]
+  uint32_t* cnt;    // [64 k + lane]
+  __device__ __forceinline__ PlanLanes(const Plan& p, double* xw, uint32_t* cw)
+      : G(p.G), lane(threadIdx.x & 63u), lead((threadIdx.x & 63u) - p.c), col(xw), cnt(cw) {}
+  __device__ __forceinline__ uint32_t& counter(const Plan& p, uint32_t s) {
+    return cnt[((uint32_t)(p.tc >> (4 * s)) & 15) * 64 + lane];
   }
-  wave_sync_lds();
-}
-
-// The same for an overlapped plan (variant pass): the lane of class c costs
-// the syncs of stages c, c + G, ... (one layer's bucket per stage, the
-// embedding's and the head's, in columns S and S + 1) into its plan's column,
-// then every lane walks its own buckets' readiness against them and leaves
-// the tail of stage s in its own column.
-template <int S, int kMode>
-__device__ __forceinline__ void grouped_overlap_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, double* x,
-                                                      uint32_t lead) {
-  const uint32_t G = p.G, lane = threadIdx.x & 63u;
-  const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
-  for (uint32_t s = p.c; s < (uint32_t)S; s += G) {
-    const OvlSyncs y = overlap_syncs<kMode, true>(t, h, p, s, rp, rpe);
-    x[s * 64 + lead] = (double)y.dl;
-    if (s == 0) x[S * 64 + lead] = (double)y.demb;
-    if (s == (uint32_t)S - 1) x[(S + 1) * 64 + lead] = (double)y.dhead;
+  __device__ __forceinline__ void start(const Tab& t, const Plan& p) {
+    for (uint32_t k = 0; k < t.K; ++k) cnt[64 * k + lane] = 0;
+    if (G == 1) return;
+#pragma unroll
+    for (uint32_t s = 0; s < (uint32_t)S; ++s) __hip_atomic_fetch_add(&counter(p, s), p.rc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    wave_sync_lds();
+    for (uint32_t k = 0; k < t.K; ++k) {
+      uint32_t before = 0;
+      for (uint32_t c = 0; c + 1 < G; ++c) {
+        const uint32_t n = cnt[64 * k + lead + c];
+        before += c < p.c ? n : 0;
+      }
+      wave_sync_lds();
+      cnt[64 * k + lane] = before;
+    }
   }
-  wave_sync_lds();
-  const OvlSyncs ends = {0, (uint64_t)x[S * 64 + lead], (uint64_t)x[(S + 1) * 64 + lead]};
-  uint32_t lo = 0;
-  for (uint32_t s = 0; s < (uint32_t)S; ++s) {
-    const uint32_t hi = cut_at(p, s);
-    const OvlSyncs y = {(uint64_t)x[s * 64 + lead], ends.demb, ends.dhead};
-    const double e = (double)overlap_walk<kMode>(t, h, p, s, lo, hi, (uint32_t)(p.tc >> (4 * s)) & 15, y);
-    wave_sync_lds();   // every lane of the plan has read stage s's bucket
-    x[s * 64 + lane] = e;
-    lo = hi;
+  __device__ __forceinline__ uint32_t first_device(const Plan& p, uint32_t k) {
+    return __hip_atomic_fetch_add(&cnt[64 * k + lane], p.rc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) * p.tp;
   }
-}
+  __device__ __forceinline__ void placed(uint32_t s, const StagePlace& sp) {
+    reinterpret_cast<uint2*>(col)[64 * s + lane] =
+        make_uint2(sp.bq_nic > sp.ti.bq_pcie ? sp.bq_nic : sp.ti.bq_pcie,
+                   sp.k << 24 | (sp.nl == sp.nh ? sp.nl : kNoNode));
+  }
+  template <int kMode, bool kHier>
+  __device__ __forceinline__ DpLink link(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s, HierShape& hs) {
+    hs.ok = false;
+    if (kHier && t.ccl_hier) return stage_link<kMode, true>(t, h, p, s, hs);
+    return exchanged_link(h, G, reinterpret_cast<const uint2*>(col) + 64 * s + lead);
+  }
+  // the stages' syncs into col[64 s + lead]; ns(s): the stage's layers
+  template <int kMode, bool kHier, typename Layers>
+  __device__ __forceinline__ void syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, Layers ns) {
+    wave_sync_lds();
+    const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
+    const Params par(h.size(), p.tpl, p.epl);
+    for (uint32_t s = p.c; s < (uint32_t)S; s += G) {
+      double x = 0;
+      if (p.psum > 1) {
+        HierShape hs;
+        const DpLink l = link<kMode, kHier>(t, h, p, s, hs);
+        const uint32_t n = ns(s);
+        x = link_dp<kHier>(t, p, l, hs, rp, rpe, par.stage(n, s == 0, s == (uint32_t)S - 1), (double)n * par.expert);
+      }
+      col[64 * s + lead] = x;
+    }
+    wave_sync_lds();
+  }
+  // the same for an overlapped plan: one layer's bucket sync per stage, the
+  // embedding's and the head's in columns S and S + 1; then every lane walks
+  // its own buckets' readiness against them and leaves the tail of stage s in
+  // its own entry
+  template <int kMode>
+  __device__ __forceinline__ void overlap(const Tab& t, const Hot<kMode>& h, const Plan& p) {
+    wave_sync_lds();
+    const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
+    for (uint32_t s = p.c; s < (uint32_t)S; s += G) {
+      OvlSyncs y = {0, 0, 0};
+      if (p.psum > 1) {
+        HierShape hs;
+        const DpLink l = link<kMode, true>(t, h, p, s, hs);
+        y = overlap_syncs(t, h, p, s, l, hs, rp, rpe);
+      }
+      col[64 * s + lead] = y.dl;
+      if (s == 0) col[64 * S + lead] = y.demb;
+      if (s == (uint32_t)S - 1) col[64 * (S + 1) + lead] = y.dhead;
+    }
+    wave_sync_lds();
+    const double demb = col[64 * S + lead], dhead = col[64 * (S + 1) + lead];
+    uint32_t lo = 0;
+    for (uint32_t s = 0; s < (uint32_t)S; ++s) {
+      const uint32_t hi = cut_at(p, s);
+      const double x = overlap_walk<kMode, double>(t, h, p, s, lo, hi, (uint32_t)(p.tc >> (4 * s)) & 15,
+                                                   OvlSyncs{col[64 * s + lead], demb, dhead});
+      wave_sync_lds();   // every lane of the plan has read stage s's bucket
+      col[64 * s + lane] = x;
+      lo = hi;
+    }
+  }
+};
 
 // One pipeline of the first pass (kKind 0) or of the variant pass (overlapped
 // sync, zero-bubble order; with two-level collectives, kHier, also plain
 // ones): setup, syncs, chain, and the recurrence with the first pass's budget.
-// xw: the wavefront's exchange columns (shared layout); bw: its placement
-// cache, when the group has one.
+// xw, cw: the wavefront's columns and counters (shared layout).
 template <int S, int kMode, bool kHet, int kKind, bool kHier>
 __device__ __forceinline__ void eval_one(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t slot,
-                                         double* xw, uint32_t* bw = nullptr) {
+                                         double* xw, uint32_t* cw) {
   constexpr bool kZb = kKind == 2, kOvl = kKind == 1;
-  const uint32_t lane = threadIdx.x & 63u;
   typename std::conditional<kZb, ZbSink<S>, RegSink<S>>::type r;
   const Plan p = load_plan<kHet>(e.packed, e.pcut, slot);
-  const uint32_t M = class_mb(p), G = p.G, lead = lane - p.c;
-  if constexpr (!kHet && !kZb)
-    if (bw) r.bs = bw + lane * S;
-  class_setup<kMode, kHet>(t, h, p, slot & 3, r, nullptr);
+  const uint32_t M = class_mb(p), G = p.G, lead = (threadIdx.x & 63u) - p.c;
   Chain<S, double> ch;
   {
     double x[S];
     if constexpr (!kHet) {
-      if constexpr (kOvl) grouped_overlap_syncs<S, kMode>(t, h, p, xw, lead);
-      else grouped_syncs<S, kMode, kHier>(t, h, p, xw, lead, kZb ? nullptr : bw);
+      PlanLanes<S> pl(p, xw, cw);
+      pl.start(t, p);
+      class_setup<kMode, false>(t, h, p, r, [&](uint32_t, uint32_t k) { return pl.first_device(p, k); },
+                                [&](uint32_t s, const StagePlace& sp) { pl.placed(s, sp); });
+      if constexpr (kOvl) pl.template overlap<kMode>(t, h, p);
+      else pl.template syncs<kMode, kHier>(t, h, p, [&](uint32_t s) { return cut_at(p, s) - (s ? cut_at(p, s - 1) : 0); });
 #pragma unroll
-      for (int s = 0; s < S; ++s) x[s] = xw[s * 64 + (kOvl ? lane : lead)];
+      for (int s = 0; s < S; ++s) x[s] = xw[s * 64 + (kOvl ? pl.lane : lead)];
       wave_sync_lds();
     } else {
+      class_setup<kMode, true>(t, h, p, r, [&](uint32_t s, uint32_t k) { return dev_before_own<true>(p, s, k); },
+                               [](uint32_t, const StagePlace&) {});
       // per-class layout: the syncs the plan pass stored for this pipeline's stages
-      const uint64_t* drow = e.hdp + (size_t)slot * kMaxStages;
+      const double* drow = e.hdp + (size_t)slot * kMaxStages;
 #pragma unroll
-      for (int s = 0; s < S; ++s) x[s] = (double)drow[s];
+      for (int s = 0; s < S; ++s) x[s] = drow[s];
     }
     if constexpr (kZb) reduce_chain<S, double, true>(r.f, r.bi, r.w, r.c, x, M, ch);
     else reduce_chain<S, double, false>(r.f, r.b, r.b, r.c, x, M, ch);
@@ -1989,62 +2100,40 @@ __device__ __forceinline__ void eval_one(const Tab& t, const Hot<kMode>& h, cons
 // of S v, the chunk of every op is a compile-time constant, so every
 // duration is a register.
 
-// Hop between the devices of two stages of one class, a placed before b
-// when they share a pool: inside a node iff every replica's pair is, i.e.
-// iff a's first device and b's last one share a node.
-__device__ __forceinline__ uint64_t il_hop(const Tab& t, uint32_t ka, const TypeInfo& ta, uint32_t basea,
-                                           uint32_t ina, uint32_t nica, uint32_t kb, const TypeInfo& tb,
-                                           uint32_t baseb, uint32_t inb, uint32_t nicb, uint32_t reps, uint32_t tp,
-                                           uint64_t act, bool a_sends) {
-  const uint32_t dpl = tb.dpl;
-  const bool intra = ka == kb && (basea >> dpl) == ((baseb + (reps - 1) * tp) >> dpl);
-  const uint64_t alpha = intra ? tb.a_intra : ta.a_side + tb.a_side;
-  uint32_t bq;
-  if (intra) {
-    bq = ina > inb ? ina : inb;
-  } else {
-    const uint32_t x = nica > nicb ? nica : nicb;
-    const uint32_t y = ta.bq_pcie > tb.bq_pcie ? ta.bq_pcie : tb.bq_pcie;
-    bq = x > y ? x : y;
-  }
-  uint64_t hop = alpha + link_ps(act, bq);
-  if (t.rail_only && !intra)
-    hop += a_sends ? rail_extra(reps * tp, ta, basea, ina, tb, baseb, inb, act)
-                   : rail_extra(reps * tp, tb, baseb, inb, ta, basea, ina, act);
-  return hop;
-}
-
 // Per virtual stage forward and backward time (f, b), hops between devices
 // (c[s]: s -> s + 1, c[S - 1]: the wrap hop S - 1 -> 0).
-template <int S, int v, int kMode, typename V>
+template <int S, int v, int kMode, typename V, typename First, typename Placed>
 __device__ __forceinline__ void il_setup(const Tab& t, const Hot<kMode>& h, const Plan& p, V (&f)[S * v],
-                                         V (&b)[S * v], V (&c)[S]) {
+                                         V (&b)[S * v], V (&c)[S], First first_device, Placed placed) {
   constexpr int NV = S * v;
-  const uint64_t act = t.act[p.mi];
-  uint32_t k0 = 0, base0 = 0, in0 = 0, nic0 = 0, pk = 0, pbase = 0, pin = 0, pnic = 0;
-  TypeInfo ti0 = {}, pti = {};
+  const double act = h.size().act[p.mi];
+  StagePlace first = {}, prev = {};
 #pragma unroll
   for (int s = 0; s < S; ++s) {
-    uint32_t k, base, bq_in, bq_nic;
-    TypeInfo ti;
-    stage_place<kMode, false>(t, h, p, s, k, ti, base, bq_in, bq_nic);
+    const uint32_t k = (uint32_t)(p.tc >> (4 * s)) & 15;
+    const StagePlace sp = stage_place<kMode>(t, h, p, k, first_device((uint32_t)s, k));
+    placed((uint32_t)s, sp);
 #pragma unroll
     for (int j = 0; j < v; ++j) {
       const int vs = j * S + s;
       const uint32_t lo = vs ? cut_at(p, vs - 1) : 0, hi = cut_at(p, vs);
-      uint64_t fc, bc, wc;
-      stage_cost<kMode, false>(t, h, p, k, ti, base, bq_in, bq_nic, lo, hi, vs == 0, vs == NV - 1, fc, bc, wc);
+      double fc, bc, wc;
+      stage_cost<kMode, false>(t, h, p, sp, act, lo, hi, vs == 0, vs == NV - 1, fc, bc, wc);
       f[vs] = (V)fc;
       b[vs] = (V)bc;
     }
-    if (s > 0) c[s - 1] = (V)il_hop(t, pk, pti, pbase, pin, pnic, k, ti, base, bq_in, bq_nic, p.rc, p.tp, act, true);
-    if (s == 0) {
-      k0 = k; ti0 = ti; base0 = base; in0 = bq_in; nic0 = bq_nic;
-    }
+    if (s > 0) c[s - 1] = (V)hop_ps(t, p, prev, sp, act, true);
+    if (s == 0) first = sp;
     if (s == S - 1)   // the wrap hop: device S - 1 sends to device 0, placed before it
-      c[S - 1] = (V)il_hop(t, k0, ti0, base0, in0, nic0, k, ti, base, bq_in, bq_nic, p.rc, p.tp, act, false);
-    pk = k; pti = ti; pbase = base; pin = bq_in; pnic = bq_nic;
+      c[S - 1] = (V)hop_ps(t, p, first, sp, act, false);
+    prev = sp;
   }
+}
+template <int S, int v, int kMode, typename V>
+__device__ __forceinline__ void il_setup_own(const Tab& t, const Hot<kMode>& h, const Plan& p, V (&f)[S * v],
+                                             V (&b)[S * v], V (&c)[S]) {
+  il_setup<S, v, kMode, V>(t, h, p, f, b, c, [&](uint32_t s, uint32_t k) { return dev_before_own<false>(p, s, k); },
+                           [](uint32_t, const StagePlace&) {});
 }
 
 // One trip of S v steps from step t0 (a multiple of S v).  kPred: some op of
@@ -2172,7 +2261,7 @@ __device__ __forceinline__ V il_tail(const Tab& t, const Hot<kMode>& h, const Pl
 template <int S, int v, int kMode, typename V, bool kJump>
 __device__ __forceinline__ V il_time(const Tab& t, const Hot<kMode>& h, const Plan& p, int& skipped) {
   V f[S * v], b[S * v], c[S], busy[S];
-  il_setup<S, v, kMode, V>(t, h, p, f, b, c);
+  il_setup_own<S, v, kMode, V>(t, h, p, f, b, c);
   il_pipe<S, v, V, kJump>(f, b, c, class_mb(p), busy, skipped);
   return il_tail<S, v, kMode, V>(t, h, p, busy);
 }
@@ -2182,22 +2271,22 @@ __device__ __forceinline__ V il_time(const Tab& t, const Hot<kMode>& h, const Pl
 template <int S, int v>
 __device__ __forceinline__ void il_records(const Tab& t, const Hot<2>& h, const Plan& p, uint64_t* o) {
   uint64_t f[S * v], b[S * v], c[S];
-  il_setup<S, v, 2, uint64_t>(t, h, p, f, b, c);
+  il_setup_own<S, v, 2, uint64_t>(t, h, p, f, b, c);
   const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
 #pragma unroll
   for (int vs = 0; vs < S * v; ++vs) {
     o[vs * kRecWords + 0] = f[vs];
     o[vs * kRecWords + 1] = b[vs];
     o[vs * kRecWords + 2] = vs < S ? c[vs < S ? vs : 0] : 0;
-    o[vs * kRecWords + 3] = vs < S ? stage_dp(t, h, p, vs, il_device_ns<S, v>(p, vs < S ? vs : 0), rp, rpe) : 0;
+    o[vs * kRecWords + 3] =
+        vs < S ? (uint64_t)stage_dp(t, h, p, vs, il_device_ns<S, v>(p, vs < S ? vs : 0), rp, rpe) : 0;
   }
 }
 
-// One plan-sorted interleaved pipeline: as eval_one, the lane of class c costs
-// the syncs of devices c, c + G, ... for all lanes of its plan.
+// One plan-sorted interleaved pipeline.
 template <int S, int v, int kMode>
 __device__ __forceinline__ void eval_il(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t slot,
-                                        double* x) {
+                                        double* x, uint32_t* cw) {
   const uint32_t lane = threadIdx.x & 63u;
   double busy[S];
   int skipped;
@@ -2209,15 +2298,15 @@ __device__ __forceinline__ void eval_il(const Tab& t, const Hot<kMode>& h, const
       const Plan p = load_plan<false>(e.packed, e.pcut, slot);
       G = p.G;
       lead = lane - p.c;
-      const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
-      for (uint32_t s = p.c; s < (uint32_t)S; s += G)
-        x[s * 64 + lead] = (double)stage_dp(t, h, p, s, il_device_ns<S, v>(p, (int)s), rp, rpe);
-      il_setup<S, v, kMode, double>(t, h, p, f, b, c);
+      PlanLanes<S> pl(p, x, cw);
+      pl.start(t, p);
+      il_setup<S, v, kMode, double>(t, h, p, f, b, c, [&](uint32_t, uint32_t k) { return pl.first_device(p, k); },
+                                    [&](uint32_t s, const StagePlace& sp) { pl.placed(s, sp); });
+      pl.template syncs<kMode, true>(t, h, p, [&](uint32_t s) { return il_device_ns<S, v>(p, (int)s); });
       M = class_mb(p);
     }
     il_pipe<S, v, double, true>(f, b, c, M, busy, skipped);
   }
-  wave_sync_lds();
   double T = 0;
 #pragma unroll
   for (int s = 0; s < S; ++s) T = vmax(T, busy[s] + x[s * 64 + lead]);
@@ -2228,11 +2317,28 @@ __device__ __forceinline__ void eval_il(const Tab& t, const Hot<kMode>& h, const
 // Blocks of four waves share one LDS copy of the table image.
 constexpr uint32_t kEvalThreads = 256;
 
+// A wavefront's columns and counters (PlanLanes) after the table image.
+struct WaveLds {
+  double* col;
+  uint32_t* cnt;
+  __device__ __forceinline__ WaveLds(const Tab& t, uint4* lds, uint32_t image, uint32_t cols, uint32_t wave) {
+    char* const p = (char*)lds + image + wave * wave_lds_bytes(cols, t.K);
+    col = (double*)p;
+    cnt = (uint32_t*)(p + cols * 64 * 8);
+  }
+};
+
+// Words that an earlier kernel wrote and this one only reads at uniform
+// indices: in the constant address space they are scalar loads.
+__device__ __forceinline__ uint32_t fixed_word(const uint32_t* p, uint32_t i) {
+  return ((const __attribute__((address_space(4))) uint32_t*)(uintptr_t)p)[i];
+}
+
 // The group of tile q, which is one of groups [g0, g0 + n) (q is uniform in the
 // wavefront, so this is scalar code).
 __device__ __forceinline__ uint32_t tile_group(const EvalBufs& e, uint32_t q, uint32_t g0, uint32_t n) {
   uint32_t g = g0;
-  for (uint32_t j = 1; j < n; ++j) g += q >= e.tstart[g0 + j] ? 1u : 0u;
+  for (uint32_t j = 1; j < n; ++j) g += q >= fixed_word(e.tstart, g0 + j) ? 1u : 0u;
   return g;
 }
 
@@ -2240,9 +2346,9 @@ __device__ __forceinline__ uint32_t tile_group(const EvalBufs& e, uint32_t q, ui
 template <bool kHet>
 __device__ __forceinline__ bool tile_slot(const EvalBufs& e, uint32_t q, uint32_t g, uint32_t& slot) {
   const uint32_t lane = threadIdx.x & 63u, G = kHet ? 1 : kMaxClasses - g % kMaxClasses;
-  const uint32_t per = kHet ? 64 : plans_per_tile(G), j = lane / G, r = (q - e.tstart[g]) * per + j;
-  const uint32_t first = e.gstart[g];
-  if (j >= per || r >= e.gstart[g + 1] - first) return false;
+  const uint32_t per = kHet ? 64 : plans_per_tile(G), j = lane / G, r = (q - fixed_word(e.tstart, g)) * per + j;
+  const uint32_t first = fixed_word(e.gstart, g);
+  if (j >= per || r >= fixed_word(e.gstart, g + 1) - first) return false;
   const uint32_t x = e.order[first + r];
   slot = kHet ? x : x * kMaxClasses + (lane - j * G);
   return true;
@@ -2254,32 +2360,25 @@ __device__ __forceinline__ bool tile_slot(const EvalBufs& e, uint32_t q, uint32_
 // few times the blocks that fit at once (each block holds a copy of the table
 // image); its waves take the group's tiles in a fixed stride, heaviest first.
 template <int GRP, int kMode, bool kHet>
-__global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(Tab t, EvalBufs e) {
+__global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(const Tab* __restrict__ tp, EvalBufs e) {
+  const Tab& t = *tp;
   constexpr int kTop = kMaxStages - 4 * GRP;   // stage counts kTop-3 .. kTop
   constexpr uint32_t g0 = 16 * GRP;
   extern __shared__ uint4 lds[];
-  const uint32_t lo = e.tstart[g0], hi = e.tstart[g0 + 16];
+  const uint32_t lo = fixed_word(e.tstart, g0), hi = fixed_word(e.tstart, g0 + 16);
   if (lo + blockIdx.x * (kEvalThreads / 64) >= hi) return;   // the whole block, before any barrier
   fill_lds<kMode>(t, lds);
   const Hot<kMode> h(t, lds);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // the wavefront's exchange columns and its stage-placement cache, when the group has one
-  double* xw = nullptr;
-  uint32_t* bw = nullptr;
-  if constexpr (!kHet) {
-    char* const x0 = (char*)lds + (kMode < 2 ? t.lds_bytes : 0);
-    xw = (double*)x0 + wave * xchg_wave(GRP, false);
-    if (GRP < 2 && ((t.bcache >> GRP) & 1))
-      bw = (uint32_t*)(x0 + xchg_bytes(GRP, false)) + wave * bcache_words(GRP);
-  }
+  const WaveLds w(t, lds, kMode < 2 ? t.lds_bytes : 0, kHet ? 0 : plan_cols(GRP, false), wave);
   for (uint32_t q = lo + blockIdx.x * (kEvalThreads / 64) + wave; q < hi; q += gridDim.x * (kEvalThreads / 64)) {
     const uint32_t g = tile_group(e, q, g0, 16), S = kTop - (g - g0) / kMaxClasses;
     uint32_t slot;
     if (!tile_slot<kHet>(e, q, g, slot)) continue;
-    if (S == kTop) eval_one<kTop, kMode, kHet, 0, false>(t, h, e, slot, xw, bw);
-    else if (S == kTop - 1) eval_one<kTop - 1, kMode, kHet, 0, false>(t, h, e, slot, xw, bw);
-    else if (S == kTop - 2) eval_one<kTop - 2, kMode, kHet, 0, false>(t, h, e, slot, xw, bw);
-    else eval_one<kTop - 3, kMode, kHet, 0, false>(t, h, e, slot, xw, bw);
+    if (S == kTop) eval_one<kTop, kMode, kHet, 0, false>(t, h, e, slot, w.col, w.cnt);
+    else if (S == kTop - 1) eval_one<kTop - 1, kMode, kHet, 0, false>(t, h, e, slot, w.col, w.cnt);
+    else if (S == kTop - 2) eval_one<kTop - 2, kMode, kHet, 0, false>(t, h, e, slot, w.col, w.cnt);
+    else eval_one<kTop - 3, kMode, kHet, 0, false>(t, h, e, slot, w.col, w.cnt);
   }
 }
 
@@ -2292,35 +2391,35 @@ __global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(Tab t, 
 // empty lists costs next to nothing.
 template <int S, int kMode>
 __device__ __forceinline__ void eval_kind(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t kind,
-                                          uint32_t slot, double* xw) {
-  if (kind == 2) eval_one<S, kMode, false, 2, true>(t, h, e, slot, xw);
-  else if (kind == 1) eval_one<S, kMode, false, 1, true>(t, h, e, slot, xw);
-  else eval_one<S, kMode, false, 0, true>(t, h, e, slot, xw);
+                                          uint32_t slot, const WaveLds& w) {
+  if (kind == 2) eval_one<S, kMode, false, 2, true>(t, h, e, slot, w.col, w.cnt);
+  else if (kind == 1) eval_one<S, kMode, false, 1, true>(t, h, e, slot, w.col, w.cnt);
+  else eval_one<S, kMode, false, 0, true>(t, h, e, slot, w.col, w.cnt);
 }
 template <int GRP, int kMode>
 __global__ void __launch_bounds__(kEvalThreads) k_variant(const Tab* __restrict__ tp, EvalBufs e) {
   constexpr int kTop = kMaxStages - 4 * GRP;   // stage counts kTop-3 .. kTop
   constexpr uint32_t g0 = 16 * GRP, kStep = kMaxStages * kMaxClasses;
   const Tab& t = *tp;
-  const uint32_t n0 = t.ccl_hier ? e.tstart[g0 + 16] - e.tstart[g0] : 0;
-  const uint32_t n1 = n0 + e.tstart[kStep + g0 + 16] - e.tstart[kStep + g0];
-  const uint32_t tiles = n1 + e.tstart[2 * kStep + g0 + 16] - e.tstart[2 * kStep + g0];
+  const uint32_t n0 = t.ccl_hier ? fixed_word(e.tstart, g0 + 16) - fixed_word(e.tstart, g0) : 0;
+  const uint32_t n1 = n0 + fixed_word(e.tstart, kStep + g0 + 16) - fixed_word(e.tstart, kStep + g0);
+  const uint32_t tiles = n1 + fixed_word(e.tstart, 2 * kStep + g0 + 16) - fixed_word(e.tstart, 2 * kStep + g0);
   if (blockIdx.x * (kEvalThreads / 64) >= tiles) return;   // the whole block, before any barrier
   extern __shared__ uint4 lds[];
   fill_lds<kMode>(t, lds);
   const Hot<kMode> h(t, lds);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  double* xw = (double*)((char*)lds + (kMode < 2 ? t.lds_bytes : 0)) + wave * xchg_wave(GRP, true);
+  const WaveLds wl(t, lds, kMode < 2 ? t.lds_bytes : 0, plan_cols(GRP, true), wave);
   for (uint32_t w = blockIdx.x * (kEvalThreads / 64) + wave; w < tiles; w += gridDim.x * (kEvalThreads / 64)) {
     const uint32_t kind = w < n0 ? 0 : w < n1 ? 1 : 2, first = kind * kStep + g0;
-    const uint32_t q = e.tstart[first] + (w - (kind == 0 ? 0 : kind == 1 ? n0 : n1));
+    const uint32_t q = fixed_word(e.tstart, first) + (w - (kind == 0 ? 0 : kind == 1 ? n0 : n1));
     const uint32_t g = tile_group(e, q, first, 16), S = kTop - (g - first) / kMaxClasses;
     uint32_t slot;
     if (!tile_slot<false>(e, q, g, slot)) continue;
-    if (S == kTop) eval_kind<kTop, kMode>(t, h, e, kind, slot, xw);
-    else if (S == kTop - 1) eval_kind<kTop - 1, kMode>(t, h, e, kind, slot, xw);
-    else if (S == kTop - 2) eval_kind<kTop - 2, kMode>(t, h, e, kind, slot, xw);
-    else eval_kind<kTop - 3, kMode>(t, h, e, kind, slot, xw);
+    if (S == kTop) eval_kind<kTop, kMode>(t, h, e, kind, slot, wl);
+    else if (S == kTop - 1) eval_kind<kTop - 1, kMode>(t, h, e, kind, slot, wl);
+    else if (S == kTop - 2) eval_kind<kTop - 2, kMode>(t, h, e, kind, slot, wl);
+    else eval_kind<kTop - 3, kMode>(t, h, e, kind, slot, wl);
   }
 }
 
@@ -2329,13 +2428,15 @@ __global__ void __launch_bounds__(kEvalThreads) k_variant(const Tab* __restrict_
 template <int kMode>
 __global__ void __launch_bounds__(kEvalThreads) k_il(const Tab* __restrict__ tp, EvalBufs e) {
   const Tab& t = *tp;
-  const uint32_t lo = e.tstart[kPlainGroups], hi = e.tstart[kGroups];
+  const uint32_t lo = fixed_word(e.tstart, kPlainGroups), hi = fixed_word(e.tstart, kGroups);
   if (lo + blockIdx.x * (kEvalThreads / 64) >= hi) return;   // the whole block, before any barrier
   extern __shared__ uint4 lds[];
   fill_lds<kMode>(t, lds);
   const Hot<kMode> h(t, lds);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  double* xw = (double*)((char*)lds + (kMode < 2 ? t.lds_bytes : 0)) + wave * kIlXchg;
+  const WaveLds wl(t, lds, kMode < 2 ? t.lds_bytes : 0, kIlCols, wave);
+  double* const xw = wl.col;
+  uint32_t* const cw = wl.cnt;
   for (uint32_t q = lo + blockIdx.x * (kEvalThreads / 64) + wave; q < hi; q += gridDim.x * (kEvalThreads / 64)) {
     const uint32_t g = tile_group(e, q, kPlainGroups, kGroups - kPlainGroups);
     uint32_t slot;
@@ -2343,7 +2444,7 @@ __global__ void __launch_bounds__(kEvalThreads) k_il(const Tab* __restrict__ tp,
     switch ((g - kPlainGroups) / kMaxClasses) {
 #define X(S_, V_)                          \
   case il_shape(S_, V_):                   \
-    eval_il<S_, V_, kMode>(t, h, e, slot, xw); \
+    eval_il<S_, V_, kMode>(t, h, e, slot, xw, cw); \
     break;
       HETSIM_IL_SHAPES(X)
 #undef X
@@ -2400,8 +2501,7 @@ __global__ void __launch_bounds__(64) k_redo_u64(Tab t, EvalBufs e) {
     StageRec R;
     uint64_t W[kMaxStages];
     const bool w = !kHet && p.zb;
-    RecSink sink{R, W};
-    class_setup<2, kHet>(t, h, p, slot & 3, sink, kHet ? e.pcut + (slot & ~3u) : nullptr);
+    class_records<2, kHet>(t, h, p, kHet ? e.pcut + (slot & ~3u) : nullptr, R, W);
     uint64_t r;
     switch (S) {
       case 1: r = redo_one<1>(R, W, w, M); break;

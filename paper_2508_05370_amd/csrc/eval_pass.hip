@@ -25,13 +25,11 @@ static uint32_t tile_grid(uint32_t n, uint32_t cap) {
 template <int kMode, bool kHet>
 hipError_t launch_group_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s) {
   const uint32_t grid = tile_grid(max_tiles, 4 * t.grid_eval[g]);
-  // the shared layout's groups add their plans' exchange columns
-  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) +
-                    (!kHet ? xchg_bytes(g, false) + (((t.bcache >> g) & 1) ? bcache_bytes(g) : 0) : 0);
-  if (g == 0) k_eval<0, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(t, e);
-  else if (g == 1) k_eval<1, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(t, e);
-  else if (g == 2) k_eval<2, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(t, e);
-  else k_eval<3, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(t, e);
+  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) + (kHet ? 0 : block_lds_bytes(plan_cols(g, false), t.K));
+  if (g == 0) k_eval<0, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
+  else if (g == 1) k_eval<1, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
+  else if (g == 2) k_eval<2, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
+  else k_eval<3, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
   return hipGetLastError();
 }
 template hipError_t launch_group_v<HETSIM_MODE, (bool)HETSIM_HET>(const Tab&, const EvalBufs&, uint32_t, int,
@@ -40,13 +38,12 @@ template hipError_t launch_group_v<HETSIM_MODE, (bool)HETSIM_HET>(const Tab&, co
 #if !HETSIM_HET
 // Grid caps come from the shared-layout kernels; the per-class-layout ones
 // take the same caps (their fixed-stride loops cover any grid).
-// bcache: the groups whose stage-placement cache is counted (bit g)
 template <int kMode>
-hipError_t occupancy_first_v(int nb[4], size_t lds, uint32_t bcache) {
+hipError_t occupancy_first_v(int nb[4], size_t lds, uint32_t types) {
   const void* k[4] = {(const void*)k_eval<0, kMode, false>, (const void*)k_eval<1, kMode, false>,
                       (const void*)k_eval<2, kMode, false>, (const void*)k_eval<3, kMode, false>};
   for (int i = 0; i < 4; ++i) {
-    const size_t b = lds + xchg_bytes(i, false) + (((bcache >> i) & 1) ? bcache_bytes(i) : 0);
+    const size_t b = lds + block_lds_bytes(plan_cols(i, false), types);
     hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[i], k[i], kEvalThreads, b);
     if (r != hipSuccess) return r;
   }
@@ -59,7 +56,7 @@ template hipError_t occupancy_first_v<HETSIM_MODE>(int[4], size_t, uint32_t);
 template <int kMode>
 hipError_t launch_variant_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s) {
   const uint32_t grid = tile_grid(max_tiles, t.grid_variant[g]);
-  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) + xchg_bytes(g, true);
+  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) + block_lds_bytes(plan_cols(g, true), t.K);
   if (g == 0) k_variant<0, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
   else if (g == 1) k_variant<1, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
   else if (g == 2) k_variant<2, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
@@ -69,32 +66,33 @@ hipError_t launch_variant_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles,
 template hipError_t launch_variant_v<HETSIM_MODE>(const Tab&, const EvalBufs&, uint32_t, int, hipStream_t);
 
 template <int kMode>
-hipError_t occupancy_variant_v(int nb[4], size_t lds) {
+hipError_t occupancy_variant_v(int nb[4], size_t lds, uint32_t types) {
   const void* k[4] = {(const void*)k_variant<0, kMode>, (const void*)k_variant<1, kMode>,
                       (const void*)k_variant<2, kMode>, (const void*)k_variant<3, kMode>};
   for (int i = 0; i < 4; ++i) {
-    hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[i], k[i], kEvalThreads, lds + xchg_bytes(i, true));
+    const size_t b = lds + block_lds_bytes(plan_cols(i, true), types);
+    hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[i], k[i], kEvalThreads, b);
     if (r != hipSuccess) return r;
   }
   return hipSuccess;
 }
-template hipError_t occupancy_variant_v<HETSIM_MODE>(int[4], size_t);
+template hipError_t occupancy_variant_v<HETSIM_MODE>(int[4], size_t, uint32_t);
 
 #else
 template <int kMode>
 hipError_t launch_il_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s) {
   k_il<kMode><<<tile_grid(max_tiles, t.grid_il), kEvalThreads,
-                (kMode < 2 ? t.lds_bytes : 0) + kIlXchgBytes, s>>>(e.dtab, e);
+                (kMode < 2 ? t.lds_bytes : 0) + block_lds_bytes(kIlCols, t.K), s>>>(e.dtab, e);
   return hipGetLastError();
 }
 template hipError_t launch_il_v<HETSIM_MODE>(const Tab&, const EvalBufs&, uint32_t, hipStream_t);
 
 template <int kMode>
-hipError_t occupancy_il_v(int nb[1], size_t lds) {
+hipError_t occupancy_il_v(int nb[1], size_t lds, uint32_t types) {
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[0], (const void*)k_il<kMode>, kEvalThreads,
-                                                      lds + kIlXchgBytes);
+                                                      lds + block_lds_bytes(kIlCols, types));
 }
-template hipError_t occupancy_il_v<HETSIM_MODE>(int[1], size_t);
+template hipError_t occupancy_il_v<HETSIM_MODE>(int[1], size_t, uint32_t);
 #endif
 
 }  // namespace hetsim

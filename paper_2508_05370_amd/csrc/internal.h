@@ -30,23 +30,21 @@ constexpr uint32_t kPlainGroups = kKinds * kMaxStages * kMaxClasses;
 constexpr uint32_t kGroups = kPlainGroups + kIlShapes * kMaxClasses;
 constexpr uint32_t kBuckets = kGroups * kBucketsM;
 __host__ __device__ constexpr uint32_t plans_per_tile(uint32_t G) { return G == 3 ? 21 : 64 / G; }
-// LDS of the first and variant passes over plan-sorted pipelines: per
-// wavefront one column of 64 doubles per stage (up to the kernel's largest
-// stage count, and in the variant pass two more for the embedding's and the
-// head's buckets of an overlapped sync), where the lanes of a plan exchange
-// its stages' syncs.
-__host__ __device__ constexpr uint32_t xchg_wave(int group, bool variant) {
-  return 64u * ((uint32_t)(kMaxStages - 4 * group) + (variant ? 2u : 0u));
+// LDS of the passes over plan-sorted pipelines: per wavefront one column of 64
+// doubles per stage (up to the kernel's largest stage count, and in the
+// variant pass two more for the embedding's and the head's buckets of an
+// overlapped sync; a column per device in the interleaved pass), and one
+// column of 64 counters per device type.
+__host__ __device__ constexpr uint32_t plan_cols(int group, bool variant) {
+  return (uint32_t)(kMaxStages - 4 * group) + (variant ? 2u : 0u);
 }
-__host__ __device__ constexpr uint32_t xchg_bytes(int group, bool variant) { return 4 * xchg_wave(group, variant) * 8; }
-// the interleaved pass: a column per device (at most 8)
-constexpr uint32_t kIlXchg = 64u * 8u, kIlXchgBytes = 4 * kIlXchg * 8;
-// The first pass of the two long stage-count groups keeps each lane's stage
-// placements (first device in the pool, u32 per stage) in LDS from setup to
-// the DP tail, where the plan's lanes read each other's instead of counting
-// them again: 64 lanes x the group's longest stage count per wavefront.
-__host__ __device__ constexpr uint32_t bcache_words(int group) { return group < 2 ? 64u * (kMaxStages - 4 * group) : 0u; }
-__host__ __device__ constexpr uint32_t bcache_bytes(int group) { return 4 * bcache_words(group) * 4; }
+constexpr uint32_t kIlCols = 8;
+__host__ __device__ constexpr uint32_t wave_lds_bytes(uint32_t cols, uint32_t types) {
+  return cols ? cols * 64 * 8 + types * 64 * 4 : 0;
+}
+__host__ __device__ constexpr uint32_t block_lds_bytes(uint32_t cols, uint32_t types) {
+  return 4 * wave_lds_bytes(cols, types);
+}
 
 // A validated plan packed into 80 contiguous bytes, so that the pipelines of
 // one plan gather it with five 16-byte loads.
@@ -62,14 +60,30 @@ struct TypeInfo {
   uint32_t node_off, dev_off;     // first global node / device of the pool
   uint32_t dpl;                   // log2 devices per node
   uint32_t bq_pcie;               // PCIe ps/byte in 2^-16 units, 0 = absent
-  uint64_t a_intra;               // intra-node message latency
-  uint64_t a_side;                // one end of an inter-node path: two PCIe trips + NIC
+  double a_intra;                 // intra-node message latency (ps; integers below 2^43)
+  double a_side;                  // one end of an inter-node path: two PCIe trips + NIC
+};
+
+// Device speed of a pool (TFLOP/s, GB/s of HBM) and the reciprocals rounded to
+// nearest (for exact ceilings): the gradient weighting of classes with
+// different micro-batch sizes.
+struct SpeedInfo {
+  uint32_t tflops, hbm, pad0, pad1;
+  double rtflops, rhbm;
+};
+
+// Quantities by TP degree, EP degree and micro-batch size (log2 or index), in
+// fp64: parameters of one layer (non-expert, expert), the embedding and the
+// head on one TP rank, and the bytes of one micro-batch activation.
+struct SizeInfo {
+  double layer[4], embed[4], head[4], expert[4][4], act[4];
 };
 
 // The tables of the per-pipeline setup form one byte image in device memory
 // that the evaluation kernels copy into LDS, where lanes gather from it at
-// LDS rather than vector-cache rates.  Sections, each 16-byte aligned:
-//   TypeInfo [K]; {forward, backward} layer prefix sums
+// LDS rather than vector-cache rates.  Times are whole numbers in fp64.
+// Sections, each 16-byte aligned:
+//   TypeInfo [K]; SizeInfo; SpeedInfo [K]; {forward, backward} layer prefix sums
 //   [K][4 log2 TP][n_mbs][nep][L+1] (nep = 4 EP slots for MoE models, 1 for
 //   dense ones), or, when every layer costs the same (dense models), one
 //   {forward, backward} layer cost [K][4][n_mbs] (uniform_layers);
@@ -81,14 +95,24 @@ struct TypeInfo {
 // fit; 2: nothing is copied and every table is read from device memory.
 constexpr uint32_t kLdsBudget = 64 * 1024;
 
+// What the plan check gathers by per-lane indices (k_prep keeps a copy in LDS:
+// a gather from the kernel argument block goes to host memory).
+struct CheckTab {
+  uint32_t type_ok[4];            // [log2 TP] bit k: type k exists and TP 2^j divides its node size
+  uint32_t mbs[4];
+  uint64_t par_layer[4];          // non-expert parameters of one layer on one TP rank, by log2 TP
+  uint64_t par_expert[4][4];      // expert parameters of one layer per rank [log2 TP][log2 EP]
+  uint64_t par_embed[4], par_head[4];
+  uint64_t act_layer[4][4];       // bytes one layer stores for backward per micro-batch [log2 TP][mbs index]
+  uint64_t mem_cap[kMaxTypes];    // device memory of type k, bytes
+};
+
 // Everything a kernel needs about one (model, cluster) pair.  Scalars travel
 // by value in the kernel argument block; tables live in device memory.
-struct Tab {
+struct Tab : CheckTab {
   uint32_t L, K, E, n_mbs, gbs;
-  uint32_t mbs[4];
   uint32_t tp_ok;                 // bit j: TP 2^j divides heads, kv heads and MLP widths
   uint32_t ep_ok;                 // bit j: EP 2^j allowed (dense models: EP 1 only)
-  uint32_t type_ok[4];            // [log2 TP] bit k: type k exists and TP 2^j divides its node size
   uint32_t D, N;                  // total devices, total nodes
   uint32_t lvl_dev, lvl_node;     // levels of the range-max tables
   uint32_t dpn_log2[kMaxTypes];
@@ -98,26 +122,19 @@ struct Tab {
   uint32_t bq_pcie[kMaxTypes];    // PCIe ps/byte in 2^-16 units, 0 = absent
   uint64_t a_intra[kMaxTypes];    // intra-node message latency
   uint64_t a_side[kMaxTypes];     // one end of an inter-node path: two PCIe trips + NIC
-  uint32_t tflops[kMaxTypes];     // device speed of pool k (TFLOP/s, GB/s of HBM): the gradient
-  uint32_t hbm[kMaxTypes];        // weighting of classes with different micro-batch sizes
-  double rtflops[kMaxTypes];      // their reciprocals, rounded to nearest (for exact ceilings)
-  double rhbm[kMaxTypes];
+  uint32_t tflops[kMaxTypes];     // device speed of pool k (TFLOP/s, GB/s of HBM)
+  uint32_t hbm[kMaxTypes];
   uint64_t act[4];                // bytes of one micro-batch activation per mbs index
   uint64_t grad_bytes, param_bytes;
-  uint64_t par_layer[4];          // non-expert parameters of one layer on one TP rank, by log2 TP
-  uint64_t par_expert[4][4];      // expert parameters of one layer per rank [log2 TP][log2 EP]
-  uint64_t par_embed[4], par_head[4];
   uint32_t mem_check;             // 1: device memory capacities given; plans must fit them
   uint32_t rail_only;             // 1: rail-only inter-node network (cross-rail hops forwarded in a node)
   uint32_t ccl_tree;              // 1: all-reduces take the faster of ring and tree
   uint32_t contention;            // 1: a stage's concurrent segment syncs share its links
   uint32_t ccl_hier;              // 1: whole-node DP groups may take the two-level all-reduce
-  uint64_t mem_cap[kMaxTypes];    // device memory of type k, bytes
   uint64_t opt_bytes;             // optimizer-state bytes per parameter
-  uint64_t act_layer[4][4];       // bytes one layer stores for backward per micro-batch [log2 TP][mbs index]
   uint32_t nep;                   // EP slots of the prefix tables
   uint32_t uniform_layers;        // 1: the layer table holds one layer's cost per row
-  uint32_t o_pfb, o_emb, o_head, o_pa, o_rmi, o_rmn;   // section byte offsets (TypeInfo at 0)
+  uint32_t o_size, o_speed, o_pfb, o_emb, o_head, o_pa, o_rmi, o_rmn;   // section byte offsets (TypeInfo at 0)
   uint32_t img_bytes;             // whole image
   uint32_t lds_bytes;             // prefix copied to LDS: img_bytes, o_rmn or 0 by mode
   uint32_t mode;
@@ -126,8 +143,6 @@ struct Tab {
   uint32_t grid_il;               // blocks of the interleaved kernel that fit the device at once
   uint32_t grid_cont;             // blocks of the continuation kernels that fit the device at once
   uint32_t grid_variant[4];       // blocks of each variant-pass kernel that fit the device at once
-  uint32_t bcache;                // bit g: first-pass group g keeps stage placements in LDS (when that
-                                  // costs no occupancy)
 };
 
 // Continuation lists.  A pipeline whose schedule is still aperiodic after the
@@ -160,7 +175,7 @@ constexpr uint32_t kSkipSlots = 512, kSkipStride = 16;
 struct EvalBufs {
   const PackedPlan* packed;
   const uint4* pcut;           // per-class layout: cut row of pipeline slot at [slot]; nullptr for the shared layout
-  const uint64_t* hdp;         // per-class layout: the syncs of pipeline slot's stages at [16 slot, + 16)
+  const double* hdp;           // per-class layout: the syncs of pipeline slot's stages at [16 slot, + 16)
   const uint32_t* order;       // plans (shared layout) or pipeline slots (per-class layout) by group
   const uint32_t* gstart;      // [kGroups + 1]
   const uint32_t* tstart;      // [kGroups + 1]
@@ -187,7 +202,7 @@ constexpr uint32_t kCounters = kBuckets + kEvalCounters + kPlanSortWords;
 struct Work {
   PackedPlan* packed;
   uint4* pcut;
-  uint64_t* hdp;
+  double* hdp;
   uint32_t *meta, *perm, *order, *hist, *ctr, *ovf, *cursor, *gstart, *tstart, *cinfo;
   uint16_t* keys;
   double* cont;
@@ -243,7 +258,7 @@ inline Work carve(void* base, int64_t ch, bool het, size_t cont_per_plan) {
   w.cont = (double*)(p + o.cont);
   w.cont_units = (uint32_t)(cont_bytes(ch, cont_per_plan) / kContUnit);
   w.pcut = het ? (uint4*)(p + o.pcut) : nullptr;
-  w.hdp = het ? (uint64_t*)(p + o.hdp) : nullptr;
+  w.hdp = het ? (double*)(p + o.hdp) : nullptr;
   w.meta = het ? (uint32_t*)(p + o.meta) : nullptr;
   w.perm = het ? (uint32_t*)(p + o.perm) : nullptr;
   w.packed = (PackedPlan*)(p + o.packed);

@@ -413,22 +413,22 @@ hipError_t launch_fill32(uint32_t* p, uint32_t n, uint32_t v, hipStream_t s) {
   k_fill32<<<blocks_for(n, 256) < 1024 ? blocks_for(n, 256) : 1024, 256, 0, s>>>(p, n, v);
   return hipGetLastError();
 }
-hipError_t launch_prep(const Tab& t, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed, uint4* pcut,
+hipError_t launch_prep(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed, uint4* pcut,
                        uint32_t* meta, uint32_t* hist, uint16_t* keys, hipStream_t s) {
   const int g = blocks_for(n, 256 * kPrepPerThread);
-  if (p.chdr) k_prep<true><<<g, 256, 0, s>>>(t, p, n, out, packed, pcut, meta, hist, keys);
-  else k_prep<false><<<g, 256, 0, s>>>(t, p, n, out, packed, pcut, meta, hist, keys);
+  if (p.chdr) k_prep<true><<<g, 256, 0, s>>>(t, dtab, p, n, out, packed, pcut, meta, hist, keys);
+  else k_prep<false><<<g, 256, 0, s>>>(t, dtab, p, n, out, packed, pcut, meta, hist, keys);
   return hipGetLastError();
 }
-hipError_t launch_memory(const Tab& t, const sim_plans& p, int64_t n, uint64_t* out, hipStream_t s) {
-  if (p.chdr) k_memory<true><<<blocks_for(n, 256), 256, 0, s>>>(t, p, n, out);
-  else k_memory<false><<<blocks_for(n, 256), 256, 0, s>>>(t, p, n, out);
+hipError_t launch_memory(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, hipStream_t s) {
+  if (p.chdr) k_memory<true><<<blocks_for(n, 256), 256, 0, s>>>(t, dtab, p, n, out);
+  else k_memory<false><<<blocks_for(n, 256), 256, 0, s>>>(t, dtab, p, n, out);
   return hipGetLastError();
 }
 
 // pc: the plan-order counters (zero on entry); perm: n words
 hipError_t launch_plan_syncs(const Tab& t, const PackedPlan* packed, const uint4* pcut, const uint32_t* meta,
-                             int64_t n, uint64_t* hdp, uint32_t* pc, uint32_t* perm, hipStream_t s) {
+                             int64_t n, double* hdp, uint32_t* pc, uint32_t* perm, hipStream_t s) {
   const int go = blocks_for(n, 256 * kPlanPer);
   k_plan_hist<<<go, 256, 0, s>>>((const uint4*)meta, (uint32_t)n, pc);
   k_plan_scatter<<<go, 256, 0, s>>>((const uint4*)meta, (uint32_t)n, pc, perm);
@@ -489,30 +489,21 @@ int eval_grids(Tab* t) {
   if (r == hipSuccess) r = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (r != hipSuccess) return (int)r;
   const size_t lds = t->mode < 2 ? t->lds_bytes : 0;
-  int nb[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, nbc[4] = {0, 0, 0, 0};
-  if (t->mode == 0) r = occupancy_first_v<0>(nb, lds, 0);
-  else if (t->mode == 1) r = occupancy_first_v<1>(nb, lds, 0);
-  else r = occupancy_first_v<2>(nb, lds, 0);
-  // the stage-placement cache of the first pass's long groups, where it costs no blocks
+  int nb[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  if (t->mode == 0) r = occupancy_first_v<0>(nb, lds, t->K);
+  else if (t->mode == 1) r = occupancy_first_v<1>(nb, lds, t->K);
+  else r = occupancy_first_v<2>(nb, lds, t->K);
   if (r == hipSuccess) {
-    if (t->mode == 0) r = occupancy_first_v<0>(nbc, lds, 3u);
-    else if (t->mode == 1) r = occupancy_first_v<1>(nbc, lds, 3u);
-    else r = occupancy_first_v<2>(nbc, lds, 3u);
-  }
-  t->bcache = 0;
-  for (int i = 0; i < 2; ++i)
-    if (nbc[i] == nb[i]) t->bcache |= 1u << i;
-  if (r == hipSuccess) {
-    if (t->mode == 0) r = occupancy_il_v<0>(nb + 4, lds);
-    else if (t->mode == 1) r = occupancy_il_v<1>(nb + 4, lds);
-    else r = occupancy_il_v<2>(nb + 4, lds);
+    if (t->mode == 0) r = occupancy_il_v<0>(nb + 4, lds, t->K);
+    else if (t->mode == 1) r = occupancy_il_v<1>(nb + 4, lds, t->K);
+    else r = occupancy_il_v<2>(nb + 4, lds, t->K);
   }
   if (r == hipSuccess)
     r = hipOccupancyMaxActiveBlocksPerMultiprocessor(nb + 9, (const void*)k_cont, 256, 0);
   if (r == hipSuccess) {
-    if (t->mode == 0) r = occupancy_variant_v<0>(nb + 5, lds);
-    else if (t->mode == 1) r = occupancy_variant_v<1>(nb + 5, lds);
-    else r = occupancy_variant_v<2>(nb + 5, lds);
+    if (t->mode == 0) r = occupancy_variant_v<0>(nb + 5, lds, t->K);
+    else if (t->mode == 1) r = occupancy_variant_v<1>(nb + 5, lds, t->K);
+    else r = occupancy_variant_v<2>(nb + 5, lds, t->K);
   }
   if (r != hipSuccess) return (int)r;
   for (int i = 0; i < 4; ++i) t->grid_eval[i] = (uint32_t)((nb[i] > 0 ? nb[i] : 1) * cus);

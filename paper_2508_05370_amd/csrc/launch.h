@@ -19,13 +19,14 @@ hipError_t launch_il_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipS
 template <int kMode>
 hipError_t launch_variant_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s);
 // Blocks per CU of the shared-layout first-pass kernels, the variant kernels
-// (nb[0..3]) or the interleaved kernel (nb[0]) at the given LDS size.
+// (nb[0..3]) or the interleaved kernel (nb[0]) with `lds` bytes of table image
+// and `types` device types.
 template <int kMode>
-hipError_t occupancy_first_v(int nb[4], size_t lds, uint32_t bcache);
+hipError_t occupancy_first_v(int nb[4], size_t lds, uint32_t types);
 template <int kMode>
-hipError_t occupancy_variant_v(int nb[4], size_t lds);
+hipError_t occupancy_variant_v(int nb[4], size_t lds, uint32_t types);
 template <int kMode>
-hipError_t occupancy_il_v(int nb[1], size_t lds);
+hipError_t occupancy_il_v(int nb[1], size_t lds, uint32_t types);
 
 #define HETSIM_EXTERN_MODE(M)                                                                                  \
   extern template hipError_t launch_group_v<M, false>(const Tab&, const EvalBufs&, uint32_t, int, hipStream_t); \
@@ -33,8 +34,8 @@ hipError_t occupancy_il_v(int nb[1], size_t lds);
   extern template hipError_t launch_il_v<M>(const Tab&, const EvalBufs&, uint32_t, hipStream_t);                \
   extern template hipError_t launch_variant_v<M>(const Tab&, const EvalBufs&, uint32_t, int, hipStream_t);      \
   extern template hipError_t occupancy_first_v<M>(int[4], size_t, uint32_t);                                   \
-  extern template hipError_t occupancy_variant_v<M>(int[4], size_t);                                           \
-  extern template hipError_t occupancy_il_v<M>(int[1], size_t);
+  extern template hipError_t occupancy_variant_v<M>(int[4], size_t, uint32_t);                                           \
+  extern template hipError_t occupancy_il_v<M>(int[1], size_t, uint32_t);
 HETSIM_EXTERN_MODE(0)
 HETSIM_EXTERN_MODE(1)
 HETSIM_EXTERN_MODE(2)

@@ -132,7 +132,9 @@ void build_image(HostTables* h) {
   const uint32_t row = uniform ? 1 : L1;   // entries per (type, TP, mbs, EP slot)
   auto a16 = [](size_t x) { return (uint32_t)((x + 15) & ~(size_t)15); };
   const uint32_t n_pfb = K * 4 * nm * t.nep * row;
-  t.o_pfb = a16((size_t)K * sizeof(TypeInfo));
+  t.o_size = a16((size_t)K * sizeof(TypeInfo));
+  t.o_speed = t.o_size + a16(sizeof(SizeInfo));
+  t.o_pfb = t.o_speed + a16((size_t)K * sizeof(SpeedInfo));
   t.o_emb = t.o_pfb + n_pfb * 16;
   t.o_head = t.o_emb + K * nm * 16;
   t.o_pa = t.o_head + K * 4 * nm * 16;
@@ -144,7 +146,18 @@ void build_image(HostTables* h) {
   h->img.assign(t.img_bytes, 0);
   uint8_t* b = h->img.data();
   memcpy(b, h->ty.data(), K * sizeof(TypeInfo));
-  uint64_t* pfb = (uint64_t*)(b + t.o_pfb);
+  SizeInfo* z = (SizeInfo*)(b + t.o_size);
+  for (int j = 0; j < 4; ++j) {
+    z->layer[j] = (double)t.par_layer[j];
+    z->embed[j] = (double)t.par_embed[j];
+    z->head[j] = (double)t.par_head[j];
+    z->act[j] = (double)t.act[j];
+    for (int g = 0; g < 4; ++g) z->expert[j][g] = (double)t.par_expert[j][g];
+  }
+  SpeedInfo* v = (SpeedInfo*)(b + t.o_speed);
+  for (uint32_t k = 0; k < K; ++k)
+    v[k] = SpeedInfo{t.tflops[k], t.hbm[k], 0, 0, 1.0 / (double)t.tflops[k], 1.0 / (double)t.hbm[k]};
+  double* pfb = (double*)(b + t.o_pfb);
   for (uint32_t k = 0; k < K; ++k)
     for (uint32_t j = 0; j < 4; ++j)
       for (uint32_t mi = 0; mi < nm; ++mi)
@@ -152,12 +165,16 @@ void build_image(HostTables* h) {
           for (uint32_t l = 0; l < row; ++l) {
             const size_t src = ((((size_t)k * 4 + j) * nm + mi) * 4 + g) * L1 + l + (uniform ? 1 : 0);
             const size_t dst = ((((size_t)k * 4 + j) * nm + mi) * t.nep + g) * row + l;
-            pfb[2 * dst] = h->pf[src];        // uniform: pf[1] - pf[0] = the layer's cost
-            pfb[2 * dst + 1] = h->pb[src];
+            pfb[2 * dst] = (double)h->pf[src];        // uniform: pf[1] - pf[0] = the layer's cost
+            pfb[2 * dst + 1] = (double)h->pb[src];
           }
-  memcpy(b + t.o_emb, h->emb.data(), h->emb.size() * 8);
-  memcpy(b + t.o_head, h->head.data(), h->head.size() * 8);
-  if (t.E) memcpy(b + t.o_pa, h->pa.data(), h->pa.size() * 8);
+  auto put = [&](uint32_t off, const std::vector<uint64_t>& v) {
+    double* d = (double*)(b + off);
+    for (size_t i = 0; i < v.size(); ++i) d[i] = (double)v[i];
+  };
+  put(t.o_emb, h->emb);
+  put(t.o_head, h->head);
+  if (t.E) put(t.o_pa, h->pa);
   memcpy(b + t.o_rmi, h->rm_intra.data(), h->rm_intra.size() * 4);
   memcpy(b + t.o_rmn, h->rm_nic.data(), h->rm_nic.size() * 4);
 }
@@ -254,8 +271,6 @@ int build_tables(const sim_model_desc* md, const sim_cluster_desc* cd, HostTable
     t.cap[k] = cd->n_nodes[k] * cd->dev_per_node[k];
     t.tflops[k] = cd->tflops[k];
     t.hbm[k] = cd->hbm_GBps[k];
-    t.rtflops[k] = 1.0 / (double)cd->tflops[k];
-    t.rhbm[k] = 1.0 / (double)cd->hbm_GBps[k];
     t.dev_off[k] = (uint32_t)d0;
     t.node_off[k] = (uint32_t)n0;
     t.bq_pcie[k] = (uint32_t)beta_q(cd->pcie_MBps[k]);
@@ -284,7 +299,8 @@ int build_tables(const sim_model_desc* md, const sim_cluster_desc* cd, HostTable
       if (t.dpn_log2[k] >= j) t.type_ok[j] |= 1u << k;
   out->ty.assign(K, TypeInfo{});
   for (uint32_t k = 0; k < K; ++k)
-    out->ty[k] = TypeInfo{t.node_off[k], t.dev_off[k], t.dpn_log2[k], t.bq_pcie[k], t.a_intra[k], t.a_side[k]};
+    out->ty[k] = TypeInfo{t.node_off[k], t.dev_off[k], t.dpn_log2[k], t.bq_pcie[k],
+                          (double)t.a_intra[k], (double)t.a_side[k]};
   build_rmax(nic, &out->rm_nic, &t.lvl_dev);
   build_rmax(intra, &out->rm_intra, &t.lvl_node);
 
