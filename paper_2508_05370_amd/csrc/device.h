@@ -1715,11 +1715,21 @@ __device__ __forceinline__ void wave_sync_lds() {
 // (1 or 2) of its stage count; false if the list is full.
 template <int S, int kList>
 __device__ __forceinline__ bool cont_push(const EvalBufs& e, const Chain<S, double>& h, int left, uint32_t slot) {
-  constexpr int j = kMaxStages - S, info = 32 * (kList - 1) + j;
-  const uint32_t cap = e.cinfo[info + 16] * 64u;
-  const uint32_t pos = atomicAdd(&e.ctr[1 + kMaxStages * (kList - 1) + j], 1u);
-  if (pos >= cap) return false;
-  double* q = e.cont + (size_t)e.cinfo[info] * (kContUnit / 8) + (size_t)(pos >> 6) * (256 * S) + (pos & 63u);
+  constexpr uint32_t j = kMaxStages - S;
+  uint32_t first, cap, ctr;
+  if (kList == 1) {
+    const uint32_t sub = blockIdx.x & (e.cinfo[64 + j] - 1);
+    cap = e.cinfo[16 + j];
+    first = e.cinfo[j] + sub * cap * S;
+    ctr = cont1_ctr(j, sub);
+  } else {
+    first = e.cinfo[32 + j];
+    cap = e.cinfo[48 + j];
+    ctr = cont2_ctr(j);
+  }
+  const uint32_t pos = atomicAdd(&e.ctr[ctr], 1u);
+  if (pos >= cap * 64u) return false;
+  double* q = e.cont + (size_t)first * (kContUnit / 8) + (size_t)(pos >> 6) * (256 * S) + (pos & 63u);
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     q[64 * s] = h.f[s];
@@ -1878,24 +1888,56 @@ __device__ __forceinline__ void cont_one(const EvalBufs& e, const double* tile) 
   count_skipped(e, S, skipped);
 }
 
-// Tile `tile` of 64 (or entry of 1) of a list: its stage count S and place in
-// the list; false past the last one.  Most stages first.
+// The parts of a list, by the block: entries and units (a tile of 64 entries,
+// or one entry) up to the end of each part, most stages first; find() takes
+// unit q of the whole list to its part.
 template <int kList, uint32_t kPer>
-__device__ __forceinline__ bool cont_find(const EvalBufs& e, uint32_t q, uint32_t& S, uint32_t& tile, uint32_t& n) {
-  uint32_t before = 0;
-  for (uint32_t j = 0; j < (uint32_t)kMaxStages; ++j) {
-    const uint32_t cap = e.cinfo[32 * (kList - 1) + 16 + j] * 64u, c = e.ctr[1 + kMaxStages * (kList - 1) + j];
-    n = c < cap ? c : cap;
-    const uint32_t nt = (n + kPer - 1) / kPer;
-    if (q < before + nt) {
-      S = kMaxStages - j;
-      tile = q - before;
-      return true;
+struct ContIndex {
+  static constexpr int kHalves = kList == 1 ? 2 : 1;
+  static constexpr uint32_t kPerList = kList == 1 ? kContSubs : 1;
+  static_assert(kMaxStages * kPerList <= 64 * kHalves, "a lane per part");
+  uint32_t n[64 * kHalves], incl[64 * kHalves];   // in LDS
+  __device__ __forceinline__ void fill(const EvalBufs& e) {
+    if (threadIdx.x < 64) {
+      const uint32_t lane = threadIdx.x;
+      uint32_t run = 0;
+#pragma unroll
+      for (int h = 0; h < kHalves; ++h) {
+        const uint32_t x = 64 * h + lane, j = x / kPerList, sub = x % kPerList;
+        const bool on = j < (uint32_t)kMaxStages && (kList == 2 || sub < e.cinfo[64 + j]);
+        const uint32_t cap = on ? e.cinfo[(kList == 1 ? 16 : 48) + j] * 64u : 0;
+        const uint32_t c = on ? e.ctr[kList == 1 ? cont1_ctr(j, sub) : cont2_ctr(j)] : 0;
+        n[x] = c < cap ? c : cap;
+        uint32_t y = (n[x] + kPer - 1) / kPer;
+#pragma unroll
+        for (uint32_t o = 1; o < 64; o <<= 1) {
+          const uint32_t z = __shfl_up(y, o);
+          y += lane >= o ? z : 0;
+        }
+        incl[x] = run + y;
+        run = __shfl(run + y, 63);
+      }
     }
-    before += nt;
+    __syncthreads();
   }
-  return false;
-}
+  // S: stage count; at: the unit in its part; count: the part's entries; base: its first 2 KiB unit
+  __device__ __forceinline__ bool find(const EvalBufs& e, uint32_t q, uint32_t& S, uint32_t& at, uint32_t& count,
+                                       uint32_t& base) const {
+    const uint32_t lane = threadIdx.x & 63u;
+    for (int h = 0; h < kHalves; ++h) {
+      const uint64_t past = __ballot(incl[64 * h + lane] > q);
+      if (past) {
+        const uint32_t x = 64 * h + (uint32_t)__builtin_ctzll(past), j = x / kPerList, sub = x % kPerList;
+        count = __builtin_amdgcn_readfirstlane(n[x]);
+        at = q - (__builtin_amdgcn_readfirstlane(incl[x]) - (count + kPer - 1) / kPer);
+        S = kMaxStages - j;
+        base = kList == 1 ? e.cinfo[j] + sub * e.cinfo[16 + j] * S : e.cinfo[32 + j];
+        return true;
+      }
+    }
+    return false;
+  }
+};
 
 // The time of a plan whose G pipelines sit on adjacent lanes from `lead` on,
 // all of them here: the first one stores the largest result of the finished

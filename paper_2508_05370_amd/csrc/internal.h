@@ -150,18 +150,26 @@ struct Tab : CheckTab {
 // e_s and the iterations left with the pipeline's slot -- in a list of its
 // stage count, in tiles of 64 (word r of entry l of a tile at [64 r + l]), and
 // k_cont goes on with full wavefronts of them; what is left after its budget
-// moves on to a second list and k_power.  cinfo[j], j = 16 - S: the
-// list's first 2 KiB unit in the continuation buffer, cinfo[16 + j]: its
-// capacity in tiles (S units each); [32 + j] and [48 + j] the same for the
-// second list.  A pipeline that finds its list full goes on where it is.
+// moves on to a second list and k_power.  A pipeline that finds its list full
+// goes on where it is.  Most wavefronts of the first pass offer something, and
+// atomics on one address are served one by one (about 12 ns each, which alone
+// was 80-100 us of a group's pass over a million plans): the first list of a
+// stage count is cut into up to kContSubs lists, picked by the block, and
+// every counter has a cache line of its own.
+// cinfo, j = 16 - S: [j] the first list's first 2 KiB unit in the continuation
+// buffer, [16 + j] the capacity of each of its [64 + j] parts in tiles (S
+// units each); [32 + j] and [48 + j] place and capacity of the second list.
 constexpr uint32_t kContUnit = 2048;            // bytes
-constexpr uint32_t kContWords = 64;
-// Counters of a chunk: [0] pipelines to redo in u64, [1 + j] and [17 + j]
-// pipelines offered to the first and second continuation list of 16 - j
-// stages; the per-class layout's plan-order counters (kPlanSortWords) follow
-// them, then the redo list.
-constexpr uint32_t kEvalCounters = 48;
-static_assert(1 + 2 * kMaxStages <= kEvalCounters, "evaluation counters");
+constexpr uint32_t kContSubs = 8;
+constexpr uint32_t kContWords = 80;
+// Counters of a chunk, kCtrStep words apart: pipelines to redo in u64, those
+// offered to the parts of the first and to the second continuation list of
+// 16 - j stages; the per-class layout's plan-order counters (kPlanSortWords)
+// follow them, then the redo list.
+constexpr uint32_t kCtrStep = 32;
+__host__ __device__ constexpr uint32_t cont1_ctr(uint32_t j, uint32_t sub) { return (1 + j * kContSubs + sub) * kCtrStep; }
+__host__ __device__ constexpr uint32_t cont2_ctr(uint32_t j) { return (1 + kMaxStages * kContSubs + j) * kCtrStep; }
+constexpr uint32_t kEvalCounters = cont2_ctr(kMaxStages);
 // Per-class layout: plans counting-sorted by (classes, total stages) before
 // the plan-level sync pass -- counts [0, 256), cursors [256, 512), the
 // number of valid plans at 512.

@@ -106,6 +106,7 @@ __global__ void __launch_bounds__(1024) k_scan(const uint32_t* __restrict__ hist
   if (tid < 64) {
     const bool on = tid < (uint32_t)kMaxStages;
     const uint32_t S = on ? kMaxStages - tid : 0;
+    // the first list's tiles, in up to kContSubs equal parts
     uint32_t cap1 = on ? (stiles[tid] * (S + 2) + 47) / 48 : 0, cap2 = (cap1 + 3) / 4;
     auto total = [&](uint32_t x) {   // sum over the wavefront
 #pragma unroll
@@ -127,10 +128,14 @@ __global__ void __launch_bounds__(1024) k_scan(const uint32_t* __restrict__ hist
       cap1 = (uint32_t)((uint64_t)cap1 * units * 4 / want);
       cap2 = cap1 / 4;
     }
+    uint32_t subs = 1;
+    while (subs < kContSubs && 4 * subs <= cap1) subs *= 2;
+    const uint32_t part = cap1 / subs;
     const uint32_t b1 = before(cap1 * S), b2 = total(cap1 * S) + before(cap2 * S);
     if (on) {
       cinfo[tid] = b1;
-      cinfo[16 + tid] = cap1;
+      cinfo[16 + tid] = part;
+      cinfo[64 + tid] = subs;
       cinfo[32 + tid] = b2;
       cinfo[48 + tid] = cap2;
     }
@@ -229,12 +234,14 @@ __global__ void __launch_bounds__(256) k_plan_scatter(const uint4* __restrict__ 
 // ---------------------------------------------------------------- continuation passes
 // The first list: tiles dealt round-robin to the waves of the grid.
 __global__ void __launch_bounds__(256, 2) k_cont(EvalBufs e) {
+  __shared__ ContIndex<1, 64> ix;
+  ix.fill(e);
   const uint32_t lane = threadIdx.x & 63u, waves = gridDim.x * (blockDim.x >> 6);
-  uint32_t S, tile, n;
+  uint32_t S, at, count, first;
   for (uint32_t q = blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-       cont_find<1, 64>(e, q, S, tile, n); q += waves) {
-    if (tile * 64 + lane >= n) continue;
-    const double* base = e.cont + (size_t)e.cinfo[kMaxStages - S] * (kContUnit / 8) + (size_t)tile * (256 * S) + lane;
+       ix.find(e, q, S, at, count, first); q += waves) {
+    if (at * 64 + lane >= count) continue;
+    const double* base = e.cont + (size_t)first * (kContUnit / 8) + (size_t)at * (256 * S) + lane;
     switch (S) {
 #define X(S_) \
   case S_: cont_one<S_>(e, base); break;
@@ -264,10 +271,11 @@ __global__ void __launch_bounds__(256) k_power(EvalBufs e) {
   const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t j = lane & 15u, g = lane >> 4, waves = gridDim.x * 4;
   double* const v = vec[wave];
-  uint32_t S, pos, n;
-  for (uint32_t q = blockIdx.x * 4 + wave; cont_find<2, 1>(e, q, S, pos, n); q += waves) {
-    const double* p = e.cont + (size_t)e.cinfo[32 + kMaxStages - S] * (kContUnit / 8) + (size_t)(pos >> 6) * (256 * S) +
-                      (pos & 63u);
+  __shared__ ContIndex<2, 1> ix;
+  ix.fill(e);
+  uint32_t S, at, count, first;
+  for (uint32_t q = blockIdx.x * 4 + wave; ix.find(e, q, S, at, count, first); q += waves) {
+    const double* p = e.cont + (size_t)first * (kContUnit / 8) + (size_t)(at >> 6) * (256 * S) + (at & 63u);
     const uint2 ls = *(const uint2*)&p[64 * (3 * S - 1)];
     uint32_t left = ls.x - (N - S);
     // lanes 0-15 the state, 16-31 a, 32-47 d, 48-63 e of frame stage j
