@@ -66,6 +66,15 @@ __device__ __forceinline__ double ceil_div(double x, double p, double rp) {
   return q + (__builtin_fma(-q, p, x) > 0 ? 1.0 : 0.0);
 }
 
+// Order of LDS accesses within a wavefront: its lanes' accesses complete in
+// order; the fences keep the compiler from moving one lane's reads above other
+// lanes' writes.
+__device__ __forceinline__ void wave_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // max over [lo, hi] of a range-max table with row length n
 __device__ __forceinline__ uint32_t range_max(const uint32_t* __restrict__ tb, uint32_t n, uint32_t lo, uint32_t hi) {
   uint32_t j = 31u - __clz(hi - lo + 1);
@@ -73,12 +82,25 @@ __device__ __forceinline__ uint32_t range_max(const uint32_t* __restrict__ tb, u
   return a > b ? a : b;
 }
 
-// number of the nibbles selected by `sel` that equal k
+// number of the nibbles selected by `sel` that equal k (in 32-bit halves: the
+// shifts bring a nibble's bits down to its lowest one, which no neighbour
+// reaches)
 __device__ __forceinline__ uint32_t count_type(uint64_t types, uint32_t k, uint64_t sel) {
-  const uint64_t ones = 0x1111111111111111ull;
-  uint64_t x = types ^ (ones * k);
-  uint64_t nz = (x | (x >> 1) | (x >> 2) | (x >> 3)) & ones;
-  return (uint32_t)__popcll(~nz & ones & sel);
+  const uint32_t ones = 0x11111111u, kk = ones * k;
+  uint32_t lo = (uint32_t)types ^ kk, hi = (uint32_t)(types >> 32) ^ kk;
+  lo |= lo >> 1;
+  hi |= hi >> 1;
+  lo |= lo >> 2;
+  hi |= hi >> 2;
+  return (uint32_t)__popc(~lo & (ones & (uint32_t)sel)) + (uint32_t)__popc(~hi & (ones & (uint32_t)(sel >> 32)));
+}
+
+// ceil(a / b) for a < 2^16 and 1 <= b < 2^16: the fp32 quotient's floor is
+// within one of the true one, and the remainder says which.
+__device__ __forceinline__ uint32_t ceil_div16(uint32_t a, uint32_t b) {
+  const uint32_t q = (uint32_t)((float)a * __builtin_amdgcn_rcpf((float)b));
+  const int r = (int)(a - q * b);
+  return q + (r > 0 ? 1u : 0u) + (r > (int)b ? 1u : 0u);
 }
 
 // ceil(x / p) for x < 2^53 and p >= 1, given rp = RN(1/p): the rounded
@@ -256,7 +278,7 @@ __device__ __forceinline__ Plan load_plan(const PackedPlan* packed, const uint4*
 }
 
 // micro-batches per replica of the pipeline's class (its M)
-__device__ __forceinline__ uint32_t class_mb(const Plan& p) { return (p.nc + p.rc - 1) / p.rc; }
+__device__ __forceinline__ uint32_t class_mb(const Plan& p) { return ceil_div16(p.nc, p.rc); }
 
 constexpr int kPrepPerThread = 4;
 
@@ -340,30 +362,33 @@ __device__ __forceinline__ Checked check_plan(const Tab& t, const CheckTab& ct, 
       const uint32_t reps = r.cls[c] & 0xffff, nmb = r.cls[c] >> 16;
       ok = ok && reps >= 1 && nmb >= reps && (reps & (ep - 1)) == 0;
       if (!kHet && v > 1 && ok) {   // interleaving: M a multiple of S and at least 2 S
-        const uint32_t M = (nmb + reps - 1) / reps;
+        const uint32_t M = ceil_div16(nmb, reps);
         ok = M % S == 0 && M >= 2 * S;
       }
       batch += nmb * ct.mbs[mic];
       psum += reps;
-      // every stage's type exists and holds whole TP groups in a node
-      const uint32_t okm = ct.type_ok[tpl];
-      for (uint32_t s = 0; s < S; ++s) ok = ok && ((okm >> ((uint32_t)(r.tv[c] >> (4 * s)) & 15)) & 1);
     } else {
       r.cls[c] = 0;
       r.tv[c] = 0;
     }
   }
   ok = ok && batch == t.gbs;
+  // every stage's type exists and holds whole TP groups in a node, and the
   // capacity of every pool under the packing (blocks aligned to their TP degree)
-  for (uint32_t k = 0; ok && k < t.K; ++k) {
+  uint32_t bad[4];   // stages of class c not yet found on a type that it may use
+#pragma unroll
+  for (uint32_t c = 0; c < 4; ++c) bad[c] = c < G ? r.S[c] : 0;
+  for (uint32_t k = 0; k < t.K; ++k) {
     uint32_t need = 0;
 #pragma unroll
     for (uint32_t c = 0; c < 4; ++c) {
       const uint32_t nk = c < G ? count_type(r.tv[c], k, stage_sel(r.S[c])) : 0;
       if (nk) need = ((need + (1u << r.tpl[c]) - 1) >> r.tpl[c] << r.tpl[c]) + (((r.cls[c] & 0xffff) * nk) << r.tpl[c]);
+      bad[c] -= (ct.type_ok[r.tpl[c]] >> k) & 1 ? nk : 0;
     }
-    ok = need <= t.cap[k];
+    ok = ok && need <= t.cap[k];
   }
+  ok = ok && (bad[0] | bad[1] | bad[2] | bad[3]) == 0;
   r.ok = ok;
   r.hdr = hdr;
   r.psum = psum;
@@ -378,16 +403,16 @@ __device__ __forceinline__ Checked check_plan(const Tab& t, const CheckTab& ct, 
 // (all replicas for the non-expert parameters, replicas / EP for the
 // experts).
 __device__ __forceinline__ uint64_t state_bytes(const Tab& t, const CheckTab& ct, uint32_t tpl, uint32_t epl, uint32_t zero,
-                                                uint32_t psum, bool first, bool last, uint32_t ns) {
+                                                uint32_t psum, bool first, bool last, uint32_t ns, double rp,
+                                                double rpx) {
   uint64_t pd = (uint64_t)ns * ct.par_layer[tpl];
   if (first) pd += ct.par_embed[tpl];
   if (last) pd += ct.par_head[tpl];
   const uint64_t pe = (uint64_t)ns * ct.par_expert[tpl][epl];
   uint64_t od = t.opt_bytes * pd, oe = t.opt_bytes * pe;
   if (zero) {
-    const uint32_t pdx = psum >> epl;
-    od = (od + psum - 1) / psum;
-    oe = (oe + pdx - 1) / pdx;
+    od = div_up_u64(od, psum, rp);
+    if (oe) oe = div_up_u64(oe, psum >> epl, rpx);
   }
   return (t.param_bytes + t.grad_bytes) * (pd + pe) + od + oe;
 }
@@ -404,7 +429,9 @@ __device__ __forceinline__ uint32_t checked_cut(const Checked& r, uint32_t c, ui
 __device__ __forceinline__ uint64_t class_state_bytes(const Tab& t, const CheckTab& ct, const Checked& r, uint32_t c, uint32_t s,
                                                       uint32_t ns) {
   const uint32_t epl = (r.hdr >> 2) & 3, zero = (r.hdr >> 10) & 1;
-  return state_bytes(t, ct, r.tpl[c], epl, zero, r.psum, s == 0, s == r.S[c] - 1, ns);
+  // (the reciprocals are the same for every stage of the plan)
+  return state_bytes(t, ct, r.tpl[c], epl, zero, r.psum, s == 0, s == r.S[c] - 1, ns, 1.0 / (double)r.psum,
+                     1.0 / (double)(r.psum >> epl));
 }
 
 // Peak bytes of the devices of stage s (ns layers) of class c: its state plus
@@ -415,7 +442,7 @@ __device__ __forceinline__ uint64_t class_stage_bytes(const CheckTab& ct, const 
                                                       uint32_t ns, uint64_t state) {
   // the micro-batch size: the header's (shared layout) or the class's (per-class layout, header field 0)
   const uint32_t mi = ((r.hdr >> 11) & 3) | cls_mi(r.chdr, c), S = r.S[c];
-  const uint32_t reps = r.cls[c] & 0xffff, M = ((r.cls[c] >> 16) + reps - 1) / reps;
+  const uint32_t reps = r.cls[c] & 0xffff, M = ceil_div16(r.cls[c] >> 16, reps);
   const uint32_t held = ((r.hdr >> 16) & 1) ? S : S - s;
   const uint32_t fly = held < M ? held : M;
   return state + (uint64_t)ns * fly * ct.act_layer[r.tpl[c]][mi];
@@ -440,7 +467,7 @@ __device__ __forceinline__ void il_device_layers(const Checked& r, uint32_t s, u
 __device__ __forceinline__ uint64_t il_stage_bytes(const CheckTab& ct, const Checked& r, uint32_t c, uint32_t s,
                                                    uint32_t nmax, uint64_t state) {
   const uint32_t mi = (r.hdr >> 11) & 3, S = r.S[c], v = r.v;
-  const uint32_t reps = r.cls[c] & 0xffff, M = ((r.cls[c] >> 16) + reps - 1) / reps;
+  const uint32_t reps = r.cls[c] & 0xffff, M = ceil_div16(r.cls[c] >> 16, reps);
   const uint32_t w = 2 * (S - 1 - s) + (v - 1) * S + 1;
   const uint32_t fly = w < M * v ? w : M * v;
   return state + (uint64_t)nmax * fly * ct.act_layer[r.tpl[c]][mi];
@@ -532,7 +559,7 @@ __global__ void __launch_bounds__(256) k_prep(Tab t, const Tab* __restrict__ dta
     for (uint32_t c = 0; c < 4; ++c) {
       m[c] = 0;
       if (ok && c < G) {
-        const uint32_t reps = r.cls[c] & 0xffff, M = ((r.cls[c] >> 16) + reps - 1) / reps;
+        const uint32_t reps = r.cls[c] & 0xffff, M = ceil_div16(r.cls[c] >> 16, reps);
         m[c] = r.S[c] | (G << 5) | (M << 8) | ((r.v - 1) << 24);
         Mmax = M > Mmax ? M : Mmax;
       }
@@ -578,17 +605,25 @@ __global__ void __launch_bounds__(256) k_prep(Tab t, const Tab* __restrict__ dta
   }
 }
 
-// Peak memory of every (class, stage) device of plan i (one plan per lane).
+// Peak memory of every (class, stage) device, one plan per lane.  A lane's 512
+// bytes of results are four rows of 128: each class's go through LDS, so that
+// the wavefront stores whole rows (one lane's stores, 512 bytes from its
+// neighbour's, would be a partial line each).
+constexpr uint32_t kMemRow = kMaxStages + 1;   // words per row in LDS
 template <bool kHet>
 __global__ void __launch_bounds__(256) k_memory(Tab t, const Tab* __restrict__ dtab, sim_plans pl, int64_t n, uint64_t* __restrict__ out) {
   __shared__ CheckTab ct;
+  __shared__ uint64_t rows[4][64 * kMemRow];
   load_check_tab(ct, dtab);
   __syncthreads();
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + 64 * wave;
+  if (first >= n) return;
+  const int64_t i = first + lane < n ? first + lane : n - 1;   // (lanes past the end repeat the last plan)
+  const uint32_t live = n - first < 64 ? (uint32_t)(n - first) : 64u;
   const Checked r = check_plan<kHet>(t, ct, pl, i);
   const uint32_t G = ((r.hdr >> 8) & 3) + 1;
-  uint64_t* o = out + i * (kMaxClasses * kMaxStages);
+  uint64_t* const row = &rows[wave][lane * kMemRow];
 #pragma unroll
   for (uint32_t c = 0; c < 4; ++c) {
     uint32_t prev = 0;
@@ -606,8 +641,15 @@ __global__ void __launch_bounds__(256) k_memory(Tab t, const Tab* __restrict__ d
           prev = cut;
         }
       }
-      o[c * kMaxStages + s] = v;
+      row[s] = v;
     }
+    wave_sync_lds();
+#pragma unroll
+    for (uint32_t q = 0; q < 16; ++q) {   // four rows at a time
+      const uint32_t a = 4 * q + (lane >> 4), s = lane & 15u;
+      if (a < live) out[(first + a) * (kMaxClasses * kMaxStages) + c * kMaxStages + s] = rows[wave][a * kMemRow + s];
+    }
+    wave_sync_lds();
   }
 }
 
@@ -1455,39 +1497,58 @@ struct ZbSink {
   }
 };
 
-template <int S, int v>
-__device__ __forceinline__ void il_records(const Tab& t, const Hot<2>& h, const Plan& p, uint64_t* o);
-
-// per (class, stage) quantities of every plan, in plan order; for an
-// interleaved pipeline per virtual stage (hops and syncs per device, in the
-// first S records, the last hop being the wrap hop)
+// Per (class, stage) quantities of every plan, in plan order: one (virtual)
+// stage per lane, so that the sixteen lanes of a pipeline store its records
+// side by side.  For an interleaved pipeline per virtual stage, hops and syncs
+// per device, in the first PP records, the last hop being the wrap hop.
 template <bool kHet>
 __global__ void __launch_bounds__(256) k_stages(Tab t, const PackedPlan* __restrict__ packed,
                                                 const uint4* __restrict__ pcut, const uint32_t* __restrict__ meta,
                                                 int64_t n, uint64_t* __restrict__ out_stage) {
-  const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (slot >= n * 4 || meta[slot] == 0) return;
+  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, slot = id / kMaxStages;
+  const uint32_t s = (uint32_t)(id % kMaxStages);
+  if (slot >= n * kMaxClasses) return;
+  const uint32_t m = meta[slot], S = m & 31, v = (m >> 24) + 1;
+  if (s >= S * v) return;   // (S = 0: no pipeline)
   const Plan p = load_plan<kHet>(packed, pcut, (uint32_t)slot);
   const Hot<2> h(t, nullptr);
-  if (!kHet && p.v > 1) {
-    uint64_t* o = out_stage + slot * (kMaxStages * kRecWords);
-    switch (il_shape(p.S, p.v)) {
-#define X(S_, V_)                        \
-  case il_shape(S_, V_):                   \
-    il_records<S_, V_>(t, h, p, o);      \
-    break;
-      HETSIM_IL_SHAPES(X)
-#undef X
-      default: break;
+  const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl), act = h.size().act[p.mi];
+  const uint32_t d = v > 1 ? s % S : s, lo = s ? cut_at(p, s - 1) : 0, hi = cut_at(p, s);   // device d, layers [lo, hi)
+  auto place = [&](uint32_t x) {
+    const uint32_t k = (uint32_t)(p.tc >> (4 * x)) & 15;
+    return stage_place<2>(t, h, p, k, dev_before_own<kHet>(p, x, k));
+  };
+  const StagePlace sp = place(d);
+  double fc, bc, wc;
+  stage_cost<2, kHet>(t, h, p, sp, act, lo, hi, s == 0, s == S * v - 1, fc, bc, wc);
+  double hop = 0;
+  uint64_t sync = 0;
+  if (s < S) {
+    if (s + 1 < S) hop = hop_ps(t, p, sp, place(s + 1), act, true);
+    else if (v > 1) hop = hop_ps(t, p, place(0), sp, act, false);   // to device 0, placed before it
+    if (kHet) {
+      uint4 rows[4];
+      load_rows(pcut + (slot & ~3ll), rows);
+      sync = het_stage_dp(t, h, p, rows, lo, hi, rp, rpe);
+    } else if (v > 1) {
+      uint32_t ns = 0;
+      for (uint32_t j = 0; j < v; ++j) ns += cut_at(p, j * S + s) - (j * S + s ? cut_at(p, j * S + s - 1) : 0);
+      sync = (uint64_t)stage_dp(t, h, p, s, ns, rp, rpe);
+    } else {
+      sync = stage_sync(t, h, p, s, lo, hi, rp, rpe);
     }
-    return;
   }
-  uint64_t rec[kMaxStages][kRecWords];
-  class_records<2, kHet>(t, h, p, kHet ? pcut + (slot & ~3ll) : nullptr, rec, nullptr);
-  uint64_t* o = out_stage + slot * (kMaxStages * kRecWords);
-  for (uint32_t s = 0; s < p.S; ++s)
-#pragma unroll
-    for (int q = 0; q < kRecWords; ++q) o[s * kRecWords + q] = rec[s][q];
+  ulonglong2* o = reinterpret_cast<ulonglong2*>(out_stage + (slot * kMaxStages + s) * kRecWords);
+  if (((uintptr_t)out_stage & 15) == 0) {
+    o[0] = make_ulonglong2((uint64_t)fc, (uint64_t)bc);
+    o[1] = make_ulonglong2((uint64_t)hop, sync);
+  } else {
+    uint64_t* q = out_stage + (slot * kMaxStages + s) * kRecWords;
+    q[0] = (uint64_t)fc;
+    q[1] = (uint64_t)bc;
+    q[2] = (uint64_t)hop;
+    q[3] = sync;
+  }
 }
 
 // Per-class layout: the syncs of every (class, stage) of every valid plan
@@ -1700,15 +1761,6 @@ __device__ __forceinline__ V chain_time(Chain<S, V>& h, const V (&w)[S], uint32_
 // the length of a path, at most T).  Otherwise the pipeline goes on the redo
 // list and k_redo_u64 evaluates it again in u64, outside the hot kernels.
 constexpr double kExact = 9007199254740992.0;
-
-// Order of LDS accesses within a wavefront: its lanes' accesses complete in
-// order; the fences keep the compiler from moving one lane's reads above other
-// lanes' writes.
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // ---------------------------------------------------------------- continuation lists
 // Offer a pipeline's chain with `left` steady iterations to run to list kList
@@ -2306,23 +2358,6 @@ __device__ __forceinline__ V il_time(const Tab& t, const Hot<kMode>& h, const Pl
   il_setup_own<S, v, kMode, V>(t, h, p, f, b, c);
   il_pipe<S, v, V, kJump>(f, b, c, class_mb(p), busy, skipped);
   return il_tail<S, v, kMode, V>(t, h, p, busy);
-}
-
-// Stage records of an interleaved pipeline: {forward, backward, hop, sync}
-// per virtual stage; hop and sync only in the first S records (per device).
-template <int S, int v>
-__device__ __forceinline__ void il_records(const Tab& t, const Hot<2>& h, const Plan& p, uint64_t* o) {
-  uint64_t f[S * v], b[S * v], c[S];
-  il_setup_own<S, v, 2, uint64_t>(t, h, p, f, b, c);
-  const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> p.epl);
-#pragma unroll
-  for (int vs = 0; vs < S * v; ++vs) {
-    o[vs * kRecWords + 0] = f[vs];
-    o[vs * kRecWords + 1] = b[vs];
-    o[vs * kRecWords + 2] = vs < S ? c[vs < S ? vs : 0] : 0;
-    o[vs * kRecWords + 3] =
-        vs < S ? (uint64_t)stage_dp(t, h, p, vs, il_device_ns<S, v>(p, vs < S ? vs : 0), rp, rpe) : 0;
-  }
 }
 
 // One plan-sorted interleaved pipeline.

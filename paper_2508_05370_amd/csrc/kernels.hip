@@ -450,8 +450,9 @@ hipError_t launch_plan_syncs(const Tab& t, const PackedPlan* packed, const uint4
 
 hipError_t launch_stages(const Tab& t, const PackedPlan* packed, const uint4* pcut, const uint32_t* meta, int64_t n,
                          uint64_t* out_stage, hipStream_t s) {
-  if (pcut) k_stages<true><<<blocks_for(n * 4, 256), 256, 0, s>>>(t, packed, pcut, meta, n, out_stage);
-  else k_stages<false><<<blocks_for(n * 4, 256), 256, 0, s>>>(t, packed, pcut, meta, n, out_stage);
+  const int g = blocks_for(n * kMaxClasses * kMaxStages, 256);
+  if (pcut) k_stages<true><<<g, 256, 0, s>>>(t, packed, pcut, meta, n, out_stage);
+  else k_stages<false><<<g, 256, 0, s>>>(t, packed, pcut, meta, n, out_stage);
   return hipGetLastError();
 }
 hipError_t launch_scan(const Work& w, bool grouped, hipStream_t s) {
