@@ -22,8 +22,7 @@ hipError_t launch_stages(const Tab& t, const PackedPlan* packed, const uint4* pc
 hipError_t launch_scan(const Work& w, bool grouped, hipStream_t s);
 hipError_t launch_scatter(const Work& w, uint32_t n, hipStream_t s);
 hipError_t launch_group(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s);
-hipError_t launch_variant(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s);
-hipError_t launch_il(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s);
+hipError_t launch_all(const Tab& t, const EvalBufs& e, uint32_t max_tiles, bool plain, hipStream_t s);
 hipError_t launch_rest(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s);
 hipError_t launch_argmin(const uint64_t* t, int64_t n, int64_t base, sim_best* b, hipStream_t s);
 hipError_t launch_best_reduce(const sim_best* in, int64_t n, sim_best* out, hipStream_t s);
@@ -259,6 +258,20 @@ static EvalBufs eval_bufs(const sim_ctx* c, const Work& W, uint64_t* out) {
 // Tiles of n plans at most: the pipelines' lanes, and a partly filled tile per group.
 static uint32_t max_tiles(int64_t n) { return (uint32_t)(n * kMaxClasses / 63 + kGroups + 1); }
 
+// Evaluate a sorted chunk of n plans on one stream.  Up to kSmallCall plans of
+// the shared layout k_all takes every kind in one launch, whose tiles run side
+// by side; above that the plain plans run in k_eval's four, with up to twice
+// the wavefronts per SIMD.
+constexpr int64_t kSmallCall = 1 << 15;
+static hipError_t eval_chunk(sim_ctx* c, const EvalBufs& a, int64_t n, hipStream_t s) {
+  const uint32_t tiles = max_tiles(n);
+  const bool small = !a.pcut && n <= kSmallCall;
+  hipError_t e = hipSuccess;
+  for (int g = 0; g < 4 && e == hipSuccess && !small; ++g) e = launch_group(c->tab, a, tiles, g, s);
+  if (e == hipSuccess) e = launch_all(c->tab, a, tiles, small, s);
+  return e;
+}
+
 // Chunks of kChunk plans (one chunk up to 2 kChunk).  With more than one chunk, the four stage-count
 // groups of chunk i's first pass run on two side streams (paired as
 // kGroupStream says), and its interleaved plans, continuation lists and redo
@@ -320,18 +333,19 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
     EventPair e0;
     bool t0 = e == hipSuccess && begin_event(c, 0, s, &e0);
     if (nbuf == 1) {
-      for (int g = 0; g < 4 && e == hipSuccess; ++g) e = launch_group(c->tab, a, tiles, g, s);
-      for (int g = 0; g < 4 && e == hipSuccess; ++g) e = launch_variant(c->tab, a, tiles, g, s);
+      if (e == hipSuccess) e = eval_chunk(c, a, cn, s);
       if (t0) end_event(c, 0, s, &e0);
       if (e != hipSuccess) break;
     } else {
       if (e == hipSuccess) e = hipEventRecord(sorted(b), s);
       joined = false;
+      // the other kinds need the sort only
+      if (e == hipSuccess) e = hipStreamWaitEvent(aux, sorted(b), 0);
+      if (e == hipSuccess) e = launch_all(c->tab, a, tiles, false, aux);
       for (int g = 0; g < 4 && e == hipSuccess; ++g) {
         const hipStream_t gs = side.grp[kGroupStream[g]];
         e = hipStreamWaitEvent(gs, sorted(b), 0);
         if (e == hipSuccess) e = launch_group(c->tab, a, tiles, g, gs);
-        if (e == hipSuccess) e = launch_variant(c->tab, a, tiles, g, gs);
         if (e == hipSuccess) e = hipEventRecord(fin(b, g), gs);
         if (e == hipSuccess) e = hipStreamWaitEvent(aux, fin(b, g), 0);
       }
@@ -339,8 +353,7 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
       if (e != hipSuccess) break;
     }
     bool t3 = begin_event(c, 3, aux, &ev);
-    e = launch_il(c->tab, a, tiles, aux);
-    if (e == hipSuccess) e = launch_rest(c->tab, a, tiles, aux);
+    e = launch_rest(c->tab, a, tiles, aux);
     if (t3) end_event(c, 3, aux, &ev);
     if (nbuf == 2) {
       const hipError_t r = hipEventRecord(done(b), aux);
@@ -386,11 +399,8 @@ extern "C" int sim_eval_plans_noalloc(sim_ctx* c, const sim_plans* plans, int64_
   const Work W = carve(ws, n, het, kContPerPlanNoAlloc);
   hipError_t e = order_chunk(c, W, *plans, n, out, false, s);
   const EvalBufs a = eval_bufs(c, W, out);
-  const uint32_t tiles = max_tiles(n);
-  for (int g = 0; g < 4 && e == hipSuccess; ++g) e = launch_group(c->tab, a, tiles, g, s);
-  for (int g = 0; g < 4 && e == hipSuccess; ++g) e = launch_variant(c->tab, a, tiles, g, s);
-  if (e == hipSuccess) e = launch_il(c->tab, a, tiles, s);
-  if (e == hipSuccess) e = launch_rest(c->tab, a, tiles, s);
+  if (e == hipSuccess) e = eval_chunk(c, a, n, s);
+  if (e == hipSuccess) e = launch_rest(c->tab, a, max_tiles(n), s);
   // a stream under graph capture records nothing here: the launches become
   // graph nodes, and the caller owns the graph's completion
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

@@ -1613,6 +1613,14 @@ typedef uint64_t StageRec[kMaxStages][kRecWords];
 __device__ __forceinline__ double vmax(double a, double b) { return __builtin_fmax(a, b); }
 __device__ __forceinline__ uint64_t vmax(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
+// Steady iterations k_cont gives a pipeline before it moves to the second
+// list, and how many must be left for a pipeline to go on elsewhere (k_power
+// needs 16 minus the stage count).
+constexpr int kContBudget = 48, kPowerMin = 16;
+// With so few entries in the first list k_cont leaves them to k_power: their
+// tiles would not fill the chip, and a tile takes 15-60 us, an entry 6.
+constexpr uint32_t kContFew = 4096;
+
 // A wavefront of the first pass waits this many steady iterations for its
 // lanes, then the aperiodic ones leave for the continuation lists.  Most
 // schedules are periodic after a few iterations, later with more stages; at
@@ -1805,10 +1813,6 @@ __device__ __forceinline__ void raise_time(const EvalBufs& e, uint32_t slot, dou
   else e.ovf[atomicAdd(&e.ctr[0], 1u)] = slot;
 }
 
-// Steady iterations k_cont gives a pipeline before it moves to the second
-// list, and how many must be left then.
-constexpr int kContBudget = 48, kPowerMin = 32;
-
 // Schedules that are not periodic after a few iterations mostly drift, often
 // with a period of two iterations: each stage advances at its own rate, and a
 // queue between two of them fills or drains until the order of a max changes.
@@ -1930,7 +1934,7 @@ __device__ __forceinline__ void cont_one(const EvalBufs& e, const double* tile) 
 #pragma unroll
   for (int s = 0; s < S; ++s) h.e[s] = tile[64 * (3 * S + s)];
   // out of budget: the second list, or the rest here if little is left or the list is full
-  if (left >= kPowerMin && cont_push<S, 2>(e, h, left, slot)) {
+  if (left >= 2 * kPowerMin && cont_push<S, 2>(e, h, left, slot)) {
     count_skipped(e, S, skipped);
     return;
   }
@@ -1948,11 +1952,11 @@ struct ContIndex {
   static constexpr int kHalves = kList == 1 ? 2 : 1;
   static constexpr uint32_t kPerList = kList == 1 ? kContSubs : 1;
   static_assert(kMaxStages * kPerList <= 64 * kHalves, "a lane per part");
-  uint32_t n[64 * kHalves], incl[64 * kHalves];   // in LDS
+  uint32_t n[64 * kHalves], incl[64 * kHalves], entries;   // in LDS
   __device__ __forceinline__ void fill(const EvalBufs& e) {
     if (threadIdx.x < 64) {
       const uint32_t lane = threadIdx.x;
-      uint32_t run = 0;
+      uint32_t run = 0, sum = 0;
 #pragma unroll
       for (int h = 0; h < kHalves; ++h) {
         const uint32_t x = 64 * h + lane, j = x / kPerList, sub = x % kPerList;
@@ -1960,6 +1964,7 @@ struct ContIndex {
         const uint32_t cap = on ? e.cinfo[(kList == 1 ? 16 : 48) + j] * 64u : 0;
         const uint32_t c = on ? e.ctr[kList == 1 ? cont1_ctr(j, sub) : cont2_ctr(j)] : 0;
         n[x] = c < cap ? c : cap;
+        sum += n[x];
         uint32_t y = (n[x] + kPer - 1) / kPer;
 #pragma unroll
         for (uint32_t o = 1; o < 64; o <<= 1) {
@@ -1969,6 +1974,9 @@ struct ContIndex {
         incl[x] = run + y;
         run = __shfl(run + y, 63);
       }
+#pragma unroll
+      for (uint32_t o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+      entries = sum;
     }
     __syncthreads();
   }
@@ -2156,7 +2164,7 @@ __device__ __forceinline__ void eval_one(const Tab& t, const Hot<kMode>& h, cons
   while (true) {
     chain_jump<S, double>(ch, left, budget, skipped);
     if (left <= 0) break;
-    if (cont_push<S, 1>(e, ch, left, slot)) {
+    if (left >= kPowerMin && cont_push<S, 1>(e, ch, left, slot)) {
       done = false;
       break;
     }
@@ -2459,13 +2467,13 @@ __global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(const T
   }
 }
 
-// Overlap and zero-bubble plans of the four stage counts of group GRP (as
-// k_eval's groups), and with two-level collectives, whose sync code k_eval
-// lacks, the plain ones too.  The Tab is read from its copy in device memory:
-// this kernel holds every kind's code, and with the Tab as a by-value argument
-// the compiler copied the whole argument block to private memory in every
-// wave.  A block with no tile returns before touching LDS, so a launch over
-// empty lists costs next to nothing.
+// Plans of every kind and stage count in one kernel: the overlap, zero-bubble
+// and interleaved ones of every call, and with two-level collectives (whose
+// sync code k_eval lacks) or in a small call also the plain ones.  One launch,
+// where one per kind and stage-count group costs 4-5 us each even if it has
+// nothing to do; the kinds' registers (200-270) allow two wavefronts per SIMD
+// whatever the stage count, so nothing is lost by their sharing a kernel.  Tiles
+// from `first` on.
 template <int S, int kMode>
 __device__ __forceinline__ void eval_kind(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t kind,
                                           uint32_t slot, const WaveLds& w) {
@@ -2473,59 +2481,43 @@ __device__ __forceinline__ void eval_kind(const Tab& t, const Hot<kMode>& h, con
   else if (kind == 1) eval_one<S, kMode, false, 1, true>(t, h, e, slot, w.col, w.cnt);
   else eval_one<S, kMode, false, 0, true>(t, h, e, slot, w.col, w.cnt);
 }
-template <int GRP, int kMode>
-__global__ void __launch_bounds__(kEvalThreads) k_variant(const Tab* __restrict__ tp, EvalBufs e) {
-  constexpr int kTop = kMaxStages - 4 * GRP;   // stage counts kTop-3 .. kTop
-  constexpr uint32_t g0 = 16 * GRP, kStep = kMaxStages * kMaxClasses;
-  const Tab& t = *tp;
-  const uint32_t n0 = t.ccl_hier ? fixed_word(e.tstart, g0 + 16) - fixed_word(e.tstart, g0) : 0;
-  const uint32_t n1 = n0 + fixed_word(e.tstart, kStep + g0 + 16) - fixed_word(e.tstart, kStep + g0);
-  const uint32_t tiles = n1 + fixed_word(e.tstart, 2 * kStep + g0 + 16) - fixed_word(e.tstart, 2 * kStep + g0);
-  if (blockIdx.x * (kEvalThreads / 64) >= tiles) return;   // the whole block, before any barrier
-  extern __shared__ uint4 lds[];
-  fill_lds<kMode>(t, lds);
-  const Hot<kMode> h(t, lds);
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const WaveLds wl(t, lds, kMode < 2 ? t.lds_bytes : 0, plan_cols(GRP, true), wave);
-  for (uint32_t w = blockIdx.x * (kEvalThreads / 64) + wave; w < tiles; w += gridDim.x * (kEvalThreads / 64)) {
-    const uint32_t kind = w < n0 ? 0 : w < n1 ? 1 : 2, first = kind * kStep + g0;
-    const uint32_t q = fixed_word(e.tstart, first) + (w - (kind == 0 ? 0 : kind == 1 ? n0 : n1));
-    const uint32_t g = tile_group(e, q, first, 16), S = kTop - (g - first) / kMaxClasses;
-    uint32_t slot;
-    if (!tile_slot<false>(e, q, g, slot)) continue;
-    if (S == kTop) eval_kind<kTop, kMode>(t, h, e, kind, slot, wl);
-    else if (S == kTop - 1) eval_kind<kTop - 1, kMode>(t, h, e, kind, slot, wl);
-    else if (S == kTop - 2) eval_kind<kTop - 2, kMode>(t, h, e, kind, slot, wl);
-    else eval_kind<kTop - 3, kMode>(t, h, e, kind, slot, wl);
-  }
-}
-
-// Interleaved plans: tiles of one shape (S, v) and class count.  (The Tab: as
-// k_variant's.)
 template <int kMode>
-__global__ void __launch_bounds__(kEvalThreads) k_il(const Tab* __restrict__ tp, EvalBufs e) {
+__global__ void __launch_bounds__(kEvalThreads, 2) k_all(const Tab* __restrict__ tp, EvalBufs e, uint32_t plain) {
   const Tab& t = *tp;
-  const uint32_t lo = fixed_word(e.tstart, kPlainGroups), hi = fixed_word(e.tstart, kGroups);
+  const uint32_t lo = plain ? 0 : fixed_word(e.tstart, kMaxStages * kMaxClasses), hi = fixed_word(e.tstart, kGroups);
   if (lo + blockIdx.x * (kEvalThreads / 64) >= hi) return;   // the whole block, before any barrier
   extern __shared__ uint4 lds[];
   fill_lds<kMode>(t, lds);
   const Hot<kMode> h(t, lds);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const WaveLds wl(t, lds, kMode < 2 ? t.lds_bytes : 0, kIlCols, wave);
-  double* const xw = wl.col;
-  uint32_t* const cw = wl.cnt;
+  const WaveLds w(t, lds, kMode < 2 ? t.lds_bytes : 0, plan_cols(0, true), wave);
   for (uint32_t q = lo + blockIdx.x * (kEvalThreads / 64) + wave; q < hi; q += gridDim.x * (kEvalThreads / 64)) {
-    const uint32_t g = tile_group(e, q, kPlainGroups, kGroups - kPlainGroups);
+    uint32_t g = 0;   // the last group that starts at or before tile q
+    for (uint32_t step = 128; step > 0; step >>= 1)
+      if (g + step < kGroups && fixed_word(e.tstart, g + step) <= q) g += step;
     uint32_t slot;
     if (!tile_slot<false>(e, q, g, slot)) continue;
-    switch ((g - kPlainGroups) / kMaxClasses) {
-#define X(S_, V_)                          \
-  case il_shape(S_, V_):                   \
-    eval_il<S_, V_, kMode>(t, h, e, slot, xw, cw); \
+    if (g >= kPlainGroups) {
+      switch ((g - kPlainGroups) / kMaxClasses) {
+#define X(S_, V_)                                        \
+  case il_shape(S_, V_):                                 \
+    eval_il<S_, V_, kMode>(t, h, e, slot, w.col, w.cnt); \
     break;
-      HETSIM_IL_SHAPES(X)
+        HETSIM_IL_SHAPES(X)
 #undef X
-      default: break;
+        default: break;
+      }
+    } else {
+      const uint32_t kind = g / (kMaxStages * kMaxClasses);
+      switch (kMaxStages - g / kMaxClasses % kMaxStages) {
+#define X(S_)                                        \
+  case S_:                                           \
+    eval_kind<S_, kMode>(t, h, e, kind, slot, w);    \
+    break;
+        X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+#undef X
+        default: break;
+      }
     }
   }
 }

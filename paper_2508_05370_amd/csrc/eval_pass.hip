@@ -1,16 +1,14 @@
 // eval_pass.hip -- one evaluation pass of one variant: table mode HETSIM_MODE
 // (0..2), plan layout HETSIM_HET (0 shared, 1 per class), pass HETSIM_PASS
-// (0 the first pass's k_eval groups, 1 the interleaved pass, 2 the variant
-// pass of overlap and zero-bubble pipelines; the last two shared layout only).
-// The build compiles this file once per variant; kernels.hip dispatches at run
-// time.
+// (0 the first pass's k_eval groups, 1 k_all, shared layout only).  The build
+// compiles this file once per variant; kernels.hip dispatches at run time.
 #include "launch.h"
 
 #if !defined(HETSIM_MODE) || !defined(HETSIM_HET) || !defined(HETSIM_PASS)
 #error "eval_pass.hip is built once per variant: define HETSIM_MODE, HETSIM_HET and HETSIM_PASS"
 #endif
 #if HETSIM_PASS != 0 && HETSIM_HET
-#error "the interleaved and variant passes are built for the shared layout only"
+#error "k_all is built for the shared layout only"
 #endif
 
 namespace hetsim {
@@ -39,7 +37,7 @@ template hipError_t launch_group_v<HETSIM_MODE, (bool)HETSIM_HET>(const Tab&, co
 // Grid caps come from the shared-layout kernels; the per-class-layout ones
 // take the same caps (their fixed-stride loops cover any grid).
 template <int kMode>
-hipError_t occupancy_first_v(int nb[4], size_t lds, uint32_t types) {
+hipError_t occupancy_v(int nb[4], size_t lds, uint32_t types) {
   const void* k[4] = {(const void*)k_eval<0, kMode, false>, (const void*)k_eval<1, kMode, false>,
                       (const void*)k_eval<2, kMode, false>, (const void*)k_eval<3, kMode, false>};
   for (int i = 0; i < 4; ++i) {
@@ -49,50 +47,24 @@ hipError_t occupancy_first_v(int nb[4], size_t lds, uint32_t types) {
   }
   return hipSuccess;
 }
-template hipError_t occupancy_first_v<HETSIM_MODE>(int[4], size_t, uint32_t);
+template hipError_t occupancy_v<HETSIM_MODE>(int[4], size_t, uint32_t);
 #endif
-
-#elif HETSIM_PASS == 2
-template <int kMode>
-hipError_t launch_variant_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s) {
-  const uint32_t grid = tile_grid(max_tiles, t.grid_variant[g]);
-  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) + block_lds_bytes(plan_cols(g, true), t.K);
-  if (g == 0) k_variant<0, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
-  else if (g == 1) k_variant<1, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
-  else if (g == 2) k_variant<2, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
-  else k_variant<3, kMode><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
-  return hipGetLastError();
-}
-template hipError_t launch_variant_v<HETSIM_MODE>(const Tab&, const EvalBufs&, uint32_t, int, hipStream_t);
-
-template <int kMode>
-hipError_t occupancy_variant_v(int nb[4], size_t lds, uint32_t types) {
-  const void* k[4] = {(const void*)k_variant<0, kMode>, (const void*)k_variant<1, kMode>,
-                      (const void*)k_variant<2, kMode>, (const void*)k_variant<3, kMode>};
-  for (int i = 0; i < 4; ++i) {
-    const size_t b = lds + block_lds_bytes(plan_cols(i, true), types);
-    hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[i], k[i], kEvalThreads, b);
-    if (r != hipSuccess) return r;
-  }
-  return hipSuccess;
-}
-template hipError_t occupancy_variant_v<HETSIM_MODE>(int[4], size_t, uint32_t);
 
 #else
 template <int kMode>
-hipError_t launch_il_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s) {
-  k_il<kMode><<<tile_grid(max_tiles, t.grid_il), kEvalThreads,
-                (kMode < 2 ? t.lds_bytes : 0) + block_lds_bytes(kIlCols, t.K), s>>>(e.dtab, e);
+hipError_t launch_all_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, bool plain, hipStream_t s) {
+  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) + block_lds_bytes(plan_cols(0, true), t.K);
+  k_all<kMode><<<tile_grid(max_tiles, t.grid_all), kEvalThreads, lds, s>>>(e.dtab, e, plain ? 1u : 0u);
   return hipGetLastError();
 }
-template hipError_t launch_il_v<HETSIM_MODE>(const Tab&, const EvalBufs&, uint32_t, hipStream_t);
+template hipError_t launch_all_v<HETSIM_MODE>(const Tab&, const EvalBufs&, uint32_t, bool, hipStream_t);
 
 template <int kMode>
-hipError_t occupancy_il_v(int nb[1], size_t lds, uint32_t types) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[0], (const void*)k_il<kMode>, kEvalThreads,
-                                                      lds + block_lds_bytes(kIlCols, types));
+hipError_t occupancy_all_v(int nb[1], size_t lds, uint32_t types) {
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb[0], (const void*)k_all<kMode>, kEvalThreads,
+                                                      lds + block_lds_bytes(plan_cols(0, true), types));
 }
-template hipError_t occupancy_il_v<HETSIM_MODE>(int[1], size_t, uint32_t);
+template hipError_t occupancy_all_v<HETSIM_MODE>(int[1], size_t, uint32_t);
 #endif
 
 }  // namespace hetsim

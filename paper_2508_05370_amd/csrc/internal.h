@@ -31,14 +31,12 @@ constexpr uint32_t kGroups = kPlainGroups + kIlShapes * kMaxClasses;
 constexpr uint32_t kBuckets = kGroups * kBucketsM;
 __host__ __device__ constexpr uint32_t plans_per_tile(uint32_t G) { return G == 3 ? 21 : 64 / G; }
 // LDS of the passes over plan-sorted pipelines: per wavefront one column of 64
-// doubles per stage (up to the kernel's largest stage count, and in the
-// variant pass two more for the embedding's and the head's buckets of an
-// overlapped sync; a column per device in the interleaved pass), and one
-// column of 64 counters per device type.
-__host__ __device__ constexpr uint32_t plan_cols(int group, bool variant) {
-  return (uint32_t)(kMaxStages - 4 * group) + (variant ? 2u : 0u);
+// doubles per stage (up to the kernel's largest stage count, and where
+// overlapped plans run two more for the embedding's and the head's buckets),
+// and one column of 64 counters per device type.
+__host__ __device__ constexpr uint32_t plan_cols(int group, bool overlap) {
+  return (uint32_t)(kMaxStages - 4 * group) + (overlap ? 2u : 0u);
 }
-constexpr uint32_t kIlCols = 8;
 __host__ __device__ constexpr uint32_t wave_lds_bytes(uint32_t cols, uint32_t types) {
   return cols ? cols * 64 * 8 + types * 64 * 4 : 0;
 }
@@ -140,9 +138,8 @@ struct Tab : CheckTab {
   uint32_t mode;
   const void* img;                // the image in device memory (16-byte aligned)
   uint32_t grid_eval[4];          // blocks of each first-pass kernel that fit the device at once
-  uint32_t grid_il;               // blocks of the interleaved kernel that fit the device at once
+  uint32_t grid_all;              // blocks of k_all that fit the device at once
   uint32_t grid_cont;             // blocks of the continuation kernels that fit the device at once
-  uint32_t grid_variant[4];       // blocks of each variant-pass kernel that fit the device at once
 };
 
 // Continuation lists.  A pipeline whose schedule is still aperiodic after the

@@ -236,6 +236,7 @@ __global__ void __launch_bounds__(256) k_plan_scatter(const uint4* __restrict__ 
 __global__ void __launch_bounds__(256, 2) k_cont(EvalBufs e) {
   __shared__ ContIndex<1, 64> ix;
   ix.fill(e);
+  if (ix.entries <= kContFew) return;   // k_power's
   const uint32_t lane = threadIdx.x & 63u, waves = gridDim.x * (blockDim.x >> 6);
   uint32_t S, at, count, first;
   for (uint32_t q = blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -252,7 +253,8 @@ __global__ void __launch_bounds__(256, 2) k_cont(EvalBufs e) {
   }
 }
 
-// The second list: one pipeline per wavefront.  A steady iteration is a
+// The second list, and the first one when it is short: one pipeline per
+// wavefront.  A steady iteration is a
 // max-plus linear map of the state; its matrix is squared, and applied to the
 // state at the set bits of the number of iterations left, so a pipeline takes
 // log2(left) steps however its schedule behaves.  Every entry is the weight of
@@ -272,9 +274,13 @@ __global__ void __launch_bounds__(256) k_power(EvalBufs e) {
   const uint32_t j = lane & 15u, g = lane >> 4, waves = gridDim.x * 4;
   double* const v = vec[wave];
   __shared__ ContIndex<2, 1> ix;
+  __shared__ ContIndex<1, 1> ix1;
   ix.fill(e);
+  ix1.fill(e);
+  const uint32_t n1 = ix1.entries <= kContFew ? ix1.entries : 0;
   uint32_t S, at, count, first;
-  for (uint32_t q = blockIdx.x * 4 + wave; ix.find(e, q, S, at, count, first); q += waves) {
+  for (uint32_t q = blockIdx.x * 4 + wave;
+       q < n1 ? ix1.find(e, q, S, at, count, first) : ix.find(e, q - n1, S, at, count, first); q += waves) {
     const double* p = e.cont + (size_t)first * (kContUnit / 8) + (size_t)(at >> 6) * (256 * S) + (at & 63u);
     const uint2 ls = *(const uint2*)&p[64 * (3 * S - 1)];
     uint32_t left = ls.x - (N - S);
@@ -389,6 +395,35 @@ __global__ void k_best_fix(sim_best* b) {
   if (b->time_ps == kInvalid) b->index = -1;
 }
 
+// The whole reduction by one block: up to kMinSmall times it takes 5-10 us,
+// the four kernels above 17 us and more whatever the size.
+constexpr int64_t kMinSmall = 1 << 16;
+__global__ void __launch_bounds__(1024) k_min_small(const uint64_t* __restrict__ t, uint32_t n, int64_t base,
+                                                    sim_best* b) {
+  __shared__ uint64_t tpart[16], ipart[16];
+  uint64_t bt = kInvalid, bi = kInvalid;
+  for (uint32_t i = threadIdx.x; i < n; i += 1024) {   // (a later index never beats an equal time)
+    const uint64_t v = t[i];
+    if (v < bt) {
+      bt = v;
+      bi = i;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint64_t t2 = __shfl_xor(bt, o), i2 = __shfl_xor(bi, o);
+    if (t2 < bt || (t2 == bt && i2 < bi)) { bt = t2; bi = i2; }
+  }
+  if ((threadIdx.x & 63) == 0) { tpart[threadIdx.x >> 6] = bt; ipart[threadIdx.x >> 6] = bi; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w)
+      if (tpart[w] < bt || (tpart[w] == bt && ipart[w] < bi)) { bt = tpart[w]; bi = ipart[w]; }
+    b->time_ps = bt;
+    b->index = bt == kInvalid ? -1 : base + (int64_t)bi;
+  }
+}
+
 __global__ void __launch_bounds__(256) k_best_reduce(const sim_best* __restrict__ in, int64_t n, sim_best* out) {
   __shared__ uint64_t tpart[4], ipart[4];
   uint64_t bt = kInvalid, bi = kInvalid;
@@ -498,32 +533,26 @@ int eval_grids(Tab* t) {
   if (r == hipSuccess) r = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (r != hipSuccess) return (int)r;
   const size_t lds = t->mode < 2 ? t->lds_bytes : 0;
-  int nb[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  if (t->mode == 0) r = occupancy_first_v<0>(nb, lds, t->K);
-  else if (t->mode == 1) r = occupancy_first_v<1>(nb, lds, t->K);
-  else r = occupancy_first_v<2>(nb, lds, t->K);
+  int nb[6] = {0, 0, 0, 0, 0, 0};
+  if (t->mode == 0) r = occupancy_v<0>(nb, lds, t->K);
+  else if (t->mode == 1) r = occupancy_v<1>(nb, lds, t->K);
+  else r = occupancy_v<2>(nb, lds, t->K);
   if (r == hipSuccess) {
-    if (t->mode == 0) r = occupancy_il_v<0>(nb + 4, lds, t->K);
-    else if (t->mode == 1) r = occupancy_il_v<1>(nb + 4, lds, t->K);
-    else r = occupancy_il_v<2>(nb + 4, lds, t->K);
+    if (t->mode == 0) r = occupancy_all_v<0>(nb + 4, lds, t->K);
+    else if (t->mode == 1) r = occupancy_all_v<1>(nb + 4, lds, t->K);
+    else r = occupancy_all_v<2>(nb + 4, lds, t->K);
   }
   if (r == hipSuccess)
-    r = hipOccupancyMaxActiveBlocksPerMultiprocessor(nb + 9, (const void*)k_cont, 256, 0);
-  if (r == hipSuccess) {
-    if (t->mode == 0) r = occupancy_variant_v<0>(nb + 5, lds, t->K);
-    else if (t->mode == 1) r = occupancy_variant_v<1>(nb + 5, lds, t->K);
-    else r = occupancy_variant_v<2>(nb + 5, lds, t->K);
-  }
+    r = hipOccupancyMaxActiveBlocksPerMultiprocessor(nb + 5, (const void*)k_cont, 256, 0);
   if (r != hipSuccess) return (int)r;
   for (int i = 0; i < 4; ++i) t->grid_eval[i] = (uint32_t)((nb[i] > 0 ? nb[i] : 1) * cus);
-  t->grid_il = (uint32_t)((nb[4] > 0 ? nb[4] : 1) * cus);
-  t->grid_cont = (uint32_t)((nb[9] > 0 ? nb[9] : 1) * cus);
-  for (int i = 0; i < 4; ++i) t->grid_variant[i] = (uint32_t)((nb[5 + i] > 0 ? nb[5 + i] : 1) * cus);
+  t->grid_all = (uint32_t)((nb[4] > 0 ? nb[4] : 1) * cus);
+  t->grid_cont = (uint32_t)((nb[5] > 0 ? nb[5] : 1) * cus);
   return 0;
 }
 
 // first pass of one stage-count group (g = 0..3) over a chunk (with two-level
-// collectives the shared layout's plans are all the variant pass's)
+// collectives the shared layout's plans are all k_all's)
 hipError_t launch_group(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s) {
   const bool het = e.pcut != nullptr;
   if (!het && t.ccl_hier) return hipSuccess;
@@ -532,23 +561,16 @@ hipError_t launch_group(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int
   return het ? launch_group_v<2, true>(t, e, max_tiles, g, s) : launch_group_v<2, false>(t, e, max_tiles, g, s);
 }
 
-// variant pass of one stage-count group (none with the per-class layout)
-hipError_t launch_variant(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s) {
+// the plans k_eval does not take, and in a small call all of them (none with
+// the per-class layout)
+hipError_t launch_all(const Tab& t, const EvalBufs& e, uint32_t max_tiles, bool plain, hipStream_t s) {
   if (e.pcut) return hipSuccess;
-  if (t.mode == 0) return launch_variant_v<0>(t, e, max_tiles, g, s);
-  if (t.mode == 1) return launch_variant_v<1>(t, e, max_tiles, g, s);
-  return launch_variant_v<2>(t, e, max_tiles, g, s);
+  if (t.mode == 0) return launch_all_v<0>(t, e, max_tiles, plain || t.ccl_hier, s);
+  if (t.mode == 1) return launch_all_v<1>(t, e, max_tiles, plain || t.ccl_hier, s);
+  return launch_all_v<2>(t, e, max_tiles, plain || t.ccl_hier, s);
 }
 
-// the interleaved plans (none with the per-class layout)
-hipError_t launch_il(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s) {
-  if (e.pcut) return hipSuccess;
-  if (t.mode == 0) return launch_il_v<0>(t, e, max_tiles, s);
-  if (t.mode == 1) return launch_il_v<1>(t, e, max_tiles, s);
-  return launch_il_v<2>(t, e, max_tiles, s);
-}
-
-// after the first and variant passes: the continuation lists, and the u64
+// after the first passes: the continuation lists, and the u64
 // redo of the overflowed pipelines
 hipError_t launch_rest(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s) {
   const uint32_t need = (max_tiles + 3) / 4, grid = need < 1 ? 1 : need < t.grid_cont ? need : t.grid_cont;
@@ -560,13 +582,15 @@ hipError_t launch_rest(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipS
 }
 
 hipError_t launch_argmin(const uint64_t* t, int64_t n, int64_t base, sim_best* b, hipStream_t s) {
+  if (n <= kMinSmall) {
+    k_min_small<<<1, 1024, 0, s>>>(t, (uint32_t)n, base, b);
+    return hipGetLastError();
+  }
   int g = blocks_for(n, 256 * 8);
   g = g < 1 ? 1 : (g > 2048 ? 2048 : g);
   k_best_init<<<1, 1, 0, s>>>(b);
-  if (n > 0) {
-    k_min_time<<<g, 256, 0, s>>>(t, n, b);
-    k_min_index<<<g, 256, 0, s>>>(t, n, base, b);
-  }
+  k_min_time<<<g, 256, 0, s>>>(t, n, b);
+  k_min_index<<<g, 256, 0, s>>>(t, n, base, b);
   k_best_fix<<<1, 1, 0, s>>>(b);
   return hipGetLastError();
 }

@@ -1,8 +1,7 @@
-// launch.h -- host-side launchers of the evaluation kernels.  The first,
-// interleaved and variant passes of each (table mode, plan layout) pair are
-// compiled in translation units of their own (eval_pass.hip built once per
-// variant), so that the library builds in parallel; kernels.hip dispatches to
-// them.
+// launch.h -- host-side launchers of the evaluation kernels.  The first pass of
+// each (table mode, plan layout) pair and k_all of each table mode are compiled
+// in translation units of their own (eval_pass.hip built once per variant), so
+// that the library builds in parallel; kernels.hip dispatches to them.
 #pragma once
 #include "device.h"
 
@@ -12,30 +11,22 @@ namespace hetsim {
 // at most max_tiles tiles.
 template <int kMode, bool kHet>
 hipError_t launch_group_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s);
-// Interleaved plans, and stage-count group g of the overlap and zero-bubble
-// plans (shared layout).
+// The plans of every other kind, and with `plain` all of them (shared layout).
 template <int kMode>
-hipError_t launch_il_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, hipStream_t s);
+hipError_t launch_all_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, bool plain, hipStream_t s);
+// Blocks per CU of the shared-layout first-pass kernels (nb[0..3]) or of k_all
+// (nb[0]) with `lds` bytes of table image and `types` device types.
 template <int kMode>
-hipError_t launch_variant_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s);
-// Blocks per CU of the shared-layout first-pass kernels, the variant kernels
-// (nb[0..3]) or the interleaved kernel (nb[0]) with `lds` bytes of table image
-// and `types` device types.
+hipError_t occupancy_v(int nb[4], size_t lds, uint32_t types);
 template <int kMode>
-hipError_t occupancy_first_v(int nb[4], size_t lds, uint32_t types);
-template <int kMode>
-hipError_t occupancy_variant_v(int nb[4], size_t lds, uint32_t types);
-template <int kMode>
-hipError_t occupancy_il_v(int nb[1], size_t lds, uint32_t types);
+hipError_t occupancy_all_v(int nb[1], size_t lds, uint32_t types);
 
-#define HETSIM_EXTERN_MODE(M)                                                                                  \
+#define HETSIM_EXTERN_MODE(M)                                                                                   \
   extern template hipError_t launch_group_v<M, false>(const Tab&, const EvalBufs&, uint32_t, int, hipStream_t); \
   extern template hipError_t launch_group_v<M, true>(const Tab&, const EvalBufs&, uint32_t, int, hipStream_t);  \
-  extern template hipError_t launch_il_v<M>(const Tab&, const EvalBufs&, uint32_t, hipStream_t);                \
-  extern template hipError_t launch_variant_v<M>(const Tab&, const EvalBufs&, uint32_t, int, hipStream_t);      \
-  extern template hipError_t occupancy_first_v<M>(int[4], size_t, uint32_t);                                   \
-  extern template hipError_t occupancy_variant_v<M>(int[4], size_t, uint32_t);                                           \
-  extern template hipError_t occupancy_il_v<M>(int[1], size_t, uint32_t);
+  extern template hipError_t launch_all_v<M>(const Tab&, const EvalBufs&, uint32_t, bool, hipStream_t);         \
+  extern template hipError_t occupancy_v<M>(int[4], size_t, uint32_t);                                          \
+  extern template hipError_t occupancy_all_v<M>(int[1], size_t, uint32_t);
 HETSIM_EXTERN_MODE(0)
 HETSIM_EXTERN_MODE(1)
 HETSIM_EXTERN_MODE(2)
