@@ -1129,17 +1129,40 @@ __device__ __forceinline__ uint32_t row_cut(const uint4 (&rows)[4], uint32_t c, 
   return (uint32_t)(((lo & ~m) | (hi & m)) >> (8 * (s & 7))) & 0xff;
 }
 
+// Per-class layout: where class c's stages of type k start in their pool (each
+// class's blocks are contiguous from a multiple of its TP degree on), for
+// classes 0 .. last, handed to put(c, k, first device).
+template <typename Put>
+__device__ __forceinline__ void class_starts(const Tab& t, const Plan& p, uint32_t last, Put put) {
+  for (uint32_t k = 0; k < t.K; ++k) {
+    uint32_t ptr = 0;
+#pragma unroll
+    for (uint32_t c = 0; c < 4; ++c) {
+      const uint32_t tl = cls_tpl(p.chdr, c), first = align_up(ptr, tl);
+      if (c <= last) put(c, k, first);
+      const uint32_t n = c < p.G ? count_type(p.tv[c], k, stage_sel(cls_S(p.chdr, c))) : 0;
+      ptr = n ? first + ((p.reps[c] * n) << tl) : ptr;
+    }
+  }
+}
+// The next devices from a lane's counter in LDS.
+__device__ __forceinline__ uint32_t draw(uint32_t* counter, uint32_t devices) {
+  return __hip_atomic_fetch_add(counter, devices, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
 // Per-class layout: the sync each (class, stage) of a valid plan waits for
 // -- the same values as het_stage_dp -- found by one walk over the segments
 // of the whole model.  Each class's stage holding the current segment, with
 // its placement and links, is recomputed only when the walk crosses one of
 // that class's cuts; a class's running max is stored when it leaves a stage.
-// drow: the plan's four rows of 16 entries (class c, stage s at c*16 + s).  In
+// drow: the plan's four rows of 16 entries (class c, stage s at c*16 + s);
+// cnt: the lane's column of 4 K counters in LDS (class c, type k at 64 (c K + k)).  In
 // fp64: exact below 2^53, and a pipeline that waits for a longer sync is
 // redone in u64.
 template <int kMode>
 __device__ __forceinline__ void het_plan_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p,
-                                               const uint4 (&rows)[4], double* __restrict__ drow) {
+                                               const uint4 (&rows)[4], double* __restrict__ drow,
+                                               uint32_t* cnt) {
   const uint32_t G = p.G, epl = p.epl;
   const double rp = 1.0 / (double)p.psum, rpe = 1.0 / (double)(p.psum >> epl);
   uint32_t tmin = 3;
@@ -1162,6 +1185,7 @@ __device__ __forceinline__ void het_plan_syncs(const Tab& t, const Hot<kMode>& h
     stg[c2] = 0xffffffffu; nxt[c2] = c2 < G ? 0 : 0xffffffffu; kk[c2] = 0; nl[c2] = 0; nh[c2] = 0; bx[c2] = 0;
     bin[c2] = 0; as2[c2] = 0; ain[c2] = 0; cur[c2] = 0; curb[c2] = 0;
   }
+  class_starts(t, p, 3, [&](uint32_t c, uint32_t k, uint32_t first) { cnt[64 * (c * t.K + k)] = first; });
   const Params par(h.size(), tmin, epl);
   const double gb = (double)t.grad_bytes, pb = (double)t.param_bytes;
   double sl[4];   // parameters of a layer on one TP rank of each class
@@ -1180,7 +1204,7 @@ __device__ __forceinline__ void het_plan_syncs(const Tab& t, const Hot<kMode>& h
         const uint32_t s2 = ++stg[c2], tpl2 = cls_tpl(p.chdr, c2);
         const uint32_t k2 = (uint32_t)(p.tv[c2] >> (4 * s2)) & 15;
         const TypeInfo t2 = h.type(k2);
-        const uint32_t b2 = dev_before<true>(p, c2, s2, k2), n2 = p.reps[c2] << tpl2, d2 = t2.dpl;
+        const uint32_t n2 = p.reps[c2] << tpl2, b2 = draw(&cnt[64 * (c2 * t.K + k2)], n2), d2 = t2.dpl;
         const uint32_t l2 = t2.node_off + (b2 >> d2), h2 = t2.node_off + ((b2 + n2 - 1) >> d2);
         const uint32_t dl2 = t2.dev_off + b2;
         const uint32_t nic2 = range_max(h.rmn, t.D, dl2, dl2 + n2 - 1);
@@ -1569,7 +1593,9 @@ __global__ void __launch_bounds__(256) k_plan_syncs(Tab t, const PackedPlan* __r
   const Plan p = unpack(packed[i], 0);
   uint4 rows[4];
   load_rows(pcut + 4 * (size_t)i, rows);
-  het_plan_syncs(t, h, p, rows, hdp + (size_t)i * (kMaxClasses * kMaxStages));
+  uint32_t* const cnt = (uint32_t*)((char*)lds + (kMode < 2 ? t.lds_bytes : 0)) + (threadIdx.x >> 6) * (256 * t.K) +
+                        (threadIdx.x & 63u);
+  het_plan_syncs(t, h, p, rows, hdp + (size_t)i * (kMaxClasses * kMaxStages), cnt);
 }
 
 
@@ -2042,7 +2068,7 @@ struct PlanLanes {
     for (uint32_t k = 0; k < t.K; ++k) cnt[64 * k + lane] = 0;
     if (G == 1) return;
 #pragma unroll
-    for (uint32_t s = 0; s < (uint32_t)S; ++s) __hip_atomic_fetch_add(&counter(p, s), p.rc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    for (uint32_t s = 0; s < (uint32_t)S; ++s) draw(&counter(p, s), p.rc);
     wave_sync_lds();
     for (uint32_t k = 0; k < t.K; ++k) {
       uint32_t before = 0;
@@ -2055,7 +2081,7 @@ struct PlanLanes {
     }
   }
   __device__ __forceinline__ uint32_t first_device(const Plan& p, uint32_t k) {
-    return __hip_atomic_fetch_add(&cnt[64 * k + lane], p.rc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) * p.tp;
+    return draw(&cnt[64 * k + lane], p.rc) * p.tp;
   }
   __device__ __forceinline__ void placed(uint32_t s, const StagePlace& sp) {
     reinterpret_cast<uint2*>(col)[64 * s + lane] =
@@ -2144,7 +2170,12 @@ __device__ __forceinline__ void eval_one(const Tab& t, const Hot<kMode>& h, cons
       for (int s = 0; s < S; ++s) x[s] = xw[s * 64 + (kOvl ? pl.lane : lead)];
       wave_sync_lds();
     } else {
-      class_setup<kMode, true>(t, h, p, r, [&](uint32_t s, uint32_t k) { return dev_before_own<true>(p, s, k); },
+      uint32_t* const cnt = cw + (threadIdx.x & 63u);
+      class_starts(t, p, p.c, [&](uint32_t c, uint32_t k, uint32_t first) {
+        if (c == p.c) cnt[64 * k] = first;
+      });
+      const uint32_t nd = p.rc * p.tp;
+      class_setup<kMode, true>(t, h, p, r, [&](uint32_t, uint32_t k) { return draw(&cnt[64 * k], nd); },
                                [](uint32_t, const StagePlace&) {});
       // per-class layout: the syncs the plan pass stored for this pipeline's stages
       const double* drow = e.hdp + (size_t)slot * kMaxStages;

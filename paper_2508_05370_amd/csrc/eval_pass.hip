@@ -23,7 +23,7 @@ static uint32_t tile_grid(uint32_t n, uint32_t cap) {
 template <int kMode, bool kHet>
 hipError_t launch_group_v(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s) {
   const uint32_t grid = tile_grid(max_tiles, 4 * t.grid_eval[g]);
-  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) + (kHet ? 0 : block_lds_bytes(plan_cols(g, false), t.K));
+  const size_t lds = (kMode < 2 ? t.lds_bytes : 0) + block_lds_bytes(kHet ? 0 : plan_cols(g, false), t.K);
   if (g == 0) k_eval<0, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
   else if (g == 1) k_eval<1, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);
   else if (g == 2) k_eval<2, kMode, kHet><<<grid, kEvalThreads, lds, s>>>(e.dtab, e);

@@ -38,7 +38,7 @@ __host__ __device__ constexpr uint32_t plan_cols(int group, bool overlap) {
   return (uint32_t)(kMaxStages - 4 * group) + (overlap ? 2u : 0u);
 }
 __host__ __device__ constexpr uint32_t wave_lds_bytes(uint32_t cols, uint32_t types) {
-  return cols ? cols * 64 * 8 + types * 64 * 4 : 0;
+  return cols * 64 * 8 + types * 64 * 4;
 }
 __host__ __device__ constexpr uint32_t block_lds_bytes(uint32_t cols, uint32_t types) {
   return 4 * wave_lds_bytes(cols, types);

@@ -476,10 +476,10 @@ hipError_t launch_plan_syncs(const Tab& t, const PackedPlan* packed, const uint4
   k_plan_hist<<<go, 256, 0, s>>>((const uint4*)meta, (uint32_t)n, pc);
   k_plan_scatter<<<go, 256, 0, s>>>((const uint4*)meta, (uint32_t)n, pc, perm);
   const int g = blocks_for(n, 256);
-  const size_t lds = t.mode < 2 ? t.lds_bytes : 0;
+  const size_t lds = (t.mode < 2 ? t.lds_bytes : 0) + 4 * (256 * t.K) * 4;   // and the lanes' counters
   if (t.mode == 0) k_plan_syncs<0><<<g, 256, lds, s>>>(t, packed, pcut, perm, pc, n, hdp);
   else if (t.mode == 1) k_plan_syncs<1><<<g, 256, lds, s>>>(t, packed, pcut, perm, pc, n, hdp);
-  else k_plan_syncs<2><<<g, 256, 0, s>>>(t, packed, pcut, perm, pc, n, hdp);
+  else k_plan_syncs<2><<<g, 256, lds, s>>>(t, packed, pcut, perm, pc, n, hdp);
   return hipGetLastError();
 }
 
