@@ -15,7 +15,7 @@ hipError_t launch_fill32(uint32_t* p, uint32_t n, uint32_t v, hipStream_t s);
 hipError_t launch_prep(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed, uint4* pcut,
                        uint32_t* meta, uint32_t* hist, uint16_t* keys, hipStream_t s);
 hipError_t launch_memory(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, hipStream_t s);
-hipError_t launch_plan_syncs(const Tab& t, const PackedPlan* packed, const uint4* pcut, const uint32_t* meta,
+hipError_t launch_plan_syncs(const Tab& t, const uint4* pcut, const uint32_t* meta,
                              int64_t n, double* hdp, uint32_t* pc, uint32_t* perm, hipStream_t s);
 hipError_t launch_stages(const Tab& t, const PackedPlan* packed, const uint4* pcut, const uint32_t* meta, int64_t n,
                          uint64_t* out_stage, hipStream_t s);
@@ -246,7 +246,7 @@ static hipError_t order_chunk(sim_ctx* c, const Work& W, const sim_plans& p, int
   if (e == hipSuccess) e = launch_prep(c->tab, c->dtab, p, n, out, W.packed, W.pcut, W.meta, W.hist, W.keys, s);
   if (timed) end_event(c, 1, s, &ev);
   if (e == hipSuccess && het)
-    e = launch_plan_syncs(c->tab, W.packed, W.pcut, W.meta, n, W.hdp, W.ctr + kEvalCounters, W.perm, s);
+    e = launch_plan_syncs(c->tab, W.pcut, W.meta, n, W.hdp, W.ctr + kEvalCounters, W.perm, s);
   if (e == hipSuccess) e = launch_scan(W, !het, s);
   if (e == hipSuccess) e = launch_scatter(W, (uint32_t)(het ? n * 4 : n), s);
   return e;
@@ -417,11 +417,10 @@ extern "C" int sim_eval_stages(sim_ctx* c, const sim_plans* plans, int64_t n, ui
   void* ws = nullptr;
   const bool het = plans->chdr != nullptr;
   const int64_t ch = n < kChunk ? n : kChunk;
-  if (hipMallocFromPoolAsync(&ws, align256((size_t)ch * sizeof(PackedPlan)) + cut_rows_bytes(ch, het), c->pool, s) !=
-      hipSuccess)
-    return SIM_ENOMEM;
-  PackedPlan* packed = (PackedPlan*)ws;
-  uint4* pcut = het ? (uint4*)((char*)ws + align256((size_t)ch * sizeof(PackedPlan))) : nullptr;
+  const size_t bytes = (size_t)ch * (het ? kHetWords * 16 : sizeof(PackedPlan));
+  if (hipMallocFromPoolAsync(&ws, bytes, c->pool, s) != hipSuccess) return SIM_ENOMEM;
+  PackedPlan* packed = het ? nullptr : (PackedPlan*)ws;
+  uint4* pcut = het ? (uint4*)ws : nullptr;
   hipError_t e = hipSuccess;
   // chunks of kChunk plans through one workspace, in order on the stream
   for (int64_t off = 0; off < n && e == hipSuccess; off += ch) {

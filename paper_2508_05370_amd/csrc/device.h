@@ -259,22 +259,47 @@ __device__ __forceinline__ Plan unpack(const PackedPlan& q, uint32_t c = 0) {
   return p;
 }
 
+// A per-class-layout plan without its cut rows, seen as class c of the layout's
+// header; tpl, tp, S, mi and the cuts are the pipeline's own class's.
+__device__ __forceinline__ PackedPlan het_record(const uint4* line) {
+  PackedPlan q;
+  const uint4 a = line[0], b = line[1], x = line[2], y = line[3];
+  q.hdr = a.x; q.psum = a.y; q.pad0 = a.z; q.pad1 = 0;
+  uint32_t* z = reinterpret_cast<uint32_t*>(q.cut);
+  z[0] = z[1] = z[2] = z[3] = 0;
+  q.cls[0] = b.x; q.cls[1] = b.y; q.cls[2] = b.z; q.cls[3] = b.w;
+  q.types[0] = (uint64_t)x.y << 32 | x.x; q.types[1] = (uint64_t)x.w << 32 | x.z;
+  q.types[2] = (uint64_t)y.y << 32 | y.x; q.types[3] = (uint64_t)y.w << 32 | y.z;
+  return q;
+}
+
 // The plan of pipeline `slot` (plan slot / 4, class slot % 4).  With the
 // per-class layout the own class's TP degree, depth and cuts replace the
-// header's; its cut row is row `slot` of the per-class cut array.
+// header's.
 template <bool kHet>
 __device__ __forceinline__ Plan load_plan(const PackedPlan* packed, const uint4* pcut, uint32_t slot) {
-  Plan p = unpack(packed[slot >> 2], slot & 3);
-  if (kHet) {
-    p.tpl = cls_tpl(p.chdr, p.c);
-    p.tp = 1u << p.tpl;
-    p.S = cls_S(p.chdr, p.c);
-    p.mi = cls_mi(p.chdr, p.c);
-    const uint4 r = pcut[slot];
-    p.cut_lo = (uint64_t)r.y << 32 | r.x;
-    p.cut_hi = (uint64_t)r.w << 32 | r.z;
-  }
+  if constexpr (!kHet) return unpack(packed[slot >> 2], slot & 3);
+  const uint4* line = pcut + (size_t)(slot >> 2) * kHetWords;
+  const uint32_t c = slot & 3;
+  Plan p = unpack(het_record(line), 0);
+  // (the class's own fields from memory, so that no per-lane index selects among the fields above)
+  const uint32_t cc = reinterpret_cast<const uint32_t*>(line + 1)[c];
+  p.c = c;
+  p.rc = cc & 0xffff;
+  p.nc = cc >> 16;
+  p.tc = reinterpret_cast<const uint64_t*>(line + 2)[c];
+  p.tpl = cls_tpl(p.chdr, c);
+  p.tp = 1u << p.tpl;
+  p.S = cls_S(p.chdr, c);
+  p.mi = cls_mi(p.chdr, c);
+  const uint4 r = line[4 + c];
+  p.cut_lo = (uint64_t)r.y << 32 | r.x;
+  p.cut_hi = (uint64_t)r.w << 32 | r.z;
   return p;
+}
+// a per-class-layout plan's four cut rows
+__device__ __forceinline__ const uint4* cut_rows(const uint4* pcut, uint32_t plan) {
+  return pcut + (size_t)plan * kHetWords + 4;
 }
 
 // micro-batches per replica of the pipeline's class (its M)
@@ -519,8 +544,7 @@ __device__ __forceinline__ bool fits_memory(const Tab& t, const CheckTab& ct, co
 }
 
 // Decode and check plan i (every rule of the plan layout); on success pack it
-// (with the per-class layout, the class header word goes to pad0 and each
-// class's cut row to pcut[4 i + c]).  Writes out[i] (0 = valid, to be raised
+// (with the per-class layout into its line at pcut).  Writes out[i] (0 = valid, to be raised
 // by the pipelines; else invalid), and when given the per-pipeline metadata
 // S | G << 5 | M << 8 | (v - 1) << 24 with the class's own S (0 = no pipeline)
 // and the bucket keys, counted in hist.
@@ -542,17 +566,24 @@ __global__ void __launch_bounds__(256) k_prep(Tab t, const Tab* __restrict__ dta
     const bool ok = r.ok && (!t.mem_check || fits_memory<kHet>(t, ct, r));
     const uint32_t G = ((r.hdr >> 8) & 3) + 1;
     if (out) out[i] = ok ? 0 : kInvalid;
-    if (ok) {
+    if (ok && !kHet) {
       PackedPlan q;
-      q.hdr = r.hdr; q.psum = r.psum; q.pad0 = r.chdr; q.pad1 = 0;
+      q.hdr = r.hdr; q.psum = r.psum; q.pad0 = 0; q.pad1 = 0;
       uint32_t* qc = reinterpret_cast<uint32_t*>(q.cut);
 #pragma unroll
       for (int j = 0; j < 4; ++j) { qc[j] = r.cw[0][j]; q.cls[j] = r.cls[j]; q.types[j] = r.tv[j]; }
       packed[i] = q;
-      if (kHet) {
+    }
+    if (ok && kHet) {
+      uint4* q = pcut + i * kHetWords;
+      auto lo = [](uint64_t x) { return (uint32_t)x; };
+      auto hi = [](uint64_t x) { return (uint32_t)(x >> 32); };
+      q[0] = make_uint4(r.hdr, r.psum, r.chdr, 0);
+      q[1] = make_uint4(r.cls[0], r.cls[1], r.cls[2], r.cls[3]);
+      q[2] = make_uint4(lo(r.tv[0]), hi(r.tv[0]), lo(r.tv[1]), hi(r.tv[1]));
+      q[3] = make_uint4(lo(r.tv[2]), hi(r.tv[2]), lo(r.tv[3]), hi(r.tv[3]));
 #pragma unroll
-        for (int c = 0; c < 4; ++c) pcut[4 * i + c] = make_uint4(r.cw[c][0], r.cw[c][1], r.cw[c][2], r.cw[c][3]);
-      }
+      for (int c = 0; c < 4; ++c) q[4 + c] = make_uint4(r.cw[c][0], r.cw[c][1], r.cw[c][2], r.cw[c][3]);
     }
     uint32_t m[4], Mmax = 0;
 #pragma unroll
@@ -1552,7 +1583,7 @@ __global__ void __launch_bounds__(256) k_stages(Tab t, const PackedPlan* __restr
     else if (v > 1) hop = hop_ps(t, p, place(0), sp, act, false);   // to device 0, placed before it
     if (kHet) {
       uint4 rows[4];
-      load_rows(pcut + (slot & ~3ll), rows);
+      load_rows(cut_rows(pcut, (uint32_t)(slot >> 2)), rows);
       sync = het_stage_dp(t, h, p, rows, lo, hi, rp, rpe);
     } else if (v > 1) {
       uint32_t ns = 0;
@@ -1580,8 +1611,7 @@ __global__ void __launch_bounds__(256) k_stages(Tab t, const PackedPlan* __restr
 // takes plan perm[j] of the pc[512] valid plans (sorted by the length of
 // their walks).
 template <int kMode>
-__global__ void __launch_bounds__(256) k_plan_syncs(Tab t, const PackedPlan* __restrict__ packed,
-                                                    const uint4* __restrict__ pcut, const uint32_t* __restrict__ perm,
+__global__ void __launch_bounds__(256) k_plan_syncs(Tab t, const uint4* __restrict__ pcut, const uint32_t* __restrict__ perm,
                                                     const uint32_t* __restrict__ pc, int64_t n,
                                                     double* __restrict__ hdp) {
   extern __shared__ uint4 lds[];
@@ -1590,9 +1620,9 @@ __global__ void __launch_bounds__(256) k_plan_syncs(Tab t, const PackedPlan* __r
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n || j >= (int64_t)pc[2 * kPlanBuckets]) return;
   const uint32_t i = perm[j];
-  const Plan p = unpack(packed[i], 0);
+  const Plan p = unpack(het_record(pcut + (size_t)i * kHetWords));
   uint4 rows[4];
-  load_rows(pcut + 4 * (size_t)i, rows);
+  load_rows(cut_rows(pcut, i), rows);
   uint32_t* const cnt = (uint32_t*)((char*)lds + (kMode < 2 ? t.lds_bytes : 0)) + (threadIdx.x >> 6) * (256 * t.K) +
                         (threadIdx.x & 63u);
   het_plan_syncs(t, h, p, rows, hdp + (size_t)i * (kMaxClasses * kMaxStages), cnt);
@@ -2601,7 +2631,7 @@ __global__ void __launch_bounds__(64) k_redo_u64(Tab t, EvalBufs e) {
     StageRec R;
     uint64_t W[kMaxStages];
     const bool w = !kHet && p.zb;
-    class_records<2, kHet>(t, h, p, kHet ? e.pcut + (slot & ~3u) : nullptr, R, W);
+    class_records<2, kHet>(t, h, p, kHet ? cut_rows(e.pcut, slot >> 2) : nullptr, R, W);
     uint64_t r;
     switch (S) {
       case 1: r = redo_one<1>(R, W, w, M); break;

@@ -53,6 +53,11 @@ struct __attribute__((aligned(16))) PackedPlan {
   uint64_t types[4];
 };
 
+// With the per-class layout a plan takes one 128-byte line, gathered whole:
+// {header, replicas, class header, 0}, the four class words, the stage types
+// and the four classes' cut rows, as eight 16-byte words.
+constexpr uint32_t kHetWords = 8;
+
 // Per-device-type fields a kernel reads together (32 bytes, two loads).
 struct TypeInfo {
   uint32_t node_off, dev_off;     // first global node / device of the pool
@@ -178,8 +183,8 @@ constexpr uint32_t kSkipSlots = 512, kSkipStride = 16;
 
 // Device buffers of one evaluation pass over a chunk.
 struct EvalBufs {
-  const PackedPlan* packed;
-  const uint4* pcut;           // per-class layout: cut row of pipeline slot at [slot]; nullptr for the shared layout
+  const PackedPlan* packed;    // shared layout
+  const uint4* pcut;           // per-class layout: kHetWords per plan; nullptr for the shared layout
   const double* hdp;           // per-class layout: the syncs of pipeline slot's stages at [16 slot, + 16)
   const uint32_t* order;       // plans (shared layout) or pipeline slots (per-class layout) by group
   const uint32_t* gstart;      // [kGroups + 1]
@@ -200,7 +205,7 @@ constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // together), bucket cursors, group and tile starts, the bucket key of each
 // plan (u16; of each pipeline with the per-class layout), the continuation
 // lists, and with the per-class layout the pipeline metadata, the plan order
-// of the sync pass, the plans' class cut rows (64 bytes per plan) and the
+// of the sync pass, the plans' lines (in place of the packed plans) and the
 // syncs each pipeline's stages wait for (16 u64 per pipeline slot, 512 bytes
 // per plan).
 constexpr uint32_t kCounters = kBuckets + kEvalCounters + kPlanSortWords;
@@ -221,7 +226,6 @@ constexpr size_t cont_bytes(int64_t ch, size_t per_plan) {
   return ((b > (1u << 20) ? b : (1u << 20)) + kContUnit - 1) / kContUnit * kContUnit;
 }
 constexpr size_t kContPerPlan = 224, kContPerPlanNoAlloc = 32;
-constexpr size_t cut_rows_bytes(int64_t ch, bool het) { return het ? align256((size_t)ch * 64) : 0; }
 struct Carver {   // running offset
   size_t off = 0;
   constexpr size_t take(size_t bytes) {
@@ -238,11 +242,11 @@ constexpr WorkOffsets work_offsets(int64_t ch, bool het, size_t cont_per_plan) {
   Carver c;
   WorkOffsets o = {};
   o.cont = c.take(cont_bytes(ch, cont_per_plan));
-  o.pcut = c.take(nh * 64);
+  o.pcut = c.take(nh * kHetWords * 16);
   o.hdp = c.take(nh * kMaxClasses * kMaxStages * 8);
   o.meta = c.take(nh * 16);
   o.perm = c.take(nh * 4);
-  o.packed = c.take(n * sizeof(PackedPlan));
+  o.packed = c.take(het ? 0 : n * sizeof(PackedPlan));
   o.order = c.take(np * 4);
   o.hist = c.take(kCounters * 4 + n * 16);
   o.cursor = c.take(kBuckets * 4);

@@ -470,16 +470,16 @@ hipError_t launch_memory(const Tab& t, const Tab* dtab, const sim_plans& p, int6
 }
 
 // pc: the plan-order counters (zero on entry); perm: n words
-hipError_t launch_plan_syncs(const Tab& t, const PackedPlan* packed, const uint4* pcut, const uint32_t* meta,
+hipError_t launch_plan_syncs(const Tab& t, const uint4* pcut, const uint32_t* meta,
                              int64_t n, double* hdp, uint32_t* pc, uint32_t* perm, hipStream_t s) {
   const int go = blocks_for(n, 256 * kPlanPer);
   k_plan_hist<<<go, 256, 0, s>>>((const uint4*)meta, (uint32_t)n, pc);
   k_plan_scatter<<<go, 256, 0, s>>>((const uint4*)meta, (uint32_t)n, pc, perm);
   const int g = blocks_for(n, 256);
   const size_t lds = (t.mode < 2 ? t.lds_bytes : 0) + 4 * (256 * t.K) * 4;   // and the lanes' counters
-  if (t.mode == 0) k_plan_syncs<0><<<g, 256, lds, s>>>(t, packed, pcut, perm, pc, n, hdp);
-  else if (t.mode == 1) k_plan_syncs<1><<<g, 256, lds, s>>>(t, packed, pcut, perm, pc, n, hdp);
-  else k_plan_syncs<2><<<g, 256, lds, s>>>(t, packed, pcut, perm, pc, n, hdp);
+  if (t.mode == 0) k_plan_syncs<0><<<g, 256, lds, s>>>(t, pcut, perm, pc, n, hdp);
+  else if (t.mode == 1) k_plan_syncs<1><<<g, 256, lds, s>>>(t, pcut, perm, pc, n, hdp);
+  else k_plan_syncs<2><<<g, 256, lds, s>>>(t, pcut, perm, pc, n, hdp);
   return hipGetLastError();
 }
 
