@@ -305,7 +305,10 @@ __device__ __forceinline__ const uint4* cut_rows(const uint4* pcut, uint32_t pla
 // micro-batches per replica of the pipeline's class (its M)
 __device__ __forceinline__ uint32_t class_mb(const Plan& p) { return ceil_div16(p.nc, p.rc); }
 
-constexpr int kPrepPerThread = 4;
+// plans per thread of k_prep (one in smaller calls, which would leave most of
+// the chip without a block)
+constexpr uint32_t kPrepPerThread = 4;
+constexpr int64_t kPrepSmall = 1 << 18;
 
 __device__ __forceinline__ void load_check_tab(CheckTab& ct, const Tab* dtab) {
   const uint32_t* src = (const uint32_t*)static_cast<const CheckTab*>(dtab);
@@ -552,15 +555,15 @@ template <bool kHet>
 __global__ void __launch_bounds__(256) k_prep(Tab t, const Tab* __restrict__ dtab, sim_plans pl, int64_t n, uint64_t* __restrict__ out,
                                               PackedPlan* __restrict__ packed, uint4* __restrict__ pcut,
                                               uint32_t* __restrict__ meta, uint32_t* __restrict__ hist,
-                                              uint16_t* __restrict__ keys) {
+                                              uint16_t* __restrict__ keys, uint32_t per) {
   __shared__ uint32_t lh[kBuckets];
   __shared__ CheckTab ct;
   load_check_tab(ct, dtab);
   if (hist)
     for (uint32_t j = threadIdx.x; j < kBuckets; j += blockDim.x) lh[j] = 0;
   __syncthreads();
-  for (int rep = 0; rep < kPrepPerThread; ++rep) {
-    const int64_t i = ((int64_t)blockIdx.x * kPrepPerThread + rep) * blockDim.x + threadIdx.x;
+  for (uint32_t rep = 0; rep < per; ++rep) {
+    const int64_t i = ((int64_t)blockIdx.x * per + rep) * blockDim.x + threadIdx.x;
     if (i >= n) break;
     const Checked r = check_plan<kHet>(t, ct, pl, i);
     const bool ok = r.ok && (!t.mem_check || fits_memory<kHet>(t, ct, r));

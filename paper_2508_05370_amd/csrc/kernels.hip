@@ -142,11 +142,12 @@ __global__ void __launch_bounds__(1024) k_scan(const uint32_t* __restrict__ hist
   }
 }
 
-// Place every plan (or pipeline) at its bucket's next free entry.
-constexpr int kScatterPer = 16;
+// Place every plan (or pipeline) at its bucket's next free entry.  kPer entries
+// per thread: 16 where the chip is full of blocks anyway, 2 in smaller calls.
+constexpr uint32_t kScatterSmall = 1 << 20;
+template <int kPer>
 __global__ void __launch_bounds__(256) k_scatter(const uint16_t* __restrict__ keys, uint32_t n,
                                                  uint32_t* __restrict__ cursor, uint32_t* __restrict__ order) {
-  constexpr int kPer = kScatterPer;
   __shared__ uint32_t lc[kBuckets];
   for (uint32_t j = threadIdx.x; j < kBuckets; j += blockDim.x) lc[j] = 0;
   __syncthreads();
@@ -160,8 +161,15 @@ __global__ void __launch_bounds__(256) k_scatter(const uint16_t* __restrict__ ke
 #pragma unroll
   for (int j = 0; j < kPer; ++j) rank[j] = key[j] != kNoKey ? atomicAdd(&lc[key[j]], 1u) : 0;
   __syncthreads();
-  for (uint32_t j = threadIdx.x; j < kBuckets; j += blockDim.x)
-    if (lc[j]) lc[j] = atomicAdd(&cursor[j], lc[j]);
+  if (kPer <= 2) {
+    // few entries: the first one of each bucket takes the block's places
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+      if (key[j] != kNoKey && rank[j] == 0) lc[key[j]] = atomicAdd(&cursor[key[j]], lc[key[j]]);
+  } else {
+    for (uint32_t j = threadIdx.x; j < kBuckets; j += blockDim.x)
+      if (lc[j]) lc[j] = atomicAdd(&cursor[j], lc[j]);
+  }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kPer; ++j)
@@ -402,12 +410,16 @@ __global__ void __launch_bounds__(1024) k_min_small(const uint64_t* __restrict__
                                                     sim_best* b) {
   __shared__ uint64_t tpart[16], ipart[16];
   uint64_t bt = kInvalid, bi = kInvalid;
-  for (uint32_t i = threadIdx.x; i < n; i += 1024) {   // (a later index never beats an equal time)
-    const uint64_t v = t[i];
-    if (v < bt) {
-      bt = v;
-      bi = i;
-    }
+  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 8 * 1024) {   // (a later index never beats an equal time)
+    uint64_t v[8];
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j) v[j] = i0 + 1024 * j < n ? t[i0 + 1024 * j] : kInvalid;
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j)
+      if (v[j] < bt) {
+        bt = v[j];
+        bi = i0 + 1024 * j;
+      }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -458,9 +470,10 @@ hipError_t launch_fill32(uint32_t* p, uint32_t n, uint32_t v, hipStream_t s) {
 }
 hipError_t launch_prep(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed, uint4* pcut,
                        uint32_t* meta, uint32_t* hist, uint16_t* keys, hipStream_t s) {
-  const int g = blocks_for(n, 256 * kPrepPerThread);
-  if (p.chdr) k_prep<true><<<g, 256, 0, s>>>(t, dtab, p, n, out, packed, pcut, meta, hist, keys);
-  else k_prep<false><<<g, 256, 0, s>>>(t, dtab, p, n, out, packed, pcut, meta, hist, keys);
+  const uint32_t per = n < kPrepSmall ? 1 : kPrepPerThread;
+  const int g = blocks_for(n, 256 * per);
+  if (p.chdr) k_prep<true><<<g, 256, 0, s>>>(t, dtab, p, n, out, packed, pcut, meta, hist, keys, per);
+  else k_prep<false><<<g, 256, 0, s>>>(t, dtab, p, n, out, packed, pcut, meta, hist, keys, per);
   return hipGetLastError();
 }
 hipError_t launch_memory(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, hipStream_t s) {
@@ -495,7 +508,8 @@ hipError_t launch_scan(const Work& w, bool grouped, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_scatter(const Work& w, uint32_t n, hipStream_t s) {
-  k_scatter<<<blocks_for(n, 256 * kScatterPer), 256, 0, s>>>(w.keys, n, w.cursor, w.order);
+  if (n < kScatterSmall) k_scatter<2><<<blocks_for(n, 512), 256, 0, s>>>(w.keys, n, w.cursor, w.order);
+  else k_scatter<16><<<blocks_for(n, 4096), 256, 0, s>>>(w.keys, n, w.cursor, w.order);
   return hipGetLastError();
 }
 // ---------------------------------------------------------------- node-rate probe
