@@ -2302,14 +2302,18 @@ __device__ __forceinline__ void il_setup_own(const Tab& t, const Hot<kMode>& h, 
                            [](uint32_t, const StagePlace&) {});
 }
 
-// One trip of S v steps from step t0 (a multiple of S v).  kPred: some op of
-// the trip may lie outside its device's schedule (warm-up, cool-down);
-// otherwise every device runs a forward and a backward at every step.
+// One trip of S v steps from a step that is a multiple of S v.  n = M v is
+// such a multiple too and at least 2 S v, and W_0 <= 2 S v, so which ops of
+// a trip exist is known at compile time: kOff is the trip's first step in a
+// warm-up trip (kPhase < 0), its first step minus n in a cool-down trip
+// (kPhase > 0), and in a steady trip every device runs a forward and a
+// backward at every step.  Against one trip with each op predicated at run
+// time for both ends: k_all over 2M plans 1149 -> 658 us.
 // F[s], B[s]: end of device s's latest forward / backward; busy[s]: of its
 // latest op.
-template <int S, int v, typename V, bool kPred>
-__device__ __forceinline__ void il_trip(int t0, int n, const V (&f)[S * v], const V (&b)[S * v], const V (&c)[S],
-                                        V (&F)[S], V (&B)[S], V (&busy)[S]) {
+template <int S, int v, typename V, int kPhase, int kOff>
+__device__ __forceinline__ void il_trip(const V (&f)[S * v], const V (&b)[S * v], const V (&c)[S], V (&F)[S],
+                                        V (&B)[S], V (&busy)[S]) {
   constexpr int NV = S * v;
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
@@ -2319,28 +2323,19 @@ __device__ __forceinline__ void il_trip(int t0, int n, const V (&f)[S * v], cons
       const int W = 2 * (S - 1 - s) + (v - 1) * S;
       const int jf = ((u - s) % NV + NV) % NV / S, vf = jf * S + s;
       const int jb = v - 1 - ((u - s - W) % NV + NV) % NV / S, vb = jb * S + s;
-      V x = busy[s];
-      const V rf = s > 0 ? F[s - 1] + c[s - 1] : jf > 0 ? F[S - 1] + c[S - 1] : (V)0;
-      V ef = vmax(x, rf) + f[vf];
-      if (kPred) {
-        const bool a = (unsigned)(t0 + u - s) < (unsigned)n;
-        ef = a ? ef : F[s];
-        x = a ? ef : x;
-      } else {
-        x = ef;
+      const int kf = kOff + u - s, kb = kf - W;   // op numbers (in cool-down: minus n)
+      const bool has_f = kPhase < 0 ? kf >= 0 : kPhase == 0 || kf < 0;
+      const bool has_b = kPhase < 0 ? kb >= 0 : kPhase == 0 || kb < 0;
+      nF[s] = F[s];
+      nB[s] = B[s];
+      if (has_f) {
+        const V rf = s > 0 ? F[s - 1] + c[s - 1] : jf > 0 ? F[S - 1] + c[S - 1] : (V)0;
+        busy[s] = nF[s] = vmax(busy[s], rf) + f[vf];
       }
-      nF[s] = ef;
-      const V rb = vb == NV - 1 ? ef : s < S - 1 ? B[s + 1] + c[s] : B[0] + c[S - 1];
-      V eb = vmax(x, rb) + b[vb];
-      if (kPred) {
-        const bool a = (unsigned)(t0 + u - s - W) < (unsigned)n;
-        eb = a ? eb : B[s];
-        x = a ? eb : x;
-      } else {
-        x = eb;
+      if (has_b) {
+        const V rb = vb == NV - 1 ? nF[s] : s < S - 1 ? B[s + 1] + c[s] : B[0] + c[S - 1];
+        busy[s] = nB[s] = vmax(busy[s], rb) + b[vb];
       }
-      nB[s] = eb;
-      busy[s] = x;
     }
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -2359,46 +2354,46 @@ template <int S, int v, typename V, bool kJump>
 __device__ __forceinline__ void il_pipe(const V (&f)[S * v], const V (&b)[S * v], const V (&c)[S], uint32_t M,
                                         V (&busy)[S], int& skipped) {
   constexpr int NV = S * v, W0 = 2 * (S - 1) + (v - 1) * S;
-  const int n = (int)M * v, steps = n + W0;
+  static_assert(W0 <= 2 * NV, "at most two trips of warm-up and of cool-down");
+  const int n = (int)M * v;   // (a multiple of NV, at least 2 NV)
   V F[S], B[S], pF[S], pB[S];
 #pragma unroll
-  for (int s = 0; s < S; ++s) F[s] = B[s] = busy[s] = pF[s] = pB[s] = 0;
+  for (int s = 0; s < S; ++s) F[s] = B[s] = busy[s] = 0;
   skipped = 0;
-  bool prev_steady = false;
-  for (int t0 = 0; t0 < steps; t0 += NV) {
-    if (t0 >= W0 && t0 + NV <= n) {
-      if (kJump) {
+  il_trip<S, v, V, -1, 0>(f, b, c, F, B, busy);
+  if (W0 > NV) il_trip<S, v, V, -1, NV>(f, b, c, F, B, busy);
+  bool first = true;
+  for (int t0 = W0 > NV ? 2 * NV : NV; t0 < n; t0 += NV) {
+    if (kJump) {
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        pF[s] = F[s];
+        pB[s] = B[s];
+      }
+    }
+    il_trip<S, v, V, 0, 0>(f, b, c, F, B, busy);
+    if (kJump && !first) {
+      const V lam = B[0] - pB[0];
+      bool same = true;
+#pragma unroll
+      for (int s = 0; s < S; ++s) same = same && F[s] - pF[s] == lam && B[s] - pB[s] == lam;
+      const int r = (n - (t0 + NV)) / NV;
+      if (same && r > 0) {
+        const V k = (V)r * lam;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-          pF[s] = F[s];
-          pB[s] = B[s];
+          F[s] += k;
+          B[s] += k;
+          busy[s] += k;
         }
+        t0 += r * NV;
+        skipped += r;
       }
-      il_trip<S, v, V, false>(t0, n, f, b, c, F, B, busy);
-      if (kJump && prev_steady) {
-        const V lam = B[0] - pB[0];
-        bool same = true;
-#pragma unroll
-        for (int s = 0; s < S; ++s) same = same && F[s] - pF[s] == lam && B[s] - pB[s] == lam;
-        const int r = (n - (t0 + NV)) / NV;
-        if (same && r > 0) {
-          const V k = (V)r * lam;
-#pragma unroll
-          for (int s = 0; s < S; ++s) {
-            F[s] += k;
-            B[s] += k;
-            busy[s] += k;
-          }
-          t0 += r * NV;
-          skipped += r;
-        }
-      }
-      prev_steady = true;
-    } else {
-      il_trip<S, v, V, true>(t0, n, f, b, c, F, B, busy);
-      prev_steady = false;
     }
+    first = false;
   }
+  il_trip<S, v, V, 1, 0>(f, b, c, F, B, busy);
+  if (W0 > NV) il_trip<S, v, V, 1, NV>(f, b, c, F, B, busy);
 }
 
 // Layers on device s: the sum over its chunks.
