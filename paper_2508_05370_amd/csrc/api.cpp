@@ -261,8 +261,9 @@ static uint32_t max_tiles(int64_t n) { return (uint32_t)(n * kMaxClasses / 63 + 
 // Evaluate a sorted chunk of n plans on one stream.  Up to kSmallCall plans of
 // the shared layout k_all takes every kind in one launch, whose tiles run side
 // by side; above that the plain plans run in k_eval's four, with up to twice
-// the wavefronts per SIMD.
-constexpr int64_t kSmallCall = 1 << 15;
+// the wavefronts per SIMD.  60000 plans take 152 us in one launch and 196 in
+// four, 131072 plans 203-222 and 242-259, 2^20 plans 500 and 380.
+constexpr int64_t kSmallCall = 1 << 17;
 static hipError_t eval_chunk(sim_ctx* c, const EvalBufs& a, int64_t n, hipStream_t s) {
   const uint32_t tiles = max_tiles(n);
   const bool small = !a.pcut && n <= kSmallCall;

@@ -305,10 +305,11 @@ __device__ __forceinline__ const uint4* cut_rows(const uint4* pcut, uint32_t pla
 // micro-batches per replica of the pipeline's class (its M)
 __device__ __forceinline__ uint32_t class_mb(const Plan& p) { return ceil_div16(p.nc, p.rc); }
 
-// plans per thread of k_prep (one in smaller calls, which would leave most of
-// the chip without a block)
+// plans per thread of k_prep: one in smaller calls, which would leave most of
+// the chip without a block (29470 plans 133 us with four, 128 with one, 262144
+// plans 242 and 250; even at 131072)
 constexpr uint32_t kPrepPerThread = 4;
-constexpr int64_t kPrepSmall = 1 << 18;
+constexpr int64_t kPrepSmall = 1 << 17;
 
 __device__ __forceinline__ void load_check_tab(CheckTab& ct, const Tab* dtab) {
   const uint32_t* src = (const uint32_t*)static_cast<const CheckTab*>(dtab);
@@ -1677,8 +1678,10 @@ __device__ __forceinline__ uint64_t vmax(uint64_t a, uint64_t b) { return a > b 
 // needs 16 minus the stage count).
 constexpr int kContBudget = 48, kPowerMin = 16;
 // With so few entries in the first list k_cont leaves them to k_power: their
-// tiles would not fill the chip, and a tile takes 15-60 us, an entry 6.
-constexpr uint32_t kContFew = 4096;
+// tiles would not fill the chip, and a tile takes 15-60 us, an entry 6.  A
+// call of 60000 random plans takes 226 us with the line at 4096 entries and 196
+// at 16384, one of 131072 plans 242 and 259: the line lies between.
+constexpr uint32_t kContFew = 12288;
 
 // A wavefront of the first pass waits this many steady iterations for its
 // lanes, then the aperiodic ones leave for the continuation lists.  Most

@@ -143,8 +143,9 @@ __global__ void __launch_bounds__(1024) k_scan(const uint32_t* __restrict__ hist
 }
 
 // Place every plan (or pipeline) at its bucket's next free entry.  kPer entries
-// per thread: 16 where the chip is full of blocks anyway, 2 in smaller calls.
-constexpr uint32_t kScatterSmall = 1 << 20;
+// per thread: 16, or 2 in smaller calls (a call of 29470 plans 128 us with 16,
+// 121 with 2, 262144 plans 250 and 260; even at 60000).
+constexpr uint32_t kScatterSmall = 1 << 16;
 template <int kPer>
 __global__ void __launch_bounds__(256) k_scatter(const uint16_t* __restrict__ keys, uint32_t n,
                                                  uint32_t* __restrict__ cursor, uint32_t* __restrict__ order) {
@@ -468,8 +469,8 @@ hipError_t launch_fill32(uint32_t* p, uint32_t n, uint32_t v, hipStream_t s) {
   k_fill32<<<blocks_for(n, 256) < 1024 ? blocks_for(n, 256) : 1024, 256, 0, s>>>(p, n, v);
   return hipGetLastError();
 }
-hipError_t launch_prep(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed, uint4* pcut,
-                       uint32_t* meta, uint32_t* hist, uint16_t* keys, hipStream_t s) {
+hipError_t launch_prep(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed,
+                       uint4* pcut, uint32_t* meta, uint32_t* hist, uint16_t* keys, hipStream_t s) {
   const uint32_t per = n < kPrepSmall ? 1 : kPrepPerThread;
   const int g = blocks_for(n, 256 * per);
   if (p.chdr) k_prep<true><<<g, 256, 0, s>>>(t, dtab, p, n, out, packed, pcut, meta, hist, keys, per);

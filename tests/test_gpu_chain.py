@@ -88,3 +88,14 @@ def test_continuation_lists_overflow(B, oracle_mod, workloads, kind):
     p["hdr"] |= np.uint32(KINDS[kind])
     print("case: %s, %d plans" % (kind, len(p["hdr"])), flush=True)
     _check(B, oracle_mod, model, cluster, p, noalloc=True)
+
+
+# lists long enough for both continuation passes, in calls on either side of the one-launch limit (2^17 plans)
+@pytest.mark.parametrize("n", [60001, 131072, 131073])
+def test_continuation_lists_long(B, oracle_mod, workloads, n):
+    w = workloads.workload(2)
+    model = dict(w["model"], global_batch=96)
+    cluster = dict(w["cluster"], types=[dict(t, nic_MBps=t["nic_MBps"] // 8) for t in w["cluster"]["types"]])
+    p = _plans(w, [13], n, 11, 96, 2)
+    print("case: %d plans" % n, flush=True)
+    _check(B, oracle_mod, model, cluster, p)
