@@ -67,7 +67,7 @@ def _fields(p):
 
 def pipeline_ops(p, valid, per_node=3, first=1):
     """VALU ops of the whole pipeline recurrence, per plan: `per_node` per schedule node with a
-    cross-stage input, `first` per node without one (3 and 1 in fp64 as the kernels run it; the
+    cross-stage input, `first` per node without one (3 and 1 in fp64 on the times themselves; the
     int32 count of the same nodes is 7 and 2)."""
     f = _fields(p)
     S, G = f["S"], f["G"]
@@ -436,7 +436,7 @@ def main():
                 "unit": "TOP/s", "frac": round(achieved / peak, 4),
                 "traffic": None if a.plans else measured_traffic(a.workload, a.chunk),
                 "kernel": "one sim_eval_plans call: k_fill32, k_prep, k_scan, k_scatter, k_eval x4 groups, "
-                          "k_variant x4, k_il, k_cont, k_power, k_redo_u64 per 2M-plan chunk",
+                          "k_all, k_cont, k_power, k_redo_u64 per 2M-plan chunk",
                 "avg_launch_ms": round(avg_ms, 4), "launches": call_n,
                 "work_per_launch": work,
                 "recurrence_ops_per_launch": rec_per_launch, "setup_ops_per_launch": setup_per_launch,

@@ -332,12 +332,12 @@ int sim_best_reduce(sim_ctx* ctx, const sim_best* bests, int64_t n, sim_best* ou
  * accumulated milliseconds and pair counts, then clears them.
  * kind 0 = first evaluation pass (per-pipeline setup and 1F1B recurrence
  * with the periodic shortcut), 1 = plan check/pack kernel, 2 = whole
- * sim_eval_plans call, 3 = deferred pass (full-loop pipelines and the u64
- * redo).  A call of more than 2^22 plans works in chunks of 2^21 and runs
- * each chunk's first pass on two side streams of the context and its
- * deferred pass on a third, overlapped with the next chunk; the call's
- * stream waits for them before the call's work is complete, so kinds 0 and
- * 3 may overlap in time.
+ * sim_eval_plans call, 3 = the passes after it (schedules still aperiodic,
+ * and the u64 redo).  A call of more than 2^22 plans works in chunks of
+ * 2^21 and runs each chunk's first pass on three side streams of the context
+ * and the later passes on one of them, overlapped with the next chunk; the
+ * call's stream waits for them before the call's work is complete, so kinds
+ * 0 and 3 may overlap in time.
  */
 int sim_set_timing(sim_ctx* ctx, int enable);
 int sim_get_timing(sim_ctx* ctx, int kind, double* total_ms, int64_t* launches);
@@ -351,7 +351,8 @@ int sim_get_timing(sim_ctx* ctx, int kind, double* total_ms, int64_t* launches);
  * enabled sim_eval_plans sums, on the device, the recurrence work this
  * skipped: s skipped iterations of an S-stage pipeline count
  * s * (6 (S - 1) + 2) VALU ops, the cost of S forward and S backward nodes
- * at 3 ops per node (1 for a node without a cross-stage input).
+ * on the times themselves, at 3 ops per node (1 for a node without a
+ * cross-stage input).
  * sim_get_skipped_ops synchronises the device, writes the sum to *ops (host
  * memory) and clears it (it starts at zero).
  */

@@ -12,7 +12,8 @@
 
 namespace hetsim {
 hipError_t launch_fill32(uint32_t* p, uint32_t n, uint32_t v, hipStream_t s);
-hipError_t launch_prep(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed, uint4* pcut,
+hipError_t launch_prep(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, PackedPlan* packed,
+                       uint4* pcut,
                        uint32_t* meta, uint32_t* hist, uint16_t* keys, hipStream_t s);
 hipError_t launch_memory(const Tab& t, const Tab* dtab, const sim_plans& p, int64_t n, uint64_t* out, hipStream_t s);
 hipError_t launch_plan_syncs(const Tab& t, const uint4* pcut, const uint32_t* meta,
@@ -41,7 +42,7 @@ struct EventPair {
 }  // namespace
 
 // Side streams of multi-chunk calls made on one caller stream: two for the
-// four first-pass groups and one for the deferred pass.  Each caller stream
+// four k_eval launches and one for the other passes.  Each caller stream
 // gets its own set, so calls on different caller streams do not queue behind
 // each other.  The groups pair up long with short -- 13-16 with 1-4 stages,
 // 9-12 with 5-8 -- so two evaluation kernels run at once: measured on the
@@ -273,11 +274,11 @@ static hipError_t eval_chunk(sim_ctx* c, const EvalBufs& a, int64_t n, hipStream
   return e;
 }
 
-// Chunks of kChunk plans (one chunk up to 2 kChunk).  With more than one chunk, the four stage-count
-// groups of chunk i's first pass run on two side streams (paired as
-// kGroupStream says), and its interleaved plans, continuation lists and redo
-// on a third that waits for them, while the call's stream packs and sorts
-// chunk i + 1.  The two workspaces alternate; the call's
+// Chunks of kChunk plans (one chunk up to 2 kChunk).  With more than one
+// chunk, the four k_eval launches of chunk i run on two side streams (paired
+// as kGroupStream says), its k_all beside them on a third, which then waits
+// for them and runs the continuation lists and the redo, while the call's
+// stream packs and sorts chunk i + 1.  The two workspaces alternate; the call's
 // stream waits for chunk i's last pass before reusing its workspace for
 // chunk i + 2 and, at the end, for the last one.
 extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uint64_t* out, void* stream) {
@@ -293,7 +294,7 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
   const int nbuf = n > ch ? 2 : 1;
   hipStream_t aux = s;
   SideStreams side = {};
-  constexpr int kEv = 2 * 6;   // per buffer: sorted, four group ends, deferred end
+  constexpr int kEv = 2 * 6;   // per buffer: sorted, four group ends, last pass's end
   hipEvent_t evs[kEv] = {};
   auto sorted = [&](int b) { return evs[b * 6]; };
   auto fin = [&](int b, int g) { return evs[b * 6 + 1 + g]; };

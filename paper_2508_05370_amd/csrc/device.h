@@ -2,11 +2,12 @@
 // translation units (kernels.hip and the evaluation-pass variants).
 //
 // Data flow of one chunk of plans (all in HBM):
-//   k_prep     one plan per lane: decode and check the plan, pack it into 80
-//              contiguous bytes, and count it per bucket: in the shared
-//              layout the whole plan by (kind of schedule or interleaved
-//              shape, stages, classes, longest micro-batch count), with the
-//              per-class layout each pipeline (one per replica class).
+//   k_prep     one plan per lane: decode and check the plan, pack it (with
+//              the per-class layout into one 128-byte line), and count it per
+//              bucket: in the shared layout the whole plan by (kind of
+//              schedule or interleaved shape, stages, classes, longest
+//              micro-batch count), with the per-class layout each pipeline
+//              (one per replica class).
 //   k_scan     one block: first entry of each bucket, entry and tile of each
 //              group, places of the continuation lists.
 //   k_scatter  places the plans (pipelines) in that order.
@@ -25,11 +26,13 @@
 //              remaining ones are added in one step (periodic shortcut); lanes
 //              still aperiodic after a fixed budget leave for a continuation
 //              list.  One store of the plan's time.
-//   k_variant  the overlap and zero-bubble plans, the same way.
-//   k_il       the interleaved plans.
+//   k_all      one launch for every other kind of the shared layout -- overlap,
+//              zero-bubble and interleaved plans -- and in small calls for
+//              all plans.
 //   k_cont     the first continuation list, with full wavefronts of it.
-//   k_power    what is still left, a pipeline per wavefront, by powers of the
-//              iteration's max-plus matrix.
+//   k_power    what is still left, and a first list too short for k_cont, a
+//              pipeline per wavefront, by powers of the iteration's max-plus
+//              matrix.
 //   k_redo_u64 pipelines whose time reached 2^53 ps, again in u64.
 //              Later passes raise a plan's time with atomic max.
 #pragma once
@@ -431,7 +434,8 @@ __device__ __forceinline__ Checked check_plan(const Tab& t, const CheckTab& ct, 
 // rank holds, and the optimizer state, split with ZeRO over the DP group
 // (all replicas for the non-expert parameters, replicas / EP for the
 // experts).
-__device__ __forceinline__ uint64_t state_bytes(const Tab& t, const CheckTab& ct, uint32_t tpl, uint32_t epl, uint32_t zero,
+__device__ __forceinline__ uint64_t state_bytes(const Tab& t, const CheckTab& ct, uint32_t tpl, uint32_t epl,
+                                                uint32_t zero,
                                                 uint32_t psum, bool first, bool last, uint32_t ns, double rp,
                                                 double rpx) {
   uint64_t pd = (uint64_t)ns * ct.par_layer[tpl];
@@ -455,7 +459,8 @@ __device__ __forceinline__ uint32_t checked_cut(const Checked& r, uint32_t c, ui
 }
 
 // State bytes of stage s (ns layers) of class c of a checked plan.
-__device__ __forceinline__ uint64_t class_state_bytes(const Tab& t, const CheckTab& ct, const Checked& r, uint32_t c, uint32_t s,
+__device__ __forceinline__ uint64_t class_state_bytes(const Tab& t, const CheckTab& ct, const Checked& r, uint32_t c,
+                                                      uint32_t s,
                                                       uint32_t ns) {
   const uint32_t epl = (r.hdr >> 2) & 3, zero = (r.hdr >> 10) & 1;
   // (the reciprocals are the same for every stage of the plan)
@@ -548,12 +553,16 @@ __device__ __forceinline__ bool fits_memory(const Tab& t, const CheckTab& ct, co
 }
 
 // Decode and check plan i (every rule of the plan layout); on success pack it
-// (with the per-class layout into its line at pcut).  Writes out[i] (0 = valid, to be raised
-// by the pipelines; else invalid), and when given the per-pipeline metadata
-// S | G << 5 | M << 8 | (v - 1) << 24 with the class's own S (0 = no pipeline)
-// and the bucket keys, counted in hist.
+// (with the per-class layout into its line at pcut).  Writes out[i] (0 = valid,
+// to be raised by the pipelines; else invalid), and when given the per-pipeline
+// metadata S | G << 5 | M << 8 | (v - 1) << 24 with the class's own S (0 = no
+// pipeline) and the bucket keys, counted in hist.  Bound by instruction issue
+// and the 150-odd bytes per plan: 2M plans of a sweep, beside the evaluation
+// kernels, 227 us with the rules checked class by class over the packed types,
+// 132 in one pass over them (106 with no other kernel beside it).
 template <bool kHet>
-__global__ void __launch_bounds__(256) k_prep(Tab t, const Tab* __restrict__ dtab, sim_plans pl, int64_t n, uint64_t* __restrict__ out,
+__global__ void __launch_bounds__(256) k_prep(Tab t, const Tab* __restrict__ dtab, sim_plans pl, int64_t n,
+                                              uint64_t* __restrict__ out,
                                               PackedPlan* __restrict__ packed, uint4* __restrict__ pcut,
                                               uint32_t* __restrict__ meta, uint32_t* __restrict__ hist,
                                               uint16_t* __restrict__ keys, uint32_t per) {
@@ -643,10 +652,12 @@ __global__ void __launch_bounds__(256) k_prep(Tab t, const Tab* __restrict__ dta
 // Peak memory of every (class, stage) device, one plan per lane.  A lane's 512
 // bytes of results are four rows of 128: each class's go through LDS, so that
 // the wavefront stores whole rows (one lane's stores, 512 bytes from its
-// neighbour's, would be a partial line each).
+// neighbour's, would be a partial line each).  250000 plans, 145 MB: 204 us with
+// one lane's stores, 64 by rows.
 constexpr uint32_t kMemRow = kMaxStages + 1;   // words per row in LDS
 template <bool kHet>
-__global__ void __launch_bounds__(256) k_memory(Tab t, const Tab* __restrict__ dtab, sim_plans pl, int64_t n, uint64_t* __restrict__ out) {
+__global__ void __launch_bounds__(256) k_memory(Tab t, const Tab* __restrict__ dtab, sim_plans pl, int64_t n,
+                                                uint64_t* __restrict__ out) {
   __shared__ CheckTab ct;
   __shared__ uint64_t rows[4][64 * kMemRow];
   load_check_tab(ct, dtab);
@@ -949,8 +960,8 @@ struct OvlSyncs {
   double dl, demb, dhead;
 };
 template <int kMode>
-__device__ __forceinline__ OvlSyncs overlap_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s, const DpLink& l,
-                                                  const HierShape& hs, double rp, double rpe) {
+__device__ __forceinline__ OvlSyncs overlap_syncs(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
+                                                  const DpLink& l, const HierShape& hs, double rp, double rpe) {
   OvlSyncs r = {0, 0, 0};
   const Params par(h.size(), p.tpl, p.epl);
   const double gb = (double)t.grad_bytes, pb = (double)t.param_bytes;
@@ -1560,6 +1571,8 @@ struct ZbSink {
 // stage per lane, so that the sixteen lanes of a pipeline store its records
 // side by side.  For an interleaved pipeline per virtual stage, hops and syncs
 // per device, in the first PP records, the last hop being the wrap hop.
+// 20011 plans: a pipeline per lane, its records in private memory, 97 us, a
+// stage per lane 30.
 template <bool kHet>
 __global__ void __launch_bounds__(256) k_stages(Tab t, const PackedPlan* __restrict__ packed,
                                                 const uint4* __restrict__ pcut, const uint32_t* __restrict__ meta,
@@ -1613,9 +1626,12 @@ __global__ void __launch_bounds__(256) k_stages(Tab t, const PackedPlan* __restr
 // Per-class layout: the syncs of every (class, stage) of every valid plan
 // (one plan per lane), once per plan rather than once per pipeline; lane j
 // takes plan perm[j] of the pc[512] valid plans (sorted by the length of
-// their walks).
+// their walks).  Bound by instruction issue; 3M plans 1203 us with u64 links
+// and earlier devices counted over the packed types, 951 with exact fp64
+// links, 846 with the counts in LDS, 736 with a plan in one 128-byte line.
 template <int kMode>
-__global__ void __launch_bounds__(256) k_plan_syncs(Tab t, const uint4* __restrict__ pcut, const uint32_t* __restrict__ perm,
+__global__ void __launch_bounds__(256) k_plan_syncs(Tab t, const uint4* __restrict__ pcut,
+                                                    const uint32_t* __restrict__ perm,
                                                     const uint32_t* __restrict__ pc, int64_t n,
                                                     double* __restrict__ hdp) {
   extern __shared__ uint4 lds[];
@@ -2201,7 +2217,9 @@ __device__ __forceinline__ void eval_one(const Tab& t, const Hot<kMode>& h, cons
       class_setup<kMode, false>(t, h, p, r, [&](uint32_t, uint32_t k) { return pl.first_device(p, k); },
                                 [&](uint32_t s, const StagePlace& sp) { pl.placed(s, sp); });
       if constexpr (kOvl) pl.template overlap<kMode>(t, h, p);
-      else pl.template syncs<kMode, kHier>(t, h, p, [&](uint32_t s) { return cut_at(p, s) - (s ? cut_at(p, s - 1) : 0); });
+      else
+        pl.template syncs<kMode, kHier>(t, h, p,
+                                        [&](uint32_t s) { return cut_at(p, s) - (s ? cut_at(p, s - 1) : 0); });
 #pragma unroll
       for (int s = 0; s < S; ++s) x[s] = xw[s * 64 + (kOvl ? pl.lane : lead)];
       wave_sync_lds();
@@ -2506,6 +2524,9 @@ __device__ __forceinline__ bool tile_slot(const EvalBufs& e, uint32_t q, uint32_
 // small pipelines independent of the 16-stage code.  The grid is capped at a
 // few times the blocks that fit at once (each block holds a copy of the table
 // image); its waves take the group's tiles in a fixed stride, heaviest first.
+// Bound by instruction issue.  Per 2M-plan chunk of the 512-device sweep the
+// four took 805, 714, 269 and 148 us with the recurrence on the times, u64
+// setup and 40 iterations of waiting, and take 593, 216, 268 and 91.
 template <int GRP, int kMode, bool kHet>
 __global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(const Tab* __restrict__ tp, EvalBufs e) {
   const Tab& t = *tp;
@@ -2534,8 +2555,10 @@ __global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(const T
 // sync code k_eval lacks) or in a small call also the plain ones.  One launch,
 // where one per kind and stage-count group costs 4-5 us each even if it has
 // nothing to do; the kinds' registers (200-270) allow two wavefronts per SIMD
-// whatever the stage count, so nothing is lost by their sharing a kernel.  Tiles
-// from `first` on.
+// whatever the stage count, so nothing is lost by their sharing a kernel.
+// Bound by instruction issue and the chains' latency at that occupancy: the
+// two thirds of 2.5M plans that overlap or run the zero-bubble order take 553
+// us, where kernels fed with tiles a third full took 2460.
 template <int S, int kMode>
 __device__ __forceinline__ void eval_kind(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t kind,
                                           uint32_t slot, const WaveLds& w) {

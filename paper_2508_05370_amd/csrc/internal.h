@@ -169,7 +169,9 @@ constexpr uint32_t kContWords = 80;
 // 16 - j stages; the per-class layout's plan-order counters (kPlanSortWords)
 // follow them, then the redo list.
 constexpr uint32_t kCtrStep = 32;
-__host__ __device__ constexpr uint32_t cont1_ctr(uint32_t j, uint32_t sub) { return (1 + j * kContSubs + sub) * kCtrStep; }
+__host__ __device__ constexpr uint32_t cont1_ctr(uint32_t j, uint32_t sub) {
+  return (1 + j * kContSubs + sub) * kCtrStep;
+}
 __host__ __device__ constexpr uint32_t cont2_ctr(uint32_t j) { return (1 + kMaxStages * kContSubs + j) * kCtrStep; }
 constexpr uint32_t kEvalCounters = cont2_ctr(kMaxStages);
 // Per-class layout: plans counting-sorted by (classes, total stages) before

@@ -190,7 +190,8 @@ __device__ __forceinline__ uint32_t plan_key(uint4 m) {
   return (G - 1) * 64 + st - 1;
 }
 constexpr int kPlanPer = 8;   // plans per thread of the plan-order kernels
-__global__ void __launch_bounds__(256) k_plan_hist(const uint4* __restrict__ meta, uint32_t n, uint32_t* __restrict__ pc) {
+__global__ void __launch_bounds__(256) k_plan_hist(const uint4* __restrict__ meta, uint32_t n,
+                                                   uint32_t* __restrict__ pc) {
   __shared__ uint32_t lh[kPlanBuckets];
   lh[threadIdx.x] = 0;
   __syncthreads();
@@ -241,7 +242,13 @@ __global__ void __launch_bounds__(256) k_plan_scatter(const uint4* __restrict__ 
 }
 
 // ---------------------------------------------------------------- continuation passes
-// The first list: tiles dealt round-robin to the waves of the grid.
+// The first list: tiles dealt round-robin to the waves of the grid.  Bound by
+// the serial chain of each lane's iterations (a wave of 16 stages takes 0.12 us
+// for one of them alone); most of a tile's lanes end after a few, so a sixth of
+// the lane slots is busy.  Redoing such pipelines from the start with the
+// whole loop, as a list of slots instead of states would need, took 446 us per
+// 2M-plan chunk of a random 512-device sweep where this takes 303 (126 with no
+// other kernel beside it) and k_power 149 (54).
 __global__ void __launch_bounds__(256, 2) k_cont(EvalBufs e) {
   __shared__ ContIndex<1, 64> ix;
   ix.fill(e);
@@ -293,6 +300,7 @@ __global__ void __launch_bounds__(256) k_power(EvalBufs e) {
     const double* p = e.cont + (size_t)first * (kContUnit / 8) + (size_t)(at >> 6) * (256 * S) + (at & 63u);
     const uint2 ls = *(const uint2*)&p[64 * (3 * S - 1)];
     uint32_t left = ls.x - (N - S);
+    if (lane == 0) count_skipped(e, (int)S, (int)left);
     // lanes 0-15 the state, 16-31 a, 32-47 d, 48-63 e of frame stage j
     {
       const int s = (int)j - (int)(N - S);
@@ -571,8 +579,10 @@ int eval_grids(Tab* t) {
 hipError_t launch_group(const Tab& t, const EvalBufs& e, uint32_t max_tiles, int g, hipStream_t s) {
   const bool het = e.pcut != nullptr;
   if (!het && t.ccl_hier) return hipSuccess;
-  if (t.mode == 0) return het ? launch_group_v<0, true>(t, e, max_tiles, g, s) : launch_group_v<0, false>(t, e, max_tiles, g, s);
-  if (t.mode == 1) return het ? launch_group_v<1, true>(t, e, max_tiles, g, s) : launch_group_v<1, false>(t, e, max_tiles, g, s);
+  if (t.mode == 0)
+    return het ? launch_group_v<0, true>(t, e, max_tiles, g, s) : launch_group_v<0, false>(t, e, max_tiles, g, s);
+  if (t.mode == 1)
+    return het ? launch_group_v<1, true>(t, e, max_tiles, g, s) : launch_group_v<1, false>(t, e, max_tiles, g, s);
   return het ? launch_group_v<2, true>(t, e, max_tiles, g, s) : launch_group_v<2, false>(t, e, max_tiles, g, s);
 }
 
