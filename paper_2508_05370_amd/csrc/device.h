@@ -826,11 +826,9 @@ struct Params {
 // replicas on the slowest NIC of the participating devices, or inside one
 // node when every replica of the stage sits in the same node; MoE models add
 // the expert ring over the EP-sized groups.  The same for every class of the
-// plan.  Its link is put together from each class's share of the stage:
-struct ClassLink {
-  uint32_t bx;     // slowest NIC or PCIe rate of the class's devices
-  uint32_t where;  // type << 24 | the node that holds them all (kNoNode: several)
-};
+// plan.  Its link is put together from each class's share of the stage: the
+// slowest NIC or PCIe rate of the class's devices, and type << 24 | the node
+// that holds them all (kNoNode: several).
 constexpr uint32_t kNoNode = 0xffffff;
 struct DpLink {
   double alpha;

@@ -12,7 +12,6 @@ constexpr int kMaxTypes = 16;
 constexpr int kMaxStages = 16;
 constexpr int kMaxClasses = 4;
 constexpr int kRecWords = 4;                    // per (plan, class, stage): fwd, bwd, hop, dp
-constexpr int kPlanWords = kMaxClasses * kMaxStages * kRecWords;
 // Order of a chunk.  Shared-layout plans are sorted by plan into groups of one
 // kind of schedule, stage count S and class count G, and inside a group into
 // micro-batch buckets (most micro-batches first); with the per-class layout
