@@ -14,8 +14,9 @@ ARCH = "gfx950"
 HIP_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-Wall",
              # packed fp32 VALU forms are kept out of every kernel
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# the pipeline recurrence carries integer times in fp64: no NaN/inf ever occurs,
-# which lets max() compile to one v_max_f64 (no reassociation is enabled)
+# the kernels carry whole numbers in fp64 and take no quotient by zero, so no
+# NaN or infinity arises: max() compiles to one v_max_f64 (no reassociation is
+# enabled)
 KERNEL_FLAGS = ["-ffinite-math-only"]
 # (source, object, extra flags): the common kernels, the C ABI, the table
 # builder, and one object per evaluation pass and table mode (0..2) -- the

@@ -1900,13 +1900,24 @@ __device__ __forceinline__ void raise_time(const EvalBufs& e, uint32_t slot, dou
 // them are taken in one step.  (A periodic schedule is the case of equal
 // rates, J without bound.)
 //
+// For how many steps x stays on its side of max(x, y) when x - y = dx changes by
+// dr per step (whole numbers): -dx / dr where that is positive, as the bits of
+// an fp32 number read unsigned, so that what sets no bound is larger than any
+// bound: a negative quotient, a tie (a tiny negative number), and equal rates.
+// Those divide by 2^-60, which is lost beside any other rate: the quotient is
+// negative or at least 2^60 and, as |dx| < 2^62, finite.  (This file is compiled
+// with -ffinite-math-only, under which an infinity or a NaN is an undefined
+// value.)  rcp: an fp32 reciprocal within one unit in the last place.
+template <typename Rcp>
+__host__ __device__ __forceinline__ uint32_t lead_bits(double dx, double dr, Rcp rcp) {
+  const float j = __builtin_fmaf(-(float)dx, rcp((float)dr + 0x1p-60f), -1e-30f);
+  return __builtin_bit_cast(uint32_t, j);
+}
+
 // One iteration with the rates r of the state (on return of the new state).
 // The argument of max(x, y) is x if the difference x - y, or at a tie that of
 // the rates, is positive: the sign of (x - y) + 2^-60 (rx - ry), as all are
-// integers below 2^53.  J: lowered to the bound -(x - y) / (rx - ry) where
-// that is positive, as the bits of an fp32 number read unsigned, so that
-// negative bounds (and the tiny negative number a tie gives) and NaN are
-// larger than any positive one.
+// integers below 2^53.  J: lowered to the bits of each max's bound (lead_bits).
 template <int S>
 __device__ __forceinline__ void rate_iter(Chain<S, double>& h, double (&r)[S], uint32_t& J) {
   double B = 0, rB = 0;
@@ -1914,8 +1925,7 @@ __device__ __forceinline__ void rate_iter(Chain<S, double>& h, double (&r)[S], u
     const double dx = x - y, dr = rx - ry;
     v = vmax(x, y);
     rv = __builtin_fma(dr, 0x1p-60, dx) > 0 ? rx : ry;
-    const float j = __builtin_fmaf(-(float)dx, __builtin_amdgcn_rcpf((float)dr), -1e-30f);
-    const uint32_t b = __float_as_uint(j);
+    const uint32_t b = lead_bits(dx, dr, [](float y) { return __builtin_amdgcn_rcpf(y); });
     J = b < J ? b : J;
   };
 #pragma unroll

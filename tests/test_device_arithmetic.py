@@ -1,0 +1,63 @@
+"""Device code that also compiles for the host, checked there (CPU only).
+
+The kernels are compiled with -ffinite-math-only, under which an infinity or a NaN is an undefined
+value: the arithmetic of the continuation pass's jump bound must not raise either.
+"""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2508_05370_amd", "csrc")
+
+HARNESS = r"""
+#include <fenv.h>
+#include "device.h"
+
+// lead_bits over n pairs; returns the floating-point exceptions that an infinity or a NaN raises
+extern "C" int lead_bits_all(const double* dx, const double* dr, int64_t n, uint32_t* bits) {
+  feclearexcept(FE_ALL_EXCEPT);
+  for (int64_t i = 0; i < n; ++i) bits[i] = hetsim::lead_bits(dx[i], dr[i], [](float y) { return 1.0f / y; });
+  return fetestexcept(FE_DIVBYZERO | FE_INVALID | FE_OVERFLOW);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host_build")
+    src, lib = str(d / "harness.hip"), str(d / "harness.so")
+    with open(src, "w") as f:
+        f.write(HARNESS)
+    subprocess.run(["hipcc", "--offload-host-only", "-O0", "-std=c++17", "-fPIC", "-shared", "-I", CSRC, "-I",
+                    os.path.join(ROOT, "include"), src, "-o", lib], check=True, stderr=subprocess.PIPE)
+    return C.CDLL(lib)
+
+
+def _lead_bits(host, dx, dr):
+    dx, dr = np.ascontiguousarray(dx, np.float64), np.ascontiguousarray(dr, np.float64)
+    bits = np.empty(dx.size, np.uint32)
+    host.lead_bits_all.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]
+    return host.lead_bits_all(dx.ctypes.data, dr.ctypes.data, dx.size, bits.ctypes.data), bits
+
+
+def test_jump_bound_is_finite_and_right(host):
+    """An argument of max(x, y) that leads by |dx| and loses |dr| per step leads for |dx| / |dr| steps
+    (bits of an fp32 number, shortened by 1e-5 where they are used: rounding dx and dr to fp32, the
+    reciprocal and the product lose less than 4 * 2^-24 of it); every other pair gives bits above any
+    number's, so that a minimum drops them.  Ties and equal rates, the commonest pairs, included."""
+    v = [0, 1, 2, 3, 7, 1000, 2**24 + 1, 2**40, 2**52, 2**53 - 1, 2**62]
+    v = np.array([-x for x in v] + v, np.float64)
+    dx, dr = (a.ravel() for a in np.meshgrid(v, v))
+    rng = np.random.default_rng(1)
+    r = rng.integers(-2**53, 2**53, (2, 20000)) >> rng.integers(0, 53, (2, 20000))
+    dx, dr = np.concatenate([dx, r[0]]), np.concatenate([dr, r[1]])
+    raised, bits = _lead_bits(host, dx, dr)
+    assert raised == 0
+    meets = (dx != 0) & (dr != 0) & (np.sign(dx) != np.sign(dr))
+    assert np.all(bits[~meets] > np.float32(1e9).view(np.uint32))
+    want = -dx[meets] / dr[meets]
+    assert np.all(np.abs(bits[meets].view(np.float32) - want) <= 4 * 2.0**-24 * want + 1e-30)
