@@ -200,6 +200,14 @@ static bool plans_ok(const sim_plans* p, int64_t n) {
          p->stride >= n && n >= 0;
 }
 
+// The plans from plan `off` on.
+static sim_plans from_plan(sim_plans p, int64_t off) {
+  p.hdr += off; p.cls += off; p.types += off;
+  if (p.cut) p.cut += off;
+  if (p.chdr) { p.chdr += off; p.ccut += off; }
+  return p;
+}
+
 static bool begin_event(sim_ctx* c, int kind, hipStream_t s, EventPair* e) {
   if (!c->timing) return false;
   if (hipEventCreate(&e->a) != hipSuccess) return false;
@@ -311,11 +319,11 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
   }
   void* ws = nullptr;
   const bool het = plans->chdr != nullptr;
-  const size_t bytes = work_bytes(ch, het, kContPerPlan);
+  const size_t cont = cont_bytes(ch, kContPerPlan), bytes = work_bytes(ch, het, cont);
   hipError_t e = hipMallocFromPoolAsync(&ws, nbuf * bytes, c->pool, s);
   if (e != hipSuccess) ws = nullptr;
   Work w[2];
-  for (int j = 0; ws && j < nbuf; ++j) w[j] = carve((char*)ws + j * bytes, ch, het, kContPerPlan);
+  for (int j = 0; ws && j < nbuf; ++j) w[j] = carve((char*)ws + j * bytes, ch, het, cont);
   EventPair call, ev;
   bool tcall = ws && begin_event(c, 2, s, &call);
   bool joined = true;
@@ -324,10 +332,7 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
     const int64_t cn = n - off < ch ? n - off : ch;
     const int b = (int)(i % nbuf);
     const Work& W = w[b];
-    sim_plans p = *plans;
-    p.hdr += off; p.cls += off; p.types += off;
-    if (p.cut) p.cut += off;
-    if (het) { p.chdr += off; p.ccut += off; }
+    const sim_plans p = from_plan(*plans, off);
     if (i >= 2) e = hipStreamWaitEvent(s, done(b), 0);
     if (e == hipSuccess) e = order_chunk(c, W, p, cn, out + off, true, s);
     const EvalBufs a = eval_bufs(c, W, out + off);
@@ -387,8 +392,9 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
 static_assert(SIM_NOALLOC_MAX_PLANS == kNoAllocPlans && SIM_NOALLOC_MAX_PLANS_PER_CLASS == kNoAllocPlansHet,
               "allocation-free limits");
 
-// One chunk on the caller's stream, with the workspace in the static device
-// array: no allocation, no side streams, no events.
+// A chunk or a few, one after the other on the caller's stream, with the
+// workspace in the static device array: no allocation, no side streams, no
+// events.
 extern "C" int sim_eval_plans_noalloc(sim_ctx* c, const sim_plans* plans, int64_t n, uint64_t* out, void* stream) {
   if (!c || !plans_ok(plans, n) || (n > 0 && !out)) return SIM_EINVAL;
   if (n == 0) return SIM_OK;
@@ -398,11 +404,16 @@ extern "C" int sim_eval_plans_noalloc(sim_ctx* c, const sim_plans* plans, int64_
   if (hipSetDevice(c->device) != hipSuccess) return SIM_EHIP;
   void* ws = nullptr;
   if (noalloc_scratch(c->device, &ws) != 0) return SIM_EHIP;
-  const Work W = carve(ws, n, het, kContPerPlanNoAlloc);
-  hipError_t e = order_chunk(c, W, *plans, n, out, false, s);
-  const EvalBufs a = eval_bufs(c, W, out);
-  if (e == hipSuccess) e = eval_chunk(c, a, n, s);
-  if (e == hipSuccess) e = launch_rest(c->tab, a, max_tiles(n), s);
+  const int64_t ch = noalloc_chunk(n, het);
+  const Work W = carve(ws, ch, het, noalloc_cont(ch, het));
+  hipError_t e = hipSuccess;
+  for (int64_t off = 0; off < n && e == hipSuccess; off += ch) {
+    const int64_t cn = n - off < ch ? n - off : ch;
+    const EvalBufs a = eval_bufs(c, W, out + off);
+    e = order_chunk(c, W, from_plan(*plans, off), cn, out + off, false, s);
+    if (e == hipSuccess) e = eval_chunk(c, a, cn, s);
+    if (e == hipSuccess) e = launch_rest(c->tab, a, max_tiles(cn), s);
+  }
   // a stream under graph capture records nothing here: the launches become
   // graph nodes, and the caller owns the graph's completion
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -427,10 +438,7 @@ extern "C" int sim_eval_stages(sim_ctx* c, const sim_plans* plans, int64_t n, ui
   // chunks of kChunk plans through one workspace, in order on the stream
   for (int64_t off = 0; off < n && e == hipSuccess; off += ch) {
     const int64_t cn = n - off < ch ? n - off : ch;
-    sim_plans p = *plans;
-    p.hdr += off; p.cls += off; p.types += off;
-    if (p.cut) p.cut += off;
-    if (het) { p.chdr += off; p.ccut += off; }
+    const sim_plans p = from_plan(*plans, off);
     e = launch_prep(c->tab, c->dtab, p, cn, nullptr, packed, pcut, out_class + off * 4, nullptr, nullptr, s);
     if (e == hipSuccess)
       e = launch_stages(c->tab, packed, pcut, out_class + off * 4, cn, out_stage + off * 4 * kMaxStages * 4, s);
@@ -448,10 +456,7 @@ extern "C" int sim_eval_memory(sim_ctx* c, const sim_plans* plans, int64_t n, ui
   hipError_t e = hipSuccess;
   for (int64_t off = 0; off < n && e == hipSuccess; off += kChunk) {
     const int64_t cn = n - off < kChunk ? n - off : kChunk;
-    sim_plans p = *plans;
-    p.hdr += off; p.cls += off; p.types += off;
-    if (p.cut) p.cut += off;
-    if (p.chdr) { p.chdr += off; p.ccut += off; }
+    const sim_plans p = from_plan(*plans, off);
     e = launch_memory(c->tab, c->dtab, p, cn, out_mem + off * 4 * kMaxStages, s);
   }
   track(c, s);

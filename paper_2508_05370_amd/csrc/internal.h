@@ -226,7 +226,7 @@ constexpr size_t cont_bytes(int64_t ch, size_t per_plan) {
   const size_t b = (size_t)ch * per_plan;
   return ((b > (1u << 20) ? b : (1u << 20)) + kContUnit - 1) / kContUnit * kContUnit;
 }
-constexpr size_t kContPerPlan = 224, kContPerPlanNoAlloc = 32;
+constexpr size_t kContPerPlan = 224;
 struct Carver {   // running offset
   size_t off = 0;
   constexpr size_t take(size_t bytes) {
@@ -238,11 +238,11 @@ struct Carver {   // running offset
 struct WorkOffsets {
   size_t cont, pcut, hdp, meta, perm, packed, order, hist, cursor, gstart, tstart, cinfo, keys, total;
 };
-constexpr WorkOffsets work_offsets(int64_t ch, bool het, size_t cont_per_plan) {
+constexpr WorkOffsets work_offsets(int64_t ch, bool het, size_t cont) {
   const size_t n = (size_t)ch, np = het ? 4 * n : n, nh = het ? n : 0;
   Carver c;
   WorkOffsets o = {};
-  o.cont = c.take(cont_bytes(ch, cont_per_plan));
+  o.cont = c.take(cont);
   o.pcut = c.take(nh * kHetWords * 16);
   o.hdp = c.take(nh * kMaxClasses * kMaxStages * 8);
   o.meta = c.take(nh * 16);
@@ -258,15 +258,14 @@ constexpr WorkOffsets work_offsets(int64_t ch, bool het, size_t cont_per_plan) {
   o.total = c.off;
   return o;
 }
-constexpr size_t work_bytes(int64_t ch, bool het, size_t cont_per_plan) {
-  return work_offsets(ch, het, cont_per_plan).total;
-}
-inline Work carve(void* base, int64_t ch, bool het, size_t cont_per_plan) {
-  const WorkOffsets o = work_offsets(ch, het, cont_per_plan);
+// (cont: bytes of the continuation lists, whole units)
+constexpr size_t work_bytes(int64_t ch, bool het, size_t cont) { return work_offsets(ch, het, cont).total; }
+inline Work carve(void* base, int64_t ch, bool het, size_t cont) {
+  const WorkOffsets o = work_offsets(ch, het, cont);
   char* p = (char*)base;
   Work w;
   w.cont = (double*)(p + o.cont);
-  w.cont_units = (uint32_t)(cont_bytes(ch, cont_per_plan) / kContUnit);
+  w.cont_units = (uint32_t)(cont / kContUnit);
   w.pcut = het ? (uint4*)(p + o.pcut) : nullptr;
   w.hdp = het ? (double*)(p + o.hdp) : nullptr;
   w.meta = het ? (uint32_t*)(p + o.meta) : nullptr;
@@ -284,15 +283,28 @@ inline Work carve(void* base, int64_t ch, bool het, size_t cont_per_plan) {
   return w;
 }
 
-// The allocation-free entry point's workspace: one chunk of at most
-// kNoAllocPlans plans in the shared layout or kNoAllocPlansHet in the
-// per-class layout, in a static device array (one per GPU).
+// The allocation-free entry point's workspace, a static device array (one per
+// GPU): one chunk of at most kNoAllocPlans plans in the shared layout or
+// kNoAllocPlansHet in the per-class layout.  The continuation lists take what
+// the chunk's other buffers leave.  A call whose lists would hold less than
+// kNoAllocCont bytes per plan is worked in equal chunks, one after the other:
+// random plans leave 28-58 B each in the lists, and a pipeline that finds its
+// list full keeps its wavefront to the end.  262144 plans took 1080 us in one
+// chunk with lists of 32 B per plan and take 390 us in two, 65536 per-class
+// plans 940 and 505.
 constexpr int64_t kNoAllocPlans = 1 << 18;
 constexpr int64_t kNoAllocPlansHet = 1 << 16;
-constexpr size_t kNoAllocBytes =
-    work_bytes(kNoAllocPlans, false, kContPerPlanNoAlloc) > work_bytes(kNoAllocPlansHet, true, kContPerPlanNoAlloc)
-        ? work_bytes(kNoAllocPlans, false, kContPerPlanNoAlloc)
-        : work_bytes(kNoAllocPlansHet, true, kContPerPlanNoAlloc);
+constexpr size_t kNoAllocCont = 96;
+constexpr size_t kNoAllocBytes = work_bytes(kNoAllocPlansHet, true, cont_bytes(kNoAllocPlansHet, 32));
+constexpr size_t noalloc_cont(int64_t n, bool het) {
+  return (kNoAllocBytes - work_bytes(n, het, 0)) / kContUnit * kContUnit;
+}
+constexpr int64_t noalloc_chunk(int64_t n, bool het) {
+  int64_t ch = n;
+  for (int64_t parts = 2; noalloc_cont(ch, het) < kNoAllocCont * (size_t)ch; ++parts) ch = (n + parts - 1) / parts;
+  return ch;
+}
+static_assert(work_bytes(kNoAllocPlans, false, 0) < kNoAllocBytes, "the shared layout's largest call");
 // Address of this device's copy of that array (the current device); 0 or a
 // HIP error code.
 int noalloc_scratch(int device, void** ptr);

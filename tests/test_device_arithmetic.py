@@ -1,7 +1,8 @@
-"""Device code that also compiles for the host, checked there (CPU only).
+"""Code of the library's headers that also compiles for the host, checked there (CPU only): the
+continuation pass's jump bound, and the sizes of the workspaces.
 
 The kernels are compiled with -ffinite-math-only, under which an infinity or a NaN is an undefined
-value: the arithmetic of the continuation pass's jump bound must not raise either.
+value: the arithmetic of the bound must not raise either.
 """
 import ctypes as C
 import os
@@ -16,6 +17,16 @@ CSRC = os.path.join(ROOT, "paper_2508_05370_amd", "csrc")
 HARNESS = r"""
 #include <fenv.h>
 #include "device.h"
+
+// the allocation-free workspace: bytes of it, and of a call of n plans the plans of a chunk, the chunk's bytes with its
+// continuation lists, and those of the lists
+extern "C" uint64_t noalloc_bytes() { return hetsim::kNoAllocBytes; }
+extern "C" void noalloc_call(int64_t n, int het, uint64_t* r) {
+  const int64_t ch = hetsim::noalloc_chunk(n, het);
+  r[0] = ch;
+  r[2] = hetsim::noalloc_cont(ch, het);
+  r[1] = hetsim::work_bytes(ch, het, r[2]);
+}
 
 // lead_bits over n pairs; returns the floating-point exceptions that an infinity or a NaN raises
 extern "C" int lead_bits_all(const double* dx, const double* dr, int64_t n, uint32_t* bits) {
@@ -61,3 +72,20 @@ def test_jump_bound_is_finite_and_right(host):
     assert np.all(bits[~meets] > np.float32(1e9).view(np.uint32))
     want = -dx[meets] / dr[meets]
     assert np.all(np.abs(bits[meets].view(np.float32) - want) <= 4 * 2.0**-24 * want + 1e-30)
+
+
+@pytest.mark.parametrize("het", [0, 1])
+def test_allocation_free_workspace(host, het):
+    """Every call of the allocation-free entry point fits its static workspace, at most 46 MiB, with
+    continuation lists of at least 96 bytes per plan of each chunk: random plans leave 28-58 there, and
+    a full list keeps whole wavefronts to the end of their longest pipeline."""
+    from paper_2508_05370_amd import binding as B
+    host.noalloc_bytes.restype = C.c_uint64
+    total = host.noalloc_bytes()
+    assert total <= 46 << 20
+    most = B.SIM_NOALLOC_MAX_PLANS_PER_CLASS if het else B.SIM_NOALLOC_MAX_PLANS
+    r = (C.c_uint64 * 3)()
+    for n in list(range(1, 300)) + list(range(301, most, 97)) + [most - 1, most]:
+        host.noalloc_call(C.c_int64(n), het, r)
+        chunk, used, lists = r
+        assert 1 <= chunk <= n and used <= total and lists >= max(96 * chunk, 1 << 20), (n, chunk, used, lists)
