@@ -317,11 +317,18 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
         return SIM_EHIP;
       }
   }
-  void* ws = nullptr;
   const bool het = plans->chdr != nullptr;
-  const size_t cont = cont_bytes(ch, kContPerPlan), bytes = work_bytes(ch, het, cont);
-  hipError_t e = hipMallocFromPoolAsync(&ws, nbuf * bytes, c->pool, s);
-  if (e != hipSuccess) ws = nullptr;
+  size_t cont = 0;
+  void* ws = alloc_work(
+      [&](size_t bytes) {
+        void* p = nullptr;
+        if (hipMallocFromPoolAsync(&p, bytes, c->pool, s) == hipSuccess) return p;
+        (void)hipGetLastError();   // (the launches below report the last error)
+        return (void*)nullptr;
+      },
+      nbuf, ch, het, &cont);
+  const size_t bytes = work_bytes(ch, het, cont);
+  hipError_t e = hipSuccess;
   Work w[2];
   for (int j = 0; ws && j < nbuf; ++j) w[j] = carve((char*)ws + j * bytes, ch, het, cont);
   EventPair call, ev;

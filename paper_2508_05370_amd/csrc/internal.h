@@ -227,6 +227,11 @@ constexpr size_t cont_bytes(int64_t ch, size_t per_plan) {
   return ((b > (1u << 20) ? b : (1u << 20)) + kContUnit - 1) / kContUnit * kContUnit;
 }
 constexpr size_t kContPerPlan = 224;
+// Where the device has no room for that, the lists of a chunk get this instead:
+// less in all than a call took before there were lists (168 B per plan in the
+// shared layout, 744 in the per-class layout), at up to three times the time of
+// a random sweep.
+constexpr size_t kContPerPlanLow = 32;
 struct Carver {   // running offset
   size_t off = 0;
   constexpr size_t take(size_t bytes) {
@@ -281,6 +286,17 @@ inline Work carve(void* base, int64_t ch, bool het, size_t cont) {
   w.cinfo = (uint32_t*)(p + o.cinfo);
   w.keys = (uint16_t*)(p + o.keys);
   return w;
+}
+
+// nbuf chunks' workspace from alloc (nullptr: no room); *cont: the bytes of each
+// one's lists.
+template <typename Alloc>
+inline void* alloc_work(Alloc alloc, int nbuf, int64_t ch, bool het, size_t* cont) {
+  for (const size_t per : {kContPerPlan, kContPerPlanLow}) {
+    *cont = cont_bytes(ch, per);
+    if (void* p = alloc(nbuf * work_bytes(ch, het, *cont))) return p;
+  }
+  return nullptr;
 }
 
 // The allocation-free entry point's workspace, a static device array (one per

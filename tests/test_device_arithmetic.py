@@ -28,6 +28,18 @@ extern "C" void noalloc_call(int64_t n, int het, uint64_t* r) {
   r[1] = hetsim::work_bytes(ch, het, r[2]);
 }
 
+// bytes of the workspace a call takes where the largest allocation is `most` (0: none)
+extern "C" uint64_t taken(int nbuf, int64_t ch, int het, uint64_t most) {
+  size_t got = 0, cont = 0;
+  const bool ok = hetsim::alloc_work(
+      [&](size_t bytes) {
+        got = bytes <= most ? bytes : 0;
+        return got ? (void*)&got : nullptr;
+      },
+      nbuf, ch, het, &cont);
+  return ok && got == nbuf * hetsim::work_bytes(ch, het, cont) ? got : 0;
+}
+
 // lead_bits over n pairs; returns the floating-point exceptions that an infinity or a NaN raises
 extern "C" int lead_bits_all(const double* dx, const double* dr, int64_t n, uint32_t* bits) {
   feclearexcept(FE_ALL_EXCEPT);
@@ -89,3 +101,18 @@ def test_allocation_free_workspace(host, het):
         host.noalloc_call(C.c_int64(n), het, r)
         chunk, used, lists = r
         assert 1 <= chunk <= n and used <= total and lists >= max(96 * chunk, 1 << 20), (n, chunk, used, lists)
+
+
+@pytest.mark.parametrize("het,per_plan", [(0, 168), (1, 744)])
+def test_workspace_where_memory_is_short(host, het, per_plan):
+    """A call goes on with smaller continuation lists where the device has no room for the full ones: it
+    then needs at most 2 MiB (counters, and the smallest lists) beside the bytes per plan that it took
+    before there were lists."""
+    host.taken.restype = C.c_uint64
+
+    def taken(nbuf, n, most):
+        return host.taken(nbuf, C.c_int64(n), het, C.c_uint64(most))
+    for nbuf, n in [(1, 1), (1, 4096), (1, 100003), (1, 1 << 20), (1, 1 << 22), (2, 1 << 21)]:
+        plenty, short = taken(nbuf, n, 1 << 40), nbuf * (per_plan * n + (2 << 20))
+        assert 0 < taken(nbuf, n, short) <= short and plenty >= taken(nbuf, n, short)
+        assert taken(nbuf, n, plenty) == plenty and taken(nbuf, n, 1 << 10) == 0
