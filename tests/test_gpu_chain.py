@@ -2,8 +2,8 @@
 
 The recurrence starts from a closed form of the warm-up, runs steady iterations with a shortcut for
 periodic schedules, hands schedules that stay aperiodic to the continuation lists, and ends with a drain:
-micro-batch counts around each of those lengths for every stage count, every order of passes, and lists
-that are too small for what they are offered.
+micro-batch counts around each of those lengths for every stage count, every order of passes, lists that
+one pass or the other goes on with, and lists that are too small for what they are offered.
 """
 import numpy as np
 import pytest
@@ -78,9 +78,9 @@ def test_micro_batch_counts(B, oracle_mod, workloads, batch):
             _check(B, oracle_mod, model, w["cluster"], p)
 
 
-# 16-stage plans over slow links on a workspace with room for few continuations: lists overflow
+# 16-stage plans over slow links through the allocation-free entry point
 @pytest.mark.parametrize("kind", list(KINDS))
-def test_continuation_lists_overflow(B, oracle_mod, workloads, kind):
+def test_continuation_lists_no_allocation(B, oracle_mod, workloads, kind):
     w = workloads.workload(2)
     model = dict(w["model"], global_batch=160)
     cluster = dict(w["cluster"], types=[dict(t, nic_MBps=t["nic_MBps"] // 8) for t in w["cluster"]["types"]])
@@ -90,12 +90,72 @@ def test_continuation_lists_overflow(B, oracle_mod, workloads, kind):
     _check(B, oracle_mod, model, cluster, p, noalloc=True)
 
 
-# lists long enough for both continuation passes, in calls on either side of the one-launch limit (2^17 plans)
+# first lists on either side of the length that the matrix powers take alone, in calls on either side of the one-launch
+# limit (2^17 plans); all end within the first continuation pass's budget
 @pytest.mark.parametrize("n", [60001, 131072, 131073])
-def test_continuation_lists_long(B, oracle_mod, workloads, n):
+def test_continuation_lists_96(B, oracle_mod, workloads, n):
     w = workloads.workload(2)
     model = dict(w["model"], global_batch=96)
     cluster = dict(w["cluster"], types=[dict(t, nic_MBps=t["nic_MBps"] // 8) for t in w["cluster"]["types"]])
     p = _plans(w, [13], n, 11, 96, 2)
     print("case: %d plans" % n, flush=True)
     _check(B, oracle_mod, model, cluster, p)
+
+
+def _two_class_plans(w, S, n, seed, batch):
+    """n plans of S stages and two classes of one replica each, random cuts, types and shares."""
+    rng = np.random.default_rng(seed)
+    L, K = w["model"]["L"], len(w["cluster"]["types"])
+    p = dict(hdr=np.full(n, (S - 1) << 4 | 1 << 8, np.uint32), cut=np.zeros((16, n), np.uint8),
+             cls=np.zeros((4, n), np.uint32), types=np.zeros((4, n), np.uint64))
+    p["cut"][:S - 1] = np.sort(np.argsort(rng.random((n, L - 1)), axis=1)[:, :S - 1] + 1, axis=1).T
+    p["cut"][S - 1] = L
+    share = rng.binomial(batch - 2, 0.5, n).astype(np.uint32) + 1
+    for c, m in enumerate((share, np.uint32(batch) - share)):
+        p["cls"][c] = 1 | m << 16
+        for s in range(S):
+            p["types"][c] |= rng.integers(0, K, n).astype(np.uint64) << np.uint64(4 * s)
+    return p
+
+
+# Where plans whose schedules stay aperiodic go, as the host's replay of a sample says before the GPU runs them:
+# "power": the first list is short enough for the matrix powers alone;
+# "cont":  the first continuation pass runs, and what it leaves fits the second list;
+# "full":  both lists are offered more than they hold (links a 32nd as fast).
+# In the one-launch kernel (up to 2^17 plans) and the four-launch one, every kind that uses the lists, both layouts
+# and both entry points.
+@pytest.mark.parametrize("kind,S,slow,batch,n,where", [
+    ("1f1b", 13, 8, 600, 20001, "power"),
+    ("1f1b", 13, 8, 2400, 60001, "cont"), ("1f1b", 13, 8, 2400, 131072, "cont"), ("1f1b", 13, 8, 2400, 131073, "cont"),
+    ("overlap", 13, 8, 2400, 131073, "cont"), ("zero_bubble", 13, 8, 2400, 131073, "cont"),
+    ("per_class", 13, 8, 2400, 60001, "cont"),
+    ("1f1b", 16, 32, 600, 60001, "full"), ("1f1b", 13, 32, 600, 131073, "full"), ("overlap", 16, 32, 600, 60001, "full"),
+    ("zero_bubble", 16, 32, 600, 60001, "full"), ("per_class", 16, 32, 600, 60001, "full"),
+    ("noalloc", 16, 32, 600, 60001, "full"), ("noalloc", 16, 32, 600, 262144, "full")])
+def test_continuation_lists(B, oracle_mod, workloads, kind, S, slow, batch, n, where):
+    import chain_replay as R
+    w = workloads.workload(2)
+    model = dict(w["model"], global_batch=batch)
+    cluster = dict(w["cluster"], types=[dict(t, nic_MBps=t["nic_MBps"] // slow) for t in w["cluster"]["types"]])
+    p = _two_class_plans(w, S, n, 11, batch)
+    p["hdr"] |= np.uint32(KINDS.get(kind, 0))
+    zb = kind == "zero_bubble"
+    ch = R.chains(oracle_mod.Oracle(model, cluster), p, range(400), S, zb)
+    left = ch.first_pass(zb)
+    offered = left >= R.POWER_MIN
+    second = ch.cont_pass(np.where(offered, left, 0)) >= 2 * R.POWER_MIN
+    # entries offered to the first list and held there -- (S + 2) / 48 of the pipelines, or four fifths of lists of
+    # 224 bytes per plan (264 in the larger allocation-free call) -- and offered to the second one, a quarter of it
+    first = 2 * n * offered.mean()
+    held = min(2 * n * (S + 2) / 48, 0.8 * (264 if kind == "noalloc" else 224) * n / (32 * S))
+    then = second[offered].mean() * min(first, held)
+    print("case: %s, %d plans of %d stages: %.0f then %.0f entries offered, %.0f and %.0f held" % (
+        kind, n, S, first, then, held, held / 4), flush=True)
+    if where == "power":
+        assert 1000 < first < 0.9 * R.CONT_FEW and first < held
+    elif where == "cont":
+        assert 1.2 * R.CONT_FEW < first < 0.9 * held and 500 < then < 0.9 * held / 4
+    else:
+        assert first > 1.1 * held > 1.3 * R.CONT_FEW and then > 1.1 * held / 4
+    _check(B, oracle_mod, model, cluster, workloads.as_per_class(p) if kind == "per_class" else p,
+           noalloc=kind == "noalloc")
