@@ -32,7 +32,7 @@
 //   k_cont     the first continuation list, with full wavefronts of it.
 //   k_power    what is still left, and a first list too short for k_cont, a
 //              pipeline per wavefront, by powers of the iteration's max-plus
-//              matrix.
+//              matrix (where very much is left, a pipeline per lane).
 //   k_redo_u64 pipelines whose time reached 2^53 ps, again in u64.
 //              Later passes raise a plan's time with atomic max.
 #pragma once
@@ -1696,6 +1696,16 @@ constexpr int kContBudget = 48, kPowerMin = 16;
 // call of 60000 random plans takes 226 us with the line at 4096 entries and 196
 // at 16384, one of 131072 plans 242 and 259: the line lies between.
 constexpr uint32_t kContFew = 12288;
+// A second list of more entries than this goes on lane by lane, a tile per
+// wavefront: a matrix power takes a SIMD about 6.8 us however many there are,
+// an iteration of a tile 7.5 ns per stage, so the entries of a full tile of n
+// share a run of up to kPowerCost n iterations and stages for what n powers
+// would cost; those with more left keep to the powers.  Random sweeps leave
+// 3000-10000 entries there, and gain nothing (a line at 16384 took sweeps that
+// leave 20000 from 660 to 805 us, behind the tiles' longest runs); sweeps over
+// links an eighth or a sixteenth as fast leave 70000-90000: 2^20 plans of
+// Llama-7B 1189 -> 794 us, of Mixtral 1031 -> 741.
+constexpr uint32_t kPowerLong = 32768, kPowerCost = 1000;
 
 // A wavefront of the first pass waits this many steady iterations for its
 // lanes, then the aperiodic ones leave for the continuation lists.  Most
@@ -2027,6 +2037,25 @@ __device__ __forceinline__ void cont_one(const EvalBufs& e, const double* tile) 
   for (; left > 0; --left) chain_iter<S, double, false>(h, h.a, 0, 0);
   // (M enters the end only where it is below S: never here)
   raise_time(e, slot, chain_end<S, double, false>(h, h.a, S));
+  count_skipped(e, S, skipped);
+}
+
+// An entry of the second list to its end, on its lane.
+template <int S>
+__device__ __forceinline__ void cont_rest(const EvalBufs& e, const double* tile) {
+  Chain<S, double> h;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    h.f[s] = tile[64 * s];
+    h.a[s] = tile[64 * (S + s)];
+    h.d[s] = s < S - 1 ? tile[64 * (2 * S + s)] : 0;
+  }
+  const uint2 ls = *(const uint2*)&tile[64 * (3 * S - 1)];
+  int left = (int)ls.x, skipped = 0;
+  chain_jump<S, double>(h, left, INT_MAX, skipped);
+#pragma unroll
+  for (int s = 0; s < S; ++s) h.e[s] = tile[64 * (3 * S + s)];
+  raise_time(e, ls.y, chain_end<S, double, false>(h, h.a, S));   // (M enters only where it is below S)
   count_skipped(e, S, skipped);
 }
 

@@ -60,9 +60,12 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* part) {
 // Bucket offsets: cursor[b] the first entry of bucket b in order[], gstart and
 // tstart each group's first entry and tile (grouped: shared layout, plans;
 // otherwise pipelines), and the continuation lists' places and capacities in a
-// buffer of `units` units: of the tiles of S stages (S + 2) / 48 in the first
-// list -- about twice what the first pass leaves on the random sweeps -- and a
-// quarter of that in the second, or as much of it as fits.
+// buffer of `units` units, all of it: in proportion to (S + 2) / 48 of the tiles
+// of S stages in the first list -- about twice what the first pass leaves on the
+// random sweeps -- and a quarter of that in the second.  Lists of no more than
+// that overflowed over links an eighth as fast, and a pipeline that finds its
+// list full keeps its wavefront: 240000 plans of Llama-7B 608 us, 385 with the
+// whole buffer; 2^20 plans of Mixtral at a 32nd 1507 and 1235.
 // Four threads per group, eight buckets each.
 __global__ void __launch_bounds__(1024) k_scan(const uint32_t* __restrict__ hist, uint32_t* __restrict__ cursor,
                                                uint32_t* __restrict__ gstart, uint32_t* __restrict__ tstart,
@@ -122,7 +125,16 @@ __global__ void __launch_bounds__(1024) k_scan(const uint32_t* __restrict__ hist
       }
       return y - x;
     };
-    if (total((cap1 + cap2) * S) > units) {
+    const uint32_t all = total((cap1 + cap2) * S);
+    if (all && all <= units) {
+      // what is left of the buffer too, in the same proportions: over slow
+      // links more of the shorter pipelines stay aperiodic.  (Rounded down, the
+      // factor's own error included; a list needs no more than its tiles.)
+      const double f = (double)units / (double)all * (1 - 0x1p-20);
+      const uint32_t most = on ? stiles[tid] : 0;
+      cap1 = (uint32_t)((double)cap1 * f) < most ? (uint32_t)((double)cap1 * f) : most;
+      cap2 = (uint32_t)((double)cap2 * f) < most ? (uint32_t)((double)cap2 * f) : most;
+    } else if (all) {
       // the first lists in proportion, so that the second ones fit in their quarter
       const uint64_t want = (uint64_t)total(cap1 * S) * 5;
       cap1 = (uint32_t)((uint64_t)cap1 * units * 4 / want);
@@ -282,83 +294,112 @@ __global__ void __launch_bounds__(256, 2) k_cont(EvalBufs e) {
 // 16 stages, where one lane takes 120 us.
 constexpr double kNoPath = -1e30;
 constexpr uint32_t kPowerRow = 17;   // doubles per matrix row: the row groups hit different banks
-__global__ void __launch_bounds__(256) k_power(EvalBufs e) {
+// p: the entry; A, A2: two matrices and v: 64 doubles of the wavefront's LDS
+__device__ __forceinline__ void power_one(const EvalBufs& e, const double* p, uint32_t S, double* A, double* A2,
+                                          double* v) {
   constexpr int N = kMaxStages;
-  __shared__ double mats[4][2][N * kPowerRow];
-  __shared__ double vec[4][4 * N];
-  const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t j = lane & 15u, g = lane >> 4, waves = gridDim.x * 4;
-  double* const v = vec[wave];
+  const uint32_t lane = threadIdx.x & 63u, j = lane & 15u, g = lane >> 4;
+  const uint2 ls = *(const uint2*)&p[64 * (3 * S - 1)];
+  uint32_t left = ls.x - (N - S);
+  if (lane == 0) count_skipped(e, (int)S, (int)left);
+  // lanes 0-15 the state, 16-31 a, 32-47 d, 48-63 e of frame stage j
+  {
+    const int s = (int)j - (int)(N - S);
+    const bool real = s >= 0 && !(g == 2 && s == (int)S - 1);
+    v[lane] = real ? p[64 * ((g == 3 ? 3 * S : g * S) + s)] : g == 0 || g == 3 ? kNoPath : 0;
+  }
+  wave_sync_lds();
+  Chain<N, double> h;
+#pragma unroll
+  for (int s = 0; s < N; ++s) {
+    h.f[s] = s == (int)j ? 0 : kNoPath;
+    h.a[s] = v[N + s];
+    h.d[s] = v[2 * N + s];
+    h.e[s] = v[3 * N + s];
+  }
+  double x = v[j];   // the state, one component per lane (four copies)
+  // column j of the matrix, and the longest path from state component j to the end
+  Chain<N, double> u = h;
+  const double last = chain_end<N, double, false>(u, u.a, N);
+  chain_iter<N, double, false>(h, h.a, 0, 0);
+  if (g == 0) {
+#pragma unroll
+    for (int s = 0; s < N; ++s) A[s * kPowerRow + j] = h.f[s];
+  }
+  wave_sync_lds();
+  while (true) {
+    if (left & 1) {
+      v[lane] = x;
+      wave_sync_lds();
+      double y = kNoPath;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) y = vmax(y, A[j * kPowerRow + 4 * g + k] + v[4 * g + k]);
+      y = vmax(y, __shfl_xor(y, 16));
+      x = vmax(y, __shfl_xor(y, 32));
+    }
+    left >>= 1;
+    if (!left) break;
+    double c[4] = {kNoPath, kNoPath, kNoPath, kNoPath};
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const double w = A[k * kPowerRow + j];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[i] = vmax(c[i], A[(4 * g + i) * kPowerRow + k] + w);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) A2[(4 * g + i) * kPowerRow + j] = c[i];
+    wave_sync_lds();
+    double* t = A;
+    A = A2;
+    A2 = t;
+  }
+  double T = x + last;
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) T = vmax(T, __shfl_xor(T, o));
+  if (lane == 0) raise_time(e, ls.y, T);
+  wave_sync_lds();
+}
+
+// (A second list of more than kPowerLong entries is taken by tiles of 64: the
+// entries with little left to their end on their lanes, then the others.)
+__global__ void __launch_bounds__(256) k_power(EvalBufs e) {
+  __shared__ double mats[4][2][kMaxStages * kPowerRow];
+  __shared__ double vec[4][4 * kMaxStages];
   __shared__ ContIndex<2, 1> ix;
+  __shared__ ContIndex<2, 64> tiles;
   __shared__ ContIndex<1, 1> ix1;
   ix.fill(e);
   ix1.fill(e);
-  const uint32_t n1 = ix1.entries <= kContFew ? ix1.entries : 0;
+  const bool by_tile = ix.entries > kPowerLong;
+  if (by_tile) tiles.fill(e);
+  const uint32_t n1 = ix1.entries <= kContFew ? ix1.entries : 0;   // (the second list is empty then)
+  const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t waves = gridDim.x * 4;
   uint32_t S, at, count, first;
   for (uint32_t q = blockIdx.x * 4 + wave;
-       q < n1 ? ix1.find(e, q, S, at, count, first) : ix.find(e, q - n1, S, at, count, first); q += waves) {
-    const double* p = e.cont + (size_t)first * (kContUnit / 8) + (size_t)(at >> 6) * (256 * S) + (at & 63u);
-    const uint2 ls = *(const uint2*)&p[64 * (3 * S - 1)];
-    uint32_t left = ls.x - (N - S);
-    if (lane == 0) count_skipped(e, (int)S, (int)left);
-    // lanes 0-15 the state, 16-31 a, 32-47 d, 48-63 e of frame stage j
-    {
-      const int s = (int)j - (int)(N - S);
-      const bool real = s >= 0 && !(g == 2 && s == (int)S - 1);
-      v[lane] = real ? p[64 * ((g == 3 ? 3 * S : g * S) + s)] : g == 0 || g == 3 ? kNoPath : 0;
+       by_tile ? tiles.find(e, q, S, at, count, first)
+               : q < n1 ? ix1.find(e, q, S, at, count, first) : ix.find(e, q - n1, S, at, count, first);
+       q += waves) {
+    const double* base = e.cont + (size_t)first * (kContUnit / 8);
+    if (!by_tile) {
+      power_one(e, base + (size_t)(at >> 6) * (256 * S) + (at & 63u), S, mats[wave][0], mats[wave][1], vec[wave]);
+      continue;
     }
-    wave_sync_lds();
-    Chain<N, double> h;
-#pragma unroll
-    for (int s = 0; s < N; ++s) {
-      h.f[s] = s == (int)j ? 0 : kNoPath;
-      h.a[s] = v[N + s];
-      h.d[s] = v[2 * N + s];
-      h.e[s] = v[3 * N + s];
-    }
-    double x = v[j];   // the state, one component per lane (four copies)
-    // column j of the matrix, and the longest path from state component j to the end
-    Chain<N, double> u = h;
-    const double last = chain_end<N, double, false>(u, u.a, N);
-    chain_iter<N, double, false>(h, h.a, 0, 0);
-    double* A = mats[wave][0];
-    double* A2 = mats[wave][1];
-    if (g == 0) {
-#pragma unroll
-      for (int s = 0; s < N; ++s) A[s * kPowerRow + j] = h.f[s];
-    }
-    wave_sync_lds();
-    while (true) {
-      if (left & 1) {
-        v[lane] = x;
-        wave_sync_lds();
-        double y = kNoPath;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) y = vmax(y, A[j * kPowerRow + 4 * g + k] + v[4 * g + k]);
-        y = vmax(y, __shfl_xor(y, 16));
-        x = vmax(y, __shfl_xor(y, 32));
+    base += (size_t)at * (256 * S);
+    const uint32_t n = count - 64 * at < 64 ? count - 64 * at : 64;
+    const uint32_t left = lane < n ? ((const uint2*)&base[64 * (3 * S - 1) + lane])->x : 0;
+    const bool far = left * S >= kPowerCost * n;
+    if (lane < n && !far) {
+      switch (S) {
+#define X(S_) \
+  case S_: cont_rest<S_>(e, base + lane); break;
+        X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+#undef X
+        default: break;
       }
-      left >>= 1;
-      if (!left) break;
-      double c[4] = {kNoPath, kNoPath, kNoPath, kNoPath};
-#pragma unroll
-      for (int k = 0; k < N; ++k) {
-        const double w = A[k * kPowerRow + j];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c[i] = vmax(c[i], A[(4 * g + i) * kPowerRow + k] + w);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) A2[(4 * g + i) * kPowerRow + j] = c[i];
-      wave_sync_lds();
-      double* t = A;
-      A = A2;
-      A2 = t;
     }
-    double T = x + last;
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) T = vmax(T, __shfl_xor(T, o));
-    if (lane == 0) raise_time(e, ls.y, T);
-    wave_sync_lds();
+    for (uint64_t todo = __ballot(far); todo; todo &= todo - 1)
+      power_one(e, base + __builtin_ctzll(todo), S, mats[wave][0], mats[wave][1], vec[wave]);
   }
 }
 

@@ -131,7 +131,7 @@ def _two_class_plans(w, S, n, seed, batch):
     ("per_class", 13, 8, 2400, 60001, "cont"),
     ("1f1b", 16, 32, 600, 60001, "full"), ("1f1b", 13, 32, 600, 131073, "full"), ("overlap", 16, 32, 600, 60001, "full"),
     ("zero_bubble", 16, 32, 600, 60001, "full"), ("per_class", 16, 32, 600, 60001, "full"),
-    ("noalloc", 16, 32, 600, 60001, "full"), ("noalloc", 16, 32, 600, 262144, "full")])
+    ("noalloc", 16, 16, 600, 60001, "cont"), ("noalloc", 16, 32, 600, 262144, "full")])
 def test_continuation_lists(B, oracle_mod, workloads, kind, S, slow, batch, n, where):
     import chain_replay as R
     w = workloads.workload(2)
@@ -144,10 +144,10 @@ def test_continuation_lists(B, oracle_mod, workloads, kind, S, slow, batch, n, w
     left = ch.first_pass(zb)
     offered = left >= R.POWER_MIN
     second = ch.cont_pass(np.where(offered, left, 0)) >= 2 * R.POWER_MIN
-    # entries offered to the first list and held there -- (S + 2) / 48 of the pipelines, or four fifths of lists of
-    # 224 bytes per plan (264 in the larger allocation-free call) -- and offered to the second one, a quarter of it
+    # entries offered to the first list and held there -- four fifths of lists of 224 bytes per plan (of 690 and 264 in
+    # the allocation-free calls) -- and offered to the second one, a quarter of it
     first = 2 * n * offered.mean()
-    held = min(2 * n * (S + 2) / 48, 0.8 * (264 if kind == "noalloc" else 224) * n / (32 * S))
+    held = 0.8 * (224 if kind != "noalloc" else 264 if n > 131072 else 690) * n / (32 * S)
     then = second[offered].mean() * min(first, held)
     print("case: %s, %d plans of %d stages: %.0f then %.0f entries offered, %.0f and %.0f held" % (
         kind, n, S, first, then, held, held / 4), flush=True)
@@ -159,3 +159,63 @@ def test_continuation_lists(B, oracle_mod, workloads, kind, S, slow, batch, n, w
         assert first > 1.1 * held > 1.3 * R.CONT_FEW and then > 1.1 * held / 4
     _check(B, oracle_mod, model, cluster, workloads.as_per_class(p) if kind == "per_class" else p,
            noalloc=kind == "noalloc")
+
+
+# Second lists of more than 32768 entries, which go on lane by lane: all of them (600 micro-batches), and all but the
+# few that have thousands of iterations left and keep to the matrix powers (replicas of 5700 short micro-batches among
+# replicas of 475)
+@pytest.mark.parametrize("kind,far", [("1f1b", False), ("zero_bubble", False), ("per_class", False), ("1f1b", True)])
+def test_long_second_list(B, oracle_mod, workloads, kind, far):
+    import chain_replay as R
+    S, n, batch, slow = 13, 400001, 6000 if far else 600, 32
+    w = workloads.workload(2)
+    model = dict(w["model"], global_batch=batch)
+    cluster = w["cluster"]
+    if far:
+        model["seq"], cluster = 256, workloads.cluster_random(2, [40, 40, 40])
+    cluster = dict(cluster, types=[dict(t, nic_MBps=t["nic_MBps"] // slow) for t in cluster["types"]])
+    p = _two_class_plans(w, S, n, 11, batch)
+    if far:
+        reps = np.where(np.random.default_rng(3).random(n) < 0.06, 1, 12).astype(np.uint32)
+        share = np.minimum(p["cls"][0] >> 16, 300).astype(np.uint32)
+        p["cls"][0], p["cls"][1] = 1 | share << 16, reps | (np.uint32(batch) - share) << 16
+    p["hdr"] |= np.uint32(KINDS.get(kind, 0))
+    zb = kind == "zero_bubble"
+    ch = R.chains(oracle_mod.Oracle(model, cluster), p, range(400), S, zb)
+    left = ch.first_pass(zb)
+    offered = left >= R.POWER_MIN
+    left = ch.cont_pass(np.where(offered, left, 0))
+    second = left >= 2 * R.POWER_MIN
+    # (capacities as in test_continuation_lists)
+    held = 0.8 * 224 * n / (32 * S)
+    then = min(second[offered].mean() * min(2 * n * offered.mean(), held), held / 4)
+    print("case: %s, far %d: %.0f entries in the second list, %.2f %% of them far" % (
+        kind, far, then, 100 * np.mean(left[second] * S >= 64000)), flush=True)
+    assert then > 1.1 * 32768 and np.any(left[second] * S >= 64000) == far
+    _check(B, oracle_mod, model, cluster, workloads.as_per_class(p) if kind == "per_class" else p)
+
+
+# Sweeps over slow links beside the same plans over the workload's own: 3.0 times as long with one matrix power per
+# entry of the second list (70000 of them), 2.0 lane by lane
+def test_pace_over_slow_links(B, workloads):
+    import torch
+    w = workloads.workload(2)
+    dp = B.device_plans(workloads.plans(w, 0, 1 << 20))
+    out = torch.empty(1 << 20, dtype=torch.int64, device="cuda")
+    took = []
+    for slow in (1, 8):
+        print("case: links 1/%d" % slow, flush=True)
+        sim = B.Sim(w["model"], dict(w["cluster"], types=[dict(t, nic_MBps=t["nic_MBps"] // slow)
+                                                           for t in w["cluster"]["types"]]))
+        t = []
+        for i in range(14):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            sim.eval_plans(dp, out=out)
+            b.record()
+            b.synchronize()
+            if i >= 3:
+                t.append(a.elapsed_time(b))
+        took.append(sorted(t)[len(t) // 2])
+    print("%.0f us, slow links %.0f" % (took[0] * 1e3, took[1] * 1e3), flush=True)
+    assert took[1] < 2.5 * took[0]
