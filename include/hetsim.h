@@ -240,7 +240,7 @@ int sim_eval_plans(sim_ctx* ctx, const sim_plans* plans, int64_t n, uint64_t* ou
  * capture, tight serving loops, harnesses that forbid allocation): the same
  * results as sim_eval_plans, computed by the same kernels, with no
  * hipMalloc, hipFree, pool allocation, stream or event creation.  The
- * workspace is a static device array of about 46 MiB that every GPU the
+ * workspace is a static device array of about 82 MiB that every GPU the
  * library runs on holds from the first sim_create on it until the process
  * ends.  Every call on one GPU shares that GPU's array: calls that overlap
  * in time on one GPU (on two streams, from two threads or two contexts)

@@ -399,9 +399,8 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
 static_assert(SIM_NOALLOC_MAX_PLANS == kNoAllocPlans && SIM_NOALLOC_MAX_PLANS_PER_CLASS == kNoAllocPlansHet,
               "allocation-free limits");
 
-// A chunk or a few, one after the other on the caller's stream, with the
-// workspace in the static device array: no allocation, no side streams, no
-// events.
+// One chunk on the caller's stream, with the workspace in the static device
+// array: no allocation, no side streams, no events.
 extern "C" int sim_eval_plans_noalloc(sim_ctx* c, const sim_plans* plans, int64_t n, uint64_t* out, void* stream) {
   if (!c || !plans_ok(plans, n) || (n > 0 && !out)) return SIM_EINVAL;
   if (n == 0) return SIM_OK;
@@ -411,16 +410,11 @@ extern "C" int sim_eval_plans_noalloc(sim_ctx* c, const sim_plans* plans, int64_
   if (hipSetDevice(c->device) != hipSuccess) return SIM_EHIP;
   void* ws = nullptr;
   if (noalloc_scratch(c->device, &ws) != 0) return SIM_EHIP;
-  const int64_t ch = noalloc_chunk(n, het);
-  const Work W = carve(ws, ch, het, noalloc_cont(ch, het));
-  hipError_t e = hipSuccess;
-  for (int64_t off = 0; off < n && e == hipSuccess; off += ch) {
-    const int64_t cn = n - off < ch ? n - off : ch;
-    const EvalBufs a = eval_bufs(c, W, out + off);
-    e = order_chunk(c, W, from_plan(*plans, off), cn, out + off, false, s);
-    if (e == hipSuccess) e = eval_chunk(c, a, cn, s);
-    if (e == hipSuccess) e = launch_rest(c->tab, a, max_tiles(cn), s);
-  }
+  const Work W = carve(ws, n, het, noalloc_cont(n, het));
+  const EvalBufs a = eval_bufs(c, W, out);
+  hipError_t e = order_chunk(c, W, *plans, n, out, false, s);
+  if (e == hipSuccess) e = eval_chunk(c, a, n, s);
+  if (e == hipSuccess) e = launch_rest(c->tab, a, max_tiles(n), s);
   // a stream under graph capture records nothing here: the launches become
   // graph nodes, and the caller owns the graph's completion
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

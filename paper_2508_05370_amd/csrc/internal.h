@@ -301,26 +301,20 @@ inline void* alloc_work(Alloc alloc, int nbuf, int64_t ch, bool het, size_t* con
 
 // The allocation-free entry point's workspace, a static device array (one per
 // GPU): one chunk of at most kNoAllocPlans plans in the shared layout or
-// kNoAllocPlansHet in the per-class layout.  The continuation lists take what
-// the chunk's other buffers leave.  A call whose lists would hold less than
-// kNoAllocCont bytes per plan is worked in equal chunks, one after the other:
-// random plans leave 28-58 B each in the lists, and a pipeline that finds its
-// list full keeps its wavefront to the end.  262144 plans took 1080 us in one
-// chunk with lists of 32 B per plan and take 390 us in two, 65536 per-class
-// plans 940 and 505.
+// kNoAllocPlansHet in the per-class layout, with lists of at least kContPerPlan
+// bytes per plan; they take what the chunk's other buffers leave.  A pipeline
+// that finds its list full keeps its wavefront to the end: with 46 MiB, and a
+// call whose lists would have less than 96 bytes per plan in two chunks, 262144
+// plans took 390 us and take 255, and 240000 plans over links a 16th as fast
+// took 1310 and take 380.
 constexpr int64_t kNoAllocPlans = 1 << 18;
 constexpr int64_t kNoAllocPlansHet = 1 << 16;
-constexpr size_t kNoAllocCont = 96;
-constexpr size_t kNoAllocBytes = work_bytes(kNoAllocPlansHet, true, cont_bytes(kNoAllocPlansHet, 32));
+constexpr size_t larger(size_t a, size_t b) { return a > b ? a : b; }
+constexpr size_t kNoAllocBytes = larger(work_bytes(kNoAllocPlans, false, cont_bytes(kNoAllocPlans, kContPerPlan)),
+                                        work_bytes(kNoAllocPlansHet, true, cont_bytes(kNoAllocPlansHet, kContPerPlan)));
 constexpr size_t noalloc_cont(int64_t n, bool het) {
   return (kNoAllocBytes - work_bytes(n, het, 0)) / kContUnit * kContUnit;
 }
-constexpr int64_t noalloc_chunk(int64_t n, bool het) {
-  int64_t ch = n;
-  for (int64_t parts = 2; noalloc_cont(ch, het) < kNoAllocCont * (size_t)ch; ++parts) ch = (n + parts - 1) / parts;
-  return ch;
-}
-static_assert(work_bytes(kNoAllocPlans, false, 0) < kNoAllocBytes, "the shared layout's largest call");
 // Address of this device's copy of that array (the current device); 0 or a
 // HIP error code.
 int noalloc_scratch(int device, void** ptr);

@@ -10,7 +10,7 @@ namespace hetsim {
 
 // ---------------------------------------------------------------- allocation-free workspace
 // The workspace of sim_eval_plans_noalloc: one chunk's buffers (kNoAllocBytes,
-// about 46 MiB) in a static device array.  Every GPU the library runs on holds
+// about 82 MiB) in a static device array.  Every GPU the library runs on holds
 // its own copy until the process ends; host code reaches it only through the
 // address hipGetSymbolAddress returns for the current device (the array's
 // name in host code is a host-side stand-in, not a device address).

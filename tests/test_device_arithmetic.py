@@ -18,14 +18,12 @@ HARNESS = r"""
 #include <fenv.h>
 #include "device.h"
 
-// the allocation-free workspace: bytes of it, and of a call of n plans the plans of a chunk, the chunk's bytes with its
-// continuation lists, and those of the lists
+// the allocation-free workspace: bytes of it, and of a call of n plans its bytes with its continuation lists, and those
+// of the lists
 extern "C" uint64_t noalloc_bytes() { return hetsim::kNoAllocBytes; }
 extern "C" void noalloc_call(int64_t n, int het, uint64_t* r) {
-  const int64_t ch = hetsim::noalloc_chunk(n, het);
-  r[0] = ch;
-  r[2] = hetsim::noalloc_cont(ch, het);
-  r[1] = hetsim::work_bytes(ch, het, r[2]);
+  r[1] = hetsim::noalloc_cont(n, het);
+  r[0] = hetsim::work_bytes(n, het, r[1]);
 }
 
 // bytes of the workspace a call takes where the largest allocation is `most` (0: none)
@@ -88,19 +86,20 @@ def test_jump_bound_is_finite_and_right(host):
 
 @pytest.mark.parametrize("het", [0, 1])
 def test_allocation_free_workspace(host, het):
-    """Every call of the allocation-free entry point fits its static workspace, at most 46 MiB, with
-    continuation lists of at least 96 bytes per plan of each chunk: random plans leave 28-58 there, and
-    a full list keeps whole wavefronts to the end of their longest pipeline."""
+    """Every call of the allocation-free entry point fits its static workspace, at most 82 MiB, with
+    continuation lists of at least sim_eval_plans' 224 bytes per plan: random plans leave 28-58 there,
+    sweeps over slow links more than 96, and a full list keeps whole wavefronts to the end of their
+    longest pipeline."""
     from paper_2508_05370_amd import binding as B
     host.noalloc_bytes.restype = C.c_uint64
     total = host.noalloc_bytes()
-    assert total <= 46 << 20
+    assert total <= 82 << 20
     most = B.SIM_NOALLOC_MAX_PLANS_PER_CLASS if het else B.SIM_NOALLOC_MAX_PLANS
-    r = (C.c_uint64 * 3)()
+    r = (C.c_uint64 * 2)()
     for n in list(range(1, 300)) + list(range(301, most, 97)) + [most - 1, most]:
         host.noalloc_call(C.c_int64(n), het, r)
-        chunk, used, lists = r
-        assert 1 <= chunk <= n and used <= total and lists >= max(96 * chunk, 1 << 20), (n, chunk, used, lists)
+        used, lists = r
+        assert used <= total and lists >= max(224 * n, 1 << 20), (n, used, lists)
 
 
 @pytest.mark.parametrize("het,per_plan", [(0, 168), (1, 744)])

@@ -144,10 +144,10 @@ def test_continuation_lists(B, oracle_mod, workloads, kind, S, slow, batch, n, w
     left = ch.first_pass(zb)
     offered = left >= R.POWER_MIN
     second = ch.cont_pass(np.where(offered, left, 0)) >= 2 * R.POWER_MIN
-    # entries offered to the first list and held there -- four fifths of lists of 224 bytes per plan (of 690 and 264 in
-    # the allocation-free calls) -- and offered to the second one, a quarter of it
+    # entries offered to the first list and held there -- four fifths of lists of 224 bytes per plan (of 1300 in
+    # the smaller allocation-free call) -- and offered to the second one, a quarter of it
     first = 2 * n * offered.mean()
-    held = 0.8 * (224 if kind != "noalloc" else 264 if n > 131072 else 690) * n / (32 * S)
+    held = 0.8 * (1300 if kind == "noalloc" and n < 131072 else 224) * n / (32 * S)
     then = second[offered].mean() * min(first, held)
     print("case: %s, %d plans of %d stages: %.0f then %.0f entries offered, %.0f and %.0f held" % (
         kind, n, S, first, then, held, held / 4), flush=True)

@@ -1,13 +1,10 @@
-"""Calls of the allocation-free entry point near its limits, which it works in chunks: the results of
-sim_eval_plans bit for bit around the size where a second chunk begins, also replayed from a HIP graph,
-and at its pace.
+"""Calls of the allocation-free entry point near its limits: the results of sim_eval_plans bit for bit, also
+replayed from a HIP graph, and at its pace.
 """
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
-
-SHARED_EDGE, PER_CLASS_EDGE = 242282, 60266   # the largest calls of one chunk
 
 
 @pytest.fixture(scope="module")
@@ -34,8 +31,8 @@ def _plans(workloads, w, layout, n):
 
 
 @pytest.mark.parametrize("layout,n,offset", [
-    ("shared", SHARED_EDGE, 0), ("shared", SHARED_EDGE + 1, 1), ("shared", 262143, 3),
-    ("per_class", PER_CLASS_EDGE, 0), ("per_class", PER_CLASS_EDGE + 1, 1), ("per_class", 65535, 2)])
+    ("shared", 242282, 0), ("shared", 242283, 1), ("shared", 262143, 3), ("shared", 262144, 0),
+    ("per_class", 60266, 0), ("per_class", 60267, 1), ("per_class", 65535, 2), ("per_class", 65536, 0)])
 def test_matches_eval_plans(torch, B, workloads, layout, n, offset):
     w = workloads.workload(3)
     sim = B.Sim(w["model"], w["cluster"])
@@ -69,16 +66,18 @@ def test_replayed_from_a_graph(torch, B, workloads, layout, n):
         assert torch.equal(out, want), shift
 
 
-# the allocating entry point has continuation lists of 224 bytes per plan; lists that fill up cost a
-# factor of three at these sizes, a second chunk's launches half
-@pytest.mark.parametrize("layout,n", [("shared", 242000), ("shared", 262144), ("per_class", 30000),
-                                      ("per_class", 65536)])
-def test_pace(torch, B, workloads, layout, n):
+# Both entry points have continuation lists of at least 224 bytes per plan.  With 32 in the allocation-free one, whose
+# lists then overflowed, the ratio was 2.6 to 3.7; with 96, over links a 16th as fast, 3.5 (240000 plans)
+@pytest.mark.parametrize("layout,n,slow", [("shared", 240000, 1), ("shared", 262144, 1), ("per_class", 30000, 1),
+                                           ("per_class", 65536, 1), ("shared", 240000, 16), ("per_class", 60000, 16)])
+def test_pace(torch, B, workloads, layout, n, slow):
     w = workloads.workload(3)
-    sim = B.Sim(w["model"], w["cluster"])
+    c = dict(w["cluster"], types=[dict(t, nic_MBps=t["nic_MBps"] // slow) for t in w["cluster"]["types"]])
+    c["nic_MBps_dev"] = np.asarray(c["nic_MBps_dev"]) // np.uint32(slow)
+    sim = B.Sim(w["model"], c)
     dp = B.device_plans(_plans(workloads, w, layout, n))
     out = torch.empty(n, dtype=torch.int64, device="cuda")
-    print("case: pace of %d %s plans" % (n, layout), flush=True)
+    print("case: pace of %d %s plans, links 1/%d" % (n, layout, slow), flush=True)
 
     def median(call):
         t = []
@@ -91,6 +90,6 @@ def test_pace(torch, B, workloads, layout, n):
             if i >= 3:
                 t.append(a.elapsed_time(b))
         return sorted(t)[len(t) // 2]
-    slow, fast = median(sim.eval_plans_noalloc), median(sim.eval_plans)
-    print("allocation-free %.0f us, allocating %.0f" % (slow * 1e3, fast * 1e3), flush=True)
-    assert slow < 2.1 * fast
+    free, fast = median(sim.eval_plans_noalloc), median(sim.eval_plans)
+    print("allocation-free %.0f us, allocating %.0f" % (free * 1e3, fast * 1e3), flush=True)
+    assert free < 1.5 * fast
