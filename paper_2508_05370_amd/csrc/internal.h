@@ -221,12 +221,20 @@ struct Work {
 };
 // Bytes of the continuation lists: about what k_scan would take for a random
 // sweep's chunk (two to three pipelines per plan), at least one tile of every
-// list.
+// list.  Small calls get up to four times as much: over slow links up to a half
+// of their pipelines stay aperiodic, and an overfull list keeps wavefronts to
+// the end (60000 per-class plans over links a 16th as fast 602 us with
+// kContPerPlan).
 constexpr size_t cont_bytes(int64_t ch, size_t per_plan) {
   const size_t b = (size_t)ch * per_plan;
   return ((b > (1u << 20) ? b : (1u << 20)) + kContUnit - 1) / kContUnit * kContUnit;
 }
 constexpr size_t kContPerPlan = 224;
+constexpr size_t kContSmall = (size_t)64 << 20;   // bytes below which a call's lists may exceed kContPerPlan
+constexpr size_t cont_per_plan(int64_t ch) {
+  const size_t n = (size_t)ch, most = kContSmall / n;
+  return most <= kContPerPlan ? kContPerPlan : most < 4 * kContPerPlan ? most : 4 * kContPerPlan;
+}
 // Where the device has no room for that, the lists of a chunk get this instead:
 // less in all than a call took before there were lists (168 B per plan in the
 // shared layout, 744 in the per-class layout), at up to three times the time of
@@ -292,7 +300,7 @@ inline Work carve(void* base, int64_t ch, bool het, size_t cont) {
 // one's lists.
 template <typename Alloc>
 inline void* alloc_work(Alloc alloc, int nbuf, int64_t ch, bool het, size_t* cont) {
-  for (const size_t per : {kContPerPlan, kContPerPlanLow}) {
+  for (const size_t per : {cont_per_plan(ch), kContPerPlanLow}) {
     *cont = cont_bytes(ch, per);
     if (void* p = alloc(nbuf * work_bytes(ch, het, *cont))) return p;
   }

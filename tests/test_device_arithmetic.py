@@ -115,3 +115,14 @@ def test_workspace_where_memory_is_short(host, het, per_plan):
         plenty, short = taken(nbuf, n, 1 << 40), nbuf * (per_plan * n + (2 << 20))
         assert 0 < taken(nbuf, n, short) <= short and plenty >= taken(nbuf, n, short)
         assert taken(nbuf, n, plenty) == plenty and taken(nbuf, n, 1 << 10) == 0
+
+
+@pytest.mark.parametrize("het,other", [(0, 110), (1, 700)])
+def test_small_calls_have_longer_lists(host, het, other):
+    """Lists of a call, from its workspace without the other buffers (about `other` bytes per plan): 224
+    bytes per plan, in calls of up to 300000 plans as much as 64 MiB or 896 bytes per plan, the smaller."""
+    host.taken.restype = C.c_uint64
+    for n in (1, 1000, 30000, 60000, 120000, 240000, 300000, 1 << 20, 1 << 22):
+        lists = host.taken(1, C.c_int64(n), het, C.c_uint64(1 << 40)) - other * n
+        want = max(224 * n, min(896 * n, 64 << 20), 1 << 20)
+        assert abs(lists - want) < (2 << 20) + want // 16, (n, lists, want)
