@@ -6,13 +6,16 @@ of every replica class, the DP sync, and the argmin over all plans.  Plans are
 resident in HBM before timing starts.
 
 Prints one JSON line.  Roofline: the evaluation is bound by VALU issue.  The
-work of one call is counted from the plans themselves: every schedule node
-the evaluation executes -- all nodes of the 1F1B recurrence (3 fp64 VALU
-ops per node with a cross-stage input, 1 without), less those the periodic
-shortcut skips, which the library counts on the device -- plus the cost model's per-stage and per-plan setup arithmetic priced
-by formula.  The peak is the lower of the chip's issue rate (256 CUs x 64
-lanes x 2.4 GHz) and the node probe's measured rate times 3, measured in the
-same run.
+work of one call is counted from the plans themselves, as the kernels execute
+it: the 1F1B recurrence on potentials (its constants, warm-up in closed form,
+4 fp64 VALU ops per stage and steady iteration, and the drain), less the steady
+iterations that are skipped, which the library counts on the device, plus the
+cost model's per-stage and per-plan setup arithmetic priced by formula.  (The
+few schedules taken by matrix powers count as skipped; their products are not
+counted.)  The rate of the schedule's nodes at 3 ops each, done or skipped, is
+reported beside it under a name of its own.  The peak is the lower of the
+chip's issue rate (256 CUs x 64 lanes x 2.4 GHz) and the node probe's measured
+rate times 3, measured in the same run.
 """
 import argparse
 import hashlib
@@ -32,10 +35,11 @@ METRIC = "candidate plans evaluated/sec on 1 MI355X; % of binding roofline"
 MAXU = np.uint64(2**64 - 1)
 
 # Setup arithmetic of the cost model, priced in gfx950 VALU instructions per
-# operation of the definition: u64 add/sub 2, u64 max 3, u64 x u32 product 2,
-# link time ceil(bytes x beta / 2^16) with a 96-bit product 8, ceiling
-# division by a run-time divisor 12, range maximum over a sparse table 4.
-PRICE = dict(add=2, max=3, mul=2, link=8, cdiv=12, rmax=4)
+# operation of the definition as the kernels run it, whole numbers in fp64:
+# add/sub, max and product 1, link time ceil(bytes x beta / 2^16) with its
+# rounding error 8, ceiling division by a run-time divisor 6, range maximum over
+# a sparse table 4.
+PRICE = dict(add=1, max=1, mul=1, link=8, cdiv=6, rmax=4)
 P = PRICE
 # per (pipeline, stage): stage compute (two prefix differences), the stage's
 # place in its pool (one bump-pointer add), its slowest fabric and NIC
@@ -79,6 +83,28 @@ def pipeline_ops(p, valid, per_node=3, first=1):
         M = np.where(has, -(-nmb // np.maximum(reps, 1)), 0)
         ops += 2 * M * (per_node * (S - 1) + first)
     return ops
+
+
+def chain_ops(p, valid):
+    """VALU ops of the recurrence on potentials per plan, as executed: outside the steady iterations
+    (constants, closed-form warm-up, drain), and in all M - S steady iterations of each pipeline; and
+    what the skipped-work counter charges for the latter (6 S - 4 each)."""
+    f = _fields(p)
+    S, G = f["S"], f["G"]
+    ends, steady, charged = (np.zeros(S.shape[0], dtype=np.int64) for _ in range(3))
+    for c in range(4):
+        reps = (p["cls"][c] & 0xFFFF).astype(np.int64)
+        nmb = (p["cls"][c] >> 16).astype(np.int64)
+        has = (G > c) & valid & (reps > 0)
+        M = np.where(has, -(-nmb // np.maximum(reps, 1)), 0)
+        k = np.minimum(S, M)
+        # d, phi, e: 9 per stage; the drain's backwards 3 per stage and step; a, F: 4; the end's triangle of
+        # steps and its S exits 4 each
+        ends += np.where(has, 13 * S + 3 * (k * S - k * (k + 1) // 2) + 4 * (k * (k - 1) // 2) + 4 * S, 0)
+        left = np.maximum(M - S, 0)
+        steady += left * np.maximum(4 * S - 3, 1)
+        charged += left * (6 * S - 4)
+    return ends, steady, charged
 
 
 def setup_ops(p, valid, moe):
@@ -420,7 +446,7 @@ def main():
         pipe_ms, pipe_n = sim.get_timing(0)
         setup_ms, setup_n = sim.get_timing(1)
         call_ms, call_n = sim.get_timing(2)
-        defer_ms, defer_n = sim.get_timing(3)
+        later_ms, _ = sim.get_timing(3)
         node_rate = B.measure_node_rate()
         peak = min(PEAK_VALU_SPEC, 3 * node_rate)
         # one launch = one sim_eval_plans call (all its kernels, on all its
@@ -428,7 +454,9 @@ def main():
         avg_ms = call_ms / max(call_n, 1)
         full_per_launch = float(ops.sum()) / calls_per_step
         int32_per_launch = float(pipeline_ops(p, valid, 7, 2).sum()) / calls_per_step
-        rec_per_launch = full_per_launch - skipped / timed / calls_per_step
+        skipped_per_launch = skipped / timed / calls_per_step
+        ends, steady, charged = (float(x.sum()) / calls_per_step for x in chain_ops(p, valid))
+        rec_per_launch = ends + steady * max(0.0, 1 - skipped_per_launch / max(charged, 1.0))
         setup_per_launch = float(setup.sum()) / calls_per_step
         work = rec_per_launch + setup_per_launch
         achieved = work / (avg_ms * 1e-3)
@@ -440,13 +468,14 @@ def main():
                 "avg_launch_ms": round(avg_ms, 4), "launches": call_n,
                 "work_per_launch": work,
                 "recurrence_ops_per_launch": rec_per_launch, "setup_ops_per_launch": setup_per_launch,
-                "full_recurrence_ops_per_launch": full_per_launch,
-                "skipped_by_periodic_shortcut": round(1 - rec_per_launch / full_per_launch, 4),
+                "skipped_steady_iterations": round(skipped_per_launch / max(charged, 1.0), 4),
                 "peak_spec": round(PEAK_VALU_SPEC / 1e12, 3),
                 "peak_measured_node_probe": round(3 * node_rate / 1e12, 3),
                 "node_probe_nodes_per_s": round(node_rate, 1),
-                # labelled comparisons, not the roofline fraction: the int32 count of every node (7 ops with a
-                # cross-stage input, 2 without) whether the shortcut skips it or not, over the call
+                # labelled comparisons, not the roofline fraction: every schedule node whether it is skipped or not,
+                # over the call, at 3 fp64 ops (1 without a cross-stage input) and at 7 (2) in int32
+                "all_nodes_ops_per_launch": full_per_launch,
+                "all_nodes_rate_over_peak": round(full_per_launch / (avg_ms * 1e-3) / peak, 4),
                 "int32_all_nodes_ops_per_launch": int32_per_launch,
                 "int32_all_nodes_rate_over_peak": round(int32_per_launch / (avg_ms * 1e-3) / peak, 4)}
         # every VALU instruction the evaluation kernels execute (setup, recurrence, syncs), from counters
@@ -456,7 +485,7 @@ def main():
         extra = {"timed_steps_with_kernel_events": timed,
                  "prep_ms_per_step": round(setup_ms / timed, 4),
                  "first_pass_span_ms_per_step": round(pipe_ms / timed, 4),
-                 "deferred_pass_ms_per_step": round(defer_ms / timed, 4),
+                 "later_passes_ms_per_step": round(later_ms / timed, 4),
                  "eval_call_ms_per_step": round(call_ms / timed, 4)}
 
     # The same sweep with device memory capacities: plans that do not fit become invalid

@@ -277,7 +277,7 @@ def _steady_periodic_at(S, M, f, b, c, limit):
 def test_link_bound_schedules(torch, B, oracle_mod, workloads, slow):
     """Plans whose pipeline hops dominate (NICs and fabrics slowed `slow` times):
     many schedules never settle into a one-iteration period, so the evaluator's
-    deferred full-loop pass carries a large share of the pipelines."""
+    continuation passes carry a large share of the pipelines."""
     import copy
     w = workloads.workload(2)
     c = copy.deepcopy(w["cluster"])
@@ -293,7 +293,7 @@ def test_link_bound_schedules(torch, B, oracle_mod, workloads, slow):
     _assert_equal(got, want, "links slowed %dx" % slow)
     assert np.count_nonzero(want != MAXU) > n // 2
     if slow == 200:
-        # the case does reach pipelines that stay aperiodic past the shortcut's budget
+        # the case does reach pipelines that stay aperiodic past the first pass's budget (S + 8 iterations)
         aperiodic = 0
         for i in range(300):
             d = o.detail(p, i)
@@ -308,8 +308,8 @@ def test_link_bound_schedules(torch, B, oracle_mod, workloads, slow):
 
 
 def test_concurrent_multichunk_calls(torch, B, workloads):
-    """Calls of several internal chunks (their deferred passes overlap on the
-    context's second stream) issued concurrently on two streams of one
+    """Calls of several internal chunks (their passes overlap on the
+    context's side streams) issued concurrently on two streams of one
     context give the results of the same calls made one at a time."""
     w = workloads.workload(3)
     n = 4_500_001                                     # three internal chunks, the last ragged
