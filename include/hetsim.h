@@ -352,7 +352,8 @@ int sim_get_timing(sim_ctx* ctx, int kind, double* total_ms, int64_t* launches);
  * skipped: s skipped iterations of an S-stage pipeline count
  * s * (6 (S - 1) + 2) VALU ops, the cost of S forward and S backward nodes
  * on the times themselves, at 3 ops per node (1 for a node without a
- * cross-stage input).
+ * cross-stage input).  Interleaved pipelines' skipped iterations are not
+ * counted.
  * sim_get_skipped_ops synchronises the device, writes the sum to *ops (host
  * memory) and clears it (it starts at zero).
  */

@@ -49,7 +49,7 @@ namespace hetsim {
 constexpr uint64_t kInvalid = ~0ull;
 
 // ---------------------------------------------------------------- helpers
-// Stage and sync times are integers below 2^52 and messages below 2^50 bytes
+// Stage and sync times are integers below 2^52 and messages below 2^48 bytes
 // (sim_create checks both), carried in fp64: sums and products of them are
 // exact, and fp64 runs at the full VALU rate, where a 64-bit integer product
 // takes several quarter-rate instructions.
@@ -167,9 +167,12 @@ __device__ __forceinline__ void ring_parts(uint32_t p, double rp, uint32_t zero,
   }
 }
 
-// micro-batch counts: exact up to 20, then two buckets per power of two (a
-// pipeline runs at most its first pass's budget of steady iterations, so
-// larger counts need no finer sort)
+// micro-batch counts: exact up to 20, then two buckets per power of two, and
+// one for 768 and more.  A plain pipeline leaves its tile for a continuation
+// list after its first budget of steady iterations, so larger counts need no
+// finer sort for it.  The zero-bubble order's S - 1 iterations before that, and
+// interleaved pipelines, which stay until they are periodic or at their end,
+// are bounded by the bucket only.
 __device__ __forceinline__ uint32_t m_bucket(uint32_t M) {
   if (M <= 20) return M - 1;
   const uint32_t e = 31u - __clz(M), j = 2 * (e - 4) + ((M >> (e - 1)) & 1);
@@ -846,14 +849,14 @@ struct HierShape {
 };
 
 // The link of stage s found from the plan alone.
-template <int kMode, bool kHier>
+template <int kMode>
 __device__ __forceinline__ DpLink stage_link(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s,
                                              HierShape& hs) {
   const uint32_t G = p.G, tp = p.tp;
   bool same = true;
   uint32_t k0 = 0, nmin = 0xffffffffu, nmax = 0, bq_dp = 0;
   double a_dp = 0;
-  hs.ok = kHier && t.ccl_hier != 0;
+  hs.ok = t.ccl_hier != 0;
   hs.g = 0; hs.N = 0; hs.bq_in = 0; hs.a_in = 0;
 #pragma unroll
   for (uint32_t c2 = 0; c2 < 4; ++c2) {
@@ -870,7 +873,7 @@ __device__ __forceinline__ DpLink stage_link(const Tab& t, const Hot<kMode>& h, 
     const uint32_t bx = nic2 > t2.bq_pcie ? nic2 : t2.bq_pcie;
     bq_dp = bx > bq_dp ? bx : bq_dp;
     a_dp = 2 * t2.a_side > a_dp ? 2 * t2.a_side : a_dp;
-    if (kHier && t.ccl_hier) {
+    if (t.ccl_hier) {
       const uint32_t dm = (1u << d2) - 1, gm = (1u << d2) >> p.tpl;
       hs.ok = hs.ok && (b2 & dm) == 0 && (n2 & dm) == 0 && (c2 == 0 || gm == hs.g);
       hs.g = gm;
@@ -938,7 +941,7 @@ __device__ __forceinline__ double stage_dp(const Tab& t, const Hot<kMode>& h, co
                                            uint32_t ns, double rp, double rpe) {
   if (p.psum <= 1) return 0;
   HierShape hs;
-  const DpLink l = stage_link<kMode, true>(t, h, p, s, hs);
+  const DpLink l = stage_link<kMode>(t, h, p, s, hs);
   const Params par(h.size(), p.tpl, p.epl);
   return link_dp<true>(t, p, l, hs, rp, rpe, par.stage(ns, s == 0, s == p.S - 1), (double)ns * par.expert);
 }
@@ -1021,7 +1024,7 @@ __device__ __forceinline__ uint64_t stage_sync(const Tab& t, const Hot<kMode>& h
   if (!p.overlap) return (uint64_t)stage_dp(t, h, p, s, hi - lo, rp, rpe);
   if (p.psum <= 1) return 0;
   HierShape hs;
-  const DpLink l = stage_link<kMode, true>(t, h, p, s, hs);
+  const DpLink l = stage_link<kMode>(t, h, p, s, hs);
   return (uint64_t)overlap_walk<kMode, int64_t>(t, h, p, s, lo, hi, (uint32_t)(p.tc >> (4 * s)) & 15,
                                                 overlap_syncs(t, h, p, s, l, hs, rp, rpe));
 }
@@ -2180,7 +2183,7 @@ struct PlanLanes {
   template <int kMode, bool kHier>
   __device__ __forceinline__ DpLink link(const Tab& t, const Hot<kMode>& h, const Plan& p, uint32_t s, HierShape& hs) {
     hs.ok = false;
-    if (kHier && t.ccl_hier) return stage_link<kMode, true>(t, h, p, s, hs);
+    if (kHier && t.ccl_hier) return stage_link<kMode>(t, h, p, s, hs);
     return exchanged_link(h, G, reinterpret_cast<const uint2*>(col) + 64 * s + lead);
   }
   // the stages' syncs into col[64 s + lead]; ns(s): the stage's layers
@@ -2410,14 +2413,13 @@ __device__ __forceinline__ void il_trip(const V (&f)[S * v], const V (&b)[S * v]
 // taken in one step (the argument of the plain pipeline's shortcut).
 template <int S, int v, typename V, bool kJump>
 __device__ __forceinline__ void il_pipe(const V (&f)[S * v], const V (&b)[S * v], const V (&c)[S], uint32_t M,
-                                        V (&busy)[S], int& skipped) {
+                                        V (&busy)[S]) {
   constexpr int NV = S * v, W0 = 2 * (S - 1) + (v - 1) * S;
   static_assert(W0 <= 2 * NV, "at most two trips of warm-up and of cool-down");
   const int n = (int)M * v;   // (a multiple of NV, at least 2 NV)
   V F[S], B[S], pF[S], pB[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) F[s] = B[s] = busy[s] = 0;
-  skipped = 0;
   il_trip<S, v, V, -1, 0>(f, b, c, F, B, busy);
   if (W0 > NV) il_trip<S, v, V, -1, NV>(f, b, c, F, B, busy);
   bool first = true;
@@ -2445,7 +2447,6 @@ __device__ __forceinline__ void il_pipe(const V (&f)[S * v], const V (&b)[S * v]
           busy[s] += k;
         }
         t0 += r * NV;
-        skipped += r;
       }
     }
     first = false;
@@ -2478,10 +2479,10 @@ __device__ __forceinline__ V il_tail(const Tab& t, const Hot<kMode>& h, const Pl
 }
 
 template <int S, int v, int kMode, typename V, bool kJump>
-__device__ __forceinline__ V il_time(const Tab& t, const Hot<kMode>& h, const Plan& p, int& skipped) {
+__device__ __forceinline__ V il_time(const Tab& t, const Hot<kMode>& h, const Plan& p) {
   V f[S * v], b[S * v], c[S], busy[S];
   il_setup_own<S, v, kMode, V>(t, h, p, f, b, c);
-  il_pipe<S, v, V, kJump>(f, b, c, class_mb(p), busy, skipped);
+  il_pipe<S, v, V, kJump>(f, b, c, class_mb(p), busy);
   return il_tail<S, v, kMode, V>(t, h, p, busy);
 }
 
@@ -2491,7 +2492,6 @@ __device__ __forceinline__ void eval_il(const Tab& t, const Hot<kMode>& h, const
                                         double* x, uint32_t* cw) {
   const uint32_t lane = threadIdx.x & 63u;
   double busy[S];
-  int skipped;
   uint32_t G, lead;
   {
     double f[S * v], b[S * v], c[S];
@@ -2507,7 +2507,7 @@ __device__ __forceinline__ void eval_il(const Tab& t, const Hot<kMode>& h, const
       pl.template syncs<kMode, true>(t, h, p, [&](uint32_t s) { return il_device_ns<S, v>(p, (int)s); });
       M = class_mb(p);
     }
-    il_pipe<S, v, double, true>(f, b, c, M, busy, skipped);
+    il_pipe<S, v, double, true>(f, b, c, M, busy);
   }
   double T = 0;
 #pragma unroll
@@ -2565,7 +2565,7 @@ __device__ __forceinline__ bool tile_slot(const EvalBufs& e, uint32_t q, uint32_
 // four took 805, 714, 269 and 148 us with the recurrence on the times, u64
 // setup and 40 iterations of waiting, and take 593, 216, 268 and 91.
 template <int GRP, int kMode, bool kHet>
-__global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(const Tab* __restrict__ tp, EvalBufs e) {
+__global__ void __launch_bounds__(kEvalThreads) k_eval(const Tab* __restrict__ tp, EvalBufs e) {
   const Tab& t = *tp;
   constexpr int kTop = kMaxStages - 4 * GRP;   // stage counts kTop-3 .. kTop
   constexpr uint32_t g0 = 16 * GRP;
@@ -2591,11 +2591,15 @@ __global__ void __launch_bounds__(kEvalThreads, GRP == 2 ? 3 : 1) k_eval(const T
 // and interleaved ones of every call, and with two-level collectives (whose
 // sync code k_eval lacks) or in a small call also the plain ones.  One launch,
 // where one per kind and stage-count group costs 4-5 us each even if it has
-// nothing to do; the kinds' registers (200-270) allow two wavefronts per SIMD
-// whatever the stage count, so nothing is lost by their sharing a kernel.
+// nothing to do.  The price is occupancy: the whole kernel takes 256 registers,
+// two wavefronts per SIMD for every kind and stage count, where compiled apart
+// the kinds of up to four stages would take 167 and those of five to eight
+// 187-209 (117-153 without the two-level collectives: three and four
+// wavefronts), and it keeps a few registers in private memory.
 // Bound by instruction issue and the chains' latency at that occupancy: the
 // two thirds of 2.5M plans that overlap or run the zero-bubble order take 553
-// us, where kernels fed with tiles a third full took 2460.
+// us, where kernels fed with tiles a third full took 2460; 2^20 overlapped plans
+// of at most four stages 308 us in all, and 787 with kernels of their own.
 template <int S, int kMode>
 __device__ __forceinline__ void eval_kind(const Tab& t, const Hot<kMode>& h, const EvalBufs& e, uint32_t kind,
                                           uint32_t slot, const WaveLds& w) {
@@ -2676,11 +2680,10 @@ __global__ void __launch_bounds__(64) k_redo_u64(Tab t, EvalBufs e) {
     const Hot<2> h(t, nullptr);
     if (!kHet && p.v > 1) {
       uint64_t r = 0;
-      int skipped;
       switch (il_shape(S, p.v)) {
 #define X(S_, V_)                                                    \
   case il_shape(S_, V_):                                             \
-    r = il_time<S_, V_, 2, uint64_t, true>(t, h, p, skipped);        \
+    r = il_time<S_, V_, 2, uint64_t, true>(t, h, p);                 \
     break;
         HETSIM_IL_SHAPES(X)
 #undef X

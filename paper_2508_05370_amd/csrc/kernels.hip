@@ -257,7 +257,8 @@ __global__ void __launch_bounds__(256) k_plan_scatter(const uint4* __restrict__ 
 // The first list: tiles dealt round-robin to the waves of the grid.  Bound by
 // the serial chain of each lane's iterations (a wave of 16 stages takes 0.12 us
 // for one of them alone); most of a tile's lanes end after a few, so a sixth of
-// the lane slots is busy.  Redoing such pipelines from the start with the
+// the lane slots is busy.  (The rates of 16 stages beside their state do not fit
+// the 256 registers: 148 bytes per lane are in private memory.)  Redoing such pipelines from the start with the
 // whole loop, as a list of slots instead of states would need, took 446 us per
 // 2M-plan chunk of a random 512-device sweep where this takes 303 (126 with no
 // other kernel beside it) and k_power 149 (54).
