@@ -3,6 +3,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -39,6 +40,155 @@ constexpr int64_t kChunk = 1 << 21;
 struct EventPair {
   hipEvent_t a, b;
 };
+
+// Workspaces of calls, kept between them: one set per device, shared by its
+// contexts, given back with the last of them.  Freed to a stream-ordered pool
+// after each call instead, a workspace went back to the system at the next
+// synchronisation, whatever the pool's release threshold, and the next call now
+// and then waited 10 ms to 2 s for it (with 1 GB, in 1 to 5 % of the passes over
+// three contexts in turn).
+// A call takes the smallest block that is large enough and either idle or last
+// used on the call's own stream, so calls on other streams never wait for each
+// other; a larger block takes the place of an idle smaller one, and of more than
+// kKeep blocks the extra ones are freed after their call.
+struct Block {
+  void* p;
+  size_t bytes;
+  hipStream_t s;      // of its latest call
+  hipEvent_t done;    // recorded after that call
+  bool busy;          // a call is being launched on it
+};
+class Workspaces {
+ public:
+  // a context more on the current device
+  bool attach(int device) {
+    std::lock_guard<std::mutex> g(mu_);
+    if (contexts_ == 0) {
+      hipMemPoolProps props;
+      memset(&props, 0, sizeof(props));
+      props.allocType = hipMemAllocationTypePinned;
+      props.location.type = hipMemLocationTypeDevice;
+      props.location.id = device;
+      if (hipMemPoolCreate(&pool_, &props) != hipSuccess) return false;
+    }
+    ++contexts_;
+    return true;
+  }
+  // a context less, whose work is done
+  void detach() {
+    std::lock_guard<std::mutex> g(mu_);
+    if (--contexts_ > 0) return;
+    for (auto& b : blocks_) {
+      (void)hipEventSynchronize(b->done);
+      (void)hipFree(b->p);
+      (void)hipEventDestroy(b->done);
+    }
+    blocks_.clear();
+    (void)hipMemPoolDestroy(pool_);
+    pool_ = nullptr;
+  }
+  // A block of `bytes` for work on stream s (nullptr: no room).  Under capture
+  // it is the graph's own.
+  Block* take(size_t bytes, hipStream_t s) {
+    std::lock_guard<std::mutex> g(mu_);
+    const Relaxed mode;
+    if (capturing(s)) return fresh(bytes, s);
+    Block* best = nullptr;
+    bool wait = false;
+    for (auto& b : blocks_) {
+      if (b->busy || b->bytes < bytes || (best && best->bytes <= b->bytes)) continue;
+      const bool idle = is_idle(*b);
+      if (!idle && b->s != s) continue;
+      best = b.get();
+      wait = !idle;
+    }
+    if (best) {
+      // (nothing to wait for on the stream itself, but its handle may be a later stream's)
+      if (wait && hipStreamWaitEvent(s, best->done, 0) != hipSuccess) return nullptr;
+      best->busy = true;
+      return best;
+    }
+    drop_one_idle(bytes, s);
+    // sizes in eighths of a power of two, so that calls of similar sizes share a block
+    size_t step = 1;
+    while (step < bytes / 16) step *= 2;
+    Block* b = fresh((bytes + step - 1) / step * step, s);
+    if (!b) b = fresh(bytes, s);
+    if (!b) {   // give back what is idle
+      while (drop_one_idle(SIZE_MAX, s)) {}
+      (void)hipStreamSynchronize(s);
+      (void)hipMemPoolTrimTo(pool_, 0);
+      b = fresh(bytes, s);
+    }
+    if (!b) return nullptr;
+    b->busy = true;
+    blocks_.emplace_back(b);
+    return b;
+  }
+  // after the call's last launch on s
+  void give_back(Block* b, hipStream_t s) {
+    std::lock_guard<std::mutex> g(mu_);
+    const Relaxed mode;
+    size_t j = 0;
+    while (j < blocks_.size() && blocks_[j].get() != b) ++j;
+    const bool kept = j < blocks_.size();
+    if (kept && blocks_.size() <= kKeep && hipEventRecord(b->done, s) == hipSuccess) {
+      b->s = s;
+      b->busy = false;
+      return;
+    }
+    (void)hipFreeAsync(b->p, s);
+    (void)hipEventDestroy(b->done);
+    if (kept) blocks_.erase(blocks_.begin() + (long)j);
+    else delete b;   // (a captured call's)
+  }
+
+ private:
+  static constexpr size_t kKeep = 8;
+  // Queries and allocations of this thread, none of which touches a capturing
+  // stream, while another thread captures one.
+  struct Relaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  };
+  static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
+  }
+  static bool is_idle(const Block& b) {
+    if (hipEventQuery(b.done) == hipSuccess) return true;
+    (void)hipGetLastError();   // (the launches report the last error)
+    return false;
+  }
+  Block* fresh(size_t bytes, hipStream_t s) {
+    std::unique_ptr<Block> b(new (std::nothrow) Block{nullptr, bytes, s, nullptr, false});
+    if (!b || hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) return nullptr;
+    if (hipMallocFromPoolAsync(&b->p, bytes, pool_, s) == hipSuccess) return b.release();
+    (void)hipGetLastError();
+    (void)hipEventDestroy(b->done);
+    return nullptr;
+  }
+  // free the largest idle block smaller than `bytes`; false: none
+  bool drop_one_idle(size_t bytes, hipStream_t s) {
+    size_t at = blocks_.size();
+    for (size_t j = 0; j < blocks_.size(); ++j) {
+      const Block& b = *blocks_[j];
+      if (!b.busy && b.bytes < bytes && (at == blocks_.size() || b.bytes > blocks_[at]->bytes) && is_idle(b)) at = j;
+    }
+    if (at == blocks_.size()) return false;
+    (void)hipFreeAsync(blocks_[at]->p, s);
+    (void)hipEventDestroy(blocks_[at]->done);
+    blocks_.erase(blocks_.begin() + (long)at);
+    return true;
+  }
+  std::mutex mu_;
+  int contexts_ = 0;
+  hipMemPool_t pool_ = nullptr;
+  std::vector<std::unique_ptr<Block>> blocks_;
+};
+constexpr int kDevices = 64;   // (noalloc_scratch accepts no device beyond)
+Workspaces workspaces[kDevices];
 }  // namespace
 
 // Side streams of multi-chunk calls made on one caller stream: two for the
@@ -66,7 +216,7 @@ struct sim_ctx {
   Tab tab;
   int device;
   void* tables;        // one device allocation holding every table
-  hipMemPool_t pool;   // stream-ordered pool for per-call workspace
+  bool attached;       // to its device's workspaces
   std::mutex mu;
   bool timing;
   std::vector<EventPair> ev[4];
@@ -105,7 +255,7 @@ extern "C" int sim_create(const sim_model_desc* model, const sim_cluster_desc* c
   c->tab = ht->tab;
   c->timing = false;
   c->tables = nullptr;
-  c->pool = nullptr;
+  c->attached = false;
   c->nseen = 0;
   c->untracked = false;
   for (auto& e : c->seen_ev) e = nullptr;
@@ -140,18 +290,9 @@ extern "C" int sim_create(const sim_model_desc* model, const sim_cluster_desc* c
   c->skipped_ops = (uint64_t*)((char*)c->tables + img);
   c->dtab = (Tab*)((char*)c->tables + img + kSkipBytes);
   if (hipMemcpy(c->dtab, &c->tab, sizeof(Tab), hipMemcpyHostToDevice) != hipSuccess) return fail(SIM_EHIP);
-  hipMemPoolProps props;
-  memset(&props, 0, sizeof(props));
-  props.allocType = hipMemAllocationTypePinned;
-  props.location.type = hipMemLocationTypeDevice;
-  props.location.id = c->device;
-  if (hipMemPoolCreate(&c->pool, &props) != hipSuccess) {
-    c->pool = nullptr;
-    return fail(SIM_EHIP);
-  }
+  if (!workspaces[c->device].attach(c->device)) return fail(SIM_EHIP);
+  c->attached = true;
   delete ht;
-  uint64_t keep = UINT64_MAX;   // keep workspace memory cached between calls
-  (void)hipMemPoolSetAttribute(c->pool, hipMemPoolAttrReleaseThreshold, &keep);
   *out = c;
   return SIM_OK;
 }
@@ -190,7 +331,7 @@ extern "C" void sim_destroy(sim_ctx* c) {
     (void)hipStreamDestroy(q.aux);
     for (auto g : q.grp) (void)hipStreamDestroy(g);
   }
-  if (c->pool) (void)hipMemPoolDestroy(c->pool);
+  if (c->attached) workspaces[c->device].detach();
   if (c->tables) (void)hipFree(c->tables);
   delete c;
 }
@@ -319,14 +460,9 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
   }
   const bool het = plans->chdr != nullptr;
   size_t cont = 0;
-  void* ws = alloc_work(
-      [&](size_t bytes) {
-        void* p = nullptr;
-        if (hipMallocFromPoolAsync(&p, bytes, c->pool, s) == hipSuccess) return p;
-        (void)hipGetLastError();   // (the launches below report the last error)
-        return (void*)nullptr;
-      },
-      nbuf, ch, het, &cont);
+  Workspaces& pool = workspaces[c->device];
+  Block* const block = alloc_work([&](size_t bytes) { return pool.take(bytes, s); }, nbuf, ch, het, &cont);
+  void* const ws = block ? block->p : nullptr;
   const size_t bytes = work_bytes(ch, het, cont);
   hipError_t e = hipSuccess;
   Work w[2];
@@ -388,7 +524,7 @@ extern "C" int sim_eval_plans(sim_ctx* c, const sim_plans* plans, int64_t n, uin
     if (e == hipSuccess) e = r;
   }
   if (tcall) end_event(c, 2, s, &call);
-  if (ws) (void)hipFreeAsync(ws, s);
+  if (block) pool.give_back(block, s);
   track(c, s);
   for (auto& x : evs)
     if (x) (void)hipEventDestroy(x);
@@ -428,11 +564,12 @@ extern "C" int sim_eval_stages(sim_ctx* c, const sim_plans* plans, int64_t n, ui
   if (n == 0) return SIM_OK;
   hipStream_t s = (hipStream_t)stream;
   if (hipSetDevice(c->device) != hipSuccess) return SIM_EHIP;
-  void* ws = nullptr;
   const bool het = plans->chdr != nullptr;
   const int64_t ch = n < kChunk ? n : kChunk;
   const size_t bytes = (size_t)ch * (het ? kHetWords * 16 : sizeof(PackedPlan));
-  if (hipMallocFromPoolAsync(&ws, bytes, c->pool, s) != hipSuccess) return SIM_ENOMEM;
+  Block* const block = workspaces[c->device].take(bytes, s);
+  if (!block) return SIM_ENOMEM;
+  void* const ws = block->p;
   PackedPlan* packed = het ? nullptr : (PackedPlan*)ws;
   uint4* pcut = het ? (uint4*)ws : nullptr;
   hipError_t e = hipSuccess;
@@ -444,7 +581,7 @@ extern "C" int sim_eval_stages(sim_ctx* c, const sim_plans* plans, int64_t n, ui
     if (e == hipSuccess)
       e = launch_stages(c->tab, packed, pcut, out_class + off * 4, cn, out_stage + off * 4 * kMaxStages * 4, s);
   }
-  (void)hipFreeAsync(ws, s);
+  workspaces[c->device].give_back(block, s);
   track(c, s);
   return e == hipSuccess ? SIM_OK : SIM_EHIP;
 }

@@ -299,12 +299,12 @@ inline Work carve(void* base, int64_t ch, bool het, size_t cont) {
 // nbuf chunks' workspace from alloc (nullptr: no room); *cont: the bytes of each
 // one's lists.
 template <typename Alloc>
-inline void* alloc_work(Alloc alloc, int nbuf, int64_t ch, bool het, size_t* cont) {
+inline auto alloc_work(Alloc alloc, int nbuf, int64_t ch, bool het, size_t* cont) {
   for (const size_t per : {cont_per_plan(ch), kContPerPlanLow}) {
     *cont = cont_bytes(ch, per);
-    if (void* p = alloc(nbuf * work_bytes(ch, het, *cont))) return p;
+    if (auto p = alloc(nbuf * work_bytes(ch, het, *cont))) return p;
   }
-  return nullptr;
+  return decltype(alloc((size_t)0))();
 }
 
 // The allocation-free entry point's workspace, a static device array (one per
