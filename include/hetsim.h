@@ -223,9 +223,11 @@ int sim_create(const sim_model_desc* model, const sim_cluster_desc* cluster, sim
  * point-to-point hops (Table 1 exposure) on each group's slowest link (Sec.
  * 4.1 [C4]), a 1F1B pipeline per class (interleaved when the header says
  * so), then the DP gradient sync per stage (per device) across all
- * replicas.  n = 0 is a no-op.  Temporary device memory is taken
- * from a stream-ordered pool on `stream` (a hipStream_t; NULL = null
- * stream).  Returns SIM_EINVAL for a NULL pointer, n < 0 or stride < n,
+ * replicas.  n = 0 is a no-op.  All work is ordered on `stream` (a
+ * hipStream_t; NULL = null stream).  Temporary device memory is kept for
+ * later calls: the contexts of a device share at most eight workspaces, one
+ * per stream in use at a time, until the last context is destroyed.  Returns
+ * SIM_EINVAL for a NULL pointer, n < 0 or stride < n,
  * SIM_ENOMEM if the temporary memory cannot be allocated, SIM_EHIP if a
  * launch fails.
  */

@@ -154,7 +154,9 @@ class Workspaces {
   };
   static bool capturing(hipStream_t s) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();   // (the null stream while another thread captures one)
+    return false;
   }
   static bool is_idle(const Block& b) {
     if (hipEventQuery(b.done) == hipSuccess) return true;
